@@ -2,6 +2,7 @@
 #include <math.h>
 #include <string.h>
 
+#include <algorithm>
 #include <mutex>
 #include <new>
 
@@ -10,6 +11,45 @@
 namespace tbe {
 
 static size_t align256(size_t x) { return (x + 255) & ~(size_t)255; }
+
+// Batches up to kSelfScanMax lookups: the histograms of a segment's chunks are few enough for every scatter workgroup to
+// add up itself (at most 512 chunks of 4096 in all).  What that reads grows with the square of the chunks per segment and
+// with the digit's width, so small tiles (more workgroups) and digits of more than 8 bits (fewer passes) are for batches
+// with at most kSelfScanChunks chunks per segment.  Measured: 26 tables of 45 k lookups, 20-bit ids, two 10-bit passes on
+// 22 chunks per segment 50 us against 59 us for three 8-bit ones; 12 tables of 164 k lookups, 80 chunks per segment: 108
+// against 75 us.
+constexpr int64_t kSelfScanMax = (int64_t)1 << 21;
+constexpr int64_t kSelfScanChunks = 32;
+// Bytes of chunk histograms that wide digits may take, ascending in N, so that a workspace made for more lookups serves
+// fewer as well.
+static size_t hist_cap(int64_t N) {
+    const size_t c = (size_t)(N < kSelfScanMax ? N : kSelfScanMax) * 5 / 4;
+    return c > (512u << 10) ? c : (512u << 10);
+}
+SortShape sort_shape(const tbe_handle* h, int64_t N) {
+    SortShape sh;
+    sh.nseg = h->segmented ? h->T : 1;
+    sh.self_scan = N <= kSelfScanMax;
+    const int64_t few = kSelfScanChunks * sh.nseg;   // chunks in all
+    if (sh.self_scan && N <= 32 * 4096 && N <= few * 1024) sh.tile = 1024;
+    else if (sh.self_scan && N <= 4 * few * 2048) sh.tile = 2048;
+    else sh.tile = kRadixTile;
+    const int64_t tile = sh.tile;
+    const int64_t tiles = (N + tile - 1) / tile;
+    const int64_t blocks = tiles < kRadixMaxBlocks ? tiles : kRadixMaxBlocks;
+    sh.chunk = (tiles + blocks - 1) / blocks * tile;
+    sh.max_chunks = (int)((N + sh.chunk - 1) / sh.chunk) + sh.nseg;
+    // few passes of wide digits where the batch is small enough for them and their histograms stay within hist_cap
+    for (int wide = sh.self_scan && tiles <= few ? 1 : 0; wide >= 0; --wide) {
+        const int most = wide ? 11 : 8;
+        sh.passes = (h->sort_bits + most - 1) / most;
+        sh.bits = (h->sort_bits + sh.passes - 1) / sh.passes;
+        sh.bins = sh.bits <= 8 ? 256 : (sh.bits <= 10 ? 1024 : 2048);
+        sh.hist_bytes = (size_t)(sh.self_scan ? 2 : 4) * (size_t)sh.bins * (size_t)(sh.max_chunks + 1);
+        if (sh.hist_bytes <= hist_cap(N)) break;
+    }
+    return sh;
+}
 
 Workspace carve(const tbe_handle* h, int64_t N) {
     Workspace w;
@@ -26,21 +66,14 @@ Workspace carve(const tbe_handle* h, int64_t N) {
     w.keys[1] = take(4 * (n + 1));
     w.vals[0] = take(4 * (n + 1));
     w.vals[1] = take(4 * (n + 1));
-    w.bag_of_pos = w.vals[0];   // read by the first radix pass only, which writes keys[1] / vals[1]: no buffer of its own
     w.seg_start = take(4 * (n + 1));
-    // radix: G blocks, each owning a contiguous slice that is a whole number of tiles
-    int64_t tiles = ((int64_t)n + kRadixTile - 1) / kRadixTile;
-    int64_t G = tiles < kRadixMaxBlocks ? tiles : kRadixMaxBlocks;
-    int64_t tiles_per_block = (tiles + G - 1) / G;
-    w.radix_chunk = tiles_per_block * kRadixTile;
-    w.radix_blocks = (int)(((int64_t)n + w.radix_chunk - 1) / w.radix_chunk);
-    w.nseg = h->segmented ? h->T : 1;
-    w.radix_maxc = w.radix_blocks + w.nseg;
-    w.radix_hist = take(4 * (size_t)256 * (size_t)(w.radix_maxc + 1));
-    w.bin_tot = take(4 * 256 * (size_t)w.nseg);
-    w.seg_bounds = take(4 * (size_t)(w.nseg + 1));
-    w.seg_chunk0 = take(4 * (size_t)(w.nseg + 1));
-    w.chunk_desc = take(16 * (size_t)w.radix_maxc);
+    w.sort = sort_shape(h, N > 0 ? N : 1);
+    // (8-bit digits in a handle of many tables may exceed the cap; their histograms grow with N by themselves)
+    const size_t least8 = 2 * 256 * (size_t)(w.sort.max_chunks + 1);
+    w.radix_hist = take(std::max(std::max(w.sort.hist_bytes, hist_cap(N)), least8));
+    w.bin_tot = take(w.sort.self_scan ? 0 : 4 * 256 * (size_t)w.sort.nseg);
+    w.seg_chunk0 = take(w.sort.self_scan ? 0 : 4 * (size_t)(w.sort.nseg + 1));
+    w.chunk_desc = take(32 * (size_t)w.sort.max_chunks);
     w.rle_blocks = (int)(((int64_t)n + kRleTile - 1) / kRleTile);
     w.rle_counts = take(4 * (size_t)(w.rle_blocks + 1));
     w.counters = take(4 * kCounterWords);
@@ -181,9 +214,9 @@ tbe_status tbe_create(int32_t T, const int64_t* rows, const int32_t* D, tbe_dtyp
         int64_t max_rows = 0;
         for (int t = 0; t < T; ++t) max_rows = rows[t] > max_rows ? rows[t] : max_rows;
         const int local_bits = bits_for((uint64_t)max_rows);  // the local key of an invalid id is rows[t] itself
-        h->segmented = T > 1 && T <= kMaxSortSegments && (local_bits + 7) / 8 < (h->key_bits + 7) / 8;
+        // table by table whenever that sorts fewer key bits; a single 8-bit pass gains nothing from it
+        h->segmented = T > 1 && T <= kMaxSortSegments && h->key_bits > 8;
         h->sort_bits = h->segmented ? local_bits : h->key_bits;
-        h->sort_passes = (h->sort_bits + 7) / 8;
     }
     {   // row-weighted share of the rows as wide as a wavefront (129..256 columns) among the tables up to 256 columns
         double wide = 0.0, all = 0.0;
@@ -332,14 +365,9 @@ static tbe_status backward_impl(const tbe_handle* h, const void* grad_out, tbe_i
     hipStream_t s = static_cast<hipStream_t>(hip_stream);
     const int idx32 = index_dtype == TBE_I32;
     hipError_t e = hipSuccess;
-    int buf = h->sort_passes & 1;  // every pass flips the double buffer, starting from 0
+    const int buf = w.sort.passes & 1;  // every pass flips the double buffer, starting from 0
     if (prep) {
-        e = launch_linearize(h, indices, offsets, idx32, B, nnz, reinterpret_cast<uint32_t*>(ws + w.keys[0]),
-                             reinterpret_cast<uint32_t*>(ws + w.bag_of_pos), s);
-        if (e != hipSuccess) return TBE_EHIP;
-        // pooled: the bag id of every position travels with its key; non-pooled: the position itself
-        e = launch_radix_sort(h, w, ws, nnz, seq ? nullptr : reinterpret_cast<const uint32_t*>(ws + w.bag_of_pos),
-                              offsets, idx32, B, &buf, s);
+        e = launch_sort(h, w, ws, indices, offsets, idx32, B, nnz, seq != 0, s);
         if (e != hipSuccess) return TBE_EHIP;
         e = launch_run_lengths(h, w, ws, buf, nnz, s);
         if (e != hipSuccess) return TBE_EHIP;
@@ -450,7 +478,7 @@ tbe_status tbe_debug_sorted(const tbe_handle* h, void* workspace, int32_t B, int
     const tbe_status st = check_batch(h, B, nnz);
     if (st != TBE_OK) return st;
     const Workspace w = carve(h, nnz);
-    const int buf = h->sort_passes & 1;  // every pass flips the double buffer, starting from 0
+    const int buf = w.sort.passes & 1;  // every pass flips the double buffer, starting from 0
     char* ws = static_cast<char*>(workspace);
     if (keys_sorted) *keys_sorted = reinterpret_cast<const uint32_t*>(ws + w.keys[buf]);
     if (vals_sorted) *vals_sorted = reinterpret_cast<const uint32_t*>(ws + w.vals[buf]);

@@ -12,10 +12,9 @@ namespace tbe {
 
 // ---- tunables that fix the workspace layout -------------------------------------------------
 constexpr int kSegChunk = 512;         // a unique row with more lookups than this is split into chunks of this size
-constexpr int kRadixTile = 4096;  // elements per radix-sort tile (256 threads x items per thread)
-constexpr int kRadixMaxBlocks = 8192;  // each radix block owns one contiguous slice of the input
+constexpr int kRadixTile = 4096;  // elements per radix-sort tile (256 threads x 16) of a large batch; smaller ones take 2048 or 1024
+constexpr int kRadixMaxBlocks = 8192;  // large batches: each radix block owns one contiguous slice of the input
 constexpr int kRleTile = 2048;  // elements per run-length tile (at most 4096: one wavefront scans its runs of 64)
-constexpr int kLinTile = 2048;         // positions per linearize tile
 constexpr int kMaxSlices = 64;         // sub-slices of one table's gradient block (8 XCDs x up to 8 sweeps)
 constexpr int kMaxSortSegments = 4096;  // tables beyond this are sorted as one segment on the linearised key
 constexpr int kDenseRows = 16;   // rows per table that the dense-row kernel reduces (multiple of 4)
@@ -50,7 +49,6 @@ struct tbe_handle {
     // bits(max rows of one table) needs fewer radix passes than bits(sum of rows).
     bool segmented = false;  // true: one sort segment per table, local keys; false: one segment, linearised keys
     int sort_bits = 1;       // key bits the radix passes cover
-    int sort_passes = 1;
     std::vector<int64_t> rows, row_base, w_off;
     std::vector<int32_t> D, D_off;
     // device metadata, one allocation
@@ -80,18 +78,28 @@ struct tbe_handle {
 
 namespace tbe {
 
+// How the keys of a batch of N lookups are sorted (see tbe_sort.hip).
+struct SortShape {
+    int nseg;          // sort segments
+    int passes, bits;  // radix passes, digit bits of each
+    size_t hist_bytes; // chunk histograms
+    int bins;          // 256, 1024 or 2048: histogram width of the kernels that run
+    bool self_scan;    // scatter workgroups add up their segment's chunk histograms themselves
+    int tile;          // 1024, 2048 or 4096 positions
+    int64_t chunk;     // positions per chunk (a multiple of the tile)
+    int max_chunks;    // N / chunk + number of segments (every segment may end in a partial chunk)
+};
+SortShape sort_shape(const tbe_handle* h, int64_t N);
+
 // Workspace carving for a batch of N lookups (all offsets in bytes, 256-byte aligned).
 struct Workspace {
     // keys/vals: radix double buffers of N+1 words each.  The payload of a key is the linear bag id of its lookup
     // (pooled calls) or its position (non-pooled calls), so vals[sorted] is the per-lookup stream the gradient
     // kernels read.  After the sort vals[spare] receives unique_rows.
-    size_t keys[2], vals[2], bag_of_pos, seg_start, radix_hist, bin_tot, rle_counts, counters, long_tables, tickets, seq_gbase, seg_bounds,
+    size_t keys[2], vals[2], seg_start, radix_hist, bin_tot, rle_counts, counters, long_tables, tickets, seq_gbase,
         seg_chunk0, chunk_desc, dense_rows, dense_n, dense_bounds, tile_long, tile_slots,
         long_list, unit_list, bounds, partial, total;
-    int radix_blocks;     // blocks a single segment of N keys would need
-    int radix_maxc;       // chunk descriptors: radix_blocks + number of segments (every segment may end in a partial chunk)
-    int nseg;             // sort segments
-    int64_t radix_chunk;  // elements per radix block (multiple of kRadixTile)
+    SortShape sort;
     int rle_blocks;
     int64_t cap_long, cap_main, cap_chunks, cap_units;   // long rows; slots before the dense region; all slots; units
     int long_tiles;       // tiles of unique rows that the long-row passes walk
@@ -115,13 +123,10 @@ hipError_t launch_forward(const tbe_handle* h, const void* tables, const int32_t
                           int out_io, hipStream_t s);
 // every replicas[m] (device pointers, M <= kMaxReplicas) becomes the element-wise mean; count elements each
 hipError_t launch_replica_mean(const tbe_handle* h, void* const* replicas, int M, size_t count, bool f32, hipStream_t s);
-hipError_t launch_linearize(const tbe_handle* h, const void* indices, const void* offsets, int idx32, int32_t B, int64_t N,
-                            uint32_t* keys, uint32_t* bag_of_pos, hipStream_t s);
-// sorts keys[0] of the workspace segment by segment (see tbe_handle::segmented); the payload that travels with a key
-// is payload[p] (nullptr: its position p).  The keys written by the last pass are linearised row keys in either
-// mode.  Returns in *result_buf which buffer pair (0/1) holds the sorted keys and payloads.
-hipError_t launch_radix_sort(const tbe_handle* h, const Workspace& w, char* ws, int64_t N, const uint32_t* payload,
-                             const void* offsets, int idx32, int32_t B, int* result_buf, hipStream_t s);
+// Sorts the batch's ids, segment by segment, into (linearised row key, payload) pairs; the payload is the lookup's bag, or
+// its position when seq is set.  The result lies in buffer pair w.sort.passes & 1 of the workspace.
+hipError_t launch_sort(const tbe_handle* h, const Workspace& w, char* ws, const void* indices, const void* offsets, int idx32,
+                       int32_t B, int64_t N, bool seq, hipStream_t s);
 // `sorted` is the buffer index (0/1) that holds the sorted pairs; vals of the other pair receive unique_rows
 hipError_t launch_run_lengths(const tbe_handle* h, const Workspace& w, char* ws, int sorted, int64_t N, hipStream_t s);
 // state == nullptr: plain SGD step.  seq != 0: grad_out is the non-pooled layout (one [n_t, D_t] block per table),

@@ -6,13 +6,64 @@
 namespace tbe {
 
 // =================================================================================================
-// linearize: key[p] = row_base[t(p)] + indices[p] (or the table-local id alone when the sort is segmented),
-// bag_of_pos[p] = linear bag id of p, the payload a pooled call sorts along with the key
+// Ids to sorted (key, payload) pairs: a stable LSD radix sort whose first pass reads the ids themselves.
+//
+// The positions are cut into segments (one per table, or a single one) and every segment into chunks of at most `chunk`
+// positions; a chunk never crosses a segment border.  One workgroup owns one chunk in every pass:
+//   hist    : counts the digits of its chunk (pass 0: of the keys it makes from the ids, and leaves the chunk's
+//             descriptor for the kernels that follow)
+//   binscan : large batches only - block d turns ghist[d][*] into an exclusive scan per segment
+//   scatter : ranks the chunk tile by tile and writes (key, payload) to its final place inside the segment
+// Chunk k precedes chunk k+1, and the scatter ranks elements in input order, so the sort is stable.  The last pass
+// turns table-local keys into linearised ones as it writes them.
+//   key     : the table-local id when the sort goes table by table, else row_base[t] + id; an id outside its table gets
+//             the table's number of rows (sum(rows) when the keys are linearised)
+//   payload : the lookup's bag (pooled calls) or its position (non-pooled calls)
+// Making the keys inside pass 0, twice, instead of storing them and their bags first costs one more read of the ids and
+// saves 8 bytes written and 4 read per lookup and two launches.
+//
+// Digits: up to 11 bits in batches of at most kSelfScanMax lookups, 8 bits beyond.  A small batch's time is its chain of
+// launches (about 4 us each), so it takes wide digits (fewer passes) and lets every scatter workgroup add up the
+// histograms of its segment's chunks by itself (no binscan launch).  In a large batch 2048 bins would leave runs of two
+// keys per tile and bin to write, and the chunk histograms would be too many to add up per workgroup.
 // =================================================================================================
-constexpr int kLinThreads = 256;
+constexpr int kRsThreads = 256;
+constexpr int kRsWaves = kRsThreads / kWave;
+
+struct ChunkDesc {            // written by pass 0, one per workgroup; e == s: no chunk
+    uint32_t s, e;            // positions [s, e)
+    uint32_t seg;             // segment
+    uint32_t first, count;    // the segment's first chunk, its number of chunks
+    uint32_t seg_start;       // the segment's first position
+    uint32_t pad[2];
+};
+
+// everything a pass needs to know about where its elements come from
+struct SortArgs {
+    const void* indices;     // int64 or int32, both the same: the kernels that read them are compiled for either (as a
+    const void* offsets;     // run-time flag inside divergent searches it has been miscompiled: a 4-byte load for 8-byte ids)
+    const int64_t* row_base;
+    ChunkDesc* desc;
+    uint32_t* chunk0;        // [nseg + 1] first chunk of every segment (large batches)
+    void* ghist;             // self-scan: uint16 [chunk][NB] (a chunk is one tile); else uint32 [digit][G]
+    uint32_t* bin_tot;       // [nseg][256] (large batches)
+    const uint32_t* keys_in;
+    const uint32_t* vals_in;
+    uint32_t* keys_out;
+    uint32_t* vals_out;
+    int32_t* err;
+    int64_t N, chunk, nbags;
+    int32_t B, nseg, G, max_chunks;
+    int32_t shift;
+    uint32_t mask, invalid_key;
+    int32_t by_table;        // keys are table-local (a single table counts as such)
+    int32_t iota;            // the payload is the position
+    int32_t globalize;       // last pass of a table-by-table sort: write linearised keys
+};
 
 // first i in [lo, hi] with a[i] > x   (caller guarantees a[hi] > x)
-__device__ __forceinline__ int64_t upper_bound_i64(const IdxView a, int64_t lo, int64_t hi, int64_t x) {
+template <typename IT>
+__device__ __forceinline__ int64_t upper_bound_i64(const IT* __restrict__ a, int64_t lo, int64_t hi, int64_t x) {
     while (lo < hi) {
         const int64_t mid = lo + ((hi - lo) >> 1);
         if (a[mid] > x) hi = mid;
@@ -24,7 +75,8 @@ __device__ __forceinline__ int64_t upper_bound_i64(const IdxView a, int64_t lo, 
 // The same search by a whole wavefront: 64 probes per round cut the range 64-fold, so 8 M offsets take 4 dependent
 // loads instead of 23.  Every lane returns the result.  Terminates for any contents of a (the range shrinks every
 // round) and never reads outside [lo, hi).
-__device__ __forceinline__ int64_t wave_upper_bound_i64(const IdxView a, int64_t lo, int64_t hi, const int64_t x) {
+template <typename IT>
+__device__ __forceinline__ int64_t wave_upper_bound_i64(const IT* __restrict__ a, int64_t lo, int64_t hi, const int64_t x) {
     const int lane = lane_id();
     while (lo < hi) {
         const int64_t step = (hi - lo + kWave - 1) / kWave;
@@ -40,211 +92,164 @@ __device__ __forceinline__ int64_t wave_upper_bound_i64(const IdxView a, int64_t
     return lo;
 }
 
-// A block owns kLinTile consecutive positions.  It finds the bags that own its first and last position
-// with two binary searches in the global offsets and stages that offsets segment in LDS (relative to the
-// tile start).  Every bag that starts inside the tile then marks its first position, and a running maximum
-// over the positions gives each position the last bag that starts at or before it, i.e. its owner (empty bags
-// start where the next one does and lose against it).
-__global__ __launch_bounds__(kLinThreads) void linearize_kernel(const IdxView indices, const IdxView offsets,
-                                                                const int64_t nbags, const int32_t B,
-                                                                const int64_t* __restrict__ row_base,
-                                                                const uint32_t invalid_key, const bool local_keys,
-                                                                const int64_t N, uint32_t* __restrict__ keys,
-                                                                uint32_t* __restrict__ bag_of_pos, int32_t* err) {
-    constexpr int kItems = kLinTile / kLinThreads;   // positions per thread: kItems rows of 64 per wavefront
-    __shared__ int32_t s_off[kLinTile + 2];
-    __shared__ int32_t s_own[kLinTile];
-    __shared__ int32_t s_wmax[kLinThreads / kWave];
-    __shared__ int64_t s_lo, s_hi;
-    const int64_t p0 = (int64_t)blockIdx.x * kLinTile;
-    const int64_t p1 = (p0 + kLinTile < N) ? p0 + kLinTile : N;
-    if (p0 >= N) return;
-    // owner of p: the bag with offsets[bag] <= p < offsets[bag+1]  ==  (first i with offsets[i] > p) - 1.
-    // Searching i in [0, nbags] and clamping keeps every later access in range even for malformed offsets.
-    // Wavefront 0 searches for the tile's first position, wavefront 1 for its last.
-    if ((threadIdx.x >> 6) < 2) {
-        const bool first = (threadIdx.x >> 6) == 0;
-        const int64_t r = wave_upper_bound_i64(offsets, 0, nbags, first ? p0 : p1 - 1) - 1;
-        if ((threadIdx.x & (kWave - 1)) == 0) *(first ? &s_lo : &s_hi) = r;
+// Inclusive running maximum across a block of kRsThreads threads (smem: kRsWaves words, free again on return).
+__device__ __forceinline__ uint32_t block_incl_max(uint32_t v, uint32_t* smem) {
+    const int l = lane_id();
+#pragma unroll
+    for (int o = 1; o < kWave; o <<= 1) {
+        const uint32_t n = __shfl_up(v, o, kWave);
+        if (l >= o) v = n > v ? n : v;
     }
-    for (int i = threadIdx.x; i < kLinTile; i += kLinThreads) s_own[i] = 0;
-    __syncthreads();
-    int64_t lo = s_lo, hi = s_hi;
-    lo = lo < 0 ? 0 : (lo > nbags - 1 ? nbags - 1 : lo);
-    hi = hi < lo ? lo : (hi > nbags - 1 ? nbags - 1 : hi);
-    const int64_t nb = hi - lo + 1;             // bags touched by this tile (>= 1)
-    const bool staged = nb + 1 <= kLinTile + 2;  // nb+1 offsets entries fit in LDS
-    if (staged) {
-        for (int i = threadIdx.x; i <= (int)nb; i += kLinThreads) {
-            int64_t rel = offsets[lo + i] - p0;
-            rel = rel < -1 ? -1 : (rel > kLinTile ? kLinTile : rel);
-            s_off[i] = (int32_t)rel;
-            if (i >= 1 && i < (int)nb && rel >= 0 && rel < kLinTile) atomicMax(&s_own[rel], i);   // bag lo+i starts here
-        }
-    }
-    __syncthreads();
-    const int lane = lane_id();
     const int w = threadIdx.x >> 6;
-    int32_t own[kItems];
-    if (staged) {
-        // running maximum: along each row of 64 by shuffles, carried from row to row, then across the wavefronts
-        int32_t carry = 0;
+    if (l == kWave - 1) smem[w] = v;
+    __syncthreads();
 #pragma unroll
-        for (int k = 0; k < kItems; ++k) {
-            int32_t v = s_own[w * (kWave * kItems) + k * kWave + lane];
-            for (int o = 1; o < kWave; o <<= 1) {
-                const int32_t up = __shfl_up(v, o, kWave);
-                if (lane >= o) v = up > v ? up : v;
+    for (int i = 0; i < kRsWaves; ++i)
+        if (i < w) v = smem[i] > v ? smem[i] : v;
+    __syncthreads();
+    return v;
+}
+
+// Which chunk is this workgroup's?  Segment borders are offsets[t * B], forced into [0, N] and made ascending, so that
+// the chunks always tile [0, N) exactly, whatever the offsets array holds.  kRsThreads segments per round; every round
+// scans borders and chunk counts.  Workgroup 0 also leaves chunk0 for the binscan, if there is one.
+template <typename IT>
+__device__ __forceinline__ ChunkDesc find_chunk(const SortArgs& a, const uint32_t c, uint32_t* smem, ChunkDesc* s_desc) {
+    if (threadIdx.x == 0) *s_desc = ChunkDesc{0, 0, 0, 0, 0, 0, {0, 0}};
+    __syncthreads();
+    if (a.nseg == 1) {
+        if (threadIdx.x == 0) {
+            const int64_t s = (int64_t)c * a.chunk, n = (a.N + a.chunk - 1) / a.chunk;
+            if (s < a.N) *s_desc = ChunkDesc{(uint32_t)s, (uint32_t)(s + a.chunk < a.N ? s + a.chunk : a.N), 0, 0, (uint32_t)n, 0, {0, 0}};
+            if (c == 0 && a.chunk0) {
+                a.chunk0[0] = 0;
+                a.chunk0[1] = (uint32_t)n;
             }
-            v = v > carry ? v : carry;
-            own[k] = v;
-            carry = __shfl(v, kWave - 1, kWave);
         }
-        if (lane == 0) s_wmax[w] = carry;
         __syncthreads();
-        int32_t prev = 0;
-        for (int ww = 0; ww < w; ++ww) prev = s_wmax[ww] > prev ? s_wmax[ww] : prev;
-#pragma unroll
-        for (int k = 0; k < kItems; ++k) own[k] = own[k] > prev ? own[k] : prev;
+        return *s_desc;
     }
-    // The ids and the row ranges of all of a thread's positions first (a position behind the tile's end reads the
-    // tile's last one), pinned in registers here: left to itself the compiler moves every load into the branch that
-    // uses it and waits for it there, one position after the other.
-    int64_t idv[kItems], bagv[kItems], rbv[kItems], rev[kItems];
-    if (indices.is32) {
-        const int32_t* q = static_cast<const int32_t*>(indices.p);
-#pragma unroll
-        for (int k = 0; k < kItems; ++k) {
-            const int64_t p = p0 + w * (kWave * kItems) + k * kWave + lane;
-            idv[k] = (int64_t)q[p < p1 ? p : p1 - 1];
+    uint32_t carry_b = 0, carry_c = 0;   // border and chunk count before this round's segments
+    for (int t0 = 0; t0 < a.nseg; t0 += kRsThreads) {
+        const int t = t0 + (int)threadIdx.x;
+        uint32_t b1 = 0;                 // end of segment t
+        if (t < a.nseg) {
+            int64_t b = t + 1 == a.nseg ? a.N : (int64_t)static_cast<const IT*>(a.offsets)[(int64_t)(t + 1) * a.B];
+            b = b < 0 ? 0 : (b > a.N ? a.N : b);
+            b1 = (uint32_t)b;
         }
-    } else {
-        const int64_t* q = static_cast<const int64_t*>(indices.p);
-#pragma unroll
-        for (int k = 0; k < kItems; ++k) {
-            const int64_t p = p0 + w * (kWave * kItems) + k * kWave + lane;
-            idv[k] = q[p < p1 ? p : p1 - 1];
+        b1 = block_incl_max(b1 > carry_b ? b1 : carry_b, smem);
+        uint32_t b0 = __shfl_up(b1, 1, kWave);   // its start: the segment before
+        if (lane_id() == kWave - 1) smem[threadIdx.x >> 6] = b1;
+        __syncthreads();
+        if (lane_id() == 0) b0 = threadIdx.x == 0 ? carry_b : smem[(threadIdx.x >> 6) - 1];
+        const uint32_t last = smem[kRsWaves - 1];
+        __syncthreads();
+        const uint32_t n = t < a.nseg ? (uint32_t)(((int64_t)(b1 - b0) + a.chunk - 1) / a.chunk) : 0u;
+        uint32_t tot;
+        const uint32_t f = carry_c + block_excl_scan<kRsThreads>(n, smem, &tot);
+        if (c >= f && c - f < n) {
+            const int64_t s = (int64_t)b0 + (int64_t)(c - f) * a.chunk;
+            const int64_t e = s + a.chunk < (int64_t)b1 ? s + a.chunk : (int64_t)b1;
+            *s_desc = ChunkDesc{(uint32_t)s, (uint32_t)e, (uint32_t)t, f, n, b0, {0, 0}};
         }
-    }
-#pragma unroll
-    for (int k = 0; k < kItems; ++k) {
-        const int64_t p = p0 + w * (kWave * kItems) + k * kWave + lane;
-        int64_t bag;
-        if (staged) bag = lo + own[k];
-        else bag = upper_bound_i64(offsets, lo, hi + 1, p < p1 ? p : p1 - 1) - 1;   // a tile spanning more than kLinTile bags (runs of empty bags)
-        bag = bag < lo ? lo : (bag > hi ? hi : bag);
-        bagv[k] = bag;
-        const int32_t t = (int32_t)(bag / B);
-        rbv[k] = row_base[t];
-        rev[k] = row_base[t + 1];
-    }
-#pragma unroll
-    for (int k = 0; k < kItems; ++k) asm volatile("" : "+v"(idv[k]), "+v"(rbv[k]), "+v"(rev[k]));
-#pragma unroll
-    for (int k = 0; k < kItems; ++k) {
-        const int64_t p = p0 + w * (kWave * kItems) + k * kWave + lane;
-        if (p >= p1) continue;
-        const int64_t bag = bagv[k];
-        const int64_t rb = rbv[k];
-        const int64_t R = rev[k] - rb;
-        const int64_t id = idv[k];
-        // local_keys: the table-local id (an invalid id gets R, one past the table's last row); the sort's last
-        // pass turns it into the linearised key
-        uint32_t key;
-        if (id >= 0 && id < R) {
-            key = local_keys ? (uint32_t)id : (uint32_t)(rb + id);
-        } else {
-            key = local_keys ? (uint32_t)R : invalid_key;
-            atomicOr(err, 1);
+        if (c == 0 && a.chunk0) {
+            if (t < a.nseg) a.chunk0[t] = f;
+            if (t == a.nseg - 1) a.chunk0[a.nseg] = f + n;
         }
-        keys[p] = key;
-        bag_of_pos[p] = (uint32_t)bag;
+        carry_b = last;
+        carry_c += tot;
+        if (carry_c > c && !(c == 0 && a.chunk0)) break;   // (the same for all threads) found
     }
+    __syncthreads();
+    return *s_desc;
 }
 
-hipError_t launch_linearize(const tbe_handle* h, const void* indices_p, const void* offsets_p, int idx32, int32_t B,
-                            int64_t N, uint32_t* keys, uint32_t* bag_of_pos, hipStream_t s) {
-    const IdxView indices{indices_p, idx32}, offsets{offsets_p, idx32};
-    const int64_t nbags = (int64_t)h->T * B;
-    const unsigned grid = (unsigned)((N + kLinTile - 1) / kLinTile);
-    LaunchTimer tm(h, s, "linearize");
-    linearize_kernel<<<grid, kLinThreads, 0, s>>>(indices, offsets, nbags, B, h->d_row_base, (uint32_t)h->total_rows,
-                                                  h->segmented, N, keys, bag_of_pos, h->d_err);
-    tm.done();
-    return hipGetLastError();
-}
-
-// =================================================================================================
-// Segmented LSD radix sort, <= 8 bits per pass.  The positions are cut into segments (one per table, or a single
-// one) and every segment into chunks of at most `chunk` positions; a chunk never crosses a segment border.
-//   plan    : segment borders from offsets, chunk descriptors (once per sort)
-//   hist    : block k counts the digits of chunk k                                   -> ghist[digit][k]
-//   binscan : block d turns ghist[d][*] into an exclusive scan per segment, in place -> bin_tot[segment][d]
-//   scatter : block k ranks its chunk tile by tile and writes (key, val) to its final place inside the segment
-// Chunk k precedes chunk k+1, and the scatter ranks elements in input order, so the sort is stable.
-// The last pass turns table-local keys into linearised ones as it writes them.
-// =================================================================================================
-constexpr int kRsThreads = 256;
-constexpr int kRsWaves = kRsThreads / kWave;
-constexpr int kRsItems = kRadixTile / kRsThreads;  // 16 keys per thread and tile
-constexpr int kRsBins = 256;
-
-struct SortPlan {
-    const uint32_t* bounds;   // [nseg + 1] first position of every segment; bounds[nseg] = N
-    const uint32_t* chunk0;   // [nseg + 1] first chunk of every segment; chunk0[nseg] = number of chunks
-    const uint4* desc;        // [chunks] (first position, end position, segment, -)
-    int nseg;
-    int G;                    // row length of ghist (> number of chunks)
+struct OwnerLds {
+    int64_t lo, hi;
+    int32_t wmax[kRsWaves];
 };
 
-// One workgroup.  Segment borders: offsets[t * B], forced into [0, N] and made ascending, so that the chunks
-// always tile [0, N) exactly, whatever the offsets array holds.
-__global__ __launch_bounds__(1024) void radix_plan_kernel(const IdxView offsets, const int32_t B, const int nseg,
-                                                          const int64_t N, const int64_t chunk,
-                                                          uint32_t* __restrict__ bounds, uint32_t* __restrict__ chunk0,
-                                                          uint4* __restrict__ desc, const int maxc) {
-    __shared__ uint32_t s_b[kMaxSortSegments + 1];
-    __shared__ uint32_t s_c[kMaxSortSegments + 1];
-    for (int t = threadIdx.x; t <= nseg; t += 1024) {
-        int64_t b = (t == 0) ? 0 : (t == nseg ? N : offsets[(int64_t)t * B]);
-        b = b < 0 ? 0 : (b > N ? N : b);
-        s_b[t] = (uint32_t)b;
+// The bag of every position of the tile [p0, p1): thread's item k is position p0 + w*64*ITEMS + k*64 + lane.  Two
+// wavefronts find the bags of the first and the last position among bags [blo, bhi); every bag that starts inside the
+// tile marks its first position in LDS, and a running maximum over the positions gives each position the last bag that
+// starts at or before it, i.e. its owner (empty bags start where the next one does and lose against it).  A tile that
+// spans more bags than it has positions (runs of empty bags) searches position by position instead.  Whatever the
+// offsets hold, the result lies in [blo, bhi).  s_own: 256 * ITEMS words.
+template <typename IT, int ITEMS>
+__device__ __forceinline__ void tile_owners(const IT* __restrict__ offsets, const int64_t blo, const int64_t bhi, const int64_t p0,
+                                            const int64_t p1, int32_t* s_own, OwnerLds* o, uint32_t (&bag)[ITEMS]) {
+    constexpr int kTile = ITEMS * kRsThreads;
+    const int lane = lane_id();
+    const int w = threadIdx.x >> 6;
+    if (w < 2) {
+        const int64_t r = wave_upper_bound_i64(offsets, blo, bhi, w == 0 ? p0 : p1 - 1) - 1;
+        if (lane == 0) *(w == 0 ? &o->lo : &o->hi) = r;
     }
+    for (int i = threadIdx.x; i < kTile; i += kRsThreads) s_own[i] = 0;
     __syncthreads();
-    if (threadIdx.x == 0) {   // running maximum (ascending borders) and chunk counts; nseg is small
-        uint32_t run = 0, c = 0;
-        for (int t = 0; t <= nseg; ++t) {
-            const uint32_t b = s_b[t] > run ? s_b[t] : run;
-            if (t > 0) c += (uint32_t)(((int64_t)b - run + chunk - 1) / chunk);
-            run = b;
-            s_b[t] = b;
-            s_c[t] = c;   // chunks of the segments before t
+    int64_t lo = o->lo, hi = o->hi;
+    lo = lo < blo ? blo : (lo > bhi - 1 ? bhi - 1 : lo);
+    hi = hi < lo ? lo : (hi > bhi - 1 ? bhi - 1 : hi);
+    const int64_t nb = hi - lo + 1;              // bags touched by this tile (>= 1)
+    const bool marked = nb <= kTile;
+    if (marked) {
+        for (int i = 1 + (int)threadIdx.x; i < (int)nb; i += kRsThreads) {
+            const int64_t rel = (int64_t)offsets[lo + i] - p0;
+            if (rel >= 0 && rel < kTile) atomicMax(&s_own[rel], i);   // bag lo+i starts here
         }
     }
     __syncthreads();
-    for (int t = threadIdx.x; t <= nseg; t += 1024) {
-        bounds[t] = s_b[t];
-        chunk0[t] = s_c[t];
-    }
-    // chunk c belongs to the last segment t with chunk0[t] <= c (segments without chunks are skipped by this rule)
-    const uint32_t total = s_c[nseg] < (uint32_t)maxc ? s_c[nseg] : (uint32_t)maxc;
-    for (uint32_t c = threadIdx.x; c < total; c += 1024) {
-        int lo = 0, hi = nseg;   // invariant: s_c[lo] <= c, answer in [lo, hi)
-        while (hi - lo > 1) {
-            const int mid = (lo + hi) >> 1;
-            if (s_c[mid] <= c) lo = mid;
-            else hi = mid;
+    if (marked) {
+        // running maximum, in place: every thread over ITEMS consecutive positions, then across lanes and wavefronts
+        int32_t* const mine = s_own + threadIdx.x * ITEMS;
+        int32_t run[ITEMS];
+#pragma unroll
+        for (int k = 0; k < ITEMS; k += 4) {
+            const int4 v = *reinterpret_cast<const int4*>(mine + k);
+            run[k] = v.x; run[k + 1] = v.y; run[k + 2] = v.z; run[k + 3] = v.w;
         }
-        const int64_t s = (int64_t)s_b[lo] + (int64_t)(c - s_c[lo]) * chunk;
-        const int64_t s1 = s_b[lo + 1];
-        const int64_t e = s + chunk < s1 ? s + chunk : s1;
-        desc[c] = make_uint4((uint32_t)s, (uint32_t)e, (uint32_t)lo, 0u);
+#pragma unroll
+        for (int k = 1; k < ITEMS; ++k) run[k] = run[k] > run[k - 1] ? run[k] : run[k - 1];
+        int32_t top = run[ITEMS - 1];
+#pragma unroll
+        for (int d = 1; d < kWave; d <<= 1) {
+            const int32_t up = __shfl_up(top, d, kWave);
+            if (lane >= d) top = up > top ? up : top;
+        }
+        int32_t prev = __shfl_up(top, 1, kWave);
+        if (lane == 0) prev = 0;
+        if (lane == kWave - 1) o->wmax[w] = top;
+        __syncthreads();
+        for (int ww = 0; ww < w; ++ww) prev = o->wmax[ww] > prev ? o->wmax[ww] : prev;
+#pragma unroll
+        for (int k = 0; k < ITEMS; k += 4)
+            *reinterpret_cast<int4*>(mine + k) = make_int4(run[k] > prev ? run[k] : prev, run[k + 1] > prev ? run[k + 1] : prev,
+                                                           run[k + 2] > prev ? run[k + 2] : prev, run[k + 3] > prev ? run[k + 3] : prev);
+        __syncthreads();
+#pragma unroll
+        for (int k = 0; k < ITEMS; ++k) bag[k] = (uint32_t)(lo + s_own[w * (kWave * ITEMS) + k * kWave + lane]);
+    } else {
+#pragma unroll
+        for (int k = 0; k < ITEMS; ++k) {
+            const int64_t p = p0 + w * (kWave * ITEMS) + k * kWave + lane;
+            int64_t b = upper_bound_i64(offsets, lo, hi + 1, p < p1 ? p : p1 - 1) - 1;
+            bag[k] = (uint32_t)(b < lo ? lo : (b > hi ? hi : b));
+        }
     }
+    __syncthreads();   // s_own may be reused by the caller
 }
 
-// One digit count into the wavefront's private histogram.  When every active lane holds the same digit (the
-// common case for the high digits, because ids arrive grouped by table) one lane adds the whole count instead of
-// 64 lanes queueing on one LDS word.
+// The ids of a thread's items, all loads issued before the first use (a position behind the tile's end reads its last).
+template <typename IT, int ITEMS>
+__device__ __forceinline__ void load_ids(const IT* __restrict__ indices, const int64_t p0, const int64_t p1, IT (&id)[ITEMS]) {
+    const int64_t first = p0 + (threadIdx.x >> 6) * (kWave * ITEMS) + lane_id();
+#pragma unroll
+    for (int k = 0; k < ITEMS; ++k) id[k] = indices[first + k * kWave < p1 ? first + k * kWave : p1 - 1];
+}
+
+// One digit count into a histogram.  When every active lane holds the same digit (the common case for the high digits,
+// because ids arrive grouped by table) one lane adds the whole count instead of 64 lanes queueing on one LDS word.
 __device__ __forceinline__ void hist_add(uint32_t* __restrict__ hw, const uint32_t d, const bool valid) {
     const uint64_t act = __ballot(valid);
     if (act == 0ull) return;
@@ -257,75 +262,90 @@ __device__ __forceinline__ void hist_add(uint32_t* __restrict__ hw, const uint32
     }
 }
 
-// Private histograms per wavefront: lanes are spread over kHistCopies of them, which divides the number of lanes
-// that meet on one LDS word or bank (the kernel is bound by these LDS additions, not by the key stream: 1.04 ms with
-// one copy, 0.83 ms with two, for the three passes of the largest workload).
-constexpr int kHistCopies = 2;
-__global__ __launch_bounds__(kRsThreads) void radix_hist_kernel(const uint32_t* __restrict__ keys, const SortPlan pl,
-                                                                const int shift, const uint32_t mask, const int nbins,
-                                                                uint32_t* __restrict__ ghist) {
-    __shared__ uint32_t h[kHistCopies * kRsWaves][kRsBins];
-    const uint32_t nchunks = pl.chunk0[pl.nseg];
-    if (blockIdx.x >= nchunks) {   // unused column: zeros, so that the scan can run over the whole row
-        for (int d = threadIdx.x; d < nbins; d += kRsThreads) ghist[(size_t)d * pl.G + blockIdx.x] = 0u;
-        return;
+// Private histograms: lanes are spread over kCopies of them, which divides the number of lanes that meet on one LDS word
+// or bank (the kernel is bound by these LDS additions, not by the key stream: 1.04 ms with one copy per wavefront, 0.83 ms
+// with two, for the three passes of the largest workload).
+// IDS: pass 0.  OWNER: keys are linearised over several tables, so a position's table comes from its bag.
+template <typename IT, int NB, int ITEMS, bool IDS, bool OWNER, bool SELF>
+__global__ __launch_bounds__(kRsThreads) void radix_hist_kernel(const SortArgs a) {
+    constexpr int kTile = ITEMS * kRsThreads;
+    constexpr int kCopies = NB >= 2048 ? 1 : 2048 / NB;   // 8 KB of LDS
+    __shared__ uint32_t h[kCopies][NB];
+    __shared__ uint32_t s_scan[kRsWaves];
+    __shared__ ChunkDesc s_desc;
+    __shared__ OwnerLds s_o;
+    __shared__ __align__(16) int32_t s_own[OWNER ? kTile : 1];
+    ChunkDesc ds;
+    if (IDS) {
+        ds = find_chunk<IT>(a, blockIdx.x, s_scan, &s_desc);
+        if (threadIdx.x == 0) a.desc[blockIdx.x] = ds;
+    } else {
+        ds = a.desc[blockIdx.x];
     }
-    for (int i = threadIdx.x; i < kHistCopies * kRsWaves * kRsBins; i += kRsThreads) (&h[0][0])[i] = 0u;
+    if (ds.e <= ds.s) return;
+    for (int i = threadIdx.x; i < kCopies * NB; i += kRsThreads) (&h[0][0])[i] = 0u;
     __syncthreads();
-    uint32_t* hw = h[kHistCopies * (threadIdx.x >> 6) + (threadIdx.x & (kHistCopies - 1))];
-    const uint4 ds = pl.desc[blockIdx.x];
-    const int64_t s = ds.x, e = ds.y;
-    // leading elements up to the next 16-byte boundary, whole uint4 groups, then up to 3 trailing elements
-    int64_t lead = (4 - (s & 3)) & 3;
-    if (lead > e - s) lead = e - s;
-    {
-        const int64_t i = s + threadIdx.x;
-        const bool valid = (int64_t)threadIdx.x < lead;
-        const uint32_t k = valid ? keys[i] : 0u;
-        hist_add(hw, (k >> shift) & mask, valid);
+    uint32_t* hw = h[kCopies >= 8 ? 2 * (threadIdx.x >> 6) + (threadIdx.x & 1) : (threadIdx.x & (kCopies - 1))];
+    const int64_t s = ds.s, e = ds.e;
+    int64_t R = 0;
+    if (IDS && !OWNER) R = a.row_base[ds.seg + 1] - a.row_base[ds.seg];
+    bool bad = false;
+    for (int64_t tile = s; tile < e; tile += kTile) {
+        const int64_t te = tile + kTile < e ? tile + kTile : e;
+        const int64_t first = tile + (threadIdx.x >> 6) * (kWave * ITEMS) + lane_id();
+        uint32_t key[ITEMS];
+        if (IDS) {
+            IT id[ITEMS];
+            load_ids<IT, ITEMS>(static_cast<const IT*>(a.indices), tile, te, id);
+            if (OWNER) {
+                uint32_t bag[ITEMS];
+                tile_owners<IT, ITEMS>(static_cast<const IT*>(a.offsets), 0, a.nbags, tile, te, s_own, &s_o, bag);
+#pragma unroll
+                for (int k = 0; k < ITEMS; ++k) {
+                    const int64_t rb = a.row_base[bag[k] / (uint32_t)a.B], re = a.row_base[bag[k] / (uint32_t)a.B + 1];
+                    const bool ok = id[k] >= 0 && id[k] < re - rb;
+                    bad |= !ok;
+                    key[k] = ok ? (uint32_t)(rb + id[k]) : a.invalid_key;
+                }
+            } else {
+#pragma unroll
+                for (int k = 0; k < ITEMS; ++k) {
+                    const bool ok = id[k] >= 0 && id[k] < R;
+                    bad |= !ok;
+                    key[k] = ok ? (uint32_t)id[k] : (uint32_t)R;
+                }
+            }
+        } else {
+#pragma unroll
+            for (int k = 0; k < ITEMS; ++k) key[k] = a.keys_in[first + k * kWave < te ? first + k * kWave : te - 1];
+        }
+#pragma unroll
+        for (int k = 0; k < ITEMS; ++k) hist_add(hw, (key[k] >> a.shift) & a.mask, first + k * kWave < te);
     }
-    const int64_t s4 = s + lead;
-    const int64_t n4 = (e - s4) >> 2;
-    const uint4* k4 = reinterpret_cast<const uint4*>(keys + s4);
-    for (int64_t base = 0; base < n4; base += kRsThreads) {
-        const int64_t i = base + threadIdx.x;
-        const bool valid = i < n4;
-        uint4 k = make_uint4(0u, 0u, 0u, 0u);
-        if (valid) k = k4[i];
-        hist_add(hw, (k.x >> shift) & mask, valid);
-        hist_add(hw, (k.y >> shift) & mask, valid);
-        hist_add(hw, (k.z >> shift) & mask, valid);
-        hist_add(hw, (k.w >> shift) & mask, valid);
-    }
-    {
-        const int64_t i = s4 + 4 * n4 + threadIdx.x;
-        const bool valid = i < e;
-        const uint32_t k = valid ? keys[i] : 0u;
-        hist_add(hw, (k >> shift) & mask, valid);
-    }
+    if (IDS && bad) atomicOr(a.err, 1);   // (positions behind a tile's end repeat a valid position's id)
     __syncthreads();
-    for (int d = threadIdx.x; d < nbins; d += kRsThreads) {
+    for (int d = threadIdx.x; d < NB; d += kRsThreads) {
         uint32_t c = 0;
 #pragma unroll
-        for (int ww = 0; ww < kHistCopies * kRsWaves; ++ww) c += h[ww][d];
-        ghist[(size_t)d * pl.G + blockIdx.x] = c;
+        for (int q = 0; q < kCopies; ++q) c += h[q][d];
+        if (SELF) static_cast<uint16_t*>(a.ghist)[(size_t)blockIdx.x * NB + d] = (uint16_t)c;
+        else static_cast<uint32_t*>(a.ghist)[(size_t)d * a.G + blockIdx.x] = c;
     }
 }
 
 // grid = nbins blocks; block d scans row d of ghist in place: first over all chunks, then every segment's part is
 // re-based to start at zero; bin_tot[segment][d] = number of keys with digit d in the segment
-__global__ __launch_bounds__(kRsThreads) void radix_binscan_kernel(uint32_t* __restrict__ ghist, const SortPlan pl,
-                                                                   uint32_t* __restrict__ bin_tot) {
+__global__ __launch_bounds__(kRsThreads) void radix_binscan_kernel(const SortArgs a) {
     __shared__ uint32_t smem[kRsWaves];
     __shared__ uint32_t s_b0[kMaxSortSegments];
-    uint32_t* row = ghist + (size_t)blockIdx.x * pl.G;
-    const int nchunks = (int)pl.chunk0[pl.nseg];   // < G; row[nchunks] is an unused column holding zero
+    uint32_t* row = static_cast<uint32_t*>(a.ghist) + (size_t)blockIdx.x * a.G;
+    const int nchunks = (int)a.chunk0[a.nseg];   // < G
     uint32_t carry = 0;
     for (int base = 0; base <= nchunks; base += 4 * kRsThreads) {   // four counts per thread and round
         const int i = base + 4 * (int)threadIdx.x;
         uint32_t v[4];
 #pragma unroll
-        for (int q = 0; q < 4; ++q) v[q] = (i + q <= nchunks) ? row[i + q] : 0u;
+        for (int q = 0; q < 4; ++q) v[q] = (i + q < nchunks) ? row[i + q] : 0u;
         uint32_t tot;
         uint32_t run = carry + block_excl_scan<kRsThreads>(v[0] + v[1] + v[2] + v[3], smem, &tot);
 #pragma unroll
@@ -336,62 +356,88 @@ __global__ __launch_bounds__(kRsThreads) void radix_binscan_kernel(uint32_t* __r
         carry += tot;
     }
     __syncthreads();
-    for (int t = threadIdx.x; t < pl.nseg; t += kRsThreads) {
-        const uint32_t b0 = row[pl.chunk0[t]], b1 = row[pl.chunk0[t + 1]];
+    for (int t = threadIdx.x; t < a.nseg; t += kRsThreads) {
+        const uint32_t b0 = row[a.chunk0[t]], b1 = row[a.chunk0[t + 1]];
         s_b0[t] = b0;
-        bin_tot[(size_t)t * kRsBins + blockIdx.x] = b1 - b0;
+        a.bin_tot[(size_t)t * 256 + blockIdx.x] = b1 - b0;
     }
     __syncthreads();
-    for (int i = threadIdx.x; i < nchunks; i += kRsThreads) row[i] -= s_b0[pl.desc[i].z];
+    for (int i = threadIdx.x; i < nchunks; i += kRsThreads) row[i] -= s_b0[a.desc[i].seg];
 }
 
-// One tile of a chunk.  FULL: all kRadixTile positions exist, so nothing is predicated (all but a chunk's last tile).
-template <bool FULL>
-__device__ __forceinline__ uint32_t scatter_tile(
-    const uint32_t* __restrict__ keys_in, const uint32_t* __restrict__ vals_in, uint32_t* __restrict__ keys_out,
-    uint32_t* __restrict__ vals_out, const int64_t tile, const int64_t e, const int shift, const uint32_t mask,
-    const bool iota_vals, const int globalize, const int64_t* __restrict__ row_base, const int32_t B,
-    const uint32_t invalid_key, const int seg, uint32_t (*s_cnt)[kRsBins], uint32_t* s_base, uint32_t* s_dstart,
-    uint32_t* s_keys, uint32_t* s_vals, uint32_t* s_scan) {
+template <int NB, int ITEMS>
+struct ScatterLds {
+    uint32_t cnt[kRsWaves][NB];     // per-wave digit counts, then per-wave exclusive offsets
+    uint32_t base[NB];              // where this chunk's next element of digit d goes
+    uint32_t dstart[NB];            // start of digit d inside the locally sorted tile
+    __align__(16) uint32_t keys[ITEMS * kRsThreads];
+    uint32_t vals[ITEMS * kRsThreads];
+    uint32_t scan[kRsWaves];
+    OwnerLds own;
+};
+
+// One tile of a chunk.  FULL: all positions of the tile exist, so nothing is predicated (all but a chunk's last tile).
+template <typename IT, int NB, int ITEMS, bool FIRST, bool FULL>
+__device__ __forceinline__ void scatter_tile(const SortArgs& a, const ChunkDesc& ds, const int64_t rb, const int64_t R,
+                                             const int64_t tile, const int64_t e, ScatterLds<NB, ITEMS>* L) {
+    constexpr int K = NB / kRsThreads;   // digits per thread in the scans
+    constexpr int kTile = ITEMS * kRsThreads;
     const int tid = threadIdx.x;
     const int lane = lane_id();
     const int w = tid >> 6;
     const uint64_t lt = lanemask_lt();
-    for (int i = tid; i < kRsWaves * kRsBins; i += kRsThreads) (&s_cnt[0][0])[i] = 0u;
-    __syncthreads();  // also orders the s_base update / s_keys reads of the previous tile
-
-    uint32_t key[kRsItems], val[kRsItems], off[kRsItems];
-    const int64_t wbase = tile + (int64_t)w * (kWave * kRsItems);
-    if (iota_vals) {   // the payload is the position itself (the branch sits outside the loop: inside it the compiler
-                       // waits for every key before it goes on to the next)
+    const int64_t wbase = tile + (int64_t)w * (kWave * ITEMS);
+    uint32_t key[ITEMS], val[ITEMS], off[ITEMS];
+    if (FIRST) {
+        const int64_t te = FULL ? tile + kTile : e;
+        IT id[ITEMS];
+        load_ids<IT, ITEMS>(static_cast<const IT*>(a.indices), tile, te, id);
+        if (!a.iota || !a.by_table) {
+            const int64_t blo = a.by_table ? (int64_t)ds.seg * a.B : 0, bhi = a.by_table ? blo + a.B : a.nbags;
+            tile_owners<IT, ITEMS>(static_cast<const IT*>(a.offsets), blo, bhi, tile, te, reinterpret_cast<int32_t*>(L->keys), &L->own, val);
+        }
+        if (a.by_table) {
 #pragma unroll
-        for (int k = 0; k < kRsItems; ++k) {
-            const int64_t i = wbase + k * kWave + lane;
-            const bool valid = FULL || i < e;
-            key[k] = valid ? keys_in[i] : 0xFFFFFFFFu;
-            val[k] = valid ? (uint32_t)i : 0u;
+            for (int k = 0; k < ITEMS; ++k) key[k] = (id[k] >= 0 && id[k] < R) ? (uint32_t)id[k] : (uint32_t)R;
+        } else {
+#pragma unroll
+            for (int k = 0; k < ITEMS; ++k) {
+                const int64_t b0 = a.row_base[val[k] / (uint32_t)a.B], b1 = a.row_base[val[k] / (uint32_t)a.B + 1];
+                key[k] = (id[k] >= 0 && id[k] < b1 - b0) ? (uint32_t)(b0 + id[k]) : a.invalid_key;
+            }
+        }
+        if (a.iota) {
+#pragma unroll
+            for (int k = 0; k < ITEMS; ++k) val[k] = (uint32_t)(wbase + k * kWave + lane);
         }
     } else {
 #pragma unroll
-        for (int k = 0; k < kRsItems; ++k) {
+        for (int k = 0; k < ITEMS; ++k) {
             const int64_t i = wbase + k * kWave + lane;
             const bool valid = FULL || i < e;
-            key[k] = valid ? keys_in[i] : 0xFFFFFFFFu;
-            val[k] = valid ? vals_in[i] : 0u;
+            key[k] = valid ? a.keys_in[i] : 0xFFFFFFFFu;
+        }
+#pragma unroll
+        for (int k = 0; k < ITEMS; ++k) {
+            const int64_t i = wbase + k * kWave + lane;
+            val[k] = FULL || i < e ? a.vals_in[i] : 0u;
         }
     }
+    for (int i = tid; i < kRsWaves * NB; i += kRsThreads) (&L->cnt[0][0])[i] = 0u;
+    __syncthreads();  // also orders the base update / key reads of the previous tile
     // Rank inside the wave, item by item in input order.  peers = the valid lanes that hold the same digit: per digit
     // bit one ballot, and the lanes that agree with this lane's bit are  ~(ballot ^ (all ones if the bit is set)).
+    constexpr int kBits = NB == 256 ? 8 : (NB == 1024 ? 10 : 11);
 #pragma unroll
-    for (int k = 0; k < kRsItems; ++k) {
+    for (int k = 0; k < ITEMS; ++k) {
         const int64_t i = wbase + k * kWave + lane;
         const bool valid = FULL || i < e;
-        const uint32_t d = (key[k] >> shift) & mask;
+        const uint32_t d = (key[k] >> a.shift) & a.mask;
         const uint64_t vmask = FULL ? ~0ull : __builtin_amdgcn_ballot_w64(valid);
         uint32_t plo = (uint32_t)vmask, phi = (uint32_t)(vmask >> 32);
         const uint32_t dv = (FULL || valid) ? d : 0u;   // lanes without an element vote in no ballot
 #pragma unroll
-        for (int b = 0; b < 8; ++b) {   // (bits above the digit's width are zero in every lane: those rounds change nothing)
+        for (int b = 0; b < kBits; ++b) {   // (bits above the digit's width are zero in every lane: those rounds change nothing)
             const uint64_t m = __builtin_amdgcn_uicmp(dv & (1u << b), 0u, 33 /* != */);   // lanes whose digit has bit b
             const uint32_t sel = (uint32_t)__builtin_amdgcn_sbfe((int)d, b, 1);           // all ones if this lane's has
             plo &= ~((uint32_t)m ^ sel);
@@ -400,152 +446,190 @@ __device__ __forceinline__ uint32_t scatter_tile(
         const uint64_t peers = ((uint64_t)phi << 32) | plo;   // never empty for a valid lane: it holds the lane itself
         uint32_t old = 0;
         const int leader = valid ? (__ffsll((unsigned long long)peers) - 1) : 0;
-        if (valid && lane == leader) old = atomicAdd(&s_cnt[w][d], (uint32_t)__popcll(peers));
+        if (valid && lane == leader) old = atomicAdd(&L->cnt[w][d], (uint32_t)__popcll(peers));
         old = __shfl(old, leader, kWave);
         off[k] = old + (uint32_t)__popcll(peers & lt);
     }
     __syncthreads();
     // per digit: exclusive offsets over the waves, tile total, exclusive scan over the digits
-    uint32_t my_tot = 0;
-    {
+    uint32_t mine[K], sum = 0;
+#pragma unroll
+    for (int j = 0; j < K; ++j) {
         uint32_t run = 0;
 #pragma unroll
         for (int ww = 0; ww < kRsWaves; ++ww) {
-            const uint32_t c = s_cnt[ww][tid];
-            s_cnt[ww][tid] = run;
+            const uint32_t c = L->cnt[ww][tid * K + j];
+            L->cnt[ww][tid * K + j] = run;
             run += c;
         }
-        my_tot = run;
+        mine[j] = run;
+        sum += run;
+    }
+    {
         uint32_t tot;
-        const uint32_t ex = block_excl_scan<kRsThreads>(my_tot, s_scan, &tot);
-        s_dstart[tid] = ex;
+        uint32_t ex = block_excl_scan<kRsThreads>(sum, L->scan, &tot);
+#pragma unroll
+        for (int j = 0; j < K; ++j) {
+            L->dstart[tid * K + j] = ex;
+            ex += mine[j];
+        }
     }
     __syncthreads();
 #pragma unroll
-    for (int k = 0; k < kRsItems; ++k) {
+    for (int k = 0; k < ITEMS; ++k) {
         const int64_t i = wbase + k * kWave + lane;
         if (FULL || i < e) {
-            const uint32_t d = (key[k] >> shift) & mask;
-            const uint32_t pos = s_dstart[d] + s_cnt[w][d] + off[k];
-            s_keys[pos] = key[k];
-            s_vals[pos] = val[k];
+            const uint32_t d = (key[k] >> a.shift) & a.mask;
+            const uint32_t pos = L->dstart[d] + L->cnt[w][d] + off[k];
+            L->keys[pos] = key[k];
+            L->vals[pos] = val[k];
         }
     }
     __syncthreads();
-    const int cnt = FULL ? kRadixTile : (int)(e - tile);
+    const int cnt = FULL ? kTile : (int)(e - tile);
     for (int j = tid; j < cnt; j += kRsThreads) {
-        const uint32_t kk = s_keys[j];
-        const uint32_t d = (kk >> shift) & mask;
-        const uint32_t dst = s_base[d] + ((uint32_t)j - s_dstart[d]);
-        const uint32_t vv = s_vals[j];
-        uint32_t ko = kk;
-        if (globalize) {   // last pass of a segmented sort: table-local id -> linearised row key
-            // the table comes from the lookup's bag where the payload is one (so that key and bag always agree),
-            // else from the segment
-            const int t = globalize == 1 ? (int)(vv / (uint32_t)B) : seg;
-            const int64_t rb = row_base[t];
-            ko = ((int64_t)kk >= row_base[t + 1] - rb) ? invalid_key : (uint32_t)(rb + kk);
-        }
-        keys_out[dst] = ko;
-        vals_out[dst] = vv;
+        const uint32_t kk = L->keys[j];
+        const uint32_t d = (kk >> a.shift) & a.mask;
+        const uint32_t dst = L->base[d] + ((uint32_t)j - L->dstart[d]);
+        // last pass of a table-by-table sort: table-local id -> linearised row key
+        a.keys_out[dst] = a.globalize ? ((int64_t)kk >= R ? a.invalid_key : (uint32_t)(rb + kk)) : kk;
+        a.vals_out[dst] = L->vals[j];
     }
     __syncthreads();
-    return my_tot;
+#pragma unroll
+    for (int j = 0; j < K; ++j) L->base[tid * K + j] += mine[j];
 }
 
-__global__ __launch_bounds__(kRsThreads) void radix_scatter_kernel(const uint32_t* __restrict__ keys_in,
-                                                                   const uint32_t* __restrict__ vals_in,
-                                                                   uint32_t* __restrict__ keys_out,
-                                                                   uint32_t* __restrict__ vals_out, const SortPlan pl,
-                                                                   const int shift, const uint32_t mask, const int nbins,
-                                                                   const uint32_t* __restrict__ ghist,
-                                                                   const uint32_t* __restrict__ bin_tot,
-                                                                   const bool iota_vals, const int globalize,
-                                                                   const int64_t* __restrict__ row_base, const int32_t B,
-                                                                   const uint32_t invalid_key) {
-    __shared__ uint32_t s_cnt[kRsWaves][kRsBins];  // per-wave digit counts, then per-wave exclusive offsets
-    __shared__ uint32_t s_base[kRsBins];           // where this block's next element of digit d goes
-    __shared__ uint32_t s_dstart[kRsBins];         // start of digit d inside the locally sorted tile
-    __shared__ uint32_t s_keys[kRadixTile];
-    __shared__ uint32_t s_vals[kRadixTile];
-    __shared__ uint32_t s_scan[kRsWaves];
-
+template <typename IT, int NB, int ITEMS, bool FIRST, bool SELF>
+__global__ __launch_bounds__(kRsThreads, NB == 256 && !FIRST ? 4 : 1) void radix_scatter_kernel(const SortArgs a) {
+    constexpr int K = NB / kRsThreads;
+    constexpr int kTile = ITEMS * kRsThreads;
+    __shared__ ScatterLds<NB, ITEMS> L;
+    const uint32_t chunk = (blockIdx.x & 7u) * (gridDim.x >> 3) + (blockIdx.x >> 3);   // (the grid is a multiple of 8)
+    if (chunk >= (uint32_t)a.max_chunks) return;
+    const ChunkDesc ds = a.desc[chunk];
+    if (ds.e <= ds.s) return;
     const int tid = threadIdx.x;
-    if (blockIdx.x >= pl.chunk0[pl.nseg]) return;
-    const uint4 ds = pl.desc[blockIdx.x];
-    const int64_t s = ds.x, e = ds.y;
-    const int seg = (int)ds.z;
+    const int64_t rb = a.by_table ? a.row_base[ds.seg] : 0;
+    const int64_t R = a.by_table ? a.row_base[ds.seg + 1] - rb : 0;
     {   // base of every digit for this chunk: segment start + (digits below d, whole segment) + (digit d, the
         // segment's chunks before this one)
-        const uint32_t t = (tid < nbins) ? bin_tot[(size_t)seg * kRsBins + tid] : 0u;
-        uint32_t tot;
-        const uint32_t ex = block_excl_scan<kRsThreads>(t, s_scan, &tot);
-        s_base[tid] = (tid < nbins) ? pl.bounds[seg] + ex + ghist[(size_t)tid * pl.G + blockIdx.x] : 0u;
+        uint32_t tot[K], pre[K], sum = 0;
+#pragma unroll
+        for (int j = 0; j < K; ++j) tot[j] = pre[j] = 0u;
+        if (SELF) {
+            struct __align__(2 * K) Counts { uint16_t c[K]; };
+            const uint16_t* q = static_cast<const uint16_t*>(a.ghist) + (size_t)ds.first * NB + tid * K;
+            const uint32_t before = chunk - ds.first;
+            constexpr int kU = 16;   // chunk histograms in flight
+            for (uint32_t i0 = 0; i0 < ds.count; i0 += kU) {
+                Counts v[kU];
+#pragma unroll
+                for (int u = 0; u < kU; ++u) {
+                    const uint32_t i = i0 + u < ds.count ? i0 + u : ds.count - 1u;
+                    v[u] = *reinterpret_cast<const Counts*>(q + (size_t)i * NB);
+                }
+#pragma unroll
+                for (int u = 0; u < kU; ++u)
+#pragma unroll
+                    for (int j = 0; j < K; ++j) {
+                        tot[j] += i0 + u < ds.count ? (uint32_t)v[u].c[j] : 0u;
+                        pre[j] += i0 + u < before ? (uint32_t)v[u].c[j] : 0u;
+                    }
+            }
+        } else {
+            tot[0] = (uint32_t)tid <= a.mask ? a.bin_tot[(size_t)ds.seg * 256 + tid] : 0u;
+            pre[0] = (uint32_t)tid <= a.mask ? static_cast<const uint32_t*>(a.ghist)[(size_t)tid * a.G + chunk] : 0u;
+        }
+#pragma unroll
+        for (int j = 0; j < K; ++j) sum += tot[j];
+        uint32_t all;
+        uint32_t ex = ds.seg_start + block_excl_scan<kRsThreads>(sum, L.scan, &all);
+#pragma unroll
+        for (int j = 0; j < K; ++j) {
+            L.base[tid * K + j] = ex + pre[j];
+            ex += tot[j];
+        }
     }
-    for (int64_t tile = s; tile < e; tile += kRadixTile) {
-        uint32_t my_tot;
-        if (e - tile >= (int64_t)kRadixTile)
-            my_tot = scatter_tile<true>(keys_in, vals_in, keys_out, vals_out, tile, e, shift, mask, iota_vals,
-                                        globalize, row_base, B, invalid_key, seg, s_cnt, s_base, s_dstart, s_keys, s_vals, s_scan);
-        else
-            my_tot = scatter_tile<false>(keys_in, vals_in, keys_out, vals_out, tile, e, shift, mask, iota_vals,
-                                         globalize, row_base, B, invalid_key, seg, s_cnt, s_base, s_dstart, s_keys, s_vals, s_scan);
-        s_base[tid] += my_tot;
+    const int64_t s = ds.s, e = ds.e;
+    for (int64_t tile = s; tile < e; tile += kTile) {
+        if (e - tile >= (int64_t)kTile) scatter_tile<IT, NB, ITEMS, FIRST, true>(a, ds, rb, R, tile, e, &L);
+        else scatter_tile<IT, NB, ITEMS, FIRST, false>(a, ds, rb, R, tile, e, &L);
     }
 }
 
-hipError_t launch_radix_sort(const tbe_handle* h, const Workspace& w, char* ws, int64_t N, const uint32_t* payload,
-                             const void* offsets, int idx32, int32_t B, int* result_buf, hipStream_t s) {
-    const int passes = h->sort_passes;
-    const int bits = (h->sort_bits + passes - 1) / passes;  // <= 8
-    const int nbins = 1 << bits;
-    const uint32_t mask = (uint32_t)nbins - 1u;
-    uint32_t* ghist = reinterpret_cast<uint32_t*>(ws + w.radix_hist);
-    uint32_t* bin_tot = reinterpret_cast<uint32_t*>(ws + w.bin_tot);
-    SortPlan pl;
-    pl.bounds = reinterpret_cast<const uint32_t*>(ws + w.seg_bounds);
-    pl.chunk0 = reinterpret_cast<const uint32_t*>(ws + w.seg_chunk0);
-    pl.desc = reinterpret_cast<const uint4*>(ws + w.chunk_desc);
-    pl.nseg = w.nseg;
-    pl.G = w.radix_maxc + 1;
+template <typename IT, int NB, int ITEMS, bool SELF>
+static void launch_hist0(const SortArgs& a, const unsigned grid, hipStream_t s) {
+    if (a.by_table) radix_hist_kernel<IT, NB, ITEMS, true, false, SELF><<<grid, kRsThreads, 0, s>>>(a);
+    else radix_hist_kernel<IT, NB, ITEMS, true, true, SELF><<<grid, kRsThreads, 0, s>>>(a);
+}
+
+template <int NB, int ITEMS, bool SELF>
+static void launch_pass(const tbe_handle* h, const SortArgs& a, const SortShape& sh, bool first, bool idx32, hipStream_t s) {
+    const unsigned grid = (unsigned)sh.max_chunks;
+    const unsigned sgrid = (grid + 7u) & ~7u;
     {
-        LaunchTimer tm(h, s, "radix_plan");
-        radix_plan_kernel<<<1, 1024, 0, s>>>(IdxView{offsets, idx32}, B, w.nseg, N, w.radix_chunk,
-                                             reinterpret_cast<uint32_t*>(ws + w.seg_bounds),
-                                             reinterpret_cast<uint32_t*>(ws + w.seg_chunk0),
-                                             reinterpret_cast<uint4*>(ws + w.chunk_desc), w.radix_maxc);
+        LaunchTimer tm(h, s, "radix_hist");
+        if (!first) radix_hist_kernel<int32_t, NB, ITEMS, false, false, SELF><<<grid, kRsThreads, 0, s>>>(a);
+        else if (idx32) launch_hist0<int32_t, NB, ITEMS, SELF>(a, grid, s);
+        else launch_hist0<int64_t, NB, ITEMS, SELF>(a, grid, s);
         tm.done();
     }
-    const int grid = w.radix_maxc;
-    int cur = 0;
-    for (int p = 0; p < passes; ++p) {
-        const uint32_t* kin = reinterpret_cast<const uint32_t*>(ws + w.keys[cur]);
-        const uint32_t* vin = (p == 0 && payload) ? payload : reinterpret_cast<const uint32_t*>(ws + w.vals[cur]);
-        uint32_t* kout = reinterpret_cast<uint32_t*>(ws + w.keys[cur ^ 1]);
-        uint32_t* vout = reinterpret_cast<uint32_t*>(ws + w.vals[cur ^ 1]);
-        const int shift = p * bits;
-        {
-            LaunchTimer tm(h, s, "radix_hist");
-            radix_hist_kernel<<<grid + 1, kRsThreads, 0, s>>>(kin, pl, shift, mask, nbins, ghist);
-            tm.done();
-        }
-        {
-            LaunchTimer tm(h, s, "radix_binscan");
-            radix_binscan_kernel<<<nbins, kRsThreads, 0, s>>>(ghist, pl, bin_tot);
-            tm.done();
-        }
-        {
-            LaunchTimer tm(h, s, "radix_scatter");
-            // the last pass of a segmented sort writes linearised keys: table from the bag id (pooled) or the segment
-            const int globalize = (h->segmented && p == passes - 1) ? (payload ? 1 : 2) : 0;
-            radix_scatter_kernel<<<grid, kRsThreads, 0, s>>>(kin, vin, kout, vout, pl, shift, mask, nbins, ghist, bin_tot,
-                                                             p == 0 && !payload, globalize, h->d_row_base, B,
-                                                             (uint32_t)h->total_rows);
-            tm.done();
-        }
-        cur ^= 1;
+    if (!SELF) {
+        LaunchTimer tm(h, s, "radix_binscan");
+        radix_binscan_kernel<<<a.mask + 1u, kRsThreads, 0, s>>>(a);
+        tm.done();
     }
-    *result_buf = cur;
+    LaunchTimer tm(h, s, "radix_scatter");
+    if (!first) radix_scatter_kernel<int32_t, NB, ITEMS, false, SELF><<<sgrid, kRsThreads, 0, s>>>(a);
+    else if (idx32) radix_scatter_kernel<int32_t, NB, ITEMS, true, SELF><<<sgrid, kRsThreads, 0, s>>>(a);
+    else radix_scatter_kernel<int64_t, NB, ITEMS, true, SELF><<<sgrid, kRsThreads, 0, s>>>(a);
+    tm.done();
+}
+
+hipError_t launch_sort(const tbe_handle* h, const Workspace& w, char* ws, const void* indices, const void* offsets, int idx32,
+                       int32_t B, int64_t N, bool seq, hipStream_t s) {
+    const SortShape& sh = w.sort;
+    SortArgs a;
+    a.indices = indices;
+    a.offsets = offsets;
+    a.row_base = h->d_row_base;
+    a.desc = reinterpret_cast<ChunkDesc*>(ws + w.chunk_desc);
+    a.chunk0 = sh.self_scan ? nullptr : reinterpret_cast<uint32_t*>(ws + w.seg_chunk0);
+    a.ghist = ws + w.radix_hist;
+    a.bin_tot = reinterpret_cast<uint32_t*>(ws + w.bin_tot);
+    a.err = h->d_err;
+    a.N = N;
+    a.chunk = sh.chunk;
+    a.nbags = (int64_t)h->T * B;
+    a.B = B;
+    a.nseg = sh.nseg;
+    a.G = sh.max_chunks + 1;
+    a.max_chunks = sh.max_chunks;
+    a.mask = (1u << sh.bits) - 1u;
+    a.invalid_key = (uint32_t)h->total_rows;
+    a.by_table = h->segmented || h->T == 1;
+    a.iota = seq;
+    for (int p = 0; p < sh.passes; ++p) {
+        a.keys_in = reinterpret_cast<const uint32_t*>(ws + w.keys[p & 1]);
+        a.vals_in = reinterpret_cast<const uint32_t*>(ws + w.vals[p & 1]);
+        a.keys_out = reinterpret_cast<uint32_t*>(ws + w.keys[(p & 1) ^ 1]);
+        a.vals_out = reinterpret_cast<uint32_t*>(ws + w.vals[(p & 1) ^ 1]);
+        a.shift = p * sh.bits;
+        a.globalize = h->segmented && p == sh.passes - 1;
+        const bool first = p == 0;
+        const bool idx = idx32 != 0;
+        // (the digits a.mask can hold never exceed the bins a kernel is compiled for)
+        if (!sh.self_scan && sh.bins == 256 && sh.tile == 4096) launch_pass<256, 16, false>(h, a, sh, first, idx, s);
+        else if (sh.self_scan && sh.bins == 256 && sh.tile == 4096) launch_pass<256, 16, true>(h, a, sh, first, idx, s);
+        else if (sh.self_scan && sh.bins == 256 && sh.tile == 2048) launch_pass<256, 8, true>(h, a, sh, first, idx, s);
+        else if (sh.self_scan && sh.bins == 1024 && sh.tile == 2048) launch_pass<1024, 8, true>(h, a, sh, first, idx, s);
+        else if (sh.self_scan && sh.bins == 2048 && sh.tile == 2048) launch_pass<2048, 8, true>(h, a, sh, first, idx, s);
+        else if (sh.self_scan && sh.bins == 256 && sh.tile == 1024) launch_pass<256, 4, true>(h, a, sh, first, idx, s);
+        else if (sh.self_scan && sh.bins == 1024 && sh.tile == 1024) launch_pass<1024, 4, true>(h, a, sh, first, idx, s);
+        else if (sh.self_scan && sh.bins == 2048 && sh.tile == 1024) launch_pass<2048, 4, true>(h, a, sh, first, idx, s);
+        else return hipErrorInvalidValue;
+    }
     return hipGetLastError();
 }
 
@@ -598,11 +682,8 @@ __global__ __launch_bounds__(kRleThreads) void rle_count_kernel(const uint32_t* 
     }
 }
 
-// single block: exclusive scan of the per-tile head counts in place; writes num_unique and the closing
-// seg_start entry.
-__global__ __launch_bounds__(1024) void rle_scan_kernel(uint32_t* __restrict__ block_counts, const int nblocks,
-                                                        const int64_t N, uint32_t* __restrict__ seg_start,
-                                                        uint32_t* __restrict__ counters) {
+// single block, batches of many tiles: exclusive scan of the per-tile head counts in place
+__global__ __launch_bounds__(1024) void rle_scan_kernel(uint32_t* __restrict__ block_counts, const int nblocks) {
     __shared__ uint32_t smem[1024 / kWave];
     uint32_t carry = 0;
     for (int base = 0; base < nblocks; base += 4 * 1024) {   // four counts per thread and round: a quarter of the barriers
@@ -619,28 +700,70 @@ __global__ __launch_bounds__(1024) void rle_scan_kernel(uint32_t* __restrict__ b
         }
         carry += tot;
     }
-    if (threadIdx.x == 0) {
-        counters[0] = carry;  // num_unique
-        seg_start[carry] = (uint32_t)N;
-    }
 }
 
-// Writes unique_rows and seg_start: element i is a head if its key differs from its predecessor's.
+// Writes unique_rows, seg_start and num_unique: element i is a head if its key differs from its predecessor's.  The
+// number of heads before the tile comes from, in ascending number of tiles (every variant saves a launch of about 4 us
+// against the next): counting them in the keys before the tile (kRleFromKeys), adding up the counts of the tiles before
+// it (kRleFromCounts), or the scanned counts (kRleFromScan).
+enum { kRleFromKeys, kRleFromCounts, kRleFromScan };
+constexpr int kRleKeysTiles = 16;      // at most 15 tiles of keys to look through: 30 uint4 per thread
+constexpr int kRleCountsTiles = 2048;  // at most 8 counts per thread
+template <int MODE>
 __global__ __launch_bounds__(kRleThreads) void rle_write_kernel(const uint32_t* __restrict__ keys, const int64_t N,
-                                                                const int ntiles,
                                                                 const uint32_t* __restrict__ block_base,
                                                                 uint32_t* __restrict__ unique_rows,
-                                                                uint32_t* __restrict__ seg_start) {
+                                                                uint32_t* __restrict__ seg_start,
+                                                                uint32_t* __restrict__ counters) {
     __shared__ uint32_t s_run[kRleRuns];
+    __shared__ uint32_t s_sum[kRleThreads / kWave];
+    __shared__ uint32_t s_heads;
     const int lane = lane_id();
     const int w = threadIdx.x >> 6;
     const uint64_t lt = lanemask_lt();
     const uint32_t tile = blockIdx.x;
-    if (tile >= (uint32_t)ntiles) return;
     const int64_t base = (int64_t)tile * kRleTile;
     uint64_t heads[kRleItems];
     bool head[kRleItems];
     head_flags(keys, base, N, head);
+    uint32_t before = 0;
+    if (MODE == kRleFromKeys) {
+        // (base is a multiple of 4, and keys[base] exists: every quadruple of the keys before it and its successor do)
+        const uint4* k4 = reinterpret_cast<const uint4*>(keys);
+        const int n4 = (int)(base >> 2);
+        for (int q0 = 0; q0 < n4; q0 += 8 * kRleThreads) {
+            uint4 x[8];
+            uint32_t nx[8];
+#pragma unroll
+            for (int u = 0; u < 8; ++u) {
+                const int q = q0 + u * kRleThreads + (int)threadIdx.x;
+                const int qc = q < n4 ? q : 0;
+                x[u] = k4[qc];
+                nx[u] = keys[4 * (qc + 1)];
+            }
+#pragma unroll
+            for (int u = 0; u < 8; ++u) {   // heads among the positions 4q+1 .. 4q+4
+                const bool in = q0 + u * kRleThreads + (int)threadIdx.x < n4;
+                const uint32_t c = (x[u].y != x[u].x) + (x[u].z != x[u].y) + (x[u].w != x[u].z) + (nx[u] != x[u].w);
+                before += in ? c : 0u;
+            }
+        }
+    } else if (MODE == kRleFromCounts) {
+        for (uint32_t i0 = 0; i0 < tile; i0 += 4 * kRleThreads) {
+            uint32_t v[4];
+#pragma unroll
+            for (int u = 0; u < 4; ++u) {
+                const uint32_t i = i0 + u * kRleThreads + threadIdx.x;
+                v[u] = block_base[i < tile ? i : 0u];
+            }
+#pragma unroll
+            for (int u = 0; u < 4; ++u) before += i0 + u * kRleThreads + threadIdx.x < tile ? v[u] : 0u;
+        }
+    }
+    if (MODE != kRleFromScan) {
+        const uint32_t inc = wave_incl_scan(before);
+        if (lane == kWave - 1) s_sum[w] = inc;
+    }
 #pragma unroll
     for (int k = 0; k < kRleItems; ++k) {
         heads[k] = __ballot(head[k]);
@@ -651,9 +774,19 @@ __global__ __launch_bounds__(kRleThreads) void rle_write_kernel(const uint32_t* 
         const uint32_t v = (threadIdx.x < kRleRuns) ? s_run[threadIdx.x] : 0u;
         const uint32_t inc = wave_incl_scan(v);
         if (threadIdx.x < kRleRuns) s_run[threadIdx.x] = inc - v;
+        if (threadIdx.x == kWave - 1) s_heads = inc;
     }
     __syncthreads();
-    const uint32_t bb = block_base[tile];
+    uint32_t bb;
+    if (MODE == kRleFromScan) {
+        bb = block_base[tile];
+    } else {
+        bb = 0;
+#pragma unroll
+        for (int i = 0; i < kRleThreads / kWave; ++i) bb += s_sum[i];
+        // counting in the keys sees position base itself (a head of this tile, if it is one) but not position 0
+        if (MODE == kRleFromKeys && tile > 0) bb += 1u - (keys[base] != keys[base - 1] ? 1u : 0u);
+    }
 #pragma unroll
     for (int k = 0; k < kRleItems; ++k) {
         if ((heads[k] >> lane) & 1ull) {
@@ -663,6 +796,11 @@ __global__ __launch_bounds__(kRleThreads) void rle_write_kernel(const uint32_t* 
             seg_start[u] = (uint32_t)i;
         }
     }
+    if (tile == gridDim.x - 1 && threadIdx.x == 0) {
+        const uint32_t U = bb + s_heads;
+        counters[0] = U;
+        seg_start[U] = (uint32_t)N;
+    }
 }
 
 hipError_t launch_run_lengths(const tbe_handle* h, const Workspace& w, char* ws, int sorted, int64_t N, hipStream_t s) {
@@ -671,21 +809,22 @@ hipError_t launch_run_lengths(const tbe_handle* h, const Workspace& w, char* ws,
     uint32_t* counters = reinterpret_cast<uint32_t*>(ws + w.counters);
     uint32_t* unique_rows = reinterpret_cast<uint32_t*>(ws + w.vals[sorted ^ 1]);
     uint32_t* seg_start = reinterpret_cast<uint32_t*>(ws + w.seg_start);
-    {
+    const int n = w.rle_blocks;
+    if (n > kRleKeysTiles) {
         LaunchTimer tm(h, s, "rle_count");
-        rle_count_kernel<<<w.rle_blocks, kRleThreads, 0, s>>>(keys_sorted, N, counts);
+        rle_count_kernel<<<n, kRleThreads, 0, s>>>(keys_sorted, N, counts);
         tm.done();
     }
-    {
+    if (n > kRleCountsTiles) {
         LaunchTimer tm(h, s, "rle_scan");
-        rle_scan_kernel<<<1, 1024, 0, s>>>(counts, w.rle_blocks, N, seg_start, counters);
+        rle_scan_kernel<<<1, 1024, 0, s>>>(counts, n);
         tm.done();
     }
-    {
-        LaunchTimer tm(h, s, "rle_write");
-        rle_write_kernel<<<w.rle_blocks, kRleThreads, 0, s>>>(keys_sorted, N, w.rle_blocks, counts, unique_rows, seg_start);
-        tm.done();
-    }
+    LaunchTimer tm(h, s, "rle_write");
+    if (n <= kRleKeysTiles) rle_write_kernel<kRleFromKeys><<<n, kRleThreads, 0, s>>>(keys_sorted, N, counts, unique_rows, seg_start, counters);
+    else if (n <= kRleCountsTiles) rle_write_kernel<kRleFromCounts><<<n, kRleThreads, 0, s>>>(keys_sorted, N, counts, unique_rows, seg_start, counters);
+    else rle_write_kernel<kRleFromScan><<<n, kRleThreads, 0, s>>>(keys_sorted, N, counts, unique_rows, seg_start, counters);
+    tm.done();
     return hipGetLastError();
 }
 
