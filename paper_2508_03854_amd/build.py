@@ -12,7 +12,7 @@ ROOT = os.path.dirname(HERE)
 CSRC = os.path.join(HERE, "csrc")
 OBJ = os.path.join(HERE, "_build")
 LIB = os.path.join(HERE, "libtbe355.so")
-SOURCES = ["tbe_api.hip", "tbe_forward.hip", "tbe_sort.hip", "tbe_backward.hip", "tbe_sync.hip", "tbe_calibrate.hip"]
+SOURCES = ["tbe_api.hip", "tbe_forward.hip", "tbe_sort.hip", "tbe_lists.hip", "tbe_dense.hip", "tbe_backward.hip", "tbe_sync.hip", "tbe_calibrate.hip"]
 HIPCC = os.environ.get("HIPCC", "/opt/rocm/bin/hipcc")
 FLAGS = ["--offload-arch=gfx950", "-O3", "-std=c++17", "-fPIC", "-Wall", "-Wno-unused-function",
          "-Xclang", "-target-feature", "-Xclang", "-packed-fp32-ops",
@@ -65,7 +65,7 @@ def build(force: bool = True, verbose: bool = False) -> str:
                 print(r.stderr, file=sys.stderr)
         return o
 
-    with ThreadPoolExecutor(max_workers=4) as ex:
+    with ThreadPoolExecutor(max_workers=8) as ex:
         objs = list(ex.map(compile_one, SOURCES))
     if force or not _newer(LIB, objs):
         cmd = [HIPCC, "--offload-arch=gfx950", "-shared", "-fPIC", "-o", LIB] + objs

@@ -51,7 +51,23 @@ SortShape sort_shape(const tbe_handle* h, int64_t N) {
     return sh;
 }
 
-Workspace carve(const tbe_handle* h, int64_t N) {
+// A row with more than this many lookups is long, i.e. shared out to several wavefronts in parts of this size.  A wavefront
+// walks 512 lookups of a wide row in about 60 us, so small batches, whose row updates take less than that, cut finer; the
+// borders follow from the memory of the partial sums (at most 2 n / part slots): never more than n / 48 plus a constant.
+static uint32_t long_min_of(int64_t N) {
+    return N <= ((int64_t)1 << 17) ? 64u : (N <= ((int64_t)3 << 17) ? 128u : (N <= ((int64_t)3 << 19) ? 256u : 512u));
+}
+// per_part(N / part) with the parts of this batch or of any smaller one: ascending in N
+static int64_t most_parts(int64_t N) {
+    int64_t m = 0;
+    for (const int64_t top : {(int64_t)1 << 17, (int64_t)3 << 17, (int64_t)3 << 19, N}) {
+        const int64_t n = top < N ? top : N;
+        m = std::max(m, n / (int64_t)long_min_of(n) + 1);
+    }
+    return m;
+}
+
+Workspace carve(const tbe_handle* h, int32_t B, int64_t N, bool allow_dense) {
     Workspace w;
     memset(&w, 0, sizeof(w));
     const size_t n = (size_t)(N > 0 ? N : 1);
@@ -67,41 +83,46 @@ Workspace carve(const tbe_handle* h, int64_t N) {
     w.vals[0] = take(4 * (n + 1));
     w.vals[1] = take(4 * (n + 1));
     w.seg_start = take(4 * (n + 1));
-    w.sort = sort_shape(h, N > 0 ? N : 1);
+    w.counters = take(4 * kCounterWords);
+    w.long_min = long_min_of((int64_t)n);
+    w.cap_long = most_parts((int64_t)n);           // at most n / (long_min + 1) rows are long
+    w.cap_main = 2 * w.cap_long + 1;               // ceil(len / part) slots for a row of len > part lookups
+    w.long_rows = take(8 * (size_t)w.cap_long);
+    w.long_list = take(16 * (size_t)w.cap_long);
+    w.unit_list = take(8 * (size_t)w.cap_main);
+    const bool hint = h->T <= kMaxSortSegments;
+    w.hot_ids = take(hint ? 4 * (size_t)kHotRows * (size_t)h->T : 0);
+    w.hot_n = take(hint ? 4 * (size_t)h->T : 0);
+    w.seq_gbase = take(8 * (size_t)h->T);
+    // Dense rows: some table's gradient block is large, and the batch could hold two lookups of them per bag.  A dense row
+    // leaves one partial sum per chunk of bags: enough chunks for about a thousand workgroups in all, at most 32.
+    w.dense = allow_dense && h->T <= kMaxSortSegments && (uint64_t)B * (uint64_t)h->maxD * 4u > ((uint64_t)2 << 20);
+    if (w.dense) {
+        w.dense_blocks = ((uint32_t)B + kDenseBags - 1) / kDenseBags;
+        const uint32_t want = h->T >= 1024 ? 1u : (h->T <= 32 ? 32u : 1024u / (uint32_t)h->T);
+        const uint32_t chunks = want < w.dense_blocks ? want : w.dense_blocks;
+        w.dense_per_chunk = (w.dense_blocks + chunks - 1) / chunks;
+        w.dense_chunks = (w.dense_blocks + w.dense_per_chunk - 1) / w.dense_per_chunk;
+        w.dense_n = take(4 * (size_t)h->T);
+        w.dense_rows = take(4 * (size_t)h->T * kDenseRows);
+        w.dense_index = take(4 * (size_t)h->T * kDenseRows * (w.dense_blocks + 1));
+    }
+    const size_t shared = off;
+    // while the sort runs
+    w.sort = sort_shape(h, (int64_t)n);
     // (8-bit digits in a handle of many tables may exceed the cap; their histograms grow with N by themselves)
     const size_t least8 = 2 * 256 * (size_t)(w.sort.max_chunks + 1);
-    w.radix_hist = take(std::max(std::max(w.sort.hist_bytes, hist_cap(N)), least8));
+    w.radix_hist = take(std::max(std::max(w.sort.hist_bytes, hist_cap((int64_t)n)), least8));
     w.bin_tot = take(w.sort.self_scan ? 0 : 4 * 256 * (size_t)w.sort.nseg);
     w.seg_chunk0 = take(w.sort.self_scan ? 0 : 4 * (size_t)(w.sort.nseg + 1));
     w.chunk_desc = take(32 * (size_t)w.sort.max_chunks);
     w.rle_blocks = (int)(((int64_t)n + kRleTile - 1) / kRleTile);
-    w.rle_counts = take(4 * (size_t)(w.rle_blocks + 1));
-    w.counters = take(4 * kCounterWords);
-    // Rows with more than kSegChunk lookups (at most n / (kSegChunk + 1) of them) are reduced into partial sums of
-    // maxD floats each.  In the worst case - every lookup in a row just above a threshold - they would need n / 51
-    // slots (16 to 20 bytes per lookup at 256 columns); the area holds n / 192 + 4096 (a skewed batch's few hundred
-    // thousand hot rows use a fifth of that at the largest workload), slots are given out in row order, and a row
-    // that finds none left is reduced by the kernel that applies its step.  Behind it: kDenseChunks slots for each of
-    // the at most kDenseRows dense rows of every table.
-    w.cap_long = (int64_t)n / (kSegChunk + 1) + 1;
-    w.cap_main = (int64_t)n / 192 + 4096;
-    w.cap_chunks = w.cap_main + (int64_t)kDenseChunks * kDenseRows * h->T;
-    // work units: one per long row, or len/(8*256) + 2 <= len/1024 for the heaviest, or ceil(len/512) <= len/256 shares
-    w.cap_units = w.cap_long + (int64_t)n / 1024 + (int64_t)n / 256 + 2;
-    w.long_tiles = (int)(((int64_t)n + 1023) / 1024);   // unique rows <= lookups
-    w.tile_long = take(4 * (size_t)(w.long_tiles + 1));
-    w.tile_slots = take(4 * (size_t)(w.long_tiles + 1));
-    w.unit_list = take(8 * (size_t)w.cap_units);
-    w.bounds = take(4 * (size_t)(kMaxSlices + 1) * (size_t)w.cap_long);
-    w.long_tables = take(4 * 3 * (size_t)(h->T + 1));
-    w.tickets = take(4 * (size_t)kTicketWords);   // directly behind long_tables: one loop clears both
-    w.seq_gbase = take(8 * (size_t)(h->T + 1));
-    w.dense_rows = take(4 * (size_t)kDenseRows * (size_t)h->T);
-    w.dense_n = take(4 * (size_t)h->T);
-    w.dense_bounds = take(4 * (size_t)kDenseRows * (kDenseChunks + 1) * (size_t)h->T);
-    w.long_list = take(16 * (size_t)w.cap_long);
-    w.partial = take(4 * (size_t)w.cap_chunks * (size_t)h->maxD);
+    w.rle_counts = take(8 * (size_t)w.rle_blocks);
     w.total = off;
+    // while a step is applied
+    off = shared;
+    w.partial = take(4 * ((size_t)w.cap_main + (w.dense ? (size_t)h->T * kDenseRows * w.dense_chunks : 0)) * (size_t)h->maxD);
+    w.total = std::max(w.total, off);
     return w;
 }
 
@@ -303,7 +324,7 @@ tbe_status tbe_workspace_bytes(const tbe_handle* h, int32_t B, int64_t max_nnz, 
     if (!h || !bytes) return TBE_EINVAL;
     const tbe_status st = check_batch(h, B, max_nnz);
     if (st != TBE_OK) return st;
-    *bytes = carve(h, max_nnz).total;
+    *bytes = carve(h, B, max_nnz).total;
     return TBE_OK;
 }
 
@@ -359,7 +380,9 @@ static tbe_status backward_impl(const tbe_handle* h, const void* grad_out, tbe_i
         return TBE_EINVAL;
     if (nnz == 0) return TBE_OK;  // no id appears in the batch: no row has a gradient
     if (!workspace || !aligned(workspace, 256)) return TBE_EINVAL;
-    const Workspace w = carve(h, nnz);
+    // (the library's own scratch array may be too small for the dense rows: they are then left out)
+    const Workspace whole = carve(h, B, nnz);
+    const Workspace w = workspace == h->static_scratch && workspace_bytes < whole.total ? carve(h, B, nnz, false) : whole;
     if (workspace_bytes < w.total) return TBE_EWORKSPACE;
     char* ws = static_cast<char*>(workspace);
     hipStream_t s = static_cast<hipStream_t>(hip_stream);
@@ -371,10 +394,12 @@ static tbe_status backward_impl(const tbe_handle* h, const void* grad_out, tbe_i
         if (e != hipSuccess) return TBE_EHIP;
         e = launch_run_lengths(h, w, ws, buf, nnz, s);
         if (e != hipSuccess) return TBE_EHIP;
+        e = launch_lists(h, w, ws, offsets, idx32, B, seq, grad_elems, s);
+        if (e != hipSuccess) return TBE_EHIP;
     }
     if (!apply) return TBE_OK;
-    e = launch_segment_update(h, w, ws, buf ^ 1, grad_out, (int)grad_dtype, offsets, idx32, B, pooling, lr, eps,
-                              momentum_scale, tables, state, seq, grad_elems, s);
+    e = launch_segment_update(h, w, ws, grad_out, (int)grad_dtype, offsets, idx32, B, pooling, lr, eps, momentum_scale, tables,
+                              state, seq, s);
     return e == hipSuccess ? TBE_OK : TBE_EHIP;
 }
 
@@ -395,7 +420,7 @@ tbe_status tbe_backward_rowwise_adagrad_static(const tbe_handle* h, const void* 
     if (!h || !state) return TBE_EINVAL;
     const tbe_status st = check_batch(h, B, nnz);
     if (st != TBE_OK) return st;
-    if (carve(h, nnz).total > (size_t)TBE_STATIC_SCRATCH_BYTES) return TBE_EWORKSPACE;   // beyond the fixed array
+    if (carve(h, B, nnz, false).total > (size_t)TBE_STATIC_SCRATCH_BYTES) return TBE_EWORKSPACE;   // beyond the fixed array
     if (!h->static_scratch) return TBE_EHIP;
     // per-kernel timing creates events and grows a host-side list on first use: not in a call that allocates nothing
     tbe_handle* hm = const_cast<tbe_handle*>(h);
@@ -477,7 +502,7 @@ tbe_status tbe_debug_sorted(const tbe_handle* h, void* workspace, int32_t B, int
     if (!h || !workspace) return TBE_EINVAL;
     const tbe_status st = check_batch(h, B, nnz);
     if (st != TBE_OK) return st;
-    const Workspace w = carve(h, nnz);
+    const Workspace w = carve(h, B, nnz);
     const int buf = w.sort.passes & 1;  // every pass flips the double buffer, starting from 0
     char* ws = static_cast<char*>(workspace);
     if (keys_sorted) *keys_sorted = reinterpret_cast<const uint32_t*>(ws + w.keys[buf]);

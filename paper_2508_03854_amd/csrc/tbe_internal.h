@@ -11,20 +11,18 @@
 namespace tbe {
 
 // ---- tunables that fix the workspace layout -------------------------------------------------
-constexpr int kSegChunk = 512;         // a unique row with more lookups than this is split into chunks of this size
 constexpr int kRadixTile = 4096;  // elements per radix-sort tile (256 threads x 16) of a large batch; smaller ones take 2048 or 1024
 constexpr int kRadixMaxBlocks = 8192;  // large batches: each radix block owns one contiguous slice of the input
 constexpr int kRleTile = 2048;  // elements per run-length tile (at most 4096: one wavefront scans its runs of 64)
-constexpr int kMaxSlices = 64;         // sub-slices of one table's gradient block (8 XCDs x up to 8 sweeps)
+constexpr int64_t kRleOneBlock = 32768;  // batches up to this size are segmented by one workgroup
+constexpr int kMaxParts = 1024;          // parts that a long row is cut into at most
 constexpr int kMaxSortSegments = 4096;  // tables beyond this are sorted as one segment on the linearised key
-constexpr int kDenseRows = 16;   // rows per table that the dense-row kernel reduces (multiple of 4)
-constexpr int kDenseChunks = 32;            // bag chunks (= partial sums) per dense row
+constexpr int kDenseRows = 128;  // rows per table that the dense-row kernel reduces at most (multiple of 32)
+constexpr int kDenseBags = 256;  // bags per block of that kernel
 constexpr int kFwdGroupMaxLanes = 32;   // rows of at most this many lanes use one bag per lane group
 constexpr int kHotRows = 256;           // rows per table that the forward may hold in LDS (the handle's hot-row list)
 constexpr int kMaxReplicas = 16;        // replicas of one buffer that tbe_replica_mean averages in one call
-constexpr int kTicketStride = 32;       // words between two ticket counters: each sits in a 128-byte line of its own
-constexpr int kTicketWords = (kMaxSlices / 8) * 8 * kTicketStride;  // one counter per (sweep, XCD)
-constexpr int kCounterWords = 64;      // device counters: [0]=U [1]=long rows [3]=units
+constexpr int kCounterWords = 64;      // device counters: [0]=U [1]=long rows [3]=units [4]=apply nothing
 
 struct TimingSlot {
     const char* name;
@@ -96,16 +94,20 @@ struct Workspace {
     // keys/vals: radix double buffers of N+1 words each.  The payload of a key is the linear bag id of its lookup
     // (pooled calls) or its position (non-pooled calls), so vals[sorted] is the per-lookup stream the gradient
     // kernels read.  After the sort vals[spare] receives unique_rows.
-    size_t keys[2], vals[2], seg_start, radix_hist, bin_tot, rle_counts, counters, long_tables, tickets, seq_gbase,
-        seg_chunk0, chunk_desc, dense_rows, dense_n, dense_bounds, tile_long, tile_slots,
-        long_list, unit_list, bounds, partial, total;
+    // After the sort vals[spare] receives unique_rows.  Streams of the whole batch first; behind them what the sort needs
+    // only while it runs shares its place with what the row updates write.
+    size_t keys[2], vals[2], seg_start, counters, long_rows, long_list, unit_list, hot_ids, hot_n, seq_gbase, dense_n, dense_rows,
+        dense_index, radix_hist, bin_tot, seg_chunk0, chunk_desc, rle_counts, partial, total;
     SortShape sort;
     int rle_blocks;
-    int64_t cap_long, cap_main, cap_chunks, cap_units;   // long rows; slots before the dense region; all slots; units
-    int long_tiles;       // tiles of unique rows that the long-row passes walk
+    uint32_t long_min;    // a row with more lookups is long: it is cut into parts of about that many
+    int64_t cap_long, cap_main;   // long rows; partial-sum slots of their parts (the dense rows' slots follow)
+    bool dense;           // dense rows are looked for; their sizes:
+    uint32_t dense_blocks, dense_chunks, dense_per_chunk;
     int64_t n;            // number of lookups the workspace was carved for
 };
-Workspace carve(const tbe_handle* h, int64_t N);
+// allow_dense = false leaves the dense rows out (their rows are then reduced part by part): for scratch memory of fixed size
+Workspace carve(const tbe_handle* h, int32_t B, int64_t N, bool allow_dense = true);
 
 // RAII-free helper: brackets one kernel launch with events when timing is on.
 struct LaunchTimer {
@@ -129,11 +131,17 @@ hipError_t launch_sort(const tbe_handle* h, const Workspace& w, char* ws, const 
                        int32_t B, int64_t N, bool seq, hipStream_t s);
 // `sorted` is the buffer index (0/1) that holds the sorted pairs; vals of the other pair receive unique_rows
 hipError_t launch_run_lengths(const tbe_handle* h, const Workspace& w, char* ws, int sorted, int64_t N, hipStream_t s);
+struct SegArgs;
+SegArgs seg_args(const tbe_handle* h, const Workspace& w, char* ws, const void* offsets, int idx32, int32_t B, int seq);
+// lists the long rows of the sorted batch (and, seq != 0, the gradient blocks of the non-pooled layout)
+hipError_t launch_lists(const tbe_handle* h, const Workspace& w, char* ws, const void* offsets, int idx32, int32_t B, int seq,
+                        int64_t grad_elems, hipStream_t s);
+void launch_dense(const SegArgs& a, int grad_io, bool mean, hipStream_t s);
 // state == nullptr: plain SGD step.  seq != 0: grad_out is the non-pooled layout (one [n_t, D_t] block per table),
 // offsets has T+1 entries and B is 1.
-hipError_t launch_segment_update(const tbe_handle* h, const Workspace& w, char* ws, int spare, const void* grad_out,
-                                 int grad_io, const void* offsets, int idx32, int32_t B, tbe_pooling pooling, float lr,
-                                 float eps, float c, void* tables, float* state, int seq, int64_t grad_elems, hipStream_t s);
+hipError_t launch_segment_update(const tbe_handle* h, const Workspace& w, char* ws, const void* grad_out, int grad_io,
+                                 const void* offsets, int idx32, int32_t B, tbe_pooling pooling, float lr, float eps, float c,
+                                 void* tables, float* state, int seq, hipStream_t s);
 // non-pooled lookup: out block of table t = rows indices[offsets[t] .. offsets[t+1]) of table t, one after the other
 hipError_t launch_lookup_seq(const tbe_handle* h, const void* tables, const void* indices, const void* offsets, int idx32,
                              int64_t nnz, void* out, int out_io, int64_t out_elems, hipStream_t s);

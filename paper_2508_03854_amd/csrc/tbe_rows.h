@@ -1,0 +1,83 @@
+// What the kernels that list the rows of a sorted batch (tbe_lists.hip) and those that reduce and step them
+// (tbe_backward.hip, tbe_dense.hip) share.
+#pragma once
+#include "tbe_device.h"
+#include "tbe_internal.h"
+
+namespace tbe {
+
+// Bag lengths from the offsets array, whose values are below 2^32: the low word of every entry is enough, so int64 and
+// int32 offsets differ in an index shift only.
+struct OffsetWords {
+    const uint32_t* p;
+    int shift;   // 1: int64, 0: int32
+    __device__ __forceinline__ uint32_t length(const int64_t bag) const {
+        return p[(bag + 1) << shift] - p[bag << shift];
+    }
+};
+
+constexpr uint32_t kDenseFlag = 0x80000000u;   // long_list entry: the dense-row kernel reduces the row
+
+struct SegArgs {
+    const uint32_t* keys_unique;  // unique_rows
+    const uint32_t* seg_start;
+    uint32_t* counters;           // [0] unique rows, [1] long rows, [3] work units, [4] != 0: apply nothing
+    const uint32_t* bag_sorted;   // the sorted payload: linear bag id of every sorted lookup
+    OffsetWords offsets;
+    const void* grad_out;         // [B, sum(D)] float / binary16 / bfloat16, per the kernel's GT (or the sequence layout)
+    int64_t* seq_gbase;           // non-pooled mode only: element offset of table t's gradient block minus start_t * D_t
+    int seq;                      // 1: non-pooled; bag_sorted then holds the original positions
+    const int32_t* D_off;
+    const int64_t* row_base;
+    const int64_t* w_off;
+    int32_t T, B, sumD, maxD;
+    uint32_t total_rows;
+    float lr, eps, inv_c;
+    void* tables;
+    float* state;          // nullptr: plain SGD step, no moments
+    // rows with more than long_min lookups
+    uint32_t long_min, part;      // ... are cut into equal parts of about `part` lookups
+    uint32_t cap_long;
+    const uint2* long_rows;       // [counters[1]] (unique row, key), ascending
+    uint4* long_list;             // [counters[1]] (unique row, first partial-sum slot, parts or kDenseFlag, table)
+    uint2* unit_list;             // [counters[3]] (position in long_list, part)
+    float* partial;               // [slots][maxD] partial sums
+    uint32_t* hot_ids;            // [T][kHotRows] rows with the most lookups, for the handle's hint (null: not kept)
+    uint32_t* hot_n;              // [T]
+    uint32_t* hint_ids;           // the handle's hint (null: not kept)
+    uint32_t* hint_n;
+    int min_rows_log2;            // seg_update: a wavefront takes at least 2^this consecutive rows
+    // dense rows (tbe_dense.hip); null dense_n: no table can have any
+    uint32_t* dense_n;            // [T] number of dense rows
+    uint32_t* dense_rows;         // [T][kDenseRows] their positions in long_list, longest first
+    uint32_t* dense_index;        // [T][kDenseRows][dense_blocks + 1] where each block of bags starts in the row's segment
+    uint32_t dense_slot0;         // first slot of the region reserved for them
+    uint32_t dense_blocks;        // blocks of kDenseBags bags per table
+    uint32_t dense_chunks;        // partial sums per dense row: runs of dense_per_chunk blocks
+    uint32_t dense_per_chunk;
+};
+
+// Dense rows exist only where a table's gradient block is too large for an L2 (4 MiB per die, half of it at most): a
+// block that fits is gathered from at L2 speed anyway.
+__device__ __host__ __forceinline__ bool dense_block(const uint32_t B, const uint32_t D) {
+    return (uint64_t)B * D * 4u > ((uint64_t)2 << 20);
+}
+
+// table of a linearised row key: the t with row_base[t] <= key < row_base[t+1]
+__device__ __forceinline__ int table_of_key(const int64_t* __restrict__ row_base, int T, uint32_t key) {
+    int lo = 0, hi = T;  // first t in [0, T] with row_base[t] > key, minus 1
+    while (lo < hi) {
+        const int mid = (lo + hi) >> 1;
+        if (row_base[mid] > (int64_t)key) hi = mid;
+        else lo = mid + 1;
+    }
+    return lo - 1;
+}
+
+// ... of a row whose first sorted lookup is s0: from that lookup's bag where the payload is one (one load instead of a
+// search), else from the key
+__device__ __forceinline__ int table_of_row(const SegArgs& a, const uint32_t s0, const uint32_t key) {
+    return a.seq ? table_of_key(a.row_base, a.T, key) : (int)(a.bag_sorted[s0] / (uint32_t)a.B);
+}
+
+}  // namespace tbe

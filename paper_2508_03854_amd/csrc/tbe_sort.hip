@@ -634,196 +634,249 @@ hipError_t launch_sort(const tbe_handle* h, const Workspace& w, char* ws, const 
 }
 
 // =================================================================================================
-// run-length segmentation of the sorted keys: unique_rows, seg_start, num_unique
-// Element order inside a tile: 8 rows of 256, row k / wave w / lane l is element k*256 + w*64 + l, so
-// every (k, w) pair is a run of 64 consecutive elements and ballots give exact ranks.
+// run-length segmentation of the sorted keys: unique_rows, seg_start, num_unique, and in row order the long rows, i.e.
+// those with more than long_min lookups (element i starts one if it is a head and element i + long_min has its key).
+// Element order inside a tile: 8 rows of NT, row k / wave w / lane l is element k*NT + w*64 + l, so every (k, w) pair is
+// a run of 64 consecutive elements and ballots give exact ranks.
 // =================================================================================================
 constexpr int kRleThreads = 256;
 constexpr int kRleItems = kRleTile / kRleThreads;            // 8
-constexpr int kRleRuns = kRleItems * (kRleThreads / kWave);  // runs of 64 elements per tile
-static_assert(kRleRuns <= kWave, "one wavefront scans the run counts of a tile");
+static_assert(kRleItems == 8, "the kernels below take eight elements per thread");
 
-// Head flags of a thread's kRleItems elements (element k*kRleThreads + tid of the tile): element i is a head if it
-// exists and its key differs from its predecessor's.  The loads are unconditional (indices clamped into the array,
-// which always holds at least one element) and all issued before the first comparison, so that they overlap.
-__device__ __forceinline__ void head_flags(const uint32_t* __restrict__ keys, const int64_t base, const int64_t N,
-                                           bool (&head)[kRleItems]) {
-    uint32_t cur[kRleItems], prev[kRleItems];
+struct RleArgs {
+    const uint32_t* keys;
+    int64_t N;
+    uint32_t long_min, total_rows;
+    uint2* counts;            // per tile: heads, long rows
+    uint32_t* unique_rows;
+    uint32_t* seg_start;
+    uint2* long_rows;         // (index of the unique row, key)
+    uint32_t* counters;       // [0] unique rows, [1] long rows, [3] = [4] = 0
+};
+
+// Head flags of a thread's eight elements (element k*NT + tid of the tile): element i is a head if it exists and its key
+// differs from its predecessor's; lng: a head of a long row (ids outside their table form no row).  The loads are
+// unconditional (indices clamped into the array, which always holds at least one element) and all issued before the first
+// comparison, so that they overlap.
+template <int NT>
+__device__ __forceinline__ void head_flags(const RleArgs& a, const int64_t base, uint32_t (&cur)[kRleItems],
+                                           bool (&head)[kRleItems], bool (&lng)[kRleItems]) {
+    uint32_t prev[kRleItems], far[kRleItems];
 #pragma unroll
     for (int k = 0; k < kRleItems; ++k) {
-        const int64_t i = base + k * kRleThreads + threadIdx.x;
-        const bool in = i < N;
-        cur[k] = keys[in ? i : 0];
-        prev[k] = keys[(in && i > 0) ? i - 1 : 0];
+        const int64_t i = base + k * NT + threadIdx.x;
+        const bool in = i < a.N;
+        cur[k] = a.keys[in ? i : 0];
+        prev[k] = a.keys[(in && i > 0) ? i - 1 : 0];
+        far[k] = a.keys[i + a.long_min < a.N ? i + a.long_min : a.N - 1];
     }
 #pragma unroll
     for (int k = 0; k < kRleItems; ++k) {
-        const int64_t i = base + k * kRleThreads + threadIdx.x;
-        head[k] = i < N && (i == 0 || cur[k] != prev[k]);
+        const int64_t i = base + k * NT + threadIdx.x;
+        head[k] = i < a.N && (i == 0 || cur[k] != prev[k]);
+        lng[k] = head[k] && i + a.long_min < a.N && far[k] == cur[k] && cur[k] < a.total_rows;
     }
 }
 
-__global__ __launch_bounds__(kRleThreads) void rle_count_kernel(const uint32_t* __restrict__ keys, const int64_t N,
-                                                                uint32_t* __restrict__ block_counts) {
-    __shared__ uint32_t s_w[kRleThreads / kWave];
+__global__ __launch_bounds__(kRleThreads) void rle_count_kernel(const RleArgs a) {
+    __shared__ uint2 s_w[kRleThreads / kWave];
     const int64_t base = (int64_t)blockIdx.x * kRleTile;
-    uint32_t c = 0;   // heads seen by this wavefront: one ballot and one population count per run of 64 keys
-    bool head[kRleItems];
-    head_flags(keys, base, N, head);
+    uint32_t c = 0, l = 0;   // heads seen by this wavefront: one ballot and one population count per run of 64 keys
+    uint32_t cur[kRleItems];
+    bool head[kRleItems], lng[kRleItems];
+    head_flags<kRleThreads>(a, base, cur, head, lng);
 #pragma unroll
-    for (int k = 0; k < kRleItems; ++k) c += (uint32_t)__popcll(__ballot(head[k]));
-    if (lane_id() == 0) s_w[threadIdx.x >> 6] = c;
+    for (int k = 0; k < kRleItems; ++k) {
+        c += (uint32_t)__popcll(__ballot(head[k]));
+        l += (uint32_t)__popcll(__ballot(lng[k]));
+    }
+    if (lane_id() == 0) s_w[threadIdx.x >> 6] = make_uint2(c, l);
     __syncthreads();
     if (threadIdx.x == 0) {
-        uint32_t tot = 0;
+        uint2 tot = make_uint2(0u, 0u);
 #pragma unroll
-        for (int w = 0; w < kRleThreads / kWave; ++w) tot += s_w[w];
-        block_counts[blockIdx.x] = tot;
+        for (int w = 0; w < kRleThreads / kWave; ++w) {
+            tot.x += s_w[w].x;
+            tot.y += s_w[w].y;
+        }
+        a.counts[blockIdx.x] = tot;
     }
 }
 
-// single block, batches of many tiles: exclusive scan of the per-tile head counts in place
-__global__ __launch_bounds__(1024) void rle_scan_kernel(uint32_t* __restrict__ block_counts, const int nblocks) {
+// single block, batches of many tiles: exclusive scan of the per-tile counts in place
+__global__ __launch_bounds__(1024) void rle_scan_kernel(uint2* __restrict__ counts, const int nblocks) {
     __shared__ uint32_t smem[1024 / kWave];
-    uint32_t carry = 0;
+    uint32_t carry_h = 0, carry_l = 0;
     for (int base = 0; base < nblocks; base += 4 * 1024) {   // four counts per thread and round: a quarter of the barriers
         const int i = base + 4 * (int)threadIdx.x;
-        uint32_t v[4];
-#pragma unroll
-        for (int q = 0; q < 4; ++q) v[q] = (i + q < nblocks) ? block_counts[i + q] : 0u;
-        uint32_t tot;
-        uint32_t run = carry + block_excl_scan<1024>(v[0] + v[1] + v[2] + v[3], smem, &tot);
+        uint2 v[4];
+        uint32_t sh = 0, sl = 0;
 #pragma unroll
         for (int q = 0; q < 4; ++q) {
-            if (i + q < nblocks) block_counts[i + q] = run;
-            run += v[q];
+            v[q] = (i + q < nblocks) ? counts[i + q] : make_uint2(0u, 0u);
+            sh += v[q].x;
+            sl += v[q].y;
         }
-        carry += tot;
+        uint32_t th, tl;
+        uint32_t rh = carry_h + block_excl_scan<1024>(sh, smem, &th);
+        uint32_t rl = carry_l + block_excl_scan<1024>(sl, smem, &tl);
+#pragma unroll
+        for (int q = 0; q < 4; ++q) {
+            if (i + q < nblocks) counts[i + q] = make_uint2(rh, rl);
+            rh += v[q].x;
+            rl += v[q].y;
+        }
+        carry_h += th;
+        carry_l += tl;
     }
 }
 
-// Writes unique_rows, seg_start and num_unique: element i is a head if its key differs from its predecessor's.  The
-// number of heads before the tile comes from, in ascending number of tiles (every variant saves a launch of about 4 us
-// against the next): counting them in the keys before the tile (kRleFromKeys), adding up the counts of the tiles before
-// it (kRleFromCounts), or the scanned counts (kRleFromScan).
-enum { kRleFromKeys, kRleFromCounts, kRleFromScan };
-constexpr int kRleKeysTiles = 16;      // at most 15 tiles of keys to look through: 30 uint4 per thread
-constexpr int kRleCountsTiles = 2048;  // at most 8 counts per thread
-template <int MODE>
-__global__ __launch_bounds__(kRleThreads) void rle_write_kernel(const uint32_t* __restrict__ keys, const int64_t N,
-                                                                const uint32_t* __restrict__ block_base,
-                                                                uint32_t* __restrict__ unique_rows,
-                                                                uint32_t* __restrict__ seg_start,
-                                                                uint32_t* __restrict__ counters) {
-    __shared__ uint32_t s_run[kRleRuns];
-    __shared__ uint32_t s_sum[kRleThreads / kWave];
-    __shared__ uint32_t s_heads;
+// Writes a tile's unique_rows, seg_start and long rows; the tile's first head is unique row bb, its first long row number
+// bl.  Returns the tile's (heads, long rows).  s_run: 8 * NT / 64 + 1 words.
+template <int NT>
+__device__ __forceinline__ uint2 rle_write_tile(const RleArgs& a, const int64_t base, const uint32_t bb, const uint32_t bl,
+                                                const uint32_t (&cur)[kRleItems], const bool (&head)[kRleItems],
+                                                const bool (&lng)[kRleItems], uint32_t* s_run) {
+    constexpr int kRuns = kRleItems * (NT / kWave);   // runs of 64 elements per tile: 32 or 128
     const int lane = lane_id();
     const int w = threadIdx.x >> 6;
     const uint64_t lt = lanemask_lt();
-    const uint32_t tile = blockIdx.x;
-    const int64_t base = (int64_t)tile * kRleTile;
-    uint64_t heads[kRleItems];
-    bool head[kRleItems];
-    head_flags(keys, base, N, head);
-    uint32_t before = 0;
-    if (MODE == kRleFromKeys) {
-        // (base is a multiple of 4, and keys[base] exists: every quadruple of the keys before it and its successor do)
-        const uint4* k4 = reinterpret_cast<const uint4*>(keys);
-        const int n4 = (int)(base >> 2);
-        for (int q0 = 0; q0 < n4; q0 += 8 * kRleThreads) {
-            uint4 x[8];
-            uint32_t nx[8];
-#pragma unroll
-            for (int u = 0; u < 8; ++u) {
-                const int q = q0 + u * kRleThreads + (int)threadIdx.x;
-                const int qc = q < n4 ? q : 0;
-                x[u] = k4[qc];
-                nx[u] = keys[4 * (qc + 1)];
-            }
-#pragma unroll
-            for (int u = 0; u < 8; ++u) {   // heads among the positions 4q+1 .. 4q+4
-                const bool in = q0 + u * kRleThreads + (int)threadIdx.x < n4;
-                const uint32_t c = (x[u].y != x[u].x) + (x[u].z != x[u].y) + (x[u].w != x[u].z) + (nx[u] != x[u].w);
-                before += in ? c : 0u;
-            }
-        }
-    } else if (MODE == kRleFromCounts) {
-        for (uint32_t i0 = 0; i0 < tile; i0 += 4 * kRleThreads) {
-            uint32_t v[4];
-#pragma unroll
-            for (int u = 0; u < 4; ++u) {
-                const uint32_t i = i0 + u * kRleThreads + threadIdx.x;
-                v[u] = block_base[i < tile ? i : 0u];
-            }
-#pragma unroll
-            for (int u = 0; u < 4; ++u) before += i0 + u * kRleThreads + threadIdx.x < tile ? v[u] : 0u;
-        }
-    }
-    if (MODE != kRleFromScan) {
-        const uint32_t inc = wave_incl_scan(before);
-        if (lane == kWave - 1) s_sum[w] = inc;
-    }
+    uint64_t heads[kRleItems], longs[kRleItems];
 #pragma unroll
     for (int k = 0; k < kRleItems; ++k) {
         heads[k] = __ballot(head[k]);
-        if (lane == 0) s_run[k * (kRleThreads / kWave) + w] = (uint32_t)__popcll(heads[k]);
+        longs[k] = __ballot(lng[k]);
+        if (lane == 0) s_run[k * (NT / kWave) + w] = (uint32_t)__popcll(heads[k]) | ((uint32_t)__popcll(longs[k]) << 16);
     }
     __syncthreads();
-    if (threadIdx.x < kWave) {  // one wavefront scans the 32 run counts
-        const uint32_t v = (threadIdx.x < kRleRuns) ? s_run[threadIdx.x] : 0u;
-        const uint32_t inc = wave_incl_scan(v);
-        if (threadIdx.x < kRleRuns) s_run[threadIdx.x] = inc - v;
-        if (threadIdx.x == kWave - 1) s_heads = inc;
-    }
-    __syncthreads();
-    uint32_t bb;
-    if (MODE == kRleFromScan) {
-        bb = block_base[tile];
-    } else {
-        bb = 0;
+    if (threadIdx.x < kWave) {  // one wavefront scans the run counts (heads and long rows in one word: at most 8192 each)
+        uint32_t carry = 0;
 #pragma unroll
-        for (int i = 0; i < kRleThreads / kWave; ++i) bb += s_sum[i];
-        // counting in the keys sees position base itself (a head of this tile, if it is one) but not position 0
-        if (MODE == kRleFromKeys && tile > 0) bb += 1u - (keys[base] != keys[base - 1] ? 1u : 0u);
+        for (int r0 = 0; r0 < kRuns; r0 += kWave) {
+            const uint32_t v = (r0 + lane < kRuns) ? s_run[r0 + lane] : 0u;
+            const uint32_t inc = wave_incl_scan(v);
+            if (r0 + lane < kRuns) s_run[r0 + lane] = carry + inc - v;
+            carry += __shfl(inc, kWave - 1, kWave);
+        }
+        if (lane == 0) s_run[kRuns] = carry;
     }
+    __syncthreads();
 #pragma unroll
     for (int k = 0; k < kRleItems; ++k) {
-        if ((heads[k] >> lane) & 1ull) {
-            const int64_t i = base + k * kRleThreads + threadIdx.x;
-            const uint32_t u = bb + s_run[k * (kRleThreads / kWave) + w] + (uint32_t)__popcll(heads[k] & lt);
-            unique_rows[u] = keys[i];
-            seg_start[u] = (uint32_t)i;
+        const uint32_t run = s_run[k * (NT / kWave) + w];
+        if (head[k]) {
+            const int64_t i = base + k * NT + threadIdx.x;
+            const uint32_t u = bb + (run & 0xFFFFu) + (uint32_t)__popcll(heads[k] & lt);
+            a.unique_rows[u] = cur[k];
+            a.seg_start[u] = (uint32_t)i;
+            if (lng[k]) a.long_rows[bl + (run >> 16) + (uint32_t)__popcll(longs[k] & lt)] = make_uint2(u, cur[k]);
         }
     }
-    if (tile == gridDim.x - 1 && threadIdx.x == 0) {
-        const uint32_t U = bb + s_heads;
-        counters[0] = U;
-        seg_start[U] = (uint32_t)N;
+    const uint32_t tot = s_run[kRuns];
+    return make_uint2(tot & 0xFFFFu, tot >> 16);
+}
+
+__device__ __forceinline__ void rle_finish(const RleArgs& a, const uint32_t U, const uint32_t nlong) {
+    a.counters[0] = U;
+    a.counters[1] = nlong;
+    a.counters[3] = 0u;   // work units of the long rows, counted by the kernel that lists them
+    a.counters[4] = 0u;   // set when a non-pooled batch must not be applied
+    a.seg_start[U] = (uint32_t)a.N;
+}
+
+// What lies before a tile: the sum of the counts of the tiles before it, or (SCANNED, batches of many tiles) their scan.
+constexpr int kRleSumTiles = 2048;  // at most 8 counts per thread
+template <bool SCANNED>
+__global__ __launch_bounds__(kRleThreads) void rle_write_kernel(const RleArgs a) {
+    __shared__ uint32_t s_run[kRleItems * (kRleThreads / kWave) + 1];
+    __shared__ uint2 s_sum[kRleThreads / kWave];
+    const uint32_t tile = blockIdx.x;
+    const int64_t base = (int64_t)tile * kRleTile;
+    uint32_t cur[kRleItems];
+    bool head[kRleItems], lng[kRleItems];
+    head_flags<kRleThreads>(a, base, cur, head, lng);
+    uint32_t bb = 0, bl = 0;
+    if (SCANNED) {
+        const uint2 v = a.counts[tile];
+        bb = v.x;
+        bl = v.y;
+    } else {
+        for (uint32_t i0 = 0; i0 < tile; i0 += 4 * kRleThreads) {
+            uint2 v[4];
+#pragma unroll
+            for (int u = 0; u < 4; ++u) {
+                const uint32_t i = i0 + u * kRleThreads + threadIdx.x;
+                v[u] = a.counts[i < tile ? i : 0u];
+            }
+#pragma unroll
+            for (int u = 0; u < 4; ++u) {
+                const bool in = i0 + u * kRleThreads + threadIdx.x < tile;
+                bb += in ? v[u].x : 0u;
+                bl += in ? v[u].y : 0u;
+            }
+        }
+        bb = wave_incl_scan(bb);
+        bl = wave_incl_scan(bl);
+        if (lane_id() == kWave - 1) s_sum[threadIdx.x >> 6] = make_uint2(bb, bl);
+        __syncthreads();
+        bb = bl = 0;
+#pragma unroll
+        for (int i = 0; i < kRleThreads / kWave; ++i) {
+            bb += s_sum[i].x;
+            bl += s_sum[i].y;
+        }
     }
+    const uint2 tot = rle_write_tile<kRleThreads>(a, base, bb, bl, cur, head, lng, s_run);
+    if (tile == gridDim.x - 1 && threadIdx.x == 0) rle_finish(a, bb + tot.x, bl + tot.y);
+}
+
+// Small batches (up to kRleOneBlock lookups): one workgroup walks all tiles of 8192 - one launch, nothing to add up.
+__global__ __launch_bounds__(1024) void rle_one_block_kernel(const RleArgs a) {
+    __shared__ uint32_t s_run[kRleItems * (1024 / kWave) + 1];
+    uint32_t bb = 0, bl = 0;
+    for (int64_t base = 0; base < a.N; base += kRleItems * 1024) {
+        uint32_t cur[kRleItems];
+        bool head[kRleItems], lng[kRleItems];
+        head_flags<1024>(a, base, cur, head, lng);
+        const uint2 tot = rle_write_tile<1024>(a, base, bb, bl, cur, head, lng, s_run);
+        bb += tot.x;
+        bl += tot.y;
+        __syncthreads();   // s_run is written again
+    }
+    if (threadIdx.x == 0) rle_finish(a, bb, bl);
 }
 
 hipError_t launch_run_lengths(const tbe_handle* h, const Workspace& w, char* ws, int sorted, int64_t N, hipStream_t s) {
-    const uint32_t* keys_sorted = reinterpret_cast<const uint32_t*>(ws + w.keys[sorted]);
-    uint32_t* counts = reinterpret_cast<uint32_t*>(ws + w.rle_counts);
-    uint32_t* counters = reinterpret_cast<uint32_t*>(ws + w.counters);
-    uint32_t* unique_rows = reinterpret_cast<uint32_t*>(ws + w.vals[sorted ^ 1]);
-    uint32_t* seg_start = reinterpret_cast<uint32_t*>(ws + w.seg_start);
+    RleArgs a;
+    a.keys = reinterpret_cast<const uint32_t*>(ws + w.keys[sorted]);
+    a.N = N;
+    a.long_min = w.long_min;
+    a.total_rows = (uint32_t)h->total_rows;
+    a.counts = reinterpret_cast<uint2*>(ws + w.rle_counts);
+    a.unique_rows = reinterpret_cast<uint32_t*>(ws + w.vals[sorted ^ 1]);
+    a.seg_start = reinterpret_cast<uint32_t*>(ws + w.seg_start);
+    a.long_rows = reinterpret_cast<uint2*>(ws + w.long_rows);
+    a.counters = reinterpret_cast<uint32_t*>(ws + w.counters);
     const int n = w.rle_blocks;
-    if (n > kRleKeysTiles) {
+    if (N <= kRleOneBlock) {
+        LaunchTimer tm(h, s, "rle_write");
+        rle_one_block_kernel<<<1, 1024, 0, s>>>(a);
+        tm.done();
+        return hipGetLastError();
+    }
+    {
         LaunchTimer tm(h, s, "rle_count");
-        rle_count_kernel<<<n, kRleThreads, 0, s>>>(keys_sorted, N, counts);
+        rle_count_kernel<<<n, kRleThreads, 0, s>>>(a);
         tm.done();
     }
-    if (n > kRleCountsTiles) {
+    if (n > kRleSumTiles) {
         LaunchTimer tm(h, s, "rle_scan");
-        rle_scan_kernel<<<1, 1024, 0, s>>>(counts, n);
+        rle_scan_kernel<<<1, 1024, 0, s>>>(a.counts, n);
         tm.done();
     }
     LaunchTimer tm(h, s, "rle_write");
-    if (n <= kRleKeysTiles) rle_write_kernel<kRleFromKeys><<<n, kRleThreads, 0, s>>>(keys_sorted, N, counts, unique_rows, seg_start, counters);
-    else if (n <= kRleCountsTiles) rle_write_kernel<kRleFromCounts><<<n, kRleThreads, 0, s>>>(keys_sorted, N, counts, unique_rows, seg_start, counters);
-    else rle_write_kernel<kRleFromScan><<<n, kRleThreads, 0, s>>>(keys_sorted, N, counts, unique_rows, seg_start, counters);
+    if (n <= kRleSumTiles) rle_write_kernel<false><<<n, kRleThreads, 0, s>>>(a);
+    else rle_write_kernel<true><<<n, kRleThreads, 0, s>>>(a);
     tm.done();
     return hipGetLastError();
 }
