@@ -96,7 +96,7 @@ Workspace carve(const tbe_handle* h, int32_t B, int64_t N, bool allow_dense) {
     w.seq_gbase = take(8 * (size_t)h->T);
     // Dense rows: some table's gradient block is large, and the batch could hold two lookups of them per bag.  A dense row
     // leaves one partial sum per chunk of bags: enough chunks for about a thousand workgroups in all, at most 32.
-    w.dense = allow_dense && h->T <= kMaxSortSegments && (uint64_t)B * (uint64_t)h->maxD * 4u > ((uint64_t)2 << 20);
+    w.dense = allow_dense && h->T <= kMaxSortSegments && B >= kDenseMinBags && (uint64_t)B * (uint64_t)h->maxD * 4u > ((uint64_t)2 << 20);
     if (w.dense) {
         w.dense_blocks = ((uint32_t)B + kDenseBags - 1) / kDenseBags;
         const uint32_t want = h->T >= 1024 ? 1u : (h->T <= 32 ? 32u : 1024u / (uint32_t)h->T);

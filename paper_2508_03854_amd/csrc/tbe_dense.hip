@@ -30,7 +30,6 @@ typedef _Float16 f16x8 __attribute__((ext_vector_type(8)));
 
 constexpr int kDThreads = 256;
 constexpr int kCntPitch = kDenseBags + 8;   // 16 bytes more than a power of two: the rows a wavefront reads lie in different banks
-constexpr int kMTiles = kDenseRows / 32;
 static_assert(kDenseBags == kDThreads, "one thread per bag of a block");
 
 // the two columns a lane holds of one bag's gradient row
@@ -81,25 +80,23 @@ __device__ __forceinline__ uint32_t count_bits(const uint32_t c) {
     else return __float_as_uint((float)c) >> 16;
 }
 
-template <bool MEAN, typename GT>
-__global__ __launch_bounds__(kDThreads, 2) void seg_dense_kernel(const SegArgs a, const uint32_t col_blocks) {
+struct DenseLds {
+    __align__(16) uint16_t cnt[kDenseRows * kCntPitch];
+    __align__(16) float scale[kDenseBags];
+    uint32_t lo[kDenseRows], pref[kDenseRows], scan[kDThreads / kWave], flags;
+};
+
+// MT: row tiles of 32 (compiled apart, so that the matrix instructions of a step are one straight run)
+template <int MT, bool MEAN, typename GT>
+__device__ __forceinline__ void dense_run(const SegArgs& a, const uint32_t cb, const uint32_t chunk, const int t,
+                                          const uint32_t nd, const int d0, const int D, DenseLds* S) {
     constexpr bool kExact = !MEAN && sizeof(GT) == 2;                 // a gradient element is one piece
     constexpr bool kF16 = kExact && __is_same(GT, __half);            // binary16 pieces, else bfloat16
     constexpr int kPieces = kExact ? 1 : 3;
     using raw_t = typename Pair<GT>::raw_t;
-    __shared__ __align__(16) uint16_t s_cnt[kDenseRows * kCntPitch];
-    __shared__ uint32_t s_lo[kDenseRows], s_pref[kDenseRows + 1], s_scan[kDThreads / kWave], s_flags;
-    __shared__ __align__(16) float s_scale[MEAN ? kDenseBags : 4];
-    uint32_t bx = blockIdx.x;
-    const uint32_t cb = bx % col_blocks;
-    bx /= col_blocks;
-    const uint32_t chunk = bx % a.dense_chunks;
-    const int t = (int)(bx / a.dense_chunks);
-    const uint32_t nd = a.dense_n[t];
-    if (nd == 0u) return;
-    const int d0 = a.D_off[t];
-    const int D = a.D_off[t + 1] - d0;
-    if ((int)cb * 256 >= D) return;
+    uint16_t* const s_cnt = S->cnt;
+    uint32_t* const s_lo = S->lo;
+    uint32_t* const s_pref = S->pref;
     const uint32_t tid = threadIdx.x;
     const int lane = lane_id();
     const int w = (int)(tid >> 6);
@@ -108,75 +105,88 @@ __global__ __launch_bounds__(kDThreads, 2) void seg_dense_kernel(const SegArgs a
     const int split = w / groups, splits = 4 / groups;   // which share of the bags this wavefront takes
     const int kh = lane >> 5;                            // which half of a 16-bag step
     const int col = (int)cb * 256 + cg * 64 + 2 * (lane & 31);
-    const bool col_on = col < D;
-    const uint32_t mt = (nd + 31u) >> 5;                 // row tiles in use
-    const GT* gcol = static_cast<const GT*>(a.grad_out) + d0 + col;
+    const bool col_on = col < D;                         // (other lanes read column 0 and store nothing)
+    // a lane's address: wavefront-uniform start of a bag's gradient row + 32-bit byte offset
+    const char* const gtab = static_cast<const char*>(a.grad_out) + (int64_t)d0 * (int)sizeof(GT);
+    const int64_t pitch = (int64_t)a.sumD * (int)sizeof(GT);
+    const uint32_t lane_col = (uint32_t)(col_on ? col : 0) * (uint32_t)sizeof(GT);
     const uint32_t B = (uint32_t)a.B;
     const int64_t bag0 = (int64_t)t * B;
     uint32_t* const cnt32 = reinterpret_cast<uint32_t*>(s_cnt);
-    f32x16 acc[kMTiles][2];
+    f32x16 acc[MT][2];
 #pragma unroll
-    for (int m = 0; m < kMTiles; ++m)
+    for (int m = 0; m < MT; ++m)
 #pragma unroll
         for (int r = 0; r < 16; ++r) acc[m][0][r] = acc[m][1][r] = 0.f;
 
+    const uint32_t* const my_ix = a.dense_index + ((size_t)t * kDenseRows + (tid < nd ? tid : 0u)) * (a.dense_blocks + 1u);
     const uint32_t k_lo = chunk * a.dense_per_chunk;
     const uint32_t k_hi = k_lo + a.dense_per_chunk < a.dense_blocks ? k_lo + a.dense_per_chunk : a.dense_blocks;
     for (uint32_t k = k_lo; k < k_hi; ++k) {
         const uint32_t b0 = k * kDenseBags;
         const uint32_t nb = B - b0 < (uint32_t)kDenseBags ? B - b0 : (uint32_t)kDenseBags;   // bags of the block
+        uint32_t ix0 = 0, ix1 = 0;   // this thread's row's lookups in the block
+        if (tid < nd) {
+            ix0 = my_ix[k];
+            ix1 = my_ix[k + 1u];
+        }
+        const uint32_t L = b0 + tid < B ? a.offsets.length(bag0 + b0 + tid) : 0u;   // this thread's bag's length
         for (uint32_t pass = 0;; ++pass) {   // pass 2r + d: counts' digit d (low, high byte) of round r
             const uint32_t round = pass >> 1, digit = pass & 1u;
             __syncthreads();   // the table is free (previous block, or pass)
             // ---- counts of the block: zero, then one LDS addition per lookup of a dense row
-            for (uint32_t i = tid; i < mt * 32u * (kCntPitch / 8); i += kDThreads)
+            for (uint32_t i = tid; i < MT * 32u * (kCntPitch / 8); i += kDThreads)
                 reinterpret_cast<uint4*>(s_cnt)[i] = make_uint4(0u, 0u, 0u, 0u);
-            uint32_t n = 0;
-            if (tid < nd) {
-                const uint32_t* ix = a.dense_index + ((size_t)t * kDenseRows + tid) * (a.dense_blocks + 1u) + k;
-                const uint32_t lo = ix[0];
-                n = ix[1] - lo;
-                s_lo[tid] = lo;
-            }
-            if (tid == 0) s_flags = 0u;
-            uint32_t L = 0;
-            if (tid < nb) L = a.offsets.length(bag0 + b0 + tid);
-            if (MEAN) s_scale[tid] = L > 0u ? 1.f / (float)L : 0.f;
+            const uint32_t n = ix1 - ix0;
+            if (tid < nd) s_lo[tid] = ix0;
+            if (tid == 0) S->flags = 0u;
+            if (MEAN) S->scale[tid] = L > 0u ? 1.f / (float)L : 0.f;
             uint32_t all;
-            const uint32_t ex = block_excl_scan<kDThreads>(n, s_scan, &all);
-            if (tid < nd) s_pref[tid] = ex;
-            if (L > 255u) atomicOr(&s_flags, L > 65535u ? 3u : 1u);   // (a count cannot exceed its bag's length)
+            const uint32_t ex = block_excl_scan<kDThreads>(n, S->scan, &all);
+            if (tid < (uint32_t)kDenseRows) s_pref[tid] = tid < nd ? ex : 0xFFFFFFFFu;
+            if (L > 255u) atomicOr(&S->flags, L > 65535u ? 3u : 1u);   // (a count cannot exceed its bag's length)
             __syncthreads();
-            const uint32_t flags = s_flags;
+            const uint32_t flags = S->flags;
             bool more = false;   // lookups left for a later round
-            for (uint32_t e = tid; e < all; e += kDThreads) {
-                uint32_t lo = 0, hi = nd;   // the row: last h with s_pref[h] <= e
-                while (hi - lo > 1u) {
-                    const uint32_t mid = (lo + hi) >> 1;
-                    if (s_pref[mid] <= e) lo = mid;
-                    else hi = mid;
+            constexpr int kU = 8;   // lookups in flight per thread: the searches and loads of one are a chain of LDS and L2 trips
+            for (uint32_t e0 = tid; e0 < all; e0 += kU * kDThreads) {
+                uint32_t row[kU], p[kU], bag[kU];
+#pragma unroll
+                for (int q = 0; q < kU; ++q) row[q] = 0u;
+#pragma unroll
+                for (uint32_t step = kDenseRows / 2; step > 0u; step >>= 1)   // the row: last h < nd with s_pref[h] <= e
+#pragma unroll
+                    for (int q = 0; q < kU; ++q)
+                        if (s_pref[row[q] + step] <= e0 + q * kDThreads) row[q] += step;   // (s_pref[nd ..] is above every e)
+#pragma unroll
+                for (int q = 0; q < kU; ++q) {
+                    const uint32_t e = e0 + q * kDThreads;
+                    p[q] = s_lo[row[q]] + (e - s_pref[row[q]]);
+                    bag[q] = a.bag_sorted[e < all ? p[q] : s_lo[0]];
                 }
-                const uint32_t p = s_lo[lo] + (e - s_pref[lo]);
-                const uint32_t bag = a.bag_sorted[p];
-                bool take = true;
-                if (flags & 2u) {   // position among the row's lookups of this bag: 65535 of them per round
-                    uint32_t q0 = s_lo[lo], q1 = p;   // first position in [q0, p] that holds this bag
-                    while (q0 < q1) {
-                        const uint32_t mid = q0 + ((q1 - q0) >> 1);
-                        if (a.bag_sorted[mid] < bag) q0 = mid + 1u;
-                        else q1 = mid;
+#pragma unroll
+                for (int q = 0; q < kU; ++q) {
+                    if (e0 + q * kDThreads >= all) continue;
+                    bool take = true;
+                    if (flags & 2u) {   // position among the row's lookups of this bag: 65535 of them per round
+                        uint32_t q0 = s_lo[row[q]], q1 = p[q];   // first position in [q0, p] that holds this bag
+                        while (q0 < q1) {
+                            const uint32_t mid = q0 + ((q1 - q0) >> 1);
+                            if (a.bag_sorted[mid] < bag[q]) q0 = mid + 1u;
+                            else q1 = mid;
+                        }
+                        const uint32_t r = (p[q] - q0) / 65535u;
+                        take = r == round;
+                        more |= r > round;
                     }
-                    const uint32_t r = (p - q0) / 65535u;
-                    take = r == round;
-                    more |= r > round;
+                    const uint32_t b = (uint32_t)((int64_t)bag[q] - bag0) - b0;
+                    if (take && b < nb) atomicAdd(&cnt32[row[q] * (kCntPitch / 2) + (b >> 1)], 1u << (16u * (b & 1u)));
                 }
-                const uint32_t b = (uint32_t)((int64_t)bag - bag0) - b0;
-                if (take && b < nb) atomicAdd(&cnt32[lo * (kCntPitch / 2) + (b >> 1)], 1u << (16u * (b & 1u)));
             }
-            if (more) atomicOr(&s_flags, 8u);
+            if (more) atomicOr(&S->flags, 8u);
             __syncthreads();
             bool big = false;
-            for (uint32_t i = tid; i < mt * 32u * (kCntPitch / 8); i += kDThreads) {
+            for (uint32_t i = tid; i < MT * 32u * (kCntPitch / 8); i += kDThreads) {
                 uint4 v = reinterpret_cast<uint4*>(s_cnt)[i];
                 uint32_t* x = &v.x;
 #pragma unroll
@@ -187,78 +197,79 @@ __global__ __launch_bounds__(kDThreads, 2) void seg_dense_kernel(const SegArgs a
                 }
                 reinterpret_cast<uint4*>(s_cnt)[i] = v;
             }
-            if (big) atomicOr(&s_flags, 4u);
+            if (big) atomicOr(&S->flags, 4u);
             __syncthreads();
             // ---- stream the block's gradient rows, 16 bags per step; a wavefront takes every splits-th step
             const int steps = (int)((nb + 15u) >> 4);
-            raw_t x[8];
-            auto load_step = [&](const int j) {
+            const char* const gblk = gtab + (int64_t)b0 * pitch;
+            // (a bag behind the batch's end has zero counts: any finite gradient row will do, the block's last)
+            auto load_step = [&](raw_t (&x)[8], const int j) {
+                if (nb == (uint32_t)kDenseBags) {
+                    const char* const row0 = gblk + (int64_t)(j * 16) * pitch;
+                    const uint32_t off = lane_col + (uint32_t)(kh * 8) * (uint32_t)pitch;
 #pragma unroll
-                for (int i = 0; i < 8; ++i) {
-                    const uint32_t b = (uint32_t)(j * 16 + kh * 8 + i);
-                    x[i] = (col_on && j < steps && b < nb) ? Pair<GT>::load(gcol + (int64_t)(b0 + b) * a.sumD) : Pair<GT>::zero();
-                }
-            };
-            load_step(split);
-            for (int j = split; j < steps; j += splits) {
-                // pieces of the 8 bags, packed for the matrix core: [piece][column of the pair]
-                uint4 f[kPieces][2];
-                if constexpr (kExact) {
-                    uint32_t* f0 = &f[0][0].x;
-                    uint32_t* f1 = &f[0][1].x;
-#pragma unroll
-                    for (int i = 0; i < 4; ++i) {
-                        f0[i] = lower_halves(x[2 * i], x[2 * i + 1]);
-                        f1[i] = upper_halves(x[2 * i], x[2 * i + 1]);
-                    }
+                    for (int i = 0; i < 8; ++i) x[i] = Pair<GT>::load(reinterpret_cast<const GT*>(row0 + i * pitch + off));
                 } else {
-                    float v[8][2];
 #pragma unroll
                     for (int i = 0; i < 8; ++i) {
-                        const float2 g = Pair<GT>::to_float(x[i]);
-                        v[i][0] = g.x;
-                        v[i][1] = g.y;
+                        const uint32_t b = (uint32_t)(j * 16 + kh * 8 + i);
+                        x[i] = Pair<GT>::load(reinterpret_cast<const GT*>(gblk + (int64_t)(b < nb ? b : nb - 1u) * pitch + lane_col));
                     }
+                }
+            };
+            auto multiply_step = [&](raw_t (&x)[8], const int j, const int next) {
+                uint4 f[2][kPieces];   // per column of the pair: pieces of the 8 bags, packed for the matrix core
+                if constexpr (kExact) {
+#pragma unroll
+                    for (int i = 0; i < 4; ++i) {
+                        (&f[0][0].x)[i] = lower_halves(x[2 * i], x[2 * i + 1]);
+                        (&f[1][0].x)[i] = upper_halves(x[2 * i], x[2 * i + 1]);
+                    }
+                } else {
+                    float sc[8];
                     if constexpr (MEAN) {
-                        const float4 sa = *reinterpret_cast<const float4*>(&s_scale[j * 16 + kh * 8]);
-                        const float4 sb = *reinterpret_cast<const float4*>(&s_scale[j * 16 + kh * 8 + 4]);
-                        const float sc[8] = {sa.x, sa.y, sa.z, sa.w, sb.x, sb.y, sb.z, sb.w};
-#pragma unroll
-                        for (int i = 0; i < 8; ++i) {
-                            v[i][0] *= sc[i];
-                            v[i][1] *= sc[i];
-                        }
+                        const float4 sa = *reinterpret_cast<const float4*>(&S->scale[j * 16 + kh * 8]);
+                        const float4 sb = *reinterpret_cast<const float4*>(&S->scale[j * 16 + kh * 8 + 4]);
+                        sc[0] = sa.x; sc[1] = sa.y; sc[2] = sa.z; sc[3] = sa.w;
+                        sc[4] = sb.x; sc[5] = sb.y; sc[6] = sb.z; sc[7] = sb.w;
                     }
 #pragma unroll
-                    for (int p = 0; p < 3; ++p)
+                    for (int i = 0; i < 4; ++i) {
+                        const float2 g0 = Pair<GT>::to_float(x[2 * i]), g1 = Pair<GT>::to_float(x[2 * i + 1]);
 #pragma unroll
                         for (int c = 0; c < 2; ++c) {
-                            uint32_t* o = &f[p][c].x;
-#pragma unroll
-                            for (int i = 0; i < 4; ++i) {
-                                const uint32_t u0 = __float_as_uint(v[2 * i][c]), u1 = __float_as_uint(v[2 * i + 1][c]);
-                                o[i] = upper_halves(u0, u1);
-                                if (p < 2) {   // what the upper 16 bits leave, exactly
-                                    v[2 * i][c] -= __uint_as_float(u0 & 0xFFFF0000u);
-                                    v[2 * i + 1][c] -= __uint_as_float(u1 & 0xFFFF0000u);
-                                }
+                            float v0 = c ? g0.y : g0.x, v1 = c ? g1.y : g1.x;
+                            if constexpr (MEAN) {
+                                v0 *= sc[2 * i];
+                                v1 *= sc[2 * i + 1];
                             }
-                        }
-                }
-                load_step(j + splits);
 #pragma unroll
-                for (int m = 0; m < kMTiles; ++m) {
-                    if ((uint32_t)m < mt) {
-                        const uint4 av = *reinterpret_cast<const uint4*>(&s_cnt[(m * 32 + (lane & 31)) * kCntPitch + j * 16 + kh * 8]);
-#pragma unroll
-                        for (int p = kPieces - 1; p >= 0; --p) {   // small pieces first
-                            acc[m][0] = mfma<kF16>(av, f[p][0], acc[m][0]);
-                            acc[m][1] = mfma<kF16>(av, f[p][1], acc[m][1]);
+                            for (int p = 0; p < 3; ++p) {
+                                const uint32_t u0 = __float_as_uint(v0), u1 = __float_as_uint(v1);
+                                (&f[c][p].x)[i] = upper_halves(u0, u1);
+                                v0 -= __uint_as_float(u0 & 0xFFFF0000u);   // what the upper 16 bits leave, exactly
+                                v1 -= __uint_as_float(u1 & 0xFFFF0000u);
+                            }
                         }
                     }
                 }
-            }
-            const uint32_t fl = s_flags;
+                load_step(x, next);
+#pragma unroll
+                for (int m = 0; m < MT; ++m) {
+                    const uint4 av = *reinterpret_cast<const uint4*>(&s_cnt[(m * 32 + (lane & 31)) * kCntPitch + j * 16 + kh * 8]);
+#pragma unroll
+                    for (int p = kPieces - 1; p >= 0; --p) {   // small pieces first
+                        acc[m][0] = mfma<kF16>(av, f[0][p], acc[m][0]);
+                        acc[m][1] = mfma<kF16>(av, f[1][p], acc[m][1]);
+                    }
+                }
+            };
+            raw_t x[8];   // the next step's rows are in flight while a step multiplies
+            const int last = steps - 1;
+            load_step(x, split < last ? split : last);
+#pragma unroll 1
+            for (int j = split; j < steps; j += splits) multiply_step(x, j, j + splits < last ? j + splits : last);
+            const uint32_t fl = S->flags;
             if (digit == 0u && !(fl & 4u)) {        // no count has an upper byte: skip that pass
                 if (!(fl & 8u)) break;
                 ++pass;
@@ -268,38 +279,35 @@ __global__ __launch_bounds__(kDThreads, 2) void seg_dense_kernel(const SegArgs a
         }
     }
     // ---- add up the wavefronts that shared the bags of a column group, in order
-    float* const red = reinterpret_cast<float*>(s_cnt);   // [32 * mt rows][64 * groups columns]: at most 64 KB (splits > 1: groups <= 2)
+    float* const red = reinterpret_cast<float*>(s_cnt);   // [32 * MT rows][64 * groups columns]: at most 64 KB (splits > 1: groups <= 2)
     for (int sp = 1; sp < splits; ++sp) {
         __syncthreads();
         if (split == sp) {
 #pragma unroll
-            for (int m = 0; m < kMTiles; ++m)
-                if ((uint32_t)m < mt)
+            for (int m = 0; m < MT; ++m)
 #pragma unroll
-                    for (int r = 0; r < 16; ++r) {
-                        const int h = m * 32 + (r & 3) + 8 * (r >> 2) + 4 * kh;
-                        *reinterpret_cast<float2*>(&red[h * (64 * groups) + cg * 64 + 2 * (lane & 31)]) = make_float2(acc[m][0][r], acc[m][1][r]);
-                    }
+                for (int r = 0; r < 16; ++r) {
+                    const int h = m * 32 + (r & 3) + 8 * (r >> 2) + 4 * kh;
+                    *reinterpret_cast<float2*>(&red[h * (64 * groups) + cg * 64 + 2 * (lane & 31)]) = make_float2(acc[m][0][r], acc[m][1][r]);
+                }
         }
         __syncthreads();
         if (split == 0) {
 #pragma unroll
-            for (int m = 0; m < kMTiles; ++m)
-                if ((uint32_t)m < mt)
+            for (int m = 0; m < MT; ++m)
 #pragma unroll
-                    for (int r = 0; r < 16; ++r) {
-                        const int h = m * 32 + (r & 3) + 8 * (r >> 2) + 4 * kh;
-                        const float2 o = *reinterpret_cast<const float2*>(&red[h * (64 * groups) + cg * 64 + 2 * (lane & 31)]);
-                        acc[m][0][r] += o.x;
-                        acc[m][1][r] += o.y;
-                    }
+                for (int r = 0; r < 16; ++r) {
+                    const int h = m * 32 + (r & 3) + 8 * (r >> 2) + 4 * kh;
+                    const float2 o = *reinterpret_cast<const float2*>(&red[h * (64 * groups) + cg * 64 + 2 * (lane & 31)]);
+                    acc[m][0][r] += o.x;
+                    acc[m][1][r] += o.y;
+                }
         }
     }
     if (split == 0 && col_on) {
         const size_t slot0 = (size_t)a.dense_slot0 + (size_t)t * kDenseRows * a.dense_chunks + chunk;
 #pragma unroll
-        for (int m = 0; m < kMTiles; ++m)
-            if ((uint32_t)m < mt)
+        for (int m = 0; m < MT; ++m)
 #pragma unroll
                 for (int r = 0; r < 16; ++r) {
                     const uint32_t h = (uint32_t)(m * 32 + (r & 3) + 8 * (r >> 2) + 4 * kh);
@@ -307,6 +315,25 @@ __global__ __launch_bounds__(kDThreads, 2) void seg_dense_kernel(const SegArgs a
                         *reinterpret_cast<float2*>(a.partial + (slot0 + (size_t)h * a.dense_chunks) * a.maxD + col) = make_float2(acc[m][0][r], acc[m][1][r]);
                 }
     }
+}
+
+template <bool MEAN, typename GT>
+__global__ __launch_bounds__(kDThreads, 2) void seg_dense_kernel(const SegArgs a, const uint32_t col_blocks) {
+    __shared__ DenseLds S;
+    uint32_t bx = blockIdx.x;
+    const uint32_t cb = bx % col_blocks;
+    bx /= col_blocks;
+    const uint32_t chunk = bx % a.dense_chunks;
+    const int t = (int)(bx / a.dense_chunks);
+    const uint32_t nd = a.dense_n[t];
+    if (nd == 0u) return;
+    const int d0 = a.D_off[t];
+    const int D = a.D_off[t + 1] - d0;
+    if ((int)cb * 256 >= D) return;
+    if (nd > 96u) dense_run<4, MEAN, GT>(a, cb, chunk, t, nd, d0, D, &S);
+    else if (nd > 64u) dense_run<3, MEAN, GT>(a, cb, chunk, t, nd, d0, D, &S);
+    else if (nd > 32u) dense_run<2, MEAN, GT>(a, cb, chunk, t, nd, d0, D, &S);
+    else dense_run<1, MEAN, GT>(a, cb, chunk, t, nd, d0, D, &S);
 }
 
 template <typename GT>

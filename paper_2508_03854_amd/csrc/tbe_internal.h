@@ -19,6 +19,7 @@ constexpr int kMaxParts = 1024;          // parts that a long row is cut into at
 constexpr int kMaxSortSegments = 4096;  // tables beyond this are sorted as one segment on the linearised key
 constexpr int kDenseRows = 128;  // rows per table that the dense-row kernel reduces at most (multiple of 32)
 constexpr int kDenseBags = 256;  // bags per block of that kernel
+constexpr int kDenseMinBags = 1024;   // batches of fewer samples have no dense rows
 constexpr int kFwdGroupMaxLanes = 32;   // rows of at most this many lanes use one bag per lane group
 constexpr int kHotRows = 256;           // rows per table that the forward may hold in LDS (the handle's hot-row list)
 constexpr int kMaxReplicas = 16;        // replicas of one buffer that tbe_replica_mean averages in one call

@@ -209,7 +209,7 @@ __global__ __launch_bounds__(kListThreads) void list_rows_flat_kernel(const SegA
 // of a dense row once, coalesced.)
 constexpr int kIndexSplit = 32;
 __global__ __launch_bounds__(256) void dense_index_kernel(const SegArgs a) {
-    __shared__ uint32_t s_start[kDenseRows], s_end[kDenseRows], s_pref[kDenseRows + 1];
+    __shared__ uint32_t s_start[kDenseRows], s_end[kDenseRows], s_pref[kDenseRows];
     __shared__ uint32_t smem[256 / kWave];
     const int t = blockIdx.x / kIndexSplit;
     const uint32_t y = blockIdx.x % kIndexSplit;
@@ -225,26 +225,39 @@ __global__ __launch_bounds__(256) void dense_index_kernel(const SegArgs a) {
     }
     uint32_t all;
     const uint32_t ex = block_excl_scan<256>(len, smem, &all);
-    if (tid < nd) s_pref[tid] = ex;
-    if (tid == 0) s_pref[nd] = all;
+    if (tid < (uint32_t)kDenseRows) s_pref[tid] = tid < nd ? ex : 0xFFFFFFFFu;
     __syncthreads();
     const uint32_t bag0 = (uint32_t)t * (uint32_t)a.B;
     const uint32_t e0 = (uint32_t)((uint64_t)all * y / kIndexSplit), e1 = (uint32_t)((uint64_t)all * (y + 1u) / kIndexSplit);
-    for (uint32_t e = e0 + tid; e < e1; e += 256) {
-        uint32_t lo = 0, hi = nd;   // the row: last h with s_pref[h] <= e
-        while (hi - lo > 1u) {
-            const uint32_t mid = (lo + hi) >> 1;
-            if (s_pref[mid] <= e) lo = mid;
-            else hi = mid;
+    constexpr int kU = 8;   // lookups in flight per thread
+    for (uint32_t f = e0 + tid; f < e1; f += kU * 256) {
+        uint32_t row[kU], p[kU], bag[kU], prev[kU];
+#pragma unroll
+        for (int q = 0; q < kU; ++q) row[q] = 0u;
+#pragma unroll
+        for (uint32_t step = kDenseRows / 2; step > 0u; step >>= 1)   // the row: last h < nd with s_pref[h] <= e
+#pragma unroll
+            for (int q = 0; q < kU; ++q)
+                if (s_pref[row[q] + step] <= f + q * 256) row[q] += step;   // (s_pref[nd ..] is above every e)
+#pragma unroll
+        for (int q = 0; q < kU; ++q) {
+            const uint32_t e = f + q * 256 < e1 ? f + q * 256 : e1 - 1u;
+            if (f + q * 256 >= e1) row[q] = nd - 1u;
+            p[q] = f + q * 256 < e1 ? s_start[row[q]] + (e - s_pref[row[q]]) : s_start[nd - 1u];
+            bag[q] = a.bag_sorted[p[q]];
+            prev[q] = a.bag_sorted[p[q] > s_start[row[q]] ? p[q] - 1u : p[q]];
         }
-        const uint32_t p = s_start[lo] + (e - s_pref[lo]);
-        const bool first = p == s_start[lo], last = p + 1u == s_end[lo];
-        const uint32_t b1 = (a.bag_sorted[p] - bag0) / kDenseBags;
-        const uint32_t b0 = first ? 0u : (a.bag_sorted[p - 1u] - bag0) / kDenseBags + 1u;   // borders b0 .. b1 are p
-        uint32_t* ix = a.dense_index + ((size_t)t * kDenseRows + lo) * (a.dense_blocks + 1u);
-        for (uint32_t k = b0; k <= b1 && k <= a.dense_blocks; ++k) ix[k] = p;
-        if (last)
-            for (uint32_t k = b1 + 1u; k <= a.dense_blocks; ++k) ix[k] = p + 1u;
+#pragma unroll
+        for (int q = 0; q < kU; ++q) {
+            if (f + q * 256 >= e1) continue;
+            const bool first = p[q] == s_start[row[q]], last = p[q] + 1u == s_end[row[q]];
+            const uint32_t b1 = (bag[q] - bag0) / kDenseBags;
+            const uint32_t b0 = first ? 0u : (prev[q] - bag0) / kDenseBags + 1u;   // borders b0 .. b1 are p
+            uint32_t* ix = a.dense_index + ((size_t)t * kDenseRows + row[q]) * (a.dense_blocks + 1u);
+            for (uint32_t k = b0; k <= b1 && k <= a.dense_blocks; ++k) ix[k] = p[q];
+            if (last)
+                for (uint32_t k = b1 + 1u; k <= a.dense_blocks; ++k) ix[k] = p[q] + 1u;
+        }
     }
 }
 

@@ -57,10 +57,10 @@ struct SegArgs {
     uint32_t dense_per_chunk;
 };
 
-// Dense rows exist only where a table's gradient block is too large for an L2 (4 MiB per die, half of it at most): a
-// block that fits is gathered from at L2 speed anyway.
+// Dense rows exist only where a table's gradient block is too large for an L2 (4 MiB per die, half of it at most; a block
+// that fits is gathered from at L2 speed anyway) and has enough bags to share out.
 __device__ __host__ __forceinline__ bool dense_block(const uint32_t B, const uint32_t D) {
-    return (uint64_t)B * D * 4u > ((uint64_t)2 << 20);
+    return B >= (uint32_t)kDenseMinBags && (uint64_t)B * D * 4u > ((uint64_t)2 << 20);
 }
 
 // table of a linearised row key: the t with row_base[t] <= key < row_base[t+1]
