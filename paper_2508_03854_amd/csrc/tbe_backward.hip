@@ -448,9 +448,12 @@ __global__ __launch_bounds__(kSegThreads, 4) void seg_update_wide_kernel(const S
 // ---- one workgroup per long row: add its partial sums, then the step ----------------------------------
 // Wavefront w adds slots w, w+4, ... in ascending order, the four sums are added in wavefront order, and
 // wavefront 0 applies the step: a fixed order, so the result does not depend on scheduling.
-template <typename WT>
+// A dense row whose sum is not finite is reduced again from its own lookups, each wavefront a quarter of them: its partial
+// sums hold count * gradient for every bag of the table, and a count of zero times an infinity or NaN of a bag that the row
+// is not in is NaN.  So a non-finite gradient reaches the rows of its own bag and no others.
+template <typename WT, bool MEAN, typename GT>
 __global__ __launch_bounds__(kSegThreads) void seg_long_update_kernel(const SegArgs a) {
-    __shared__ float s_sum[kSegThreads / kWave][1024];
+    __shared__ __align__(16) float s_sum[kSegThreads / kWave][1024];
     if (a.counters[4] != 0u) return;
     const uint32_t nlong = a.counters[1] < a.cap_long ? a.counters[1] : a.cap_long;
     WT* tables = static_cast<WT*>(a.tables);
@@ -461,7 +464,8 @@ __global__ __launch_bounds__(kSegThreads) void seg_long_update_kernel(const SegA
         const uint32_t key = a.keys_unique[ent.x];
         const int t = (int)ent.w;
         const int D = a.D_off[t + 1] - a.D_off[t];
-        const uint32_t nch = (ent.z & kDenseFlag) ? a.dense_chunks : ent.z;   // partial sums of the row
+        const bool dense = (ent.z & kDenseFlag) != 0u;
+        const uint32_t nch = dense ? a.dense_chunks : ent.z;   // partial sums of the row
         // here all 64 lanes cover the row (or a 256-column part of it); groups are not used
         RowGeom g;
         g.D = D; g.LPR = kWave; g.G = 1; g.sub = 0; g.lc = lane_id() * 4;
@@ -489,11 +493,40 @@ __global__ __launch_bounds__(kSegThreads) void seg_long_update_kernel(const SegA
             }
         }
         __syncthreads();
+        if (dense) {   // (the same for the whole workgroup, and so is what the wavefronts find in s_sum)
+            float bad = 0.f;   // 0 * x is 0 for every finite x, else NaN
+            for (int col = g.lc; col < D; col += 256)
+#pragma unroll
+                for (uint32_t w2 = 0; w2 < kW; ++w2) {
+                    const float4 o = *reinterpret_cast<const float4*>(&s_sum[w2][col]);
+                    bad = fmaf(0.f, (o.x + o.y) + (o.z + o.w), bad);
+                }
+            if (__any(!(bad == 0.f))) {
+                __syncthreads();   // (all wavefronts have read s_sum)
+                const uint32_t s0 = a.seg_start[ent.x];
+                const uint64_t len = a.seg_start[ent.x + 1] - s0;
+                const uint32_t lo = s0 + (uint32_t)(len * (uint32_t)wv / kW);
+                const uint32_t hi = s0 + (uint32_t)(len * ((uint32_t)wv + 1u) / kW);
+                const GradAddr ga = grad_addr(a, t, D);
+#pragma unroll 1
+                for (int c0 = 0; c0 < D; c0 += 256) {
+                    RowGeom gc = g;
+                    gc.D = D - c0;
+                    float sum[1][4] = {{0.f, 0.f, 0.f, 0.f}};
+                    segment_reduce<1, MEAN, GT>(sum, gc, static_cast<const GT*>(a.grad_out) + ga.base + c0, ga.pitch, ga.row0,
+                                                a.bag_sorted, a.offsets, lo, hi);
+                    if (c0 + g.lc < D) *reinterpret_cast<float4*>(&s_sum[wv][c0 + g.lc]) = make_float4(sum[0][0], sum[0][1], sum[0][2], sum[0][3]);
+                }
+                __syncthreads();
+            }
+        }
         if (wv == 0) {
 #pragma unroll
             for (int c = 0; c < 4; ++c) {
                 const int col = g.lc + c * 256;
                 if (col < D) {
+                    const float4 first = *reinterpret_cast<const float4*>(&s_sum[0][col]);
+                    acc[c][0] = first.x; acc[c][1] = first.y; acc[c][2] = first.z; acc[c][3] = first.w;
 #pragma unroll
                     for (int w2 = 1; w2 < kSegThreads / kWave; ++w2) {
                         const float4 o = *reinterpret_cast<const float4*>(&s_sum[w2][col]);
@@ -541,6 +574,17 @@ static void launch_row_updates(const tbe_handle* h, const SegArgs& a, bool mean,
             if (mean) seg_update_wide_kernel<__half, true, GT><<<kSegBlocks, kSegThreads, 0, s>>>(a);
             else seg_update_wide_kernel<__half, false, GT><<<kSegBlocks, kSegThreads, 0, s>>>(a);
         }
+    }
+}
+
+template <typename GT>
+static void launch_long_update(const tbe_handle* h, const SegArgs& a, bool mean, unsigned grid, hipStream_t s) {
+    if (h->dtype == TBE_F32) {
+        if (mean) seg_long_update_kernel<float, true, GT><<<grid, kSegThreads, 0, s>>>(a);
+        else seg_long_update_kernel<float, false, GT><<<grid, kSegThreads, 0, s>>>(a);
+    } else {
+        if (mean) seg_long_update_kernel<__half, true, GT><<<grid, kSegThreads, 0, s>>>(a);
+        else seg_long_update_kernel<__half, false, GT><<<grid, kSegThreads, 0, s>>>(a);
     }
 }
 
@@ -621,8 +665,9 @@ hipError_t launch_segment_update(const tbe_handle* h, const Workspace& w, char* 
         LaunchTimer tm(h, s, "seg_long_update");
         // one row per workgroup and round, a dependent chain of loads each: enough workgroups to fill every CU's slots
         const unsigned grid = (unsigned)(w.cap_long < kSegBlocks ? w.cap_long : kSegBlocks);
-        if (h->dtype == TBE_F32) seg_long_update_kernel<float><<<grid, kSegThreads, 0, s>>>(a);
-        else seg_long_update_kernel<__half><<<grid, kSegThreads, 0, s>>>(a);
+        if (grad_io == 0) launch_long_update<float>(h, a, mean, grid, s);
+        else if (grad_io == 1) launch_long_update<__half>(h, a, mean, grid, s);
+        else launch_long_update<bf16_t>(h, a, mean, grid, s);
         tm.done();
     }
     return hipGetLastError();

@@ -18,8 +18,8 @@
 // LDS, 128 accumulator registers) overlap each other's counting.  The partial sums of a row, one per workgroup run, are added
 // in order by the kernel that applies the step, so the result does not depend on scheduling.
 // Bound: the stream of the gradient block (matrix work at 128 rows and fp32 gradients is about a third of it).
-// (Gradients are taken to be finite: 0 * Inf is NaN, so a non-finite element of one bag's gradient may reach every dense row
-// of its table.)
+// 0 * Inf is NaN, so a non-finite element of one bag's gradient reaches every dense row of its table here; the kernel that
+// adds the partial sums reduces such rows again from their own lookups.
 #include "tbe_rows.h"
 
 namespace tbe {

@@ -52,3 +52,45 @@ def test_dense_rows_at_the_borders(rows, D, B, hot, repeat, dtype, pooling, io):
     rep = H.check_step(cfg, tbe, flat, state, tabs, st, idx, off, gout, ws, index_dtype=torch.int32, io=io)
     assert rep["max_seg"] > 64
     tbe.close()
+
+
+@pytest.mark.parametrize("D,dtype,pooling,io,value", [
+    (128, "f32", "sum", torch.float32, float("inf")),
+    (520, "f16", "mean", torch.bfloat16, float("nan")),            # three column blocks
+    (136, "f32", "sum", torch.float16, float("-inf")),
+])
+def test_a_non_finite_gradient_stays_with_its_own_bag(D, dtype, pooling, io, value):
+    """One element of one bag's gradient is not finite: the rows of that bag become so, all others get the step they get
+    without it (the sum of the same values in another order: both are within a few units of 2^-24 of the lookups' sum, a
+    binary16 weight may round to its neighbour)."""
+    if not torch.cuda.is_available():
+        pytest.skip("no GPU")
+    from paper_2508_03854_amd import TBE
+    B, R, hot = 4500, 400, 60
+    g = torch.Generator().manual_seed(D)
+    lens = torch.randint(2, 9, (B,), generator=g)
+    off = torch.zeros(B + 1, dtype=torch.int64)
+    off[1:] = torch.cumsum(lens, 0)
+    idx = torch.randint(0, hot, (int(off[-1]),), generator=g) * 7 % R
+    bag = B // 3
+    weights = torch.empty(R * D).uniform_(-0.01, 0.01, generator=g)
+    grad = torch.randn(B, D, generator=g).to(io)
+    spoilt = grad.clone()
+    spoilt[bag, D - 3] = value
+    tbe = TBE([R], [D], dtype)
+    ws = tbe.alloc_workspace(B, idx.numel())
+    res = []
+    for go in (grad, spoilt):
+        w, st = weights.to(tbe.torch_dtype).cuda(), torch.ones(R, device="cuda")
+        tbe.backward_rowwise_adagrad_ex(go.cuda(), idx.cuda(), off.cuda(), B, w, st, ws, pooling=pooling, lr=0.05, eps=1e-8)
+        res.append((w.cpu().view(R, D).double(), st.cpu().double()))
+    hit = torch.zeros(R, dtype=torch.bool)
+    hit[idx[int(off[bag]):int(off[bag + 1])]] = True
+    assert 0 < int(hit.sum()) < hot
+    (w0, s0), (w1, s1) = res
+    assert bool(torch.isfinite(w0).all()) and bool(torch.isfinite(s0).all())
+    assert not bool(torch.isfinite(s1[hit]).any())
+    atol = 0.05 * 1e-5 + (2.0 ** -14 if dtype == "f16" else 0.0)
+    torch.testing.assert_close(w1[~hit], w0[~hit], rtol=0.0, atol=atol)
+    torch.testing.assert_close(s1[~hit], s0[~hit], rtol=1e-5, atol=0.0)
+    tbe.close()
