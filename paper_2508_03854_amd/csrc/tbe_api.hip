@@ -51,6 +51,14 @@ SortShape sort_shape(const tbe_handle* h, int64_t N) {
     return sh;
 }
 
+// At least sort_shape(h, n).max_chunks for every n <= N: tiles of 1024 end at 128 K lookups and tiles of 2048 at
+// kSelfScanMax, so a batch above such a border may have fewer chunks than one below it.
+static size_t most_chunks(const tbe_handle* h, int64_t N) {
+    const int64_t small = std::min(N, (int64_t)32 * 4096) / 1024, middle = std::min(N, kSelfScanMax) / 2048;
+    const int64_t large = std::min(N / kRadixTile, (int64_t)kRadixMaxBlocks);
+    return (size_t)(std::max(std::max(small, middle), large) + 1 + (h->segmented ? h->T : 1));
+}
+
 // A row with more than this many lookups is long, i.e. shared out to several wavefronts in parts of this size.  A wavefront
 // walks 512 lookups of a wide row in about 60 us, so small batches, whose row updates take less than that, cut finer; the
 // borders follow from the memory of the partial sums (at most 2 n / part slots): never more than n / 48 plus a constant.
@@ -67,6 +75,7 @@ static int64_t most_parts(int64_t N) {
     return m;
 }
 
+// No part of it shrinks when B or N grows: a workspace made for a batch serves every smaller one.
 Workspace carve(const tbe_handle* h, int32_t B, int64_t N, bool allow_dense) {
     Workspace w;
     memset(&w, 0, sizeof(w));
@@ -97,31 +106,36 @@ Workspace carve(const tbe_handle* h, int32_t B, int64_t N, bool allow_dense) {
     // Dense rows: some table's gradient block is large, and the batch could hold two lookups of them per bag.  A dense row
     // leaves one partial sum per chunk of bags: enough chunks for about a thousand workgroups in all, at most 32.
     w.dense = allow_dense && h->T <= kMaxSortSegments && B >= kDenseMinBags && (uint64_t)B * (uint64_t)h->maxD * 4u > ((uint64_t)2 << 20);
+    uint32_t most_dense_chunks = 0;
     if (w.dense) {
         w.dense_blocks = ((uint32_t)B + kDenseBags - 1) / kDenseBags;
         const uint32_t want = h->T >= 1024 ? 1u : (h->T <= 32 ? 32u : 1024u / (uint32_t)h->T);
         const uint32_t chunks = want < w.dense_blocks ? want : w.dense_blocks;
+        most_dense_chunks = chunks;
         w.dense_per_chunk = (w.dense_blocks + chunks - 1) / chunks;
         w.dense_chunks = (w.dense_blocks + w.dense_per_chunk - 1) / w.dense_per_chunk;
         w.dense_n = take(4 * (size_t)h->T);
         w.dense_rows = take(4 * (size_t)h->T * kDenseRows);
         w.dense_index = take(4 * (size_t)h->T * kDenseRows * (w.dense_blocks + 1));
     }
+    // (equal runs of blocks may come to fewer chunks than were wanted, and to more again in a smaller batch)
+    const size_t dense_slots = w.dense ? (size_t)h->T * kDenseRows * most_dense_chunks : 0;
     const size_t shared = off;
     // while the sort runs
     w.sort = sort_shape(h, (int64_t)n);
     // (8-bit digits in a handle of many tables may exceed the cap; their histograms grow with N by themselves)
-    const size_t least8 = 2 * 256 * (size_t)(w.sort.max_chunks + 1);
-    w.radix_hist = take(std::max(std::max(w.sort.hist_bytes, hist_cap((int64_t)n)), least8));
+    const size_t chunks = most_chunks(h, (int64_t)n);
+    const size_t hist8 = (size_t)(w.sort.self_scan ? 2 : 4) * 256 * (chunks + 1);
+    w.radix_hist = take(std::max(std::max(w.sort.hist_bytes, hist_cap((int64_t)n)), hist8));
     w.bin_tot = take(w.sort.self_scan ? 0 : 4 * 256 * (size_t)w.sort.nseg);
     w.seg_chunk0 = take(w.sort.self_scan ? 0 : 4 * (size_t)(w.sort.nseg + 1));
-    w.chunk_desc = take(32 * (size_t)w.sort.max_chunks);
+    w.chunk_desc = take(32 * chunks);
     w.rle_blocks = (int)(((int64_t)n + kRleTile - 1) / kRleTile);
     w.rle_counts = take(8 * (size_t)w.rle_blocks);
     w.total = off;
     // while a step is applied
     off = shared;
-    w.partial = take(4 * ((size_t)w.cap_main + (w.dense ? (size_t)h->T * kDenseRows * w.dense_chunks : 0)) * (size_t)h->maxD);
+    w.partial = take(4 * ((size_t)w.cap_main + dense_slots) * (size_t)h->maxD);
     w.total = std::max(w.total, off);
     return w;
 }

@@ -1,0 +1,47 @@
+"""A workspace made for a batch serves every smaller one: the size never shrinks when the batch or its lookups grow, on both
+sides of every border at which the sort or the dense rows change their layout."""
+import pytest
+import torch
+
+pytestmark = pytest.mark.gpu
+
+
+@pytest.mark.parametrize("rows,D", [([4000] * 4, 1024), ([100_000] * 64, 128), ([50], 4), ([30_000] * 200, 8)])
+def test_workspace_grows_with_the_batch(rows, D):
+    if not torch.cuda.is_available():
+        pytest.skip("no GPU")
+    from paper_2508_03854_amd import TBE
+    tbe = TBE(rows, [D] * len(rows), "f32")
+    batches = [1, 1023, 1024] + [256 * k + e for k in (4, 8, 16, 17, 32, 33, 41, 64, 65, 130) for e in (0, 1)]
+    borders = [131072, 393216, 1572864, 1 << 21, 32 * 1024 * len(rows), 32 * 2048 * len(rows), 4 * 32 * 2048 * len(rows), 8192 * 4096]
+    lookups = sorted({1} | {n + e for n in borders for e in (0, 1, 4097)})
+    size = {(B, n): tbe.workspace_bytes(B, n) for B in batches for n in lookups}
+    for n in lookups:
+        for small, large in zip(batches, batches[1:]):
+            assert size[small, n] <= size[large, n], (n, small, large)
+    for B in batches:
+        for small, large in zip(lookups, lookups[1:]):
+            assert size[B, small] <= size[B, large], (B, small, large)
+    tbe.close()
+
+
+def test_a_smaller_last_batch_uses_the_same_workspace():
+    """33 blocks of bags in runs of two, then 32 blocks one by one: the second needs more partial sums, in the same memory."""
+    if not torch.cuda.is_available():
+        pytest.skip("no GPU")
+    from paper_2508_03854_amd import TBE
+    R, D, L = 300, 1024, 6
+    tbe = TBE([R], [D], "f32")
+    ws = tbe.alloc_workspace(33 * 256, 33 * 256 * L)
+    B = 32 * 256
+    g = torch.Generator().manual_seed(5)
+    idx = torch.randint(0, 40, (B * L,), generator=g)
+    grad = torch.randn(B, D, generator=g)
+    w, st = torch.zeros(R * D, device="cuda"), torch.ones(R, device="cuda")
+    tbe.backward_rowwise_adagrad(grad.cuda(), idx.cuda(), torch.arange(0, B * L + 1, L).cuda(), B, w, st, ws, lr=1.0, eps=0.0)
+    ref = torch.zeros(R, D, dtype=torch.float64).index_add_(0, idx, grad.double().repeat_interleave(L, 0))
+    v = 1.0 + (ref * ref).sum(1)
+    # about 1200 fp32 additions of unit values per element: sums around 35, good to 1e-4 of the largest; then / sqrt(v) of 1100
+    torch.testing.assert_close(st.cpu().double(), v, rtol=1e-5, atol=0.0)
+    torch.testing.assert_close(w.cpu().double().view(R, D), -ref / v.sqrt()[:, None], rtol=0.0, atol=1e-5)
+    tbe.close()
