@@ -71,10 +71,8 @@ def algorithmic_bytes(cfg, nnz, U_t, ib=8, eb=4):
     dense = cfg.B * cfg.sum_D * eb      # eb bytes per element of out / grad_out, ib bytes per id and offset
     return {
         "forward_pool": rows_bytes + nnz * ib + nb * ib + dense,
-        "linearize": nnz * ib + nb * ib + nnz * 8,                 # ids + offsets in; key and bag id out
         "radix_hist": nnz * 4,
-        "radix_plan": 0,
-        "radix_scatter": nnz * 16,                                  # (key, bag id) in and out
+        "radix_scatter": nnz * 16,                                  # (key, bag id) in and out (pass 0: ids in)
         "radix_binscan": 0,
         "rle_count": nnz * 4,
         "rle_scan": 0,
@@ -83,7 +81,6 @@ def algorithmic_bytes(cfg, nnz, U_t, ib=8, eb=4):
         "seg_long_list": U * 8,
         # gradient once, sorted positions and their bags, row + moment read-modify-write per unique row
         "seg_update": dense + nnz * 8 + U * 8 + 2 * rows_bytes + 8 * U,
-        "seg_long_partial": dense,                                  # the hot rows touch (nearly) every bag once more
         "seg_long_update": 0,
     }
 
@@ -385,7 +382,7 @@ def main():
     fwd_ms = kernels.get("forward_pool", {}).get("ms_per_step", 0.0)
     kernel_ms = sum(k["ms_per_step"] for k in kernels.values())
     step_alg_bytes = sum(alg.get(n, 0.0) * kernels[n]["launches_per_step"] for n in kernels)
-    # compulsory bytes of one whole step: the forward set + the backward set (ids are read once more by linearize)
+    # compulsory bytes of one whole step: the forward set + the backward set (the sort reads the ids once more)
     compulsory = alg["forward_pool"] + alg["seg_update"] + sum(nnz_all[k] for k in used) / len(used) * (8 if args.index_dtype == "i64" else 4)
 
     counter_bytes = (sum(traffic.values()) or None) if traffic else None

@@ -41,14 +41,12 @@ XCDS = 8   # GRBM_GUI_ACTIVE comes back summed over the chip's 8 dies (8 x 2.3e9
 # kernel (name without template arguments) -> timing record of tbe_timing_read / bench.py
 RECORD = {
     "forward_kernel": "forward_pool", "forward_groups_kernel": "forward_pool", "forward_hot_kernel": "forward_pool",
-    "forward_long_bags_kernel": "forward_pool", "linearize_kernel": "linearize", "radix_plan_kernel": "radix_plan",
+    "forward_long_bags_kernel": "forward_pool",
     "radix_hist_kernel": "radix_hist", "radix_binscan_kernel": "radix_binscan", "radix_scatter_kernel": "radix_scatter",
     "rle_count_kernel": "rle_count", "rle_scan_kernel": "rle_scan", "rle_write_kernel": "rle_write",
-    "seg_update_kernel": "seg_update", "seg_update_wide_kernel": "seg_update", "seg_long_scan_kernel": "seg_long_list",
-    "seg_long_fill_kernel": "seg_long_list", "hot_select_kernel": "seg_long_list", "seg_dense_select_kernel": "seg_long_list",
-    "seg_long_units_kernel": "seg_long_list", "seg_long_bounds_kernel": "seg_long_list",
-    "seg_dense_bounds_kernel": "seg_long_list", "seg_dense_partial_kernel": "seg_dense_partial",
-    "seg_long_partial_kernel": "seg_long_partial", "seg_long_update_kernel": "seg_long_update",
+    "rle_one_block_kernel": "rle_write", "list_rows_kernel": "seg_long_list", "list_rows_flat_kernel": "seg_long_list",
+    "dense_index_kernel": "seg_long_list", "seg_dense_kernel": "seg_dense_partial", "seg_update_kernel": "seg_update",
+    "seg_update_wide_kernel": "seg_update", "seg_long_update_kernel": "seg_long_update",
 }
 
 
