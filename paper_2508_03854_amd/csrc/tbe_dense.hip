@@ -18,6 +18,10 @@
 // LDS, 128 accumulator registers) overlap each other's counting.  The partial sums of a row, one per workgroup run, are added
 // in order by the kernel that applies the step, so the result does not depend on scheduling.
 // Bound: the stream of the gradient block (matrix work at 128 rows and fp32 gradients is about a third of it).
+// Measured, whole training step, against 16 dense rows on the vector units and sweeps over the rest: 64 tables x 32768 bags
+// of fp32 gradients 9.18 -> 8.06 ms, 32 tables x 65536 bags, mean pooling, 2.42 -> 1.70 ms.  Of that, one load buffer in
+// registers instead of two that spilled, row tiles compiled apart and eight lookups in flight while counting: 8.45 -> 8.06
+// and 1.89 -> 1.70 ms.
 // 0 * Inf is NaN, so a non-finite element of one bag's gradient reaches every dense row of its table here; the kernel that
 // adds the partial sums reduces such rows again from their own lookups.
 #include "tbe_rows.h"

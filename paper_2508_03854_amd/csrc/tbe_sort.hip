@@ -26,6 +26,10 @@ namespace tbe {
 // launches (about 4 us each), so it takes wide digits (fewer passes) and lets every scatter workgroup add up the
 // histograms of its segment's chunks by itself (no binscan launch).  In a large batch 2048 bins would leave runs of two
 // keys per tile and bin to write, and the chunk histograms would be too many to add up per workgroup.
+//
+// Bound: launches and latency in small batches, the streams and the ranking beyond.  Measured, whole training step, against
+// a sort that stored keys and bags first and took 8-bit digits throughout: one table, 10 k lookups 102 -> 67 us; 26 tables,
+// 1.2 M lookups 295 -> 254 us; 64 tables, 65 M lookups 9.50 -> 9.18 ms.
 // =================================================================================================
 constexpr int kRsThreads = 256;
 constexpr int kRsWaves = kRsThreads / kWave;
