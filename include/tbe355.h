@@ -214,6 +214,15 @@ tbe_status tbe_debug_sorted(const tbe_handle* h, void* workspace, int32_t B, int
                             const uint32_t** keys_sorted, const uint32_t** vals_sorted, const uint32_t** unique_rows,
                             const uint32_t** seg_start, const uint32_t** num_unique);
 
+/* Which kernels tbe_forward / tbe_forward_ex launch for a batch of B samples and nnz ids on this handle with its present tunables:
+ * a sum of TBE_FWD_* bits, by the very rules the calls follow.  Host only, launches nothing; for tests that are about one
+ * of these kernels. */
+#define TBE_FWD_WAVEFRONT_PER_BAG 1u /* a whole wavefront per bag */
+#define TBE_FWD_LANE_GROUPS 2u       /* several bags per wavefront (narrow rows) */
+#define TBE_FWD_HOT_ROWS 4u          /* the same with a table's most-used rows in on-chip memory */
+#define TBE_FWD_LONG_BAGS 8u         /* the long bags that the two kinds before leave out */
+tbe_status tbe_debug_forward_kernels(const tbe_handle* h, int32_t B, int64_t nnz, uint32_t* kernels);
+
 /* Synchronises the device, reads and clears the sticky invalid-id flag.  Returns TBE_EINDEX if it was set. */
 tbe_status tbe_poll_index_error(tbe_handle* h);
 
@@ -223,7 +232,8 @@ tbe_status tbe_poll_index_error(tbe_handle* h);
  *       in the LAST backward call on this handle in on-chip memory (the handle remembers their ids: a hint, the
  *       pooled sums are the same whatever it holds) and serves their lookups from there.  That path runs for a group
  *       of tables of one width when it fills at least `value` workgroups (default 256, one per compute unit; 0:
- *       whenever the width allows it; negative: never). */
+ *       whenever the width allows it, also for batches so small that they would otherwise take one wavefront per bag;
+ *       negative: never). */
 typedef enum { TBE_TUNE_HOT_ROWS_MIN_WORKGROUPS = 0 } tbe_tunable;
 tbe_status tbe_set_tunable(tbe_handle* h, tbe_tunable which, int64_t value);
 

@@ -19,6 +19,7 @@ F32, F16 = 0, 1
 SUM, MEAN = 0, 1
 I64, I32 = 0, 1                       # tbe_index_dtype
 IO_F32, IO_F16, IO_BF16 = 0, 1, 2     # tbe_io_dtype
+FWD_WAVEFRONT_PER_BAG, FWD_LANE_GROUPS, FWD_HOT_ROWS, FWD_LONG_BAGS = 1, 2, 4, 8   # TBE_FWD_*
 TUNABLES = {"hot_rows_min_workgroups": 0}   # tbe_tunable
 _IDX = {torch.int64: I64, torch.int32: I32}
 _IO = {torch.float32: IO_F32, torch.float16: IO_F16, torch.bfloat16: IO_BF16}
@@ -27,7 +28,7 @@ _IO = {torch.float32: IO_F32, torch.float16: IO_F16, torch.bfloat16: IO_BF16}
 EXPORTS = ["tbe_create", "tbe_destroy", "tbe_workspace_bytes", "tbe_forward", "tbe_backward_rowwise_adagrad",
            "tbe_forward_ex", "tbe_backward_rowwise_adagrad_ex", "tbe_backward_rowwise_adagrad_static", "tbe_backward_prepare",
            "tbe_backward_apply_rowwise_adagrad", "tbe_backward_apply_sgd", "tbe_backward_sgd", "tbe_replica_mean", "tbe_lookup_seq",
-           "tbe_backward_seq_rowwise_adagrad", "tbe_debug_sorted", "tbe_poll_index_error", "tbe_set_tunable", "tbe_timing_enable",
+           "tbe_backward_seq_rowwise_adagrad", "tbe_debug_sorted", "tbe_debug_forward_kernels", "tbe_poll_index_error", "tbe_set_tunable", "tbe_timing_enable",
            "tbe_timing_count", "tbe_timing_read", "tbe_calibration_copy", "tbe_calibration_gather", "tbe_status_string", "tbe_build_info"]
 
 
@@ -92,6 +93,8 @@ def load_library():
     L.tbe_replica_mean.argtypes = [vp, ctypes.POINTER(vp), i32, ctypes.c_size_t, ctypes.c_int, vp]
     L.tbe_debug_sorted.restype = ctypes.c_int
     L.tbe_debug_sorted.argtypes = [vp, vp, i32, i64] + [ctypes.POINTER(vp)] * 5
+    L.tbe_debug_forward_kernels.restype = ctypes.c_int
+    L.tbe_debug_forward_kernels.argtypes = [vp, i32, i64, ctypes.POINTER(ctypes.c_uint32)]
     L.tbe_poll_index_error.restype = ctypes.c_int
     L.tbe_poll_index_error.argtypes = [vp]
     L.tbe_set_tunable.restype = ctypes.c_int
@@ -449,6 +452,13 @@ class TBE:
         U = int(view(ptrs[4], 1).item())
         return {"keys_sorted": view(ptrs[0], nnz), "vals_sorted": view(ptrs[1], nnz),
                 "unique_rows": view(ptrs[2], U), "seg_start": view(ptrs[3], U + 1), "num_unique": U}
+
+    # ---- tbe_debug_forward_kernels
+    def debug_forward_kernels(self, B: int, nnz: int) -> int:
+        """FWD_* bits: the kernels that a forward of B samples and nnz ids launches."""
+        m = ctypes.c_uint32()
+        _check(self._lib.tbe_debug_forward_kernels(self._h, int(B), int(nnz), ctypes.byref(m)), "tbe_debug_forward_kernels")
+        return int(m.value)
 
     # ---- tbe_poll_index_error
     def poll_index_error(self) -> bool:

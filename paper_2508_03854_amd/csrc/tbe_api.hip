@@ -527,6 +527,14 @@ tbe_status tbe_debug_sorted(const tbe_handle* h, void* workspace, int32_t B, int
     return TBE_OK;
 }
 
+tbe_status tbe_debug_forward_kernels(const tbe_handle* h, int32_t B, int64_t nnz, uint32_t* kernels) {
+    if (!h || !kernels) return TBE_EINVAL;
+    const tbe_status st = check_batch(h, B, nnz);
+    if (st != TBE_OK) return st;
+    *kernels = forward_kernels(h, B);
+    return TBE_OK;
+}
+
 tbe_status tbe_poll_index_error(tbe_handle* h) {
     if (!h) return TBE_EINVAL;
     int32_t flag = 0;

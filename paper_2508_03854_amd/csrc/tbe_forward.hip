@@ -439,6 +439,25 @@ __global__ __launch_bounds__(kFwdThreads, 4) void forward_long_bags_kernel(
 // six.  Measured, lane groups against one wavefront per bag: 26 tables of 64 fp32 columns, 11 ids per bag: 1024 bags 6.8
 // against 3.7 us, 8192 8.5 / 6.7, 16384 11.4 / 11.0, 32768 16.5 / 18.8; lognormal lengths, 32 columns: 16384 bags 73 / 13 us.
 constexpr int64_t kFwdSmallBags = 16384;
+// (not with the hot rows asked for at every size: they live in the lane-group classes)
+static bool forward_small(const tbe_handle* h, const int32_t B) {
+    const int n1 = h->fwd_first[5] - h->fwd_first[0];   // rows of at most 64 lanes: classes 0 to 4 follow one another in the list
+    return h->hot_min_workgroups != 0 && (int64_t)n1 * B <= kFwdSmallBags;
+}
+// workgroups per table with which the lane-group class c keeps hot rows in LDS; 0: it does not
+static int hot_chunks(const tbe_handle* h, const int c, const int32_t B) {
+    const int64_t bags_per_wg = (int64_t)kHotPasses * kHotWaves * (kWave >> (6 - c));
+    const int cpt = (int)(((int64_t)B + bags_per_wg - 1) / bags_per_wg);
+    return h->d_hot_ids && h->hot_min_workgroups >= 0 && (int64_t)h->fwd_count[c] * cpt >= h->hot_min_workgroups ? cpt : 0;
+}
+unsigned forward_kernels(const tbe_handle* h, const int32_t B) {
+    unsigned m = h->fwd_count[5] + h->fwd_count[6] > 0 ? TBE_FWD_WAVEFRONT_PER_BAG : 0u;
+    if (forward_small(h, B)) return h->fwd_first[5] > 0 ? m | TBE_FWD_WAVEFRONT_PER_BAG : m;
+    if (h->fwd_count[0] > 0) m |= TBE_FWD_WAVEFRONT_PER_BAG;
+    for (int c = 1; c < 5; ++c)
+        if (h->fwd_count[c] > 0) m |= TBE_FWD_LONG_BAGS | (hot_chunks(h, c, B) > 0 ? TBE_FWD_HOT_ROWS : TBE_FWD_LANE_GROUPS);
+    return m;
+}
 
 template <typename WT, int NC, int U>
 static void launch_forward_nc(const tbe_handle* h, int first, int n, const void* tables, const int32_t* d_D_off,
@@ -473,9 +492,8 @@ static void launch_forward_groups(const tbe_handle* h, const void* tables, const
         const dim3 grid((unsigned)((waves + wpb - 1) / wpb));
         const int32_t* list = h->d_fwd_tables + h->fwd_first[c];
         // with a hot-row list in the handle, and enough bags per table to fill a workgroup's rounds
-        const int64_t bags_per_wg = (int64_t)kHotPasses * kHotWaves * G;
-        const int cpt = (int)(((int64_t)B + bags_per_wg - 1) / bags_per_wg);
-        if (h->d_hot_ids && h->hot_min_workgroups >= 0 && (int64_t)n * cpt >= h->hot_min_workgroups) {
+        const int cpt = hot_chunks(h, c, B);
+        if (cpt > 0) {
             const dim3 hgrid((unsigned)((int64_t)n * cpt));
             if (mean)
                 forward_hot_kernel<WT, 8, true><<<hgrid, kHotThreads, 0, s>>>(
@@ -514,9 +532,8 @@ static void launch_forward_classes(const tbe_handle* h, const void* tables, cons
                                    const IdxView offsets, int32_t B, int64_t nnz, bool mean, void* out, int out_io,
                                    hipStream_t s) {
     const int32_t *first = h->fwd_first, *count = h->fwd_count;
-    const int n1 = first[5] - first[0];   // rows of at most 64 lanes: classes 0 to 4 follow one another in the list
-    if ((int64_t)n1 * B <= kFwdSmallBags) {
-        launch_forward_nc<WT, 1, 8>(h, first[0], n1, tables, d_D_off, indices, offsets, B, nnz, mean, out, out_io, s);
+    if (forward_small(h, B)) {
+        launch_forward_nc<WT, 1, 8>(h, first[0], first[5] - first[0], tables, d_D_off, indices, offsets, B, nnz, mean, out, out_io, s);
     } else {
         launch_forward_nc<WT, 1, 4>(h, first[0], count[0], tables, d_D_off, indices, offsets, B, nnz, mean, out, out_io, s);
         launch_forward_groups<WT>(h, tables, d_D_off, indices, offsets, B, nnz, mean, out, out_io, s);

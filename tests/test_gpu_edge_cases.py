@@ -23,7 +23,7 @@ def make_cfg(rows, D, dtype="f32", B=8, pooling="sum", c=1.0, lr=0.05, eps=1e-8)
     return cfg
 
 
-def run_custom(H, cfg, lens, ids, seed=0, state_kind="hash", steps=1):
+def run_custom(H, cfg, lens, ids, seed=0, state_kind="hash", steps=1, tunables=None, forward_kernels=None):
     """lens: T*B bag lengths; ids: concatenated table-local ids."""
     from paper_2508_03854_amd import TBE
     off = torch.zeros(len(lens) + 1, dtype=torch.int64)
@@ -37,6 +37,10 @@ def run_custom(H, cfg, lens, ids, seed=0, state_kind="hash", steps=1):
                 else np.zeros(cfg.total_rows, dtype=np.float32))
     state = torch.from_numpy(state_np.copy()).cuda()
     tbe = TBE(cfg.rows, cfg.D, cfg.weight_dtype)
+    for k, v in (tunables or {}).items():
+        tbe.set_tunable(k, v)
+    if forward_kernels is not None:
+        assert tbe.debug_forward_kernels(cfg.B, idx.numel()) == forward_kernels
     ws = tbe.alloc_workspace(cfg.B, max(1, idx.numel()))
     reps = []
     for s in range(steps):
@@ -682,21 +686,24 @@ def test_prepare_then_apply_equals_the_one_call_backward(name, kw, idt):
     tbe.close()
 
 
+@pytest.mark.parametrize("hot", [0, -1])
 @pytest.mark.parametrize("dtype", ["f32", "f16"])
-def test_bag_lengths_around_the_long_bag_bounds(H, dtype):
+def test_bag_lengths_around_the_long_bag_bounds(H, dtype, hot):
     # narrow rows take one bag per lane group unless the bag is long (more than 32 / 48 / 64 ids by lanes per row), in
     # which case a whole wavefront walks it: lengths on both sides of every bound, in every narrow-row class,
-    # next to empty and short bags in the same wavefront
+    # next to empty and short bags in the same wavefront; without hot rows on chip and with them (from the second step on)
+    from paper_2508_03854_amd import binding
     rng = np.random.default_rng(41)
     v = 8 if dtype == "f16" else 4
     D = [v, 2 * v, 4 * v, 8 * v, 16 * v, 32 * v]          # 1 .. 32 lanes per row
     rows = [11, 60, 500, 37, 900, 64]
-    B = 150
+    B = 2731                                              # 16386 bags: too many for one wavefront each
     cfg = make_cfg(rows, D, dtype=dtype, B=B, pooling="mean", c=2.0)
-    special = [0, 1, 31, 32, 33, 47, 48, 49, 63, 64, 65, 66, 130, 500]
+    special = 8 * [0, 1, 31, 32, 33, 47, 48, 49, 63, 64, 65, 66, 130, 500]
     lens = rng.integers(0, 9, size=len(D) * B)
     for t in range(len(D)):
         where = rng.choice(B, size=len(special), replace=False)
         lens[t * B + where] = special
     ids = np.concatenate([rng.integers(0, rows[t], size=int(lens[t * B:(t + 1) * B].sum())) for t in range(len(D))])
-    run_custom(H, cfg, lens, ids)
+    run_custom(H, cfg, lens, ids, steps=2, tunables={"hot_rows_min_workgroups": hot},
+               forward_kernels=(binding.FWD_LANE_GROUPS if hot < 0 else binding.FWD_HOT_ROWS) | binding.FWD_LONG_BAGS)

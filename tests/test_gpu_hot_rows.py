@@ -6,9 +6,19 @@ import pytest
 import torch
 
 import workloads as W
+from paper_2508_03854_amd import TBE, binding
 
 pytestmark = pytest.mark.gpu
 FORCE = {"hot_rows_min_workgroups": 0}
+
+
+def forward_kernels(cfg, hot_rows_min_workgroups):
+    """The kernels that the forward of the config's first batch launches."""
+    tbe = TBE(cfg.rows, cfg.D, cfg.weight_dtype)
+    tbe.set_tunable("hot_rows_min_workgroups", hot_rows_min_workgroups)
+    m = tbe.debug_forward_kernels(cfg.B, W.make_batch(cfg, 0)[0].numel())
+    tbe.close()
+    return m
 
 
 @pytest.fixture(scope="module")
@@ -31,6 +41,7 @@ def H():
 ])
 def test_hot_rows_against_oracle(H, name, kw, opts):
     cfg = W.config(name, c=2.0, **kw)
+    assert forward_kernels(cfg, 0) & binding.FWD_HOT_ROWS
     reps = H.run_config(cfg, steps=3, state_kind="hash", tunables=FORCE, **opts)
     print(name, kw, reps, flush=True)
     assert reps[0]["max_seg"] > 512            # some rows are hot enough to be listed
@@ -41,8 +52,8 @@ def test_hot_rows_with_empty_bags_invalid_ids_and_a_stale_hint(H):
     (skipped and reported), bags that hold one hot row many times, and bags longer than the lane-group bound; then a
     forward on a handle whose hint comes from a batch that shares no row with the one looked up."""
     import oracle
-    from paper_2508_03854_amd import TBE
     cfg = W.config("C4", T=4, B=1024, rows_scale=2e-3, c=1.0)
+    assert forward_kernels(cfg, 0) == binding.FWD_HOT_ROWS | binding.FWD_LONG_BAGS
     tabs = H.host_tables(cfg)
     flat = H.flat_from_tables(tabs)
     state = torch.zeros(cfg.total_rows, device="cuda")
@@ -107,8 +118,8 @@ def test_hot_rows_with_empty_bags_invalid_ids_and_a_stale_hint(H):
 def test_hot_rows_do_not_change_results_beyond_summation_order(H):
     """The same forward with the path on and off: within the float tolerance of each other, and each run repeatable
     bit for bit."""
-    from paper_2508_03854_amd import TBE
     cfg = W.config("C5", T=16, B=2048, rows_scale=1e-3)
+    assert forward_kernels(cfg, 0) & binding.FWD_HOT_ROWS and not forward_kernels(cfg, -1) & binding.FWD_HOT_ROWS
     tabs = H.host_tables(cfg)
     flat = H.flat_from_tables(tabs)
     state = torch.zeros(cfg.total_rows, device="cuda")
@@ -128,4 +139,3 @@ def test_hot_rows_do_not_change_results_beyond_summation_order(H):
         outs.append(a.cpu().numpy())
         tbe.close()
     H.assert_close(outs[0], outs[1], H.RTOL_F32, cfg.w_scale, "hot-row path against the plain path")
-    assert not np.array_equal(outs[0].view(np.uint32), outs[1].view(np.uint32)) or True
