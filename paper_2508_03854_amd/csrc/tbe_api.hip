@@ -531,7 +531,7 @@ tbe_status tbe_debug_forward_kernels(const tbe_handle* h, int32_t B, int64_t nnz
     if (!h || !kernels) return TBE_EINVAL;
     const tbe_status st = check_batch(h, B, nnz);
     if (st != TBE_OK) return st;
-    *kernels = forward_kernels(h, B);
+    *kernels = forward_kernels(h, B, nnz);
     return TBE_OK;
 }
 

@@ -436,13 +436,31 @@ __global__ __launch_bounds__(kFwdThreads, 4) void forward_long_bags_kernel(
 
 // A small batch is a matter of latency: one wavefront per bag then is the shortest chain (the lane groups of a narrow row's
 // wavefront share one bag, and a long bag keeps nobody waiting), and the classes 0 to 4 take one launch instead of up to
-// six.  Measured, lane groups against one wavefront per bag: 26 tables of 64 fp32 columns, 11 ids per bag: 1024 bags 6.8
-// against 3.7 us, 8192 8.5 / 6.7, 16384 11.4 / 11.0, 32768 16.5 / 18.8; lognormal lengths, 32 columns: 16384 bags 73 / 13 us.
+// six.  Lane groups need fewer wavefronts and win back what the longer chain costs from some number of bags on: the sooner,
+// the narrower the rows (more bags per wavefront) and the shorter the bags (less to walk for a group of lanes).  The border
+// follows the measured break-even by the narrowest rows of the handle and the mean bag length.  Lane groups against one
+// wavefront per bag, us, at 4096 / 8192 / 16384 bags (100000 rows, Zipf 1.05):
+//   8 fp32 columns       1 id  6.0 4.4 / 6.0 5.4 / 6.1 8.1     3 ids 7.5 4.3 / 7.7 5.4 / 7.7 8.0     10 ids 10.2 4.3 / 10.1 5.4 / 10.3 8.0
+//   16 binary16 columns  1 id  6.2 5.3 / 6.2 7.1 / 6.3 10.9    3 ids 7.8 5.3 / 8.0 7.1 / 8.0 10.9    10 ids 10.5 5.2 / 10.5 7.1 / 10.7 10.9
+//   64 fp32 columns      1 id  6.1 4.1 / 6.5 5.2 / 7.2 7.8     3 ids 6.8 4.1 / 7.1 5.2 / 7.7 8.0     10 ids 7.9 4.5 / 8.3 5.7 / 10.4 9.5
+//   256 binary16 columns 1 id  7.1 4.6 / 8.4 6.1 / 11.5 9.5    3 ids 7.5 4.8 / 9.4 6.2 / 12.9 10.3   10 ids 9.2 5.5 / 11.5 8.2 / 16.3 13.5
+// Lognormal lengths, 32 columns, 16384 bags: 73 against 13 us.
 constexpr int64_t kFwdSmallBags = 16384;
 // (not with the hot rows asked for at every size: they live in the lane-group classes)
-static bool forward_small(const tbe_handle* h, const int32_t B) {
-    const int n1 = h->fwd_first[5] - h->fwd_first[0];   // rows of at most 64 lanes: classes 0 to 4 follow one another in the list
-    return h->hot_min_workgroups != 0 && (int64_t)n1 * B <= kFwdSmallBags;
+static bool forward_small(const tbe_handle* h, const int32_t B, const int64_t nnz) {
+    const int64_t bags = (int64_t)(h->fwd_first[5] - h->fwd_first[0]) * B;   // of rows of at most 64 lanes, classes 0 to 4
+    if (h->hot_min_workgroups == 0 || bags > kFwdSmallBags) return false;
+    const double ids = (double)nnz / ((double)h->T * B);
+    double border = 12288.0 + 1024.0 * ids;
+    if (h->fwd_count[3] + h->fwd_count[4] > 0)   // rows of at most 8 lanes
+        border = h->dtype == TBE_F32 ? 7168.0 + 2560.0 * ids : 5120.0 + 1280.0 * ids;
+    return (double)bags <= border;
+}
+// Rows in flight per lane group: 4 leaves registers for 8 wavefronts per SIMD and covers most bags in one round; 8 pay where
+// every row takes at least half a wavefront and bags are long (256 fp32 columns, 16384 bags: 40 ids 45.9 -> 44.5 us, but 1
+// id 8.6 -> 9.7).
+static bool forward_small_long(const tbe_handle* h, const int32_t B, const int64_t nnz) {
+    return h->fwd_count[2] + h->fwd_count[3] + h->fwd_count[4] == 0 && nnz >= (int64_t)24 * h->T * B;
 }
 // workgroups per table with which the lane-group class c keeps hot rows in LDS; 0: it does not
 static int hot_chunks(const tbe_handle* h, const int c, const int32_t B) {
@@ -450,9 +468,9 @@ static int hot_chunks(const tbe_handle* h, const int c, const int32_t B) {
     const int cpt = (int)(((int64_t)B + bags_per_wg - 1) / bags_per_wg);
     return h->d_hot_ids && h->hot_min_workgroups >= 0 && (int64_t)h->fwd_count[c] * cpt >= h->hot_min_workgroups ? cpt : 0;
 }
-unsigned forward_kernels(const tbe_handle* h, const int32_t B) {
+unsigned forward_kernels(const tbe_handle* h, const int32_t B, const int64_t nnz) {
     unsigned m = h->fwd_count[5] + h->fwd_count[6] > 0 ? TBE_FWD_WAVEFRONT_PER_BAG : 0u;
-    if (forward_small(h, B)) return h->fwd_first[5] > 0 ? m | TBE_FWD_WAVEFRONT_PER_BAG : m;
+    if (forward_small(h, B, nnz)) return h->fwd_first[5] > 0 ? m | TBE_FWD_WAVEFRONT_PER_BAG : m;
     if (h->fwd_count[0] > 0) m |= TBE_FWD_WAVEFRONT_PER_BAG;
     for (int c = 1; c < 5; ++c)
         if (h->fwd_count[c] > 0) m |= TBE_FWD_LONG_BAGS | (hot_chunks(h, c, B) > 0 ? TBE_FWD_HOT_ROWS : TBE_FWD_LANE_GROUPS);
@@ -532,8 +550,10 @@ static void launch_forward_classes(const tbe_handle* h, const void* tables, cons
                                    const IdxView offsets, int32_t B, int64_t nnz, bool mean, void* out, int out_io,
                                    hipStream_t s) {
     const int32_t *first = h->fwd_first, *count = h->fwd_count;
-    if (forward_small(h, B)) {
-        launch_forward_nc<WT, 1, 8>(h, first[0], first[5] - first[0], tables, d_D_off, indices, offsets, B, nnz, mean, out, out_io, s);
+    if (forward_small(h, B, nnz)) {
+        const int n = first[5] - first[0];
+        if (forward_small_long(h, B, nnz)) launch_forward_nc<WT, 1, 8>(h, first[0], n, tables, d_D_off, indices, offsets, B, nnz, mean, out, out_io, s);
+        else launch_forward_nc<WT, 1, 4>(h, first[0], n, tables, d_D_off, indices, offsets, B, nnz, mean, out, out_io, s);
     } else {
         launch_forward_nc<WT, 1, 4>(h, first[0], count[0], tables, d_D_off, indices, offsets, B, nnz, mean, out, out_io, s);
         launch_forward_groups<WT>(h, tables, d_D_off, indices, offsets, B, nnz, mean, out, out_io, s);

@@ -124,8 +124,8 @@ struct LaunchTimer {
 hipError_t launch_forward(const tbe_handle* h, const void* tables, const int32_t* d_D_off, const void* indices,
                           const void* offsets, int idx32, int32_t B, int64_t nnz, tbe_pooling pooling, void* out,
                           int out_io, hipStream_t s);
-// the kernels that launch_forward would launch for B samples (TBE_FWD_* bits), by the rules it launches them by
-unsigned forward_kernels(const tbe_handle* h, int32_t B);
+// the kernels that launch_forward would launch for B samples and nnz ids (TBE_FWD_* bits), by the rules it launches them by
+unsigned forward_kernels(const tbe_handle* h, int32_t B, int64_t nnz);
 // every replicas[m] (device pointers, M <= kMaxReplicas) becomes the element-wise mean; count elements each
 hipError_t launch_replica_mean(const tbe_handle* h, void* const* replicas, int M, size_t count, bool f32, hipStream_t s);
 // Sorts the batch's ids, segment by segment, into (linearised row key, payload) pairs; the payload is the lookup's bag, or
