@@ -6,7 +6,7 @@
 #include <mutex>
 #include <new>
 
-#include "tbe_internal.h"
+#include "tbe_rows.h"
 
 namespace tbe {
 
@@ -22,9 +22,10 @@ constexpr int64_t kSelfScanMax = (int64_t)1 << 21;
 constexpr int64_t kSelfScanChunks = 32;
 // Bytes of chunk histograms that wide digits may take, ascending in N, so that a workspace made for more lookups serves
 // fewer as well.
-static size_t hist_cap(int64_t N) {
+static size_t hist_cap(int64_t N, int nseg) {
     const size_t c = (size_t)(N < kSelfScanMax ? N : kSelfScanMax) * 5 / 4;
-    return c > (512u << 10) ? c : (512u << 10);
+    const size_t few = std::min((size_t)512 << 10, (size_t)4096 * ((size_t)N / 1024 + (size_t)nseg + 2));   // 2048 bins, tiles of 1024
+    return c > few ? c : few;
 }
 SortShape sort_shape(const tbe_handle* h, int64_t N) {
     SortShape sh;
@@ -46,7 +47,7 @@ SortShape sort_shape(const tbe_handle* h, int64_t N) {
         sh.bits = (h->sort_bits + sh.passes - 1) / sh.passes;
         sh.bins = sh.bits <= 8 ? 256 : (sh.bits <= 10 ? 1024 : 2048);
         sh.hist_bytes = (size_t)(sh.self_scan ? 2 : 4) * (size_t)sh.bins * (size_t)(sh.max_chunks + 1);
-        if (sh.hist_bytes <= hist_cap(N)) break;
+        if (sh.hist_bytes <= hist_cap(N, sh.nseg)) break;
     }
     return sh;
 }
@@ -75,7 +76,22 @@ static int64_t most_parts(int64_t N) {
     return m;
 }
 
-// No part of it shrinks when B or N grows: a workspace made for a batch serves every smaller one.
+// What the dense rows may make of a workspace.  A dense row leaves one partial sum per chunk of bags, so their area grows with
+// the columns of all tables whose gradient block is large, not with the lookups: a batch of few lookups per bag would pay
+// several times its other memory for it (32 tables of 128 columns, 16384 bags of one id: 20 + 58 MB).  So the layout with
+// dense rows takes at most 20 bytes per lookup (the five streams once more) over 20.5 bytes per lookup and n / 192 + 4096 +
+// 512 T partial sums of the widest row, and a batch that would fit the library's own scratch array by the latter does so with
+// dense rows as well; within that as many chunks as are useful.  Fewer chunks cost time only below about 512 workgroups
+// (measured: 64 tables, 4096 bags, 16 / 8 / 4 chunks 63 / 58 / 90 us; 12 tables, 8192 bags, 32 / 16 / 8 chunks 21 / 29 / 50 us).
+static size_t dense_allowance(const tbe_handle* h, size_t n) {
+    const size_t lean = 41 * n / 2 + 4 * (n / 192 + 4096 + 512 * (size_t)h->T) * (size_t)h->maxD;
+    const size_t full = lean + 20 * n;
+    return lean <= (size_t)TBE_STATIC_SCRATCH_BYTES ? std::min(full, (size_t)TBE_STATIC_SCRATCH_BYTES) : full;
+}
+
+// The total never shrinks when B or N grows: a workspace made for a batch serves every smaller one.
+// Memory is used twice where lifetimes allow it: what the sort alone needs lies where the run lengths then write seg_start;
+// the sort's spare key buffer and the run-length counts lie where the partial sums of a step go.
 Workspace carve(const tbe_handle* h, int32_t B, int64_t N, bool allow_dense) {
     Workspace w;
     memset(&w, 0, sizeof(w));
@@ -87,11 +103,24 @@ Workspace carve(const tbe_handle* h, int32_t B, int64_t N, bool allow_dense) {
         off = align256(off + bytes);
         return at;
     };
-    w.keys[0] = take(4 * (n + 1));
-    w.keys[1] = take(4 * (n + 1));
+    w.sort = sort_shape(h, (int64_t)n);
+    const int sorted = w.sort.passes & 1;   // every pass flips the double buffer, starting from 0
+    w.keys[sorted] = take(4 * (n + 1));
     w.vals[0] = take(4 * (n + 1));
     w.vals[1] = take(4 * (n + 1));
-    w.seg_start = take(4 * (n + 1));
+    {   // seg_start; until the run lengths write it, what the sort needs only while it runs
+        const size_t at = off;
+        // (8-bit digits in a handle of many tables may exceed the cap; their histograms grow with N by themselves)
+        const size_t chunks = most_chunks(h, (int64_t)n);
+        const size_t hist8 = (size_t)(w.sort.self_scan ? 2 : 4) * 256 * (chunks + 1);
+        w.radix_hist = take(std::max(std::max(w.sort.hist_bytes, hist_cap((int64_t)n, w.sort.nseg)), hist8));
+        w.bin_tot = take(w.sort.self_scan ? 0 : 4 * 256 * (size_t)w.sort.nseg);
+        w.seg_chunk0 = take(w.sort.self_scan ? 0 : 4 * (size_t)(w.sort.nseg + 1));
+        w.chunk_desc = take(32 * chunks);
+        const size_t end = off;
+        off = at;
+        w.seg_start = take(std::max(4 * (n + 1), end - at));
+    }
     w.counters = take(4 * kCounterWords);
     w.long_min = long_min_of((int64_t)n);
     w.cap_long = most_parts((int64_t)n);           // at most n / (long_min + 1) rows are long
@@ -103,40 +132,49 @@ Workspace carve(const tbe_handle* h, int32_t B, int64_t N, bool allow_dense) {
     w.hot_ids = take(hint ? 4 * (size_t)kHotRows * (size_t)h->T : 0);
     w.hot_n = take(hint ? 4 * (size_t)h->T : 0);
     w.seq_gbase = take(8 * (size_t)h->T);
-    // Dense rows: some table's gradient block is large, and the batch could hold two lookups of them per bag.  A dense row
-    // leaves one partial sum per chunk of bags: enough chunks for about a thousand workgroups in all, at most 32.
-    w.dense = allow_dense && h->T <= kMaxSortSegments && B >= kDenseMinBags && (uint64_t)B * (uint64_t)h->maxD * 4u > ((uint64_t)2 << 20);
-    uint32_t most_dense_chunks = 0;
-    if (w.dense) {
-        w.dense_blocks = ((uint32_t)B + kDenseBags - 1) / kDenseBags;
-        const uint32_t want = h->T >= 1024 ? 1u : (h->T <= 32 ? 32u : 1024u / (uint32_t)h->T);
-        const uint32_t chunks = want < w.dense_blocks ? want : w.dense_blocks;
-        most_dense_chunks = chunks;
-        w.dense_per_chunk = (w.dense_blocks + chunks - 1) / chunks;
-        w.dense_chunks = (w.dense_blocks + w.dense_per_chunk - 1) / w.dense_per_chunk;
-        w.dense_n = take(4 * (size_t)h->T);
-        w.dense_rows = take(4 * (size_t)h->T * kDenseRows);
-        w.dense_index = take(4 * (size_t)h->T * kDenseRows * (w.dense_blocks + 1));
-    }
-    // (equal runs of blocks may come to fewer chunks than were wanted, and to more again in a smaller batch)
-    const size_t dense_slots = w.dense ? (size_t)h->T * kDenseRows * most_dense_chunks : 0;
-    const size_t shared = off;
-    // while the sort runs
-    w.sort = sort_shape(h, (int64_t)n);
-    // (8-bit digits in a handle of many tables may exceed the cap; their histograms grow with N by themselves)
-    const size_t chunks = most_chunks(h, (int64_t)n);
-    const size_t hist8 = (size_t)(w.sort.self_scan ? 2 : 4) * 256 * (chunks + 1);
-    w.radix_hist = take(std::max(std::max(w.sort.hist_bytes, hist_cap((int64_t)n)), hist8));
-    w.bin_tot = take(w.sort.self_scan ? 0 : 4 * 256 * (size_t)w.sort.nseg);
-    w.seg_chunk0 = take(w.sort.self_scan ? 0 : 4 * (size_t)(w.sort.nseg + 1));
-    w.chunk_desc = take(32 * chunks);
+    const size_t parts = 4 * (size_t)w.cap_main * (size_t)h->maxD;
     w.rle_blocks = (int)(((int64_t)n + kRleTile - 1) / kRleTile);
+    const size_t front = align256(4 * (n + 1)) + align256(8 * (size_t)w.rle_blocks);   // spare keys, run-length counts
+    const size_t base = off + std::max(front, align256(parts));
+    size_t reserve = base;
+    // Dense rows: for the tables whose gradient block is large.  Enough chunks for about a thousand workgroups in all, at most
+    // 32, as far as the allowance goes.
+    uint32_t tables = 0;
+    uint64_t columns = 0;
+    if (allow_dense && h->T <= kMaxSortSegments)
+        for (const int32_t D : h->D)
+            if (dense_block((uint32_t)B, (uint32_t)D)) {
+                ++tables;
+                columns += (uint64_t)D;
+            }
+    if (tables > 0) {
+        const uint32_t blocks = ((uint32_t)B + kDenseBags - 1) / kDenseBags;
+        const uint32_t useful = std::min(blocks, h->T >= 1024 ? 1u : (h->T <= 32 ? 32u : 1024u / (uint32_t)h->T));
+        const size_t per_chunk = 4 * (size_t)kDenseRows * (size_t)columns;
+        const size_t lists = off;
+        w.dense_n = take(4 * (size_t)h->T);
+        w.dense_tab = take(8 * (size_t)h->T);
+        w.dense_rows = take(4 * (size_t)h->T * kDenseRows);
+        w.dense_index = take(4 * (size_t)tables * kDenseRows * (blocks + 1));
+        const size_t allowed = dense_allowance(h, n);
+        uint32_t chunks = 0;
+        if (off + std::max(front, parts) + 256 <= allowed) chunks = (uint32_t)std::min((size_t)useful, (allowed - 256 - off - parts) / per_chunk);
+        reserve = std::max(base, std::min(off + std::max(front, align256(parts + per_chunk * useful)), allowed));
+        w.dense = chunks > 0;
+        if (w.dense) {
+            w.dense_blocks = blocks;
+            w.dense_per_chunk = (blocks + chunks - 1) / chunks;
+            w.dense_chunks = (blocks + w.dense_per_chunk - 1) / w.dense_per_chunk;
+        } else {
+            off = lists;
+        }
+    }
+    const size_t shared = off;
+    w.keys[sorted ^ 1] = take(4 * (n + 1));
     w.rle_counts = take(8 * (size_t)w.rle_blocks);
-    w.total = off;
-    // while a step is applied
-    off = shared;
-    w.partial = take(4 * ((size_t)w.cap_main + dense_slots) * (size_t)h->maxD);
-    w.total = std::max(w.total, off);
+    w.partial = shared;
+    w.dense_partial = shared + parts;   // (a multiple of 16)
+    w.total = reserve;   // (covers both uses: at least base, and with dense rows no less than what they were fitted into)
     return w;
 }
 

@@ -466,6 +466,7 @@ __global__ __launch_bounds__(kSegThreads) void seg_long_update_kernel(const SegA
         const int D = a.D_off[t + 1] - a.D_off[t];
         const bool dense = (ent.z & kDenseFlag) != 0u;
         const uint32_t nch = dense ? a.dense_chunks : ent.z;   // partial sums of the row
+        const uint32_t pitch = (uint32_t)(dense ? D : a.maxD);
         // here all 64 lanes cover the row (or a 256-column part of it); groups are not used
         RowGeom g;
         g.D = D; g.LPR = kWave; g.G = 1; g.sub = 0; g.lc = lane_id() * 4;
@@ -475,13 +476,13 @@ __global__ __launch_bounds__(kSegThreads) void seg_long_update_kernel(const SegA
             acc[c][0] = acc[c][1] = acc[c][2] = acc[c][3] = 0.f;
             const int col = g.lc + c * 256;
             if (col < D) {
-                const float* src = a.partial + (size_t)ent.y * a.maxD + col;
+                const float* src = (dense ? a.dense_partial + (size_t)ent.y * 4u : a.partial + (size_t)ent.y * a.maxD) + col;
                 for (uint32_t k = (uint32_t)wv; k < nch; k += 8 * kW) {   // eight loads in flight
                     float4 v[8];
 #pragma unroll
                     for (uint32_t q = 0; q < 8; ++q) {
                         const uint32_t kk = k + q * kW;
-                        v[q] = *reinterpret_cast<const float4*>(src + (size_t)(kk < nch ? kk : (uint32_t)wv) * a.maxD);
+                        v[q] = *reinterpret_cast<const float4*>(src + (size_t)(kk < nch ? kk : (uint32_t)wv) * pitch);
                     }
 #pragma unroll
                     for (uint32_t q = 0; q < 8; ++q)
@@ -627,7 +628,8 @@ SegArgs seg_args(const tbe_handle* h, const Workspace& w, char* ws, const void* 
     a.dense_n = dense ? reinterpret_cast<uint32_t*>(ws + w.dense_n) : nullptr;
     a.dense_rows = reinterpret_cast<uint32_t*>(ws + w.dense_rows);
     a.dense_index = reinterpret_cast<uint32_t*>(ws + w.dense_index);
-    a.dense_slot0 = (uint32_t)w.cap_main;
+    a.dense_tab = reinterpret_cast<uint2*>(ws + w.dense_tab);
+    a.dense_partial = reinterpret_cast<float*>(ws + w.dense_partial);
     a.dense_blocks = w.dense_blocks;
     a.dense_chunks = w.dense_chunks;
     a.dense_per_chunk = w.dense_per_chunk;

@@ -123,7 +123,8 @@ __device__ __forceinline__ void dense_run(const SegArgs& a, const uint32_t cb, c
 #pragma unroll
         for (int r = 0; r < 16; ++r) acc[m][0][r] = acc[m][1][r] = 0.f;
 
-    const uint32_t* const my_ix = a.dense_index + ((size_t)t * kDenseRows + (tid < nd ? tid : 0u)) * (a.dense_blocks + 1u);
+    const uint2 tab = a.dense_tab[t];
+    const uint32_t* const my_ix = a.dense_index + ((size_t)tab.x * kDenseRows + (tid < nd ? tid : 0u)) * (a.dense_blocks + 1u);
     const uint32_t k_lo = chunk * a.dense_per_chunk;
     const uint32_t k_hi = k_lo + a.dense_per_chunk < a.dense_blocks ? k_lo + a.dense_per_chunk : a.dense_blocks;
     for (uint32_t k = k_lo; k < k_hi; ++k) {
@@ -309,14 +310,14 @@ __device__ __forceinline__ void dense_run(const SegArgs& a, const uint32_t cb, c
         }
     }
     if (split == 0 && col_on) {
-        const size_t slot0 = (size_t)a.dense_slot0 + (size_t)t * kDenseRows * a.dense_chunks + chunk;
+        float* const dst = a.dense_partial + (size_t)tab.y * 4u + (size_t)chunk * (uint32_t)D + col;
 #pragma unroll
         for (int m = 0; m < MT; ++m)
 #pragma unroll
                 for (int r = 0; r < 16; ++r) {
                     const uint32_t h = (uint32_t)(m * 32 + (r & 3) + 8 * (r >> 2) + 4 * kh);
                     if (h < nd)
-                        *reinterpret_cast<float2*>(a.partial + (slot0 + (size_t)h * a.dense_chunks) * a.maxD + col) = make_float2(acc[m][0][r], acc[m][1][r]);
+                        *reinterpret_cast<float2*>(dst + (size_t)h * a.dense_chunks * (uint32_t)D) = make_float2(acc[m][0][r], acc[m][1][r]);
                 }
     }
 }

@@ -23,7 +23,7 @@ constexpr int kDenseMinBags = 1024;   // batches of fewer samples have no dense 
 constexpr int kFwdGroupMaxLanes = 32;   // rows of at most this many lanes use one bag per lane group
 constexpr int kHotRows = 256;           // rows per table that the forward may hold in LDS (the handle's hot-row list)
 constexpr int kMaxReplicas = 16;        // replicas of one buffer that tbe_replica_mean averages in one call
-constexpr int kCounterWords = 64;      // device counters: [0]=U [1]=long rows [3]=units [4]=apply nothing
+constexpr int kCounterWords = 64;      // device counters: [0]=U [1]=long rows [2]=dense partials handed out [3]=units [4]=apply nothing [5]=tables with dense rows
 
 struct TimingSlot {
     const char* name;
@@ -95,14 +95,12 @@ struct Workspace {
     // keys/vals: radix double buffers of N+1 words each.  The payload of a key is the linear bag id of its lookup
     // (pooled calls) or its position (non-pooled calls), so vals[sorted] is the per-lookup stream the gradient
     // kernels read.  After the sort vals[spare] receives unique_rows.
-    // After the sort vals[spare] receives unique_rows.  Streams of the whole batch first; behind them what the sort needs
-    // only while it runs shares its place with what the row updates write.
-    size_t keys[2], vals[2], seg_start, counters, long_rows, long_list, unit_list, hot_ids, hot_n, seq_gbase, dense_n, dense_rows,
-        dense_index, radix_hist, bin_tot, seg_chunk0, chunk_desc, rle_counts, partial, total;
+    size_t keys[2], vals[2], seg_start, counters, long_rows, long_list, unit_list, hot_ids, hot_n, seq_gbase, dense_n, dense_tab,
+        dense_rows, dense_index, radix_hist, bin_tot, seg_chunk0, chunk_desc, rle_counts, partial, dense_partial, total;
     SortShape sort;
     int rle_blocks;
     uint32_t long_min;    // a row with more lookups is long: it is cut into parts of about that many
-    int64_t cap_long, cap_main;   // long rows; partial-sum slots of their parts (the dense rows' slots follow)
+    int64_t cap_long, cap_main;   // long rows; partial-sum slots of their parts
     bool dense;           // dense rows are looked for; their sizes:
     uint32_t dense_blocks, dense_chunks, dense_per_chunk;
     int64_t n;            // number of lookups the workspace was carved for

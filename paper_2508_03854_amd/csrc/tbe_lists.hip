@@ -97,7 +97,7 @@ __global__ __launch_bounds__(kListThreads) void list_rows_kernel(const SegArgs a
                                                                  int32_t* __restrict__ err) {
     __shared__ uint32_t s_len[kListRank], s_start[kListRank], s_row[kListRank], s_rank[kListRank];
     __shared__ uint32_t smem[kListThreads / kWave];
-    __shared__ uint32_t s_range[2], s_sum, s_base;
+    __shared__ uint32_t s_range[2], s_sum, s_base, s_first;
     const int t = blockIdx.x;
     if (t == a.T) {
         seq_blocks<IT>(a, offsets, nnz, grad_elems, err);
@@ -145,7 +145,11 @@ __global__ __launch_bounds__(kListThreads) void list_rows_kernel(const SegArgs a
         }
         __syncthreads();
         if (a.dense_n && dense_block((uint32_t)a.B, D) && s_sum >= 2u * (uint32_t)a.B) nd = n < (uint32_t)kDenseRows ? n : (uint32_t)kDenseRows;
-        if (tid == 0 && nd > 0u) a.dense_n[t] = nd;
+        if (tid == 0 && nd > 0u) {   // (which table gets which place decides nothing but addresses)
+            a.dense_n[t] = nd;
+            s_first = atomicAdd(&a.counters[2], nd * a.dense_chunks * (D / 4u));
+            a.dense_tab[t] = make_uint2(atomicAdd(&a.counters[5], 1u), s_first);
+        }
     } else if (a.hot_ids && tid < (uint32_t)kHotRows) {
         a.hot_ids[(size_t)t * kHotRows + tid] = a.long_rows[i0 + tid].y - rb;
     }
@@ -174,8 +178,7 @@ __global__ __launch_bounds__(kListThreads) void list_rows_kernel(const SegArgs a
             const uint32_t s0 = ranked ? s_start[k] : a.seg_start[u];
             if (ranked && s_rank[k] < nd) {
                 a.dense_rows[(size_t)t * kDenseRows + s_rank[k]] = i0 + k;
-                a.long_list[i0 + k] = make_uint4(u, a.dense_slot0 + ((uint32_t)t * kDenseRows + s_rank[k]) * a.dense_chunks,
-                                                 kDenseFlag, (uint32_t)t);
+                a.long_list[i0 + k] = make_uint4(u, s_first + s_rank[k] * a.dense_chunks * (D / 4u), kDenseFlag, (uint32_t)t);
             } else {
                 c = row_parts(a, ranked ? s_len[k] : a.seg_start[u + 1] - s0);
                 a.long_list[i0 + k] = make_uint4(u, s0 / a.part + i0 + k, c, (uint32_t)t);
@@ -232,7 +235,7 @@ __global__ __launch_bounds__(256) void dense_index_kernel(const SegArgs a) {
     const uint32_t ex = block_excl_scan<256>(len, smem, &all);
     if (tid < (uint32_t)kDenseRows) s_pref[tid] = tid < nd ? ex : 0xFFFFFFFFu;
     __syncthreads();
-    const uint32_t bag0 = (uint32_t)t * (uint32_t)a.B;
+    const uint32_t bag0 = (uint32_t)t * (uint32_t)a.B, place = a.dense_tab[t].x;
     const uint32_t e0 = (uint32_t)((uint64_t)all * y / kIndexSplit), e1 = (uint32_t)((uint64_t)all * (y + 1u) / kIndexSplit);
     constexpr int kU = 8;   // lookups in flight per thread
     for (uint32_t f = e0 + tid; f < e1; f += kU * 256) {
@@ -258,7 +261,7 @@ __global__ __launch_bounds__(256) void dense_index_kernel(const SegArgs a) {
             const bool first = p[q] == s_start[row[q]], last = p[q] + 1u == s_end[row[q]];
             const uint32_t b1 = (bag[q] - bag0) / kDenseBags;
             const uint32_t b0 = first ? 0u : (prev[q] - bag0) / kDenseBags + 1u;   // borders b0 .. b1 are p
-            uint32_t* ix = a.dense_index + ((size_t)t * kDenseRows + row[q]) * (a.dense_blocks + 1u);
+            uint32_t* ix = a.dense_index + ((size_t)place * kDenseRows + row[q]) * (a.dense_blocks + 1u);
             for (uint32_t k = b0; k <= b1 && k <= a.dense_blocks; ++k) ix[k] = p[q];
             if (last)
                 for (uint32_t k = b1 + 1u; k <= a.dense_blocks; ++k) ix[k] = p[q] + 1u;

@@ -21,7 +21,8 @@ constexpr uint32_t kDenseFlag = 0x80000000u;   // long_list entry: the dense-row
 struct SegArgs {
     const uint32_t* keys_unique;  // unique_rows
     const uint32_t* seg_start;
-    uint32_t* counters;           // [0] unique rows, [1] long rows, [3] work units, [4] != 0: apply nothing
+    uint32_t* counters;           // [0] unique rows, [1] long rows, [2] dense partials, [3] work units, [4] != 0: apply nothing,
+                                  // [5] tables with dense rows
     const uint32_t* bag_sorted;   // the sorted payload: linear bag id of every sorted lookup
     OffsetWords offsets;
     const void* grad_out;         // [B, sum(D)] float / binary16 / bfloat16, per the kernel's GT (or the sequence layout)
@@ -39,7 +40,8 @@ struct SegArgs {
     uint32_t long_min, part;      // ... are cut into equal parts of about `part` lookups
     uint32_t cap_long;
     const uint2* long_rows;       // [counters[1]] (unique row, key), ascending
-    uint4* long_list;             // [counters[1]] (unique row, first partial-sum slot, parts or kDenseFlag, table)
+    uint4* long_list;             // [counters[1]] (unique row, first partial-sum slot, parts, table); a dense row: (unique row,
+                                  // first partial sum in dense_partial in units of four floats, kDenseFlag, table)
     uint2* unit_list;             // [counters[3]] (position in long_list, part)
     float* partial;               // [slots][maxD] partial sums
     uint32_t* hot_ids;            // [T][kHotRows] rows with the most lookups, for the handle's hint (null: not kept)
@@ -50,8 +52,9 @@ struct SegArgs {
     // dense rows (tbe_dense.hip); null dense_n: no table can have any
     uint32_t* dense_n;            // [T] number of dense rows
     uint32_t* dense_rows;         // [T][kDenseRows] their positions in long_list, longest first
-    uint32_t* dense_index;        // [T][kDenseRows][dense_blocks + 1] where each block of bags starts in the row's segment
-    uint32_t dense_slot0;         // first slot of the region reserved for them
+    uint2* dense_tab;             // [T] (place in dense_index, first partial sum as in long_list) of a table with dense rows
+    uint32_t* dense_index;        // [place][kDenseRows][dense_blocks + 1] where each block of bags starts in the row's segment
+    float* dense_partial;         // per table with dense rows [dense rows][dense_chunks][its columns] partial sums
     uint32_t dense_blocks;        // blocks of kDenseBags bags per table
     uint32_t dense_chunks;        // partial sums per dense row: runs of dense_per_chunk blocks
     uint32_t dense_per_chunk;

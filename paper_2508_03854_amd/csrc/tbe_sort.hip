@@ -655,7 +655,7 @@ struct RleArgs {
     uint32_t* unique_rows;
     uint32_t* seg_start;
     uint2* long_rows;         // (index of the unique row, key)
-    uint32_t* counters;       // [0] unique rows, [1] long rows, [3] = [4] = 0
+    uint32_t* counters;       // [0] unique rows, [1] long rows, [2] .. [5] = 0
 };
 
 // Head flags of a thread's eight elements (element k*NT + tid of the tile): element i is a head if it exists and its key
@@ -783,7 +783,7 @@ __device__ __forceinline__ uint2 rle_write_tile(const RleArgs& a, const int64_t 
 __device__ __forceinline__ void rle_finish(const RleArgs& a, const uint32_t U, const uint32_t nlong) {
     a.counters[0] = U;
     a.counters[1] = nlong;
-    a.counters[3] = 0u;   // work units of the long rows, counted by the kernel that lists them
+    a.counters[2] = a.counters[3] = a.counters[5] = 0u;   // handed out by the kernel that lists the long rows
     a.counters[4] = 0u;   // set when a non-pooled batch must not be applied
     a.seg_start[U] = (uint32_t)a.N;
 }

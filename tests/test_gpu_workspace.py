@@ -25,6 +25,21 @@ def test_workspace_grows_with_the_batch(rows, D):
     tbe.close()
 
 
+@pytest.mark.parametrize("D,B,per_bag", [([128] * 32, 16384, 1), ([32] * 31 + [1024], 4096, 1), ([1024] * 32, 16384, 1), ([256] * 64, 4096, 2)])
+def test_dense_rows_of_a_batch_with_few_lookups_take_no_more_memory_than_its_streams(D, B, per_bag):
+    """Their partial sums depend on the tables' columns alone: bounded by 20 bytes per lookup, or the fixed array's size, over
+    what the batch needs for its streams and parts."""
+    if not torch.cuda.is_available():
+        pytest.skip("no GPU")
+    from paper_2508_03854_amd import TBE, binding
+    tbe = TBE([100_000] * len(D), D, "f32")
+    n = len(D) * B * per_bag
+    lean = 20.5 * n + 4 * (n // 192 + 4096 + 512 * len(D)) * max(D)
+    bound = lean + 20 * n
+    assert tbe.workspace_bytes(B, n) <= (min(bound, binding.STATIC_SCRATCH_BYTES) if lean <= binding.STATIC_SCRATCH_BYTES else bound)
+    tbe.close()
+
+
 def test_a_smaller_last_batch_uses_the_same_workspace():
     """33 blocks of bags in runs of two, then 32 blocks one by one: the second needs more partial sums, in the same memory."""
     if not torch.cuda.is_available():
