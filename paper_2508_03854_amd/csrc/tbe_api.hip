@@ -92,7 +92,7 @@ static size_t dense_allowance(const tbe_handle* h, size_t n) {
 // The total never shrinks when B or N grows: a workspace made for a batch serves every smaller one.
 // Memory is used twice where lifetimes allow it: what the sort alone needs lies where the run lengths then write seg_start;
 // the sort's spare key buffer and the run-length counts lie where the partial sums of a step go.
-Workspace carve(const tbe_handle* h, int32_t B, int64_t N, bool allow_dense) {
+Workspace carve(const tbe_handle* h, int32_t B, int64_t N) {
     Workspace w;
     memset(&w, 0, sizeof(w));
     const size_t n = (size_t)(N > 0 ? N : 1);
@@ -141,7 +141,7 @@ Workspace carve(const tbe_handle* h, int32_t B, int64_t N, bool allow_dense) {
     // 32, as far as the allowance goes.
     uint32_t tables = 0;
     uint64_t columns = 0;
-    if (allow_dense && h->T <= kMaxSortSegments)
+    if (h->T <= kMaxSortSegments)
         for (const int32_t D : h->D)
             if (dense_block((uint32_t)B, (uint32_t)D)) {
                 ++tables;
@@ -432,9 +432,7 @@ static tbe_status backward_impl(const tbe_handle* h, const void* grad_out, tbe_i
         return TBE_EINVAL;
     if (nnz == 0) return TBE_OK;  // no id appears in the batch: no row has a gradient
     if (!workspace || !aligned(workspace, 256)) return TBE_EINVAL;
-    // (the library's own scratch array may be too small for the dense rows: they are then left out)
-    const Workspace whole = carve(h, B, nnz);
-    const Workspace w = workspace == h->static_scratch && workspace_bytes < whole.total ? carve(h, B, nnz, false) : whole;
+    const Workspace w = carve(h, B, nnz);
     if (workspace_bytes < w.total) return TBE_EWORKSPACE;
     char* ws = static_cast<char*>(workspace);
     hipStream_t s = static_cast<hipStream_t>(hip_stream);
@@ -472,7 +470,7 @@ tbe_status tbe_backward_rowwise_adagrad_static(const tbe_handle* h, const void* 
     if (!h || !state) return TBE_EINVAL;
     const tbe_status st = check_batch(h, B, nnz);
     if (st != TBE_OK) return st;
-    if (carve(h, B, nnz, false).total > (size_t)TBE_STATIC_SCRATCH_BYTES) return TBE_EWORKSPACE;   // beyond the fixed array
+    if (carve(h, B, nnz).total > (size_t)TBE_STATIC_SCRATCH_BYTES) return TBE_EWORKSPACE;   // beyond the fixed array
     if (!h->static_scratch) return TBE_EHIP;
     // per-kernel timing creates events and grows a host-side list on first use: not in a call that allocates nothing
     tbe_handle* hm = const_cast<tbe_handle*>(h);

@@ -105,8 +105,7 @@ struct Workspace {
     uint32_t dense_blocks, dense_chunks, dense_per_chunk;
     int64_t n;            // number of lookups the workspace was carved for
 };
-// allow_dense = false leaves the dense rows out (their rows are then reduced part by part): for scratch memory of fixed size
-Workspace carve(const tbe_handle* h, int32_t B, int64_t N, bool allow_dense = true);
+Workspace carve(const tbe_handle* h, int32_t B, int64_t N);
 
 // RAII-free helper: brackets one kernel launch with events when timing is on.
 struct LaunchTimer {

@@ -62,3 +62,55 @@ def test_static_scratch_backward_equals_the_workspace_backward():
     torch.cuda.synchronize()
     assert float(flat.abs().sum()) == 0.0 and float(state.abs().sum()) == 0.0
     tbe.close()
+
+
+def skewed_batch(T, R, B, n, seed):
+    """n lookups over T tables of R rows, nine in ten of them in 40 rows, bags of random lengths."""
+    g = torch.Generator().manual_seed(seed)
+    cuts = torch.sort(torch.randint(0, n + 1, (T * B - 1,), generator=g)).values
+    off = torch.cat([torch.zeros(1, dtype=torch.int64), cuts, torch.tensor([n])])
+    idx = torch.randint(0, 40, (n,), generator=g) * 7
+    cold = torch.rand(n, generator=g) < 0.1
+    idx[cold] = torch.randint(0, R, (int(cold.sum()),), generator=g)
+    return idx.cuda(), off.cuda()
+
+
+@pytest.mark.parametrize("dtype,pooling", [("f32", "sum"), ("f16", "mean")])
+def test_static_scratch_backward_with_dense_rows(dtype, pooling):
+    """Tables whose gradient block is large enough for dense rows: the same bits as with a workspace, up to the most lookups the
+    array holds; one more is refused."""
+    if not torch.cuda.is_available():
+        pytest.skip("no GPU")
+    from paper_2508_03854_amd import TBE, binding
+    T, R, D, B = 4, 1000, 128, 8192
+    tbe = TBE([R] * T, [D] * T, dtype)
+    lo, hi = 1, 8_000_000                     # workspace_bytes ascends with the lookups
+    assert tbe.workspace_bytes(B, hi) > binding.STATIC_SCRATCH_BYTES
+    while hi - lo > 1:
+        mid = (lo + hi) // 2
+        lo, hi = (mid, hi) if tbe.workspace_bytes(B, mid) <= binding.STATIC_SCRATCH_BYTES else (lo, mid)
+    g = torch.Generator(device="cuda").manual_seed(1)
+    grad = torch.randn(B, T * D, generator=g, device="cuda")
+    bits = torch.int32 if dtype == "f32" else torch.int16
+    for n in (600_000, lo):
+        idx, off = skewed_batch(T, R, B, n, n)
+        res = []
+        for ws in (tbe.alloc_workspace(B, n), None):
+            w = torch.full((tbe.total_elems,), 0.01, device="cuda", dtype=tbe.torch_dtype)
+            st = torch.ones(tbe.total_rows, device="cuda")
+            if ws is not None:
+                tbe.backward_rowwise_adagrad_ex(grad, idx, off, B, w, st, ws, pooling=pooling, lr=0.05, eps=1e-8)
+            else:
+                tbe.backward_rowwise_adagrad_static(grad, idx, off, B, w, st, pooling=pooling, lr=0.05, eps=1e-8)
+            torch.cuda.synchronize()
+            res.append((w, st))
+        assert torch.equal(res[0][0].view(bits), res[1][0].view(bits)) and torch.equal(res[0][1], res[1][1]), n
+        assert not torch.equal(res[0][1], torch.ones_like(res[0][1]))
+    idx, off = skewed_batch(T, R, B, hi, 3)
+    w, st = torch.zeros(tbe.total_elems, device="cuda", dtype=tbe.torch_dtype), torch.ones(tbe.total_rows, device="cuda")
+    with pytest.raises(binding.TbeError) as e:
+        tbe.backward_rowwise_adagrad_static(grad, idx, off, B, w, st, pooling=pooling, lr=0.05, eps=1e-8)
+    assert e.value.status == binding.EWORKSPACE
+    torch.cuda.synchronize()
+    assert float(w.abs().sum()) == 0.0 and bool((st == 1.0).all())
+    tbe.close()
