@@ -214,6 +214,18 @@ tbe_status tbe_debug_sorted(const tbe_handle* h, void* workspace, int32_t B, int
                             const uint32_t** keys_sorted, const uint32_t** vals_sorted, const uint32_t** unique_rows,
                             const uint32_t** seg_start, const uint32_t** num_unique);
 
+/* Parity hook for the rows with many lookups, as the last pooled backward or prepare call with the same (h, workspace, B,
+ * nnz) listed them; DEVICE pointers into `workspace`, valid like those of tbe_debug_sorted.
+ *   hot_ids[T][256], hot_n[T]    per table the hint for the next forward: the table-local ids of the rows with the most
+ *                                lookups, at least 513 each, most first (ties: smaller id first)
+ *   dense_rows[T][128], dense_n[T]  per table the rows that are reduced on the matrix cores, most lookups first, as positions
+ *                                in long_rows; both NULL when no table of the handle can have any at this B
+ *   long_rows[][2]               (number among the unique rows, linearised key), ascending
+ * hot_ids and hot_n are NULL for a handle of more than 4096 tables. */
+tbe_status tbe_debug_hot_rows(const tbe_handle* h, void* workspace, int32_t B, int64_t nnz, const uint32_t** hot_ids,
+                              const uint32_t** hot_n, const uint32_t** dense_rows, const uint32_t** dense_n,
+                              const uint32_t** long_rows);
+
 /* Which kernels tbe_forward / tbe_forward_ex launch for a batch of B samples and nnz ids on this handle with its present tunables:
  * a sum of TBE_FWD_* bits, by the very rules the calls follow.  Host only, launches nothing; for tests that are about one
  * of these kernels. */

@@ -28,7 +28,7 @@ _IO = {torch.float32: IO_F32, torch.float16: IO_F16, torch.bfloat16: IO_BF16}
 EXPORTS = ["tbe_create", "tbe_destroy", "tbe_workspace_bytes", "tbe_forward", "tbe_backward_rowwise_adagrad",
            "tbe_forward_ex", "tbe_backward_rowwise_adagrad_ex", "tbe_backward_rowwise_adagrad_static", "tbe_backward_prepare",
            "tbe_backward_apply_rowwise_adagrad", "tbe_backward_apply_sgd", "tbe_backward_sgd", "tbe_replica_mean", "tbe_lookup_seq",
-           "tbe_backward_seq_rowwise_adagrad", "tbe_debug_sorted", "tbe_debug_forward_kernels", "tbe_poll_index_error", "tbe_set_tunable", "tbe_timing_enable",
+           "tbe_backward_seq_rowwise_adagrad", "tbe_debug_sorted", "tbe_debug_hot_rows", "tbe_debug_forward_kernels", "tbe_poll_index_error", "tbe_set_tunable", "tbe_timing_enable",
            "tbe_timing_count", "tbe_timing_read", "tbe_calibration_copy", "tbe_calibration_gather", "tbe_status_string", "tbe_build_info"]
 
 
@@ -93,6 +93,8 @@ def load_library():
     L.tbe_replica_mean.argtypes = [vp, ctypes.POINTER(vp), i32, ctypes.c_size_t, ctypes.c_int, vp]
     L.tbe_debug_sorted.restype = ctypes.c_int
     L.tbe_debug_sorted.argtypes = [vp, vp, i32, i64] + [ctypes.POINTER(vp)] * 5
+    L.tbe_debug_hot_rows.restype = ctypes.c_int
+    L.tbe_debug_hot_rows.argtypes = [vp, vp, i32, i64] + [ctypes.POINTER(vp)] * 5
     L.tbe_debug_forward_kernels.restype = ctypes.c_int
     L.tbe_debug_forward_kernels.argtypes = [vp, i32, i64, ctypes.POINTER(ctypes.c_uint32)]
     L.tbe_poll_index_error.restype = ctypes.c_int
@@ -452,6 +454,29 @@ class TBE:
         U = int(view(ptrs[4], 1).item())
         return {"keys_sorted": view(ptrs[0], nnz), "vals_sorted": view(ptrs[1], nnz),
                 "unique_rows": view(ptrs[2], U), "seg_start": view(ptrs[3], U + 1), "num_unique": U}
+
+    # ---- tbe_debug_hot_rows
+    def debug_hot_rows(self, workspace: torch.Tensor, B: int, nnz: int) -> Tuple[List[List[int]], List[List[int]]]:
+        """Per table the hinted and the dense rows (table-local ids) of the last pooled backward or prepare call (synchronises)."""
+        ptrs = [ctypes.c_void_p() for _ in range(5)]
+        _check(self._lib.tbe_debug_hot_rows(self._h, workspace.data_ptr(), int(B), int(nnz),
+                                            *[ctypes.byref(p) for p in ptrs]), "tbe_debug_hot_rows")
+        base = workspace.data_ptr()
+        torch.cuda.synchronize()
+
+        def view(p: ctypes.c_void_p, n: int) -> torch.Tensor:
+            off = p.value - base
+            return workspace[off:off + 4 * n].view(torch.int32).cpu().to(torch.int64) & 0xFFFFFFFF
+
+        hot, dense, row_base = [], [], 0
+        hot_n, dense_n = [view(p, self.T).tolist() if p.value else [0] * self.T for p in (ptrs[1], ptrs[3])]
+        for t in range(self.T):
+            hot.append(view(ptrs[0], 256 * self.T)[256 * t:256 * t + hot_n[t]].tolist() if hot_n[t] else [])
+            at = view(ptrs[2], 128 * self.T)[128 * t:128 * t + dense_n[t]] if dense_n[t] else torch.zeros(0, dtype=torch.int64)
+            rows = view(ptrs[4], 2 * (int(at.max()) + 1)).view(-1, 2) if dense_n[t] else None
+            dense.append((rows[at, 1] - row_base).tolist() if dense_n[t] else [])
+            row_base += self.rows[t]
+        return hot, dense
 
     # ---- tbe_debug_forward_kernels
     def debug_forward_kernels(self, B: int, nnz: int) -> int:

@@ -563,6 +563,23 @@ tbe_status tbe_debug_sorted(const tbe_handle* h, void* workspace, int32_t B, int
     return TBE_OK;
 }
 
+tbe_status tbe_debug_hot_rows(const tbe_handle* h, void* workspace, int32_t B, int64_t nnz, const uint32_t** hot_ids,
+                              const uint32_t** hot_n, const uint32_t** dense_rows, const uint32_t** dense_n,
+                              const uint32_t** long_rows) {
+    if (!h || !workspace || !hot_ids || !hot_n || !dense_rows || !dense_n || !long_rows) return TBE_EINVAL;
+    const tbe_status st = check_batch(h, B, nnz);
+    if (st != TBE_OK) return st;
+    const Workspace w = carve(h, B, nnz);
+    char* ws = static_cast<char*>(workspace);
+    const bool hint = h->d_hot_ids != nullptr;
+    *hot_ids = hint ? reinterpret_cast<uint32_t*>(ws + w.hot_ids) : nullptr;
+    *hot_n = hint ? reinterpret_cast<uint32_t*>(ws + w.hot_n) : nullptr;
+    *dense_rows = w.dense ? reinterpret_cast<uint32_t*>(ws + w.dense_rows) : nullptr;
+    *dense_n = w.dense ? reinterpret_cast<uint32_t*>(ws + w.dense_n) : nullptr;
+    *long_rows = reinterpret_cast<uint32_t*>(ws + w.long_rows);
+    return TBE_OK;
+}
+
 tbe_status tbe_debug_forward_kernels(const tbe_handle* h, int32_t B, int64_t nnz, uint32_t* kernels) {
     if (!h || !kernels) return TBE_EINVAL;
     const tbe_status st = check_batch(h, B, nnz);

@@ -22,6 +22,7 @@ constexpr int kDenseBags = 256;  // bags per block of that kernel
 constexpr int kDenseMinBags = 1024;   // batches of fewer samples have no dense rows
 constexpr int kFwdGroupMaxLanes = 32;   // rows of at most this many lanes use one bag per lane group
 constexpr int kHotRows = 256;           // rows per table that the forward may hold in LDS (the handle's hot-row list)
+constexpr uint32_t kHotMin = 512;       // ... of those with more lookups than this
 constexpr int kMaxReplicas = 16;        // replicas of one buffer that tbe_replica_mean averages in one call
 constexpr int kCounterWords = 64;      // device counters: [0]=U [1]=long rows [2]=dense partials handed out [3]=units [4]=apply nothing [5]=tables with dense rows
 
