@@ -108,7 +108,8 @@ Workspace carve(const tbe_handle* h, int32_t B, int64_t N) {
     w.keys[sorted] = take(4 * (n + 1));
     w.vals[0] = take(4 * (n + 1));
     w.vals[1] = take(4 * (n + 1));
-    {   // seg_start; until the run lengths write it, what the sort needs only while it runs
+    {   // seg_start; until the run lengths write it, what the sort needs only while it runs, at its end: few batches have so
+        // many unique rows that they get there (lines that other dies have just written cost 0.6 of rle_write's 8.2 us)
         const size_t at = off;
         // (8-bit digits in a handle of many tables may exceed the cap; their histograms grow with N by themselves)
         const size_t chunks = most_chunks(h, (int64_t)n);
@@ -117,9 +118,14 @@ Workspace carve(const tbe_handle* h, int32_t B, int64_t N) {
         w.bin_tot = take(w.sort.self_scan ? 0 : 4 * 256 * (size_t)w.sort.nseg);
         w.seg_chunk0 = take(w.sort.self_scan ? 0 : 4 * (size_t)(w.sort.nseg + 1));
         w.chunk_desc = take(32 * chunks);
-        const size_t end = off;
+        const size_t need = off - at;
         off = at;
-        w.seg_start = take(std::max(4 * (n + 1), end - at));
+        w.seg_start = take(std::max(4 * (n + 1), need));
+        const size_t shift = off - at - need;
+        w.radix_hist += shift;
+        w.bin_tot += shift;
+        w.seg_chunk0 += shift;
+        w.chunk_desc += shift;
     }
     w.counters = take(4 * kCounterWords);
     w.long_min = long_min_of((int64_t)n);
