@@ -466,7 +466,7 @@ __global__ __launch_bounds__(kSegThreads) void seg_long_update_kernel(const SegA
         const int D = a.D_off[t + 1] - a.D_off[t];
         const bool dense = (ent.z & kDenseFlag) != 0u;
         const uint32_t nch = dense ? a.dense_chunks : ent.z;   // partial sums of the row
-        const uint32_t pitch = (uint32_t)(dense ? D : a.maxD);
+        const uint32_t pitch = dense ? a.dense_n[t] * (uint32_t)D : (uint32_t)a.maxD;
         // here all 64 lanes cover the row (or a 256-column part of it); groups are not used
         RowGeom g;
         g.D = D; g.LPR = kWave; g.G = 1; g.sub = 0; g.lc = lane_id() * 4;

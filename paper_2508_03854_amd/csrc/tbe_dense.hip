@@ -93,7 +93,7 @@ struct DenseLds {
 // MT: row tiles of 32 (compiled apart, so that the matrix instructions of a step are one straight run)
 template <int MT, bool MEAN, typename GT>
 __device__ __forceinline__ void dense_run(const SegArgs& a, const uint32_t cb, const uint32_t chunk, const int t,
-                                          const uint32_t nd, const int d0, const int D, DenseLds* S) {
+                                          const uint32_t nd, const uint2 tab, const int d0, const int D, DenseLds* S) {
     constexpr bool kExact = !MEAN && sizeof(GT) == 2;                 // a gradient element is one piece
     constexpr bool kF16 = kExact && __is_same(GT, __half);            // binary16 pieces, else bfloat16
     constexpr int kPieces = kExact ? 1 : 3;
@@ -123,7 +123,6 @@ __device__ __forceinline__ void dense_run(const SegArgs& a, const uint32_t cb, c
 #pragma unroll
         for (int r = 0; r < 16; ++r) acc[m][0][r] = acc[m][1][r] = 0.f;
 
-    const uint2 tab = a.dense_tab[t];
     const uint32_t* const my_ix = a.dense_index + ((size_t)tab.x * kDenseRows + (tid < nd ? tid : 0u)) * (a.dense_blocks + 1u);
     const uint32_t k_lo = chunk * a.dense_per_chunk;
     const uint32_t k_hi = k_lo + a.dense_per_chunk < a.dense_blocks ? k_lo + a.dense_per_chunk : a.dense_blocks;
@@ -310,14 +309,14 @@ __device__ __forceinline__ void dense_run(const SegArgs& a, const uint32_t cb, c
         }
     }
     if (split == 0 && col_on) {
-        float* const dst = a.dense_partial + (size_t)tab.y * 4u + (size_t)chunk * (uint32_t)D + col;
+        float* const dst = a.dense_partial + (size_t)tab.y * 4u + (size_t)chunk * nd * (uint32_t)D + col;
 #pragma unroll
         for (int m = 0; m < MT; ++m)
 #pragma unroll
                 for (int r = 0; r < 16; ++r) {
                     const uint32_t h = (uint32_t)(m * 32 + (r & 3) + 8 * (r >> 2) + 4 * kh);
                     if (h < nd)
-                        *reinterpret_cast<float2*>(dst + (size_t)h * a.dense_chunks * (uint32_t)D) = make_float2(acc[m][0][r], acc[m][1][r]);
+                        *reinterpret_cast<float2*>(dst + (size_t)h * (uint32_t)D) = make_float2(acc[m][0][r], acc[m][1][r]);
                 }
     }
 }
@@ -331,14 +330,15 @@ __global__ __launch_bounds__(kDThreads, 2) void seg_dense_kernel(const SegArgs a
     const uint32_t chunk = bx % a.dense_chunks;
     const int t = (int)(bx / a.dense_chunks);
     const uint32_t nd = a.dense_n[t];
+    const uint2 tab = a.dense_tab[t];   // (with dense_n's load, not behind it; written where nd is not 0)
     if (nd == 0u) return;
     const int d0 = a.D_off[t];
     const int D = a.D_off[t + 1] - d0;
     if ((int)cb * 256 >= D) return;
-    if (nd > 96u) dense_run<4, MEAN, GT>(a, cb, chunk, t, nd, d0, D, &S);
-    else if (nd > 64u) dense_run<3, MEAN, GT>(a, cb, chunk, t, nd, d0, D, &S);
-    else if (nd > 32u) dense_run<2, MEAN, GT>(a, cb, chunk, t, nd, d0, D, &S);
-    else dense_run<1, MEAN, GT>(a, cb, chunk, t, nd, d0, D, &S);
+    if (nd > 96u) dense_run<4, MEAN, GT>(a, cb, chunk, t, nd, tab, d0, D, &S);
+    else if (nd > 64u) dense_run<3, MEAN, GT>(a, cb, chunk, t, nd, tab, d0, D, &S);
+    else if (nd > 32u) dense_run<2, MEAN, GT>(a, cb, chunk, t, nd, tab, d0, D, &S);
+    else dense_run<1, MEAN, GT>(a, cb, chunk, t, nd, tab, d0, D, &S);
 }
 
 template <typename GT>

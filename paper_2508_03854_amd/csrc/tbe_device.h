@@ -199,6 +199,20 @@ __device__ __forceinline__ float bcast_lane(const float x, const int src) {
     return __int_as_float(__builtin_amdgcn_readlane(__float_as_int(x), src));
 }
 
+// One digit count into a histogram.  When every active lane holds the same digit (the common case for the high digits,
+// because ids arrive grouped by table) one lane adds the whole count instead of 64 lanes queueing on one LDS word.
+__device__ __forceinline__ void hist_add(uint32_t* __restrict__ hw, const uint32_t d, const bool valid) {
+    const uint64_t act = __ballot(valid);
+    if (act == 0ull) return;
+    const uint32_t d0 = bcast_lane(d, __ffsll((unsigned long long)act) - 1);   // (the first active lane's digit)
+    const uint64_t same = __ballot(valid && d == d0);
+    if (same == act) {
+        if (lane_id() == __ffsll((unsigned long long)act) - 1) atomicAdd(&hw[d0], (uint32_t)__popcll(act));
+    } else if (valid) {
+        atomicAdd(&hw[d], 1u);
+    }
+}
+
 template <typename WT>
 struct RowIO;
 

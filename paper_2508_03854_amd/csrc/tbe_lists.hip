@@ -22,7 +22,8 @@
 namespace tbe {
 
 constexpr int kListThreads = 1024;
-constexpr uint32_t kListRank = 1024;   // long rows of one table that are ranked; a table with more lists the first kHotRows as hot and has no dense rows
+constexpr uint32_t kListRank = 1024;   // long rows of one table that are ranked; of more, the kHotRows longest are found first
+static_assert(kDenseRows <= kHotRows && kHotRows <= (int)kListRank && kListRank <= (uint32_t)kListThreads, "one thread per ranked row");
 
 // first i in [0, n) with rows[i].y >= x, or n; a whole wavefront, 64 probes per round
 __device__ __forceinline__ uint32_t wave_lower_bound_key(const uint2* __restrict__ rows, const uint32_t n, const int64_t x) {
@@ -91,14 +92,202 @@ __device__ __forceinline__ void seq_blocks(const SegArgs& a, const IT* __restric
     }
 }
 
+__device__ __forceinline__ uint32_t long_row_len(const SegArgs& a, const uint32_t i) {
+    const uint32_t u = a.long_rows[i].x;
+    return a.seg_start[u + 1] - a.seg_start[u];
+}
+
+// The lengths of a table's long rows [i0, i0 + n), row k0 + thread for k0 = 0, kListThreads, ...: the first HELD rounds in
+// registers (a length is two dependent loads away), the others loaded again by every pass.  Called by the whole workgroup.
+template <int HELD>
+struct Lengths {
+    static constexpr int kHeld = HELD;
+    uint32_t held[kHeld], u0, s0;   // u0, s0: unique row and first lookup of the first round's row
+    __device__ __forceinline__ void load(const SegArgs& a, const uint32_t i0, const uint32_t n) {
+#pragma unroll
+        for (int q = 0; q < kHeld; ++q) {
+            const uint32_t k = (uint32_t)q * kListThreads + threadIdx.x;
+            held[q] = 0u;
+            if (k - (uint32_t)lane_id() < n) {   // (a wavefront without a row loads nothing)
+                const uint32_t u = a.long_rows[i0 + (k < n ? k : n - 1u)].x;
+                const uint32_t s = a.seg_start[u], len = a.seg_start[u + 1] - s;
+                held[q] = k < n ? len : 0u;
+                if (q == 0) {
+                    u0 = u;
+                    s0 = s;
+                }
+            }
+        }
+    }
+    // f(k, length) for k of every round, length 0 behind the end (no long row is as short)
+    template <typename F>
+    __device__ __forceinline__ void each(const SegArgs& a, const uint32_t i0, const uint32_t n, F f) const {
+#pragma unroll
+        for (int q = 0; q < kHeld; ++q)
+            if ((uint32_t)q * kListThreads < n) f((uint32_t)q * kListThreads + threadIdx.x, held[q]);
+        for (uint32_t k0 = kHeld * kListThreads; k0 < n; k0 += kListThreads) {
+            const uint32_t k = k0 + threadIdx.x;
+            f(k, k < n ? long_row_len(a, i0 + k) : 0u);
+        }
+    }
+};
+
+struct ListLds {
+    uint32_t len[kListRank], k[kHotRows], hist[256], scan[kListThreads / kWave];
+    uint32_t sum, base, first, cut_len, cut_k;
+};
+
+// The kHotRows longest of the n > kListRank long rows of a table, ties by their place in the list (the key): their places k in
+// list order into S->k, their lengths into S->len.  A radix selection finds the length of the last one, eight bits a pass from
+// the top; what is longer is taken, and of that length as many as are missing, the first ones.
+template <typename LENS>
+__device__ __forceinline__ void select_longest(const SegArgs& a, const LENS& lens, const uint32_t i0, const uint32_t n, ListLds* S) {
+    uint32_t* const s_hist = S->hist;
+    const uint32_t tid = threadIdx.x;
+    uint32_t cut = 0u, need = (uint32_t)kHotRows;   // length so far, and rows still missing among those that share its upper bits
+    for (int shift = 24; shift >= 0; shift -= 8) {
+        if (tid < 256u) s_hist[tid] = 0u;
+        __syncthreads();
+        lens.each(a, i0, n, [&](const uint32_t, const uint32_t len) {
+            hist_add(s_hist, (len >> shift) & 255u, len != 0u && (shift == 24 || (len >> (shift + 8)) == (cut >> (shift + 8))));
+        });
+        __syncthreads();
+        const uint32_t c = tid < 256u ? s_hist[255u - tid] : 0u;   // digits from the largest down
+        uint32_t all;
+        const uint32_t above = block_excl_scan<kListThreads>(c, S->scan, &all);
+        if (above < need && need <= above + c) {
+            s_hist[0] = 255u - tid;
+            s_hist[1] = need - above;
+        }
+        __syncthreads();
+        cut |= s_hist[0] << shift;
+        need = s_hist[1];
+        __syncthreads();
+    }
+    uint32_t longer = 0u, equal = 0u;   // ... than / to the cut, among the rows before
+    lens.each(a, i0, n, [&](const uint32_t k, const uint32_t len) {
+        const bool gt = len > cut, eq = len == cut;
+        uint32_t tot;
+        const uint32_t ex = block_excl_scan<kListThreads>((gt ? 0x10000u : 0u) | (eq ? 1u : 0u), S->scan, &tot);
+        const uint32_t e = equal + (ex & 0xFFFFu);
+        if (gt || (eq && e < need)) {
+            const uint32_t at = longer + (ex >> 16) + (e < need ? e : need);   // below kHotRows
+            S->k[at] = k;
+            S->len[at] = len;
+        }
+        longer += tot >> 16;
+        equal += tot & 0xFFFFu;
+    });
+    __syncthreads();
+}
+
+// a row k of many that is dense, or (length 0) does not exist
+__device__ __forceinline__ bool dense_or_end(const uint32_t len, const uint32_t k, const uint32_t cut_len, const uint32_t cut_k) {
+    return len == 0u || len > cut_len || (len == cut_len && k <= cut_k);
+}
+
+// The n long rows of table t, from place i0 of the list on.  MANY: more than kListRank of them (compiled apart: the launch is
+// a chain of latencies, fetching its instructions among them).
+template <bool MANY>
+__device__ __forceinline__ void list_table(const SegArgs& a, ListLds* S, const int t, const uint32_t i0, const uint32_t n) {
+    const uint32_t tid = threadIdx.x;
+    const uint32_t rb = (uint32_t)a.row_base[t];
+    const uint32_t D = (uint32_t)(a.D_off[t + 1] - a.D_off[t]);
+    const bool ranked = a.hot_ids || a.dense_n;
+    // ---- rank the candidates, one per thread: all long rows of the table, or the kHotRows longest
+    const uint32_t nc = MANY ? (uint32_t)kHotRows : n;
+    Lengths<MANY ? 8 : 1> lens;
+    lens.load(a, i0, n);
+    if (!MANY) {
+        if (tid < n) S->len[tid] = lens.held[0];
+    } else if (ranked) select_longest(a, lens, i0, n, S);
+    __syncthreads();
+    uint32_t my_k = tid, my_len = 0, rank = 0xFFFFFFFFu, nd = 0;   // nd: dense rows
+    if (ranked) {
+        if (tid < nc) {   // longest first, ties by key (the list is ascending by key)
+            if (MANY) my_k = S->k[tid];
+            my_len = S->len[tid];
+            rank = 0u;
+            for (uint32_t j = 0; j < nc; ++j) {
+                const uint32_t l = S->len[j];
+                rank += (l > my_len || (l == my_len && j < tid)) ? 1u : 0u;
+            }
+            if (a.hot_ids && rank < (uint32_t)kHotRows && my_len > kHotMin) a.hot_ids[(size_t)t * kHotRows + rank] = a.long_rows[i0 + my_k].y - rb;
+            if (rank < (uint32_t)kDenseRows) atomicAdd(&S->sum, my_len < 0x01000000u ? my_len : 0x01000000u);
+        }
+        const uint32_t hot = (uint32_t)__syncthreads_count(my_len > kHotMin);
+        if (a.hot_n && tid == 0) a.hot_n[t] = hot < (uint32_t)kHotRows ? hot : (uint32_t)kHotRows;
+        // A table with that many long rows has most of its lookups in parts anyway, and those fill the chip: the dense rows
+        // pay only if their kernel does as well.  Measured, backward without and with them: 4 tables x 131072 bags of 128 ids,
+        // 128 columns (128 workgroups) 5.82 and 5.35 ms; 1 table x 65536 bags of 256 ids (32 workgroups) 1.24 and 1.71 ms.
+        const bool filled = !MANY || (uint32_t)a.T * a.dense_chunks * ((D + 255u) / 256u) >= 128u;
+        if (a.dense_n && filled && dense_block((uint32_t)a.B, D) && S->sum >= 2u * (uint32_t)a.B)
+            nd = nc < (uint32_t)kDenseRows ? nc : (uint32_t)kDenseRows;
+    }
+    // ---- parts of the rows that are not dense: their number, then the table's place in the unit list, and the dense rows'
+    // places (which tables come first decides the order in which units are worked on, and addresses, nothing else)
+    uint32_t c = 0, ex = 0, total = 0;
+    if (!MANY) {
+        if (tid < n && rank >= nd) c = row_parts(a, lens.held[0]);
+        ex = block_excl_scan<kListThreads>(c, S->scan, &total);
+    } else {
+        if (tid == 0) {
+            S->cut_len = 0xFFFFFFFFu;   // dense are the rows down to the last ranked so
+            S->cut_k = 0u;
+        }
+        __syncthreads();
+        if (rank < nd && rank + 1u == nd) {
+            S->cut_len = my_len;
+            S->cut_k = my_k;
+        }
+        __syncthreads();
+        lens.each(a, i0, n, [&](const uint32_t k, const uint32_t len) { c += dense_or_end(len, k, S->cut_len, S->cut_k) ? 0u : row_parts(a, len); });
+        block_excl_scan<kListThreads>(c, S->scan, &total);
+    }
+    if (tid == 0) S->base = total > 0u ? atomicAdd(&a.counters[3], total) : 0u;
+    if (tid == kWave && nd > 0u) {
+        const uint32_t place = atomicAdd(&a.counters[5], 1u);
+        S->first = atomicAdd(&a.counters[2], nd * a.dense_chunks * (D / 4u));
+        a.dense_n[t] = nd;
+        a.dense_tab[t] = make_uint2(place, S->first);
+    }
+    __syncthreads();
+    if (rank < nd) {
+        a.dense_rows[(size_t)t * kDenseRows + rank] = i0 + my_k;
+        a.long_list[i0 + my_k] = make_uint4(MANY ? a.long_rows[i0 + my_k].x : lens.u0, S->first + rank * (D / 4u), kDenseFlag, (uint32_t)t);
+    }
+    if (!MANY) {
+        if (c > 0u) a.long_list[i0 + tid] = make_uint4(lens.u0, lens.s0 / a.part + i0 + tid, c, (uint32_t)t);
+        for (uint32_t q = 0; q < c; ++q) a.unit_list[S->base + ex + q] = make_uint2(i0 + tid, q);
+        return;
+    }
+    uint32_t base = S->base;
+    const uint32_t cut_len = S->cut_len, cut_k = S->cut_k;
+    for (uint32_t k0 = 0; k0 < n; k0 += kListThreads) {
+        const uint32_t k = k0 + tid;
+        c = 0;
+        if (k < n) {
+            const uint32_t u = a.long_rows[i0 + k].x;
+            const uint32_t s0 = a.seg_start[u], len = a.seg_start[u + 1] - s0;
+            if (!dense_or_end(len, k, cut_len, cut_k)) {
+                c = row_parts(a, len);
+                a.long_list[i0 + k] = make_uint4(u, s0 / a.part + i0 + k, c, (uint32_t)t);
+            }
+        }
+        uint32_t tot;
+        const uint32_t at = base + block_excl_scan<kListThreads>(c, S->scan, &tot);
+        for (uint32_t q = 0; q < c; ++q) a.unit_list[at + q] = make_uint2(i0 + k, q);
+        base += tot;
+    }
+}
+
 // grid: one workgroup per table, and in non-pooled mode one more for the gradient blocks
 template <typename IT>
 __global__ __launch_bounds__(kListThreads) void list_rows_kernel(const SegArgs a, const IT* __restrict__ offsets,
                                                                  const int64_t nnz, const int64_t grad_elems,
                                                                  int32_t* __restrict__ err) {
-    __shared__ uint32_t s_len[kListRank], s_start[kListRank], s_row[kListRank], s_rank[kListRank];
-    __shared__ uint32_t smem[kListThreads / kWave];
-    __shared__ uint32_t s_range[2], s_sum, s_base, s_first;
+    __shared__ ListLds S;
+    __shared__ uint32_t s_range[2];
     const int t = blockIdx.x;
     if (t == a.T) {
         seq_blocks<IT>(a, offsets, nnz, grad_elems, err);
@@ -110,88 +299,16 @@ __global__ __launch_bounds__(kListThreads) void list_rows_kernel(const SegArgs a
         const uint32_t i = wave_lower_bound_key(a.long_rows, nlong, a.row_base[t + (int)(tid >> 6)]);
         if ((tid & (kWave - 1)) == 0) s_range[tid >> 6] = i;
     }
-    if (tid == 0) s_sum = 0u;
-    __syncthreads();
-    const uint32_t i0 = s_range[0], n = s_range[1] - s_range[0];
-    const uint32_t rb = (uint32_t)a.row_base[t];
-    const uint32_t D = (uint32_t)(a.D_off[t + 1] - a.D_off[t]);
     if (tid == 0) {
+        S.sum = 0u;
         if (a.hot_n) a.hot_n[t] = 0u;
         if (a.dense_n) a.dense_n[t] = 0u;
     }
-    if (n == 0u) return;
-    const bool ranked = n <= kListRank;
-    uint32_t nd = 0;   // dense rows
-    if (ranked) {
-        uint32_t my_len = 0, my_key = 0;
-        if (tid < n) {
-            const uint2 r = a.long_rows[i0 + tid];
-            const uint32_t s0 = a.seg_start[r.x];
-            my_len = a.seg_start[r.x + 1] - s0;
-            my_key = r.y;
-            s_len[tid] = my_len;
-            s_start[tid] = s0;
-            s_row[tid] = r.x;
-        }
-        __syncthreads();
-        if (tid < n) {   // longest first, ties by key (the list is ascending by key)
-            uint32_t rank = 0;
-            for (uint32_t j = 0; j < n; ++j) {
-                const uint32_t l = s_len[j];
-                rank += (l > my_len || (l == my_len && j < tid)) ? 1u : 0u;
-            }
-            s_rank[tid] = rank;
-            if (a.hot_ids && rank < (uint32_t)kHotRows && my_len > kHotMin) a.hot_ids[(size_t)t * kHotRows + rank] = my_key - rb;
-            if (rank < (uint32_t)kDenseRows) atomicAdd(&s_sum, my_len < 0x01000000u ? my_len : 0x01000000u);
-        }
-        const uint32_t hot = (uint32_t)__syncthreads_count(tid < n && my_len > kHotMin);
-        if (a.hot_n && tid == 0) a.hot_n[t] = hot < (uint32_t)kHotRows ? hot : (uint32_t)kHotRows;
-        if (a.dense_n && dense_block((uint32_t)a.B, D) && s_sum >= 2u * (uint32_t)a.B) nd = n < (uint32_t)kDenseRows ? n : (uint32_t)kDenseRows;
-        if (tid == 0 && nd > 0u) {   // (which table gets which place decides nothing but addresses)
-            a.dense_n[t] = nd;
-            s_first = atomicAdd(&a.counters[2], nd * a.dense_chunks * (D / 4u));
-            a.dense_tab[t] = make_uint2(atomicAdd(&a.counters[5], 1u), s_first);
-        }
-    } else if (a.hot_ids && tid < (uint32_t)kHotRows) {
-        a.hot_ids[(size_t)t * kHotRows + tid] = a.long_rows[i0 + tid].y - rb;
-        if (tid == 0) a.hot_n[t] = (uint32_t)kHotRows;
-    }
-    // parts of the rows that are not dense: their number first, then the table's place in the unit list (which tables come
-    // first decides the order in which units are worked on, nothing else)
-    uint32_t total = 0;
-    for (uint32_t k0 = 0; k0 < n; k0 += kListThreads) {
-        const uint32_t k = k0 + tid;
-        uint32_t c = 0;
-        if (k < n && !(ranked && s_rank[k] < nd)) {
-            const uint32_t u = a.long_rows[i0 + k].x;
-            c = row_parts(a, ranked ? s_len[k] : a.seg_start[u + 1] - a.seg_start[u]);
-        }
-        uint32_t tot;
-        block_excl_scan<kListThreads>(c, smem, &tot);
-        total += tot;
-    }
-    if (tid == 0) s_base = total > 0u ? atomicAdd(&a.counters[3], total) : 0u;
     __syncthreads();
-    uint32_t base = s_base;
-    for (uint32_t k0 = 0; k0 < n; k0 += kListThreads) {
-        const uint32_t k = k0 + tid;
-        uint32_t c = 0;
-        if (k < n) {
-            const uint32_t u = ranked ? s_row[k] : a.long_rows[i0 + k].x;
-            const uint32_t s0 = ranked ? s_start[k] : a.seg_start[u];
-            if (ranked && s_rank[k] < nd) {
-                a.dense_rows[(size_t)t * kDenseRows + s_rank[k]] = i0 + k;
-                a.long_list[i0 + k] = make_uint4(u, s_first + s_rank[k] * a.dense_chunks * (D / 4u), kDenseFlag, (uint32_t)t);
-            } else {
-                c = row_parts(a, ranked ? s_len[k] : a.seg_start[u + 1] - s0);
-                a.long_list[i0 + k] = make_uint4(u, s0 / a.part + i0 + k, c, (uint32_t)t);
-            }
-        }
-        uint32_t tot;
-        const uint32_t at = base + block_excl_scan<kListThreads>(c, smem, &tot);
-        for (uint32_t q = 0; q < c; ++q) a.unit_list[at + q] = make_uint2(i0 + k, q);
-        base += tot;
-    }
+    const uint32_t i0 = s_range[0], n = s_range[1] - s_range[0];
+    if (n == 0u) return;
+    if (n <= kListRank) list_table<false>(a, &S, t, i0, n);
+    else list_table<true>(a, &S, t, i0, n);
 }
 
 // Handles of very many tables (no hint, no dense rows): one thread per long row.

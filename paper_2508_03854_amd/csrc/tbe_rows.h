@@ -54,7 +54,7 @@ struct SegArgs {
     uint32_t* dense_rows;         // [T][kDenseRows] their positions in long_list, longest first
     uint2* dense_tab;             // [T] (place in dense_index, first partial sum as in long_list) of a table with dense rows
     uint32_t* dense_index;        // [place][kDenseRows][dense_blocks + 1] where each block of bags starts in the row's segment
-    float* dense_partial;         // per table with dense rows [dense rows][dense_chunks][its columns] partial sums
+    float* dense_partial;         // per table with dense rows [dense_chunks][dense rows][its columns] partial sums
     uint32_t dense_blocks;        // blocks of kDenseBags bags per table
     uint32_t dense_chunks;        // partial sums per dense row: runs of dense_per_chunk blocks
     uint32_t dense_per_chunk;

@@ -252,20 +252,6 @@ __device__ __forceinline__ void load_ids(const IT* __restrict__ indices, const i
     for (int k = 0; k < ITEMS; ++k) id[k] = indices[first + k * kWave < p1 ? first + k * kWave : p1 - 1];
 }
 
-// One digit count into a histogram.  When every active lane holds the same digit (the common case for the high digits,
-// because ids arrive grouped by table) one lane adds the whole count instead of 64 lanes queueing on one LDS word.
-__device__ __forceinline__ void hist_add(uint32_t* __restrict__ hw, const uint32_t d, const bool valid) {
-    const uint64_t act = __ballot(valid);
-    if (act == 0ull) return;
-    const uint32_t d0 = bcast_lane(d, __ffsll((unsigned long long)act) - 1);   // (the first active lane's digit)
-    const uint64_t same = __ballot(valid && d == d0);
-    if (same == act) {
-        if (lane_id() == __ffsll((unsigned long long)act) - 1) atomicAdd(&hw[d0], (uint32_t)__popcll(act));
-    } else if (valid) {
-        atomicAdd(&hw[d], 1u);
-    }
-}
-
 // Private histograms: lanes are spread over kCopies of them, which divides the number of lanes that meet on one LDS word
 // or bank (the kernel is bound by these LDS additions, not by the key stream: 1.04 ms with one copy per wavefront, 0.83 ms
 // with two, for the three passes of the largest workload).
