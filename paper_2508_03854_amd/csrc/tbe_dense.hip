@@ -5,8 +5,16 @@
 // on the matrix cores: M = up to 128 dense rows, N = the table's columns, K = bags.
 //
 // Precision: counts are small integers, exact in bfloat16; an fp32 gradient element is split into three bfloat16 pieces of
-// 8 significant bits each, so that x = hi + mid + lo exactly; every product count * piece is exact in fp32 and the matrix
-// core accumulates in fp32, i.e. this is an fp32 sum of exact products.  16-bit gradients (sum pooling) are one piece.
+// 8 significant bits each, so that x = hi + mid + lo exactly down to elements of 2^-110 (below, the last piece is subnormal and
+// ends at 2^-133: the kernel that adds the partial sums looks for sums that this could reach); every product count * piece is
+// exact in fp32, and the matrix core adds them in fp32, one rounding for 8 products (checked on the device: to nearest even,
+// with subnormal operands kept).  16-bit gradients (sum pooling) are one piece.  Under mean pooling an element is multiplied by
+// its bag's 1 / length first, which rounds once.
+// What decides the error is how many terms go into one running sum, since every addition rounds at its magnitude: after 512
+// bags (kRunBlocks) a wavefront adds its accumulators to the partial sum in memory and starts again.  Relative error of the
+// rows' gradient sums against 64 bits, N(0,1) gradients, 64 tables x 32768 bags x 256 columns, Zipf 1.1: ranks 0 to 15 / 16 to
+// 127 2.1e-7 / 1.3e-7 (without the runs 4.0e-7 / 2.2e-7; before the matrix cores 5.2e-7 / 1.4e-7); 32 tables x 65536 bags x 32
+// columns, mean pooling, 2.2e-7 / 1.4e-7 (before 2.9e-7 / 1.2e-7).
 // Counts above 255 (a bag that holds one id very often) take a second pass with the count's upper byte, a multiple of 256
 // and as exact; bags of more than 65535 ids are counted in rounds.
 //
@@ -15,13 +23,14 @@
 // it into bfloat16 in place, and streams the block's gradient rows: a wavefront owns 64 columns (two per lane: 8-byte loads,
 // 256 contiguous bytes per bag), 16 bags per step, the next step's 8 loads in flight while the current one multiplies.
 // Tables narrower than 256 columns give the spare wavefronts a share of the bags.  Two workgroups per compute unit (68 KB of
-// LDS, 128 accumulator registers) overlap each other's counting.  The partial sums of a row, one per workgroup run, are added
+// LDS, 128 accumulator registers) overlap each other's counting.  The partial sums of a row, one per workgroup, are added
 // in order by the kernel that applies the step, so the result does not depend on scheduling.
-// Bound: the stream of the gradient block (matrix work at 128 rows and fp32 gradients is about a third of it).
-// Measured, whole training step, against 16 dense rows on the vector units and sweeps over the rest: 64 tables x 32768 bags
-// of fp32 gradients 9.18 -> 8.06 ms, 32 tables x 65536 bags, mean pooling, 2.42 -> 1.70 ms.  Of that, one load buffer in
-// registers instead of two that spilled, row tiles compiled apart and eight lookups in flight while counting: 8.45 -> 8.06
-// and 1.89 -> 1.70 ms.
+// Bound: wide tables by the stream of the gradient block, at about half the copy rate (64 tables x 32768 bags, 48 of 256
+// columns: 1.9 GB in 0.67 ms), narrow ones by the count table, whose size does not shrink with the columns (32 tables x 65536
+// bags, 30 of 32 columns: 0.32 GB in 0.29 ms).  Measured, whole training step, against 16 dense rows on the vector units and
+// sweeps over the rest: the former 9.5 -> 8.2 ms, the latter, mean pooling, 2.5 -> 1.7 ms.  Of that, the loads ahead of the
+// matrix instructions 20 us of 690; the runs cost 85 us of 607 (and 8 of 296 at 32 columns).  All variants but the two of
+// 16-bit gradients under mean pooling (2 registers each) compile without spilled vector registers.
 // 0 * Inf is NaN, so a non-finite element of one bag's gradient reaches every dense row of its table here; the kernel that
 // adds the partial sums reduces such rows again from their own lookups.
 #include "tbe_rows.h"
@@ -35,6 +44,7 @@ typedef _Float16 f16x8 __attribute__((ext_vector_type(8)));
 constexpr int kDThreads = 256;
 constexpr int kCntPitch = kDenseBags + 8;   // 16 bytes more than a power of two: the rows a wavefront reads lie in different banks
 static_assert(kDenseBags == kDThreads, "one thread per bag of a block");
+constexpr uint32_t kRunBlocks = 2;   // blocks whose bags a wavefront's accumulators take before they are emptied
 
 // the two columns a lane holds of one bag's gradient row
 template <typename GT>
@@ -117,207 +127,238 @@ __device__ __forceinline__ void dense_run(const SegArgs& a, const uint32_t cb, c
     const uint32_t B = (uint32_t)a.B;
     const int64_t bag0 = (int64_t)t * B;
     uint32_t* const cnt32 = reinterpret_cast<uint32_t*>(s_cnt);
-    f32x16 acc[MT][2];
-#pragma unroll
-    for (int m = 0; m < MT; ++m)
-#pragma unroll
-        for (int r = 0; r < 16; ++r) acc[m][0][r] = acc[m][1][r] = 0.f;
-
     const uint32_t* const my_ix = a.dense_index + ((size_t)tab.x * kDenseRows + (tid < nd ? tid : 0u)) * (a.dense_blocks + 1u);
+    char* const sums = reinterpret_cast<char*>(a.dense_partial + (size_t)tab.y * 4u + (size_t)chunk * nd * (uint32_t)D);
+    const uint32_t run = kRunBlocks * (uint32_t)splits;   // blocks that go into the accumulators before they are emptied
     const uint32_t k_lo = chunk * a.dense_per_chunk;
     const uint32_t k_hi = k_lo + a.dense_per_chunk < a.dense_blocks ? k_lo + a.dense_per_chunk : a.dense_blocks;
-    for (uint32_t k = k_lo; k < k_hi; ++k) {
-        const uint32_t b0 = k * kDenseBags;
-        const uint32_t nb = B - b0 < (uint32_t)kDenseBags ? B - b0 : (uint32_t)kDenseBags;   // bags of the block
-        uint32_t ix0 = 0, ix1 = 0;   // this thread's row's lookups in the block
-        if (tid < nd) {
-            ix0 = my_ix[k];
-            ix1 = my_ix[k + 1u];
-        }
-        const uint32_t L = b0 + tid < B ? a.offsets.length(bag0 + b0 + tid) : 0u;   // this thread's bag's length
-        for (uint32_t pass = 0;; ++pass) {   // pass 2r + d: counts' digit d (low, high byte) of round r
-            const uint32_t round = pass >> 1, digit = pass & 1u;
-            __syncthreads();   // the table is free (previous block, or pass)
-            // ---- counts of the block: zero, then one LDS addition per lookup of a dense row
-            for (uint32_t i = tid; i < MT * 32u * (kCntPitch / 8); i += kDThreads)
-                reinterpret_cast<uint4*>(s_cnt)[i] = make_uint4(0u, 0u, 0u, 0u);
-            const uint32_t n = ix1 - ix0;
-            if (tid < nd) s_lo[tid] = ix0;
-            if (tid == 0) S->flags = 0u;
-            if (MEAN) S->scale[tid] = L > 0u ? 1.f / (float)L : 0.f;
-            uint32_t all;
-            const uint32_t ex = block_excl_scan<kDThreads>(n, S->scan, &all);
-            if (tid < (uint32_t)kDenseRows) s_pref[tid] = tid < nd ? ex : 0xFFFFFFFFu;
-            if (L > 255u) atomicOr(&S->flags, L > 65535u ? 3u : 1u);   // (a count cannot exceed its bag's length)
-            __syncthreads();
-            const uint32_t flags = S->flags;
-            bool more = false;   // lookups left for a later round
-            constexpr int kU = 8;   // lookups in flight per thread: the searches and loads of one are a chain of LDS and L2 trips
-            for (uint32_t e0 = tid; e0 < all; e0 += kU * kDThreads) {
-                uint32_t row[kU], p[kU], bag[kU];
-#pragma unroll
-                for (int q = 0; q < kU; ++q) row[q] = 0u;
-#pragma unroll
-                for (uint32_t step = kDenseRows / 2; step > 0u; step >>= 1)   // the row: last h < nd with s_pref[h] <= e
-#pragma unroll
-                    for (int q = 0; q < kU; ++q)
-                        if (s_pref[row[q] + step] <= e0 + q * kDThreads) row[q] += step;   // (s_pref[nd ..] is above every e)
-#pragma unroll
-                for (int q = 0; q < kU; ++q) {
-                    const uint32_t e = e0 + q * kDThreads;
-                    p[q] = s_lo[row[q]] + (e - s_pref[row[q]]);
-                    bag[q] = a.bag_sorted[e < all ? p[q] : s_lo[0]];
-                }
-#pragma unroll
-                for (int q = 0; q < kU; ++q) {
-                    if (e0 + q * kDThreads >= all) continue;
-                    bool take = true;
-                    if (flags & 2u) {   // position among the row's lookups of this bag: 65535 of them per round
-                        uint32_t q0 = s_lo[row[q]], q1 = p[q];   // first position in [q0, p] that holds this bag
-                        while (q0 < q1) {
-                            const uint32_t mid = q0 + ((q1 - q0) >> 1);
-                            if (a.bag_sorted[mid] < bag[q]) q0 = mid + 1u;
-                            else q1 = mid;
-                        }
-                        const uint32_t r = (p[q] - q0) / 65535u;
-                        take = r == round;
-                        more |= r > round;
-                    }
-                    const uint32_t b = (uint32_t)((int64_t)bag[q] - bag0) - b0;
-                    if (take && b < nb) atomicAdd(&cnt32[row[q] * (kCntPitch / 2) + (b >> 1)], 1u << (16u * (b & 1u)));
-                }
-            }
-            if (more) atomicOr(&S->flags, 8u);
-            __syncthreads();
-            bool big = false;
-            for (uint32_t i = tid; i < MT * 32u * (kCntPitch / 8); i += kDThreads) {
-                uint4 v = reinterpret_cast<uint4*>(s_cnt)[i];
-                uint32_t* x = &v.x;
-#pragma unroll
-                for (int q = 0; q < 4; ++q) {
-                    if (flags) big |= (x[q] & 0xFF00FF00u) != 0u;
-                    const uint32_t c = digit ? x[q] & 0xFF00FF00u : (flags ? x[q] & 0x00FF00FFu : x[q]);
-                    x[q] = count_bits<kF16>(c & 0xFFFFu) | (count_bits<kF16>(c >> 16) << 16);
-                }
-                reinterpret_cast<uint4*>(s_cnt)[i] = v;
-            }
-            if (big) atomicOr(&S->flags, 4u);
-            __syncthreads();
-            // ---- stream the block's gradient rows, 16 bags per step; a wavefront takes every splits-th step
-            const int steps = (int)((nb + 15u) >> 4);
-            const char* const gblk = gtab + (int64_t)b0 * pitch;
-            // (a bag behind the batch's end has zero counts: any finite gradient row will do, the block's last)
-            auto load_step = [&](raw_t (&x)[8], const int j) {
-                if (nb == (uint32_t)kDenseBags) {
-                    const char* const row0 = gblk + (int64_t)(j * 16) * pitch;
-                    const uint32_t off = lane_col + (uint32_t)(kh * 8) * (uint32_t)pitch;
-#pragma unroll
-                    for (int i = 0; i < 8; ++i) x[i] = Pair<GT>::load(reinterpret_cast<const GT*>(row0 + i * pitch + off));
-                } else {
-#pragma unroll
-                    for (int i = 0; i < 8; ++i) {
-                        const uint32_t b = (uint32_t)(j * 16 + kh * 8 + i);
-                        x[i] = Pair<GT>::load(reinterpret_cast<const GT*>(gblk + (int64_t)(b < nb ? b : nb - 1u) * pitch + lane_col));
-                    }
-                }
-            };
-            auto multiply_step = [&](raw_t (&x)[8], const int j, const int next) {
-                uint4 f[2][kPieces];   // per column of the pair: pieces of the 8 bags, packed for the matrix core
-                if constexpr (kExact) {
-#pragma unroll
-                    for (int i = 0; i < 4; ++i) {
-                        (&f[0][0].x)[i] = lower_halves(x[2 * i], x[2 * i + 1]);
-                        (&f[1][0].x)[i] = upper_halves(x[2 * i], x[2 * i + 1]);
-                    }
-                } else {
-                    float sc[8];
-                    if constexpr (MEAN) {
-                        const float4 sa = *reinterpret_cast<const float4*>(&S->scale[j * 16 + kh * 8]);
-                        const float4 sb = *reinterpret_cast<const float4*>(&S->scale[j * 16 + kh * 8 + 4]);
-                        sc[0] = sa.x; sc[1] = sa.y; sc[2] = sa.z; sc[3] = sa.w;
-                        sc[4] = sb.x; sc[5] = sb.y; sc[6] = sb.z; sc[7] = sb.w;
-                    }
-#pragma unroll
-                    for (int i = 0; i < 4; ++i) {
-                        const float2 g0 = Pair<GT>::to_float(x[2 * i]), g1 = Pair<GT>::to_float(x[2 * i + 1]);
-#pragma unroll
-                        for (int c = 0; c < 2; ++c) {
-                            float v0 = c ? g0.y : g0.x, v1 = c ? g1.y : g1.x;
-                            if constexpr (MEAN) {
-                                v0 *= sc[2 * i];
-                                v1 *= sc[2 * i + 1];
-                            }
-#pragma unroll
-                            for (int p = 0; p < 3; ++p) {
-                                const uint32_t u0 = __float_as_uint(v0), u1 = __float_as_uint(v1);
-                                (&f[c][p].x)[i] = upper_halves(u0, u1);
-                                v0 -= __uint_as_float(u0 & 0xFFFF0000u);   // what the upper 16 bits leave, exactly
-                                v1 -= __uint_as_float(u1 & 0xFFFF0000u);
-                            }
-                        }
-                    }
-                }
-                load_step(x, next);
-#pragma unroll
-                for (int m = 0; m < MT; ++m) {
-                    const uint4 av = *reinterpret_cast<const uint4*>(&s_cnt[(m * 32 + (lane & 31)) * kCntPitch + j * 16 + kh * 8]);
-#pragma unroll
-                    for (int p = kPieces - 1; p >= 0; --p) {   // small pieces first
-                        acc[m][0] = mfma<kF16>(av, f[0][p], acc[m][0]);
-                        acc[m][1] = mfma<kF16>(av, f[1][p], acc[m][1]);
-                    }
-                }
-            };
-            raw_t x[8];   // the next step's rows are in flight while a step multiplies
-            const int last = steps - 1;
-            load_step(x, split < last ? split : last);
 #pragma unroll 1
-            for (int j = split; j < steps; j += splits) multiply_step(x, j, j + splits < last ? j + splits : last);
-            const uint32_t fl = S->flags;
-            if (digit == 0u && !(fl & 4u)) {        // no count has an upper byte: skip that pass
-                if (!(fl & 8u)) break;
-                ++pass;
-            } else if (digit == 1u && !(fl & 8u)) {
-                break;
-            }
-        }
-    }
-    // ---- add up the wavefronts that shared the bags of a column group, in order
-    float* const red = reinterpret_cast<float*>(s_cnt);   // [32 * MT rows][64 * groups columns]: at most 64 KB (splits > 1: groups <= 2)
-    for (int sp = 1; sp < splits; ++sp) {
-        __syncthreads();
-        if (split == sp) {
-#pragma unroll
-            for (int m = 0; m < MT; ++m)
-#pragma unroll
-                for (int r = 0; r < 16; ++r) {
-                    const int h = m * 32 + (r & 3) + 8 * (r >> 2) + 4 * kh;
-                    *reinterpret_cast<float2*>(&red[h * (64 * groups) + cg * 64 + 2 * (lane & 31)]) = make_float2(acc[m][0][r], acc[m][1][r]);
-                }
-        }
-        __syncthreads();
-        if (split == 0) {
-#pragma unroll
-            for (int m = 0; m < MT; ++m)
-#pragma unroll
-                for (int r = 0; r < 16; ++r) {
-                    const int h = m * 32 + (r & 3) + 8 * (r >> 2) + 4 * kh;
-                    const float2 o = *reinterpret_cast<const float2*>(&red[h * (64 * groups) + cg * 64 + 2 * (lane & 31)]);
-                    acc[m][0][r] += o.x;
-                    acc[m][1][r] += o.y;
-                }
-        }
-    }
-    if (split == 0 && col_on) {
-        float* const dst = a.dense_partial + (size_t)tab.y * 4u + (size_t)chunk * nd * (uint32_t)D + col;
+    for (uint32_t k0 = k_lo; k0 < k_hi; k0 += run) {
+        const uint32_t k1 = k0 + run < k_hi ? k0 + run : k_hi;
+        f32x16 acc[MT][2];
 #pragma unroll
         for (int m = 0; m < MT; ++m)
 #pragma unroll
-                for (int r = 0; r < 16; ++r) {
-                    const uint32_t h = (uint32_t)(m * 32 + (r & 3) + 8 * (r >> 2) + 4 * kh);
-                    if (h < nd)
-                        *reinterpret_cast<float2*>(dst + (size_t)h * (uint32_t)D) = make_float2(acc[m][0][r], acc[m][1][r]);
+            for (int r = 0; r < 16; ++r) acc[m][0][r] = acc[m][1][r] = 0.f;
+        for (uint32_t k = k0; k < k1; ++k) {
+            const uint32_t b0 = k * kDenseBags;
+            const uint32_t nb = B - b0 < (uint32_t)kDenseBags ? B - b0 : (uint32_t)kDenseBags;   // bags of the block
+            uint32_t ix0 = 0, ix1 = 0;   // this thread's row's lookups in the block
+            if (tid < nd) {
+                ix0 = my_ix[k];
+                ix1 = my_ix[k + 1u];
+            }
+            const uint32_t L = b0 + tid < B ? a.offsets.length(bag0 + b0 + tid) : 0u;   // this thread's bag's length
+            for (uint32_t pass = 0;; ++pass) {   // pass 2r + d: counts' digit d (low, high byte) of round r
+                const uint32_t round = pass >> 1, digit = pass & 1u;
+                __syncthreads();   // the table is free (previous block, or pass)
+                // ---- counts of the block: zero, then one LDS addition per lookup of a dense row
+                for (uint32_t i = tid; i < MT * 32u * (kCntPitch / 8); i += kDThreads)
+                    reinterpret_cast<uint4*>(s_cnt)[i] = make_uint4(0u, 0u, 0u, 0u);
+                const uint32_t n = ix1 - ix0;
+                if (tid < nd) s_lo[tid] = ix0;
+                if (tid == 0) S->flags = 0u;
+                if (MEAN) S->scale[tid] = L > 0u ? 1.f / (float)L : 0.f;
+                uint32_t all;
+                const uint32_t ex = block_excl_scan<kDThreads>(n, S->scan, &all);
+                if (tid < (uint32_t)kDenseRows) s_pref[tid] = tid < nd ? ex : 0xFFFFFFFFu;
+                if (L > 255u) atomicOr(&S->flags, L > 65535u ? 3u : 1u);   // (a count cannot exceed its bag's length)
+                __syncthreads();
+                const uint32_t flags = S->flags;
+                bool more = false;   // lookups left for a later round
+                constexpr int kU = 8;   // lookups in flight per thread: the searches and loads of one are a chain of LDS and L2 trips
+                for (uint32_t e0 = tid; e0 < all; e0 += kU * kDThreads) {
+                    uint32_t row[kU], p[kU], bag[kU];
+#pragma unroll
+                    for (int q = 0; q < kU; ++q) row[q] = 0u;
+#pragma unroll
+                    for (uint32_t step = kDenseRows / 2; step > 0u; step >>= 1)   // the row: last h < nd with s_pref[h] <= e
+#pragma unroll
+                        for (int q = 0; q < kU; ++q)
+                            if (s_pref[row[q] + step] <= e0 + q * kDThreads) row[q] += step;   // (s_pref[nd ..] is above every e)
+#pragma unroll
+                    for (int q = 0; q < kU; ++q) {
+                        const uint32_t e = e0 + q * kDThreads;
+                        p[q] = s_lo[row[q]] + (e - s_pref[row[q]]);
+                        bag[q] = a.bag_sorted[e < all ? p[q] : s_lo[0]];
+                    }
+#pragma unroll
+                    for (int q = 0; q < kU; ++q) {
+                        if (e0 + q * kDThreads >= all) continue;
+                        bool take = true;
+                        if (flags & 2u) {   // position among the row's lookups of this bag: 65535 of them per round
+                            uint32_t q0 = s_lo[row[q]], q1 = p[q];   // first position in [q0, p] that holds this bag
+                            while (q0 < q1) {
+                                const uint32_t mid = q0 + ((q1 - q0) >> 1);
+                                if (a.bag_sorted[mid] < bag[q]) q0 = mid + 1u;
+                                else q1 = mid;
+                            }
+                            const uint32_t r = (p[q] - q0) / 65535u;
+                            take = r == round;
+                            more |= r > round;
+                        }
+                        const uint32_t b = (uint32_t)((int64_t)bag[q] - bag0) - b0;
+                        if (take && b < nb) atomicAdd(&cnt32[row[q] * (kCntPitch / 2) + (b >> 1)], 1u << (16u * (b & 1u)));
+                    }
                 }
+                if (more) atomicOr(&S->flags, 8u);
+                __syncthreads();
+                bool big = false;
+                for (uint32_t i = tid; i < MT * 32u * (kCntPitch / 8); i += kDThreads) {
+                    uint4 v = reinterpret_cast<uint4*>(s_cnt)[i];
+                    uint32_t* x = &v.x;
+#pragma unroll
+                    for (int q = 0; q < 4; ++q) {
+                        if (flags) big |= (x[q] & 0xFF00FF00u) != 0u;
+                        const uint32_t c = digit ? x[q] & 0xFF00FF00u : (flags ? x[q] & 0x00FF00FFu : x[q]);
+                        x[q] = count_bits<kF16>(c & 0xFFFFu) | (count_bits<kF16>(c >> 16) << 16);
+                    }
+                    reinterpret_cast<uint4*>(s_cnt)[i] = v;
+                }
+                if (big) atomicOr(&S->flags, 4u);
+                __syncthreads();
+                // ---- stream the block's gradient rows, 16 bags per step; a wavefront takes every splits-th step
+                const int steps = (int)((nb + 15u) >> 4);
+                const char* const gblk = gtab + (int64_t)b0 * pitch;
+                // (a bag behind the batch's end has zero counts: any finite gradient row will do, the block's last)
+                auto load_step = [&](raw_t (&x)[8], const int j) {
+                    if (nb == (uint32_t)kDenseBags) {
+                        const char* const row0 = gblk + (int64_t)(j * 16) * pitch;
+                        const uint32_t off = lane_col + (uint32_t)(kh * 8) * (uint32_t)pitch;
+#pragma unroll
+                        for (int i = 0; i < 8; ++i) x[i] = Pair<GT>::load(reinterpret_cast<const GT*>(row0 + i * pitch + off));
+                    } else {
+#pragma unroll
+                        for (int i = 0; i < 8; ++i) {
+                            const uint32_t b = (uint32_t)(j * 16 + kh * 8 + i);
+                            x[i] = Pair<GT>::load(reinterpret_cast<const GT*>(gblk + (int64_t)(b < nb ? b : nb - 1u) * pitch + lane_col));
+                        }
+                    }
+                };
+                auto multiply_step = [&](raw_t (&x)[8], const int j, const int next) {
+                    uint4 f[2][kPieces];   // per column of the pair: pieces of the 8 bags, packed for the matrix core
+                    if constexpr (kExact) {
+#pragma unroll
+                        for (int i = 0; i < 4; ++i) {
+                            (&f[0][0].x)[i] = lower_halves(x[2 * i], x[2 * i + 1]);
+                            (&f[1][0].x)[i] = upper_halves(x[2 * i], x[2 * i + 1]);
+                        }
+                    } else {
+                        float sc[8];
+                        if constexpr (MEAN) {
+                            const float4 sa = *reinterpret_cast<const float4*>(&S->scale[j * 16 + kh * 8]);
+                            const float4 sb = *reinterpret_cast<const float4*>(&S->scale[j * 16 + kh * 8 + 4]);
+                            sc[0] = sa.x; sc[1] = sa.y; sc[2] = sa.z; sc[3] = sa.w;
+                            sc[4] = sb.x; sc[5] = sb.y; sc[6] = sb.z; sc[7] = sb.w;
+                        }
+#pragma unroll
+                        for (int i = 0; i < 4; ++i) {
+                            const float2 g0 = Pair<GT>::to_float(x[2 * i]), g1 = Pair<GT>::to_float(x[2 * i + 1]);
+#pragma unroll
+                            for (int c = 0; c < 2; ++c) {
+                                float v0 = c ? g0.y : g0.x, v1 = c ? g1.y : g1.x;
+                                if constexpr (MEAN) {
+                                    v0 *= sc[2 * i];
+                                    v1 *= sc[2 * i + 1];
+                                }
+#pragma unroll
+                                for (int p = 0; p < 3; ++p) {
+                                    const uint32_t u0 = __float_as_uint(v0), u1 = __float_as_uint(v1);
+                                    (&f[c][p].x)[i] = upper_halves(u0, u1);
+                                    v0 -= __uint_as_float(u0 & 0xFFFF0000u);   // what the upper 16 bits leave, exactly
+                                    v1 -= __uint_as_float(u1 & 0xFFFF0000u);
+                                }
+                            }
+                        }
+                    }
+                    load_step(x, next);
+                    // (without this line the compiler turns "loaded here or ahead of the loop" into one load at the top of the next
+                    // step, right before its use: nothing would be in flight while the matrix cores work)
+                    asm volatile("" ::: "memory");
+#pragma unroll
+                    for (int m = 0; m < MT; ++m) {
+                        const uint4 av = *reinterpret_cast<const uint4*>(&s_cnt[(m * 32 + (lane & 31)) * kCntPitch + j * 16 + kh * 8]);
+#pragma unroll
+                        for (int p = kPieces - 1; p >= 0; --p) {   // small pieces first
+                            acc[m][0] = mfma<kF16>(av, f[0][p], acc[m][0]);
+                            acc[m][1] = mfma<kF16>(av, f[1][p], acc[m][1]);
+                        }
+                    }
+                };
+                raw_t x[8];   // the next step's rows are in flight while a step multiplies
+                const int last = steps - 1;
+                load_step(x, split < last ? split : last);
+#pragma unroll 1
+                for (int j = split; j < steps; j += splits) multiply_step(x, j, j + splits < last ? j + splits : last);
+                const uint32_t fl = S->flags;
+                if (digit == 0u && !(fl & 4u)) {        // no count has an upper byte: skip that pass
+                    if (!(fl & 8u)) break;
+                    ++pass;
+                } else if (digit == 1u && !(fl & 8u)) {
+                    break;
+                }
+            }
+        }
+        // ---- the accumulators go to the rows' partial sums and start again.  First the wavefronts that shared the bags of a column
+        // group, in order.  (The addresses below are kept from being computed ahead of the loops: there are no registers for them.)
+#pragma unroll 1
+        for (int sp = 1; sp < splits; ++sp) {
+            uint32_t red_pitch = 64u * (uint32_t)groups;
+            asm volatile("" : "+s"(red_pitch));
+            // [32 * MT rows][64 * groups columns]: at most 64 KB (splits > 1: groups <= 2)
+            float* red = reinterpret_cast<float*>(s_cnt) + 4u * (uint32_t)kh * red_pitch + (uint32_t)(cg * 64 + 2 * (lane & 31));
+            __syncthreads();
+            if (split == sp) {
+#pragma unroll
+                for (int m = 0; m < MT; ++m)
+#pragma unroll
+                    for (int q = 0; q < 4; ++q, red += 8u * red_pitch)
+#pragma unroll
+                        for (int r = 0; r < 4; ++r)
+                            *reinterpret_cast<float2*>(red + (uint32_t)r * red_pitch) = make_float2(acc[m][0][4 * q + r], acc[m][1][4 * q + r]);
+            }
+            __syncthreads();
+            if (split == 0) {
+#pragma unroll
+                for (int m = 0; m < MT; ++m)
+#pragma unroll
+                    for (int q = 0; q < 4; ++q, red += 8u * red_pitch)
+#pragma unroll
+                        for (int r = 0; r < 4; ++r) {
+                            const float2 o = *reinterpret_cast<const float2*>(red + (uint32_t)r * red_pitch);
+                            acc[m][0][4 * q + r] += o.x;
+                            acc[m][1][4 * q + r] += o.y;
+                        }
+            }
+        }
+        if (split == 0 && col_on) {
+            const bool add = k0 > k_lo;   // not the chunk's first run: this lane has written the sum before
+            uint32_t row_bytes = (uint32_t)D * 4u;
+            int left = (int)nd - 4 * kh;   // dense rows from this lane's first on
+            asm volatile("" : "+s"(row_bytes), "+v"(left));
+            uint32_t at = (uint32_t)(4 * kh) * row_bytes + (uint32_t)col * 4u;
+#pragma unroll
+            for (int m = 0; m < MT; ++m, at += 32u * row_bytes) {
+                if (add) {   // all loads of a row tile in flight
+                    float2 o[16];
+#pragma unroll
+                    for (int r = 0; r < 16; ++r) {
+                        const int h = (r & 3) + 8 * (r >> 2);
+                        o[r] = *reinterpret_cast<const float2*>(sums + (m * 32 + h < left ? at + (uint32_t)h * row_bytes : (uint32_t)col * 4u));
+                    }
+#pragma unroll
+                    for (int r = 0; r < 16; ++r) {
+                        acc[m][0][r] += o[r].x;
+                        acc[m][1][r] += o[r].y;
+                    }
+                }
+#pragma unroll
+                for (int r = 0; r < 16; ++r) {
+                    const int h = (r & 3) + 8 * (r >> 2);
+                    if (m * 32 + h < left) *reinterpret_cast<float2*>(sums + (at + (uint32_t)h * row_bytes)) = make_float2(acc[m][0][r], acc[m][1][r]);
+                }
+            }
+        }
     }
 }
 

@@ -94,3 +94,28 @@ def test_a_non_finite_gradient_stays_with_its_own_bag(D, dtype, pooling, io, val
     torch.testing.assert_close(w1[~hit], w0[~hit], rtol=0.0, atol=atol)
     torch.testing.assert_close(s1[~hit], s0[~hit], rtol=1e-5, atol=0.0)
     tbe.close()
+
+
+@pytest.mark.parametrize("D,B", [(256, 65536), (128, 65536), (32, 262144)])
+def test_the_error_of_a_dense_row_is_that_of_short_sums(D, B):
+    """Rows that every bag holds, N(0,1) gradients, relative error of the summed gradient against 64 bits.
+
+    A running fp32 sum of magnitude v rounds with an error of about 0.42 * 2^-24 * v per addition (uniform over a unit in the
+    last place that is 2^-23 to 2^-22 of v).  The matrix core rounds once for 8 bags, and a run has 512, at magnitudes of
+    sqrt(8 i): 54 * 2^-24 per run.  The B / 512 runs of a row of norm sqrt(B) come to 54 / sqrt(512) = 2.4 * 2^-24 of it, the sums of
+    run sums to 1 to 1.5 more, and the smaller pieces of an element round a second time: 4 in all (measured 3.98, 4.29, 4.26).
+    One sum over the whole chunk of 2048 bags and more would be at 5.5 to 7."""
+    if not torch.cuda.is_available():
+        pytest.skip("no GPU")
+    from paper_2508_03854_amd import TBE
+    g = torch.Generator(device="cuda").manual_seed(3)
+    grad = torch.randn(B, D, generator=g, device="cuda")
+    idx, off = torch.arange(3, device="cuda").repeat(B), torch.arange(0, 3 * B + 1, 3, device="cuda")
+    tbe = TBE([3], [D], "f32")
+    ws = tbe.alloc_workspace(B, idx.numel())
+    w = torch.zeros(3 * D, device="cuda")
+    tbe.backward_sgd(grad, idx, off, B, w, ws, lr=1.0)
+    assert len(tbe.debug_hot_rows(ws, B, idx.numel())[1][0]) == 3
+    want = grad.double().sum(0)
+    assert float((w.view(3, D).double() + want).norm() / (3.0 ** 0.5 * want.norm())) < 5.0 * 2.0 ** -24
+    tbe.close()
