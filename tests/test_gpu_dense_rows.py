@@ -119,3 +119,48 @@ def test_the_error_of_a_dense_row_is_that_of_short_sums(D, B):
     want = grad.double().sum(0)
     assert float((w.view(3, D).double() + want).norm() / (3.0 ** 0.5 * want.norm())) < 5.0 * 2.0 ** -24
     tbe.close()
+
+
+@pytest.mark.parametrize("scale", [1.0, 1e-20, 1e-28, 1e-33, 1e-36])
+@pytest.mark.parametrize("pooling", ["sum", "mean"])
+def test_tiny_gradients_keep_their_precision(scale, pooling):
+    """fp32 gradients whose last bits no bfloat16 can hold: the rows' sums stay as good as at N(0,1).  400 lookups per row and
+    fp32 sums: within 2^-24 * sqrt(400) of the row's norm, where the pieces alone would leave 5e-5 and 7e-4 at 1e-36."""
+    if not torch.cuda.is_available():
+        pytest.skip("no GPU")
+    from paper_2508_03854_amd import TBE
+    B, R, D, L = 4200, 60, 128, 6
+    g = torch.Generator().manual_seed(8)
+    grad = torch.randn(B, D, generator=g) * scale
+    idx = torch.randint(0, R, (B * L,), generator=g)
+    tbe = TBE([R], [D], "f32")
+    ws = tbe.alloc_workspace(B, B * L)
+    w = torch.zeros(R * D, device="cuda")
+    tbe.backward_sgd(grad.cuda(), idx.cuda(), torch.arange(0, B * L + 1, L).cuda(), B, w, ws, pooling=pooling, lr=1.0)
+    assert len(tbe.debug_hot_rows(ws, B, B * L)[1][0]) == R
+    want = torch.zeros(R, D, dtype=torch.float64).index_add_(0, idx, grad.double().repeat_interleave(L, 0)) / (L if pooling == "mean" else 1)
+    err = (w.cpu().double().view(R, D) + want).norm(dim=1) / want.norm(dim=1)
+    assert float(err.max()) < 20.0 * 2.0 ** -24
+    tbe.close()
+
+
+@pytest.mark.parametrize("scale", [1e-3, 2e-5, 3e-7])
+def test_subnormal_binary16_gradients_are_summed_exactly(scale):
+    """binary16 has its subnormals below 6.1e-5, ordinary values in mixed-precision training: multiples of 2^-24 whose sums an
+    fp32 holds exactly while they stay below 1."""
+    if not torch.cuda.is_available():
+        pytest.skip("no GPU")
+    from paper_2508_03854_amd import TBE
+    B, R, D, L = 4200, 60, 128, 6
+    g = torch.Generator().manual_seed(9)
+    grad = (torch.randn(B, D, generator=g) * scale).half()
+    grad = torch.round(grad.double() * 2 ** 24).mul(2.0 ** -24).half()
+    idx = torch.randint(0, R, (B * L,), generator=g)
+    tbe = TBE([R], [D], "f32")
+    ws = tbe.alloc_workspace(B, B * L)
+    w = torch.zeros(R * D, device="cuda")
+    tbe.backward_sgd(grad.cuda(), idx.cuda(), torch.arange(0, B * L + 1, L).cuda(), B, w, ws, lr=1.0)
+    assert len(tbe.debug_hot_rows(ws, B, B * L)[1][0]) == R
+    want = torch.zeros(R, D, dtype=torch.float64).index_add_(0, idx, grad.double().repeat_interleave(L, 0))
+    assert torch.equal(-w.cpu().double().view(R, D), want)
+    tbe.close()
