@@ -605,9 +605,11 @@ __device__ __forceinline__ void copy_fragment(const WT* __restrict__ src, void* 
     for (int v4 = 0; v4 < V; v4 += 4) store4_from_float(out, out_io, elem + v4, x[v4], x[v4 + 1], x[v4 + 2], x[v4 + 3]);
 }
 
-template <typename WT>
+// IT: int64 or int32 ids and offsets, compiled apart: the search below is a chain of loads that differs from lane to lane, and
+// with the width as a run-time flag every step of it branches around two loads.
+template <typename WT, typename IT>
 __global__ __launch_bounds__(kFwdThreads, 8) void lookup_seq_kernel(
-    const WT* __restrict__ weights, const IdxView indices, const IdxView offsets, const int32_t* __restrict__ D_off,
+    const WT* __restrict__ weights, const IT* __restrict__ indices, const IT* __restrict__ offsets, const int32_t* __restrict__ D_off,
     const int64_t* __restrict__ w_off, const int64_t* __restrict__ row_base, const int T, const int64_t nnz,
     void* __restrict__ out, const int out_io, const int64_t out_elems, int32_t* err) {
     constexpr int V = RowIO<WT>::kVec;
@@ -623,7 +625,7 @@ __global__ __launch_bounds__(kFwdThreads, 8) void lookup_seq_kernel(
         int lo = 0, hi = T;  // invariant: offsets[lo] <= q, answer in [lo, hi)
         while (hi - lo > 1) {
             const int mid = (lo + hi) >> 1;
-            if (offsets[mid] <= q) lo = mid;
+            if ((int64_t)offsets[mid] <= q) lo = mid;
             else hi = mid;
         }
         t = lo;
@@ -632,16 +634,16 @@ __global__ __launch_bounds__(kFwdThreads, 8) void lookup_seq_kernel(
     const int t0 = __shfl(t, 0, kWave);
     int64_t part = 0;
     for (int tt = lane; tt < t0; tt += kWave) {
-        const int64_t n = offsets[tt + 1] - offsets[tt];
+        const int64_t n = (int64_t)offsets[tt + 1] - (int64_t)offsets[tt];
         part += (n > 0 ? n : 0) * (int64_t)(D_off[tt + 1] - D_off[tt]);
     }
     int64_t base = wave_sum_i64(part);
     for (int tt = t0; tt < t; ++tt) {
-        const int64_t n = offsets[tt + 1] - offsets[tt];
+        const int64_t n = (int64_t)offsets[tt + 1] - (int64_t)offsets[tt];
         base += (n > 0 ? n : 0) * (int64_t)(D_off[tt + 1] - D_off[tt]);
     }
     const int D = D_off[t + 1] - D_off[t];
-    int64_t id = valid ? indices[p] : 0;
+    int64_t id = valid ? (int64_t)indices[p] : 0;
     const int64_t R = row_base[t + 1] - row_base[t];
     bool bad = false;
     if (valid && (id < 0 || id >= R)) {
@@ -650,7 +652,7 @@ __global__ __launch_bounds__(kFwdThreads, 8) void lookup_seq_kernel(
         id = 0;
     }
     const int64_t src_elem = w_off[t] + id * D;
-    int64_t dst_elem = base + (p - offsets[t]) * D;
+    int64_t dst_elem = base + (p - (int64_t)offsets[t]) * D;
     // a malformed offsets array (not ascending from 0 to nnz) must never take a store outside out[0, out_elems)
     if (valid && (dst_elem < 0 || dst_elem + D > out_elems)) {
         atomicOr(err, 1);
@@ -697,20 +699,27 @@ __global__ __launch_bounds__(kFwdThreads, 8) void lookup_seq_kernel(
     }
 }
 
-hipError_t launch_lookup_seq(const tbe_handle* h, const void* tables, const void* indices_p, const void* offsets_p,
+template <typename WT, typename IT>
+static void launch_lookup_seq_as(const tbe_handle* h, const dim3 grid, const void* tables, const void* indices, const void* offsets,
+                                 int64_t nnz, void* out, int out_io, int64_t out_elems, hipStream_t s) {
+    lookup_seq_kernel<WT, IT><<<grid, kFwdThreads, 0, s>>>(static_cast<const WT*>(tables), static_cast<const IT*>(indices),
+                                                           static_cast<const IT*>(offsets), h->d_D_off, h->d_w_off, h->d_row_base,
+                                                           h->T, nnz, out, out_io, out_elems, h->d_err);
+}
+
+hipError_t launch_lookup_seq(const tbe_handle* h, const void* tables, const void* indices, const void* offsets,
                              int idx32, int64_t nnz, void* out, int out_io, int64_t out_elems, hipStream_t s) {
     if (nnz == 0) return hipSuccess;
-    const IdxView indices{indices_p, idx32}, offsets{offsets_p, idx32};
     const int64_t per_block = (int64_t)(kFwdThreads / kWave) * kWave;
     const dim3 grid((unsigned)((nnz + per_block - 1) / per_block));
     LaunchTimer tm(h, s, "lookup_seq");
-    if (h->dtype == TBE_F32)
-        lookup_seq_kernel<float><<<grid, kFwdThreads, 0, s>>>(static_cast<const float*>(tables), indices, offsets, h->d_D_off,
-                                                              h->d_w_off, h->d_row_base, h->T, nnz, out, out_io, out_elems, h->d_err);
-    else
-        lookup_seq_kernel<__half><<<grid, kFwdThreads, 0, s>>>(static_cast<const __half*>(tables), indices, offsets,
-                                                               h->d_D_off, h->d_w_off, h->d_row_base, h->T, nnz, out, out_io,
-                                                               out_elems, h->d_err);
+    if (h->dtype == TBE_F32) {
+        if (idx32) launch_lookup_seq_as<float, int32_t>(h, grid, tables, indices, offsets, nnz, out, out_io, out_elems, s);
+        else launch_lookup_seq_as<float, int64_t>(h, grid, tables, indices, offsets, nnz, out, out_io, out_elems, s);
+    } else {
+        if (idx32) launch_lookup_seq_as<__half, int32_t>(h, grid, tables, indices, offsets, nnz, out, out_io, out_elems, s);
+        else launch_lookup_seq_as<__half, int64_t>(h, grid, tables, indices, offsets, nnz, out, out_io, out_elems, s);
+    }
     tm.done();
     return hipGetLastError();
 }

@@ -44,8 +44,8 @@ struct ChunkDesc {            // written by pass 0, one per workgroup; e == s: n
 
 // everything a pass needs to know about where its elements come from
 struct SortArgs {
-    const void* indices;     // int64 or int32, both the same: the kernels that read them are compiled for either (as a
-    const void* offsets;     // run-time flag inside divergent searches it has been miscompiled: a 4-byte load for 8-byte ids)
+    const void* indices;     // int64 or int32, both the same: the kernels that read them are compiled for either (a run-time
+    const void* offsets;     // flag costs every load of the divergent searches a branch around two forms of it)
     const int64_t* row_base;
     ChunkDesc* desc;
     uint32_t* chunk0;        // [nseg + 1] first chunk of every segment (large batches)
