@@ -65,7 +65,8 @@ tbe_status tbe_create(int32_t T, const int64_t* rows, const int32_t* D, tbe_dtyp
 tbe_status tbe_destroy(tbe_handle* h);
 
 /* Bytes of scratch that tbe_backward_rowwise_adagrad needs for a batch of B samples and at most
- * max_nnz lookups (sort double buffers, segment lists, partial sums of very hot rows). */
+ * max_nnz lookups (sort double buffers, segment lists, partial sums of very hot rows).  Never shrinks when B or max_nnz
+ * grows, so a workspace made for a batch serves every smaller one. */
 tbe_status tbe_workspace_bytes(const tbe_handle* h, int32_t B, int64_t max_nnz, size_t* bytes);
 
 /* Forward: pooled lookup (paper Section 2.1: an id selects a row of its table; the problem statement
@@ -134,7 +135,7 @@ tbe_status tbe_backward_rowwise_adagrad_static(const tbe_handle* h, const void* 
                                                float momentum_scale, void* tables, float* state, void* hip_stream);
 
 /* The backward in two calls, so that the part that needs only the ids can leave the critical path.
- * tbe_backward_prepare runs the linearise / sort / run-length steps (Section 2.1: which rows appear in the batch
+ * tbe_backward_prepare runs the sort and run-length steps and lists the rows with many lookups (Section 2.1: which rows appear in the batch
  * is known from the ids alone) and leaves their result in `workspace`; it may be enqueued on another stream as soon
  * as the batch's ids are on the device, concurrently with tbe_forward or with the dense part of the model.
  * tbe_backward_apply_rowwise_adagrad then does the per-row reduction and the step (Section 3.2, Algorithm 1 steps
@@ -241,7 +242,7 @@ tbe_status tbe_poll_index_error(tbe_handle* h);
 /* Tunables of a handle (host-side settings read by later calls; none changes any result beyond the order of
  * floating-point additions).
  *   TBE_TUNE_HOT_ROWS_MIN_WORKGROUPS  The forward keeps, for every table, a copy of the rows that had the most lookups
- *       in the LAST backward call on this handle in on-chip memory (the handle remembers their ids: a hint, the
+ *       (at least 513) in the LAST backward call on this handle in on-chip memory (the handle remembers their ids: a hint, the
  *       pooled sums are the same whatever it holds) and serves their lookups from there.  That path runs for a group
  *       of tables of one width when it fills at least `value` workgroups (default 256, one per compute unit; 0:
  *       whenever the width allows it, also for batches so small that they would otherwise take one wavefront per bag;

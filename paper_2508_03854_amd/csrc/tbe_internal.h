@@ -45,8 +45,8 @@ struct tbe_handle {
     bool seg_mostly_wavefront_rows = false;  // most rows of the tables up to 256 columns need all 64 lanes (D > 128)
     int key_bits = 1;  // bits needed to hold the value total_rows (the key given to invalid ids)
     // Sort plan.  Positions arrive grouped by table, so sorting every table's run of positions on its table-local id
-    // alone gives the same order as sorting all of them on the linearised key, with fewer key bits whenever
-    // bits(max rows of one table) needs fewer radix passes than bits(sum of rows).
+    // alone gives the same order as sorting all of them on the linearised key, with no more key bits and no search for a
+    // position's table.  Keys of at most 8 bits take one pass either way.
     bool segmented = false;  // true: one sort segment per table, local keys; false: one segment, linearised keys
     int sort_bits = 1;       // key bits the radix passes cover
     std::vector<int64_t> rows, row_base, w_off;

@@ -5,15 +5,16 @@
 // per table lists its own:
 //   - the kHotRows longest of those with more than kHotMin lookups, a hint for the next forward (with shorter rows listed, as
 //     long_min falls with the batch, the forward of 256 tables x 512 bags of 4 ids, 16 columns, went from 16.4 to 18.6 us);
-//   - the dense rows: up to kDenseRows longest, if together they hold at least two lookups per bag of a gradient block that
-//     no L2 holds.  Streaming the block once and adding every bag's gradient to all of them (tbe_dense.hip) then reads less
+//   - the dense rows: up to kDenseRows longest, if together they hold at least two lookups per bag of a large gradient block
+//     (dense_block).  Streaming the block once and adding every bag's gradient to all of them (tbe_dense.hip) then reads less
 //     than gathering it once per lookup;
 //   - the others, cut into parts of about `part` lookups, one work unit and one partial sum each.
 // Partial-sum slots need no counting: row number i of the list with its first lookup at sorted position s gets the slots
 // from s / part + i on.  A row of len lookups takes ceil(len / part) <= (s + len) / part - s / part + 1 of them, so the
 // next row's start behind its own, and n lookups in rows longer than long_min need at most n / part + n / long_min.
 //
-// Bound: latency - a table has at most a few thousand long rows, and the launch is one chain of dependent loads.  Hence one
+// Bound: latency - most tables have at most a thousand long rows, ranked by one workgroup at one row per thread, and the launch
+// is one chain of dependent loads; of more rows the longest are selected first (one table, 16.8 M lookups, Zipf 1.05: 20 us).  Hence one
 // launch (two with dense rows) in place of the up to 20 that counted, scanned, filled, ranked and sliced before.  With parts
 // sized to the batch the whole step went from 67 to 46 us (one table, 10 k lookups), 353 to 163 us (ten tables of odd widths,
 // 47 k lookups, mean pooling) and 254 to 193 us (26 tables, 1.2 M lookups).

@@ -1,6 +1,5 @@
-"""GPU parity at batch sizes where a table's gradient block (B x D elements) is larger than one 4 MiB L2 cache, so
-that the hot-row kernels take their bag-sliced form (every XCD reduces its eighth of the bags, dense rows are
-streamed), against the CPU oracle element by element.  Small enough for the oracle: a few tables, scaled row counts."""
+"""GPU parity at batch sizes where a table's gradient block (B x D elements) is large, so that its hottest rows are reduced on
+the matrix cores, against the CPU oracle element by element.  Small enough for the oracle: a few tables, scaled row counts."""
 import numpy as np
 import pytest
 import torch
@@ -21,7 +20,7 @@ def H():
 @pytest.mark.parametrize("name,kw,opts", [
     # fp16 tables, D in {128, 256}: B x 256 x 4 bytes = 4 MiB blocks
     ("C4", dict(T=4, B=4096, rows_scale=0.03), dict()),
-    # B not a multiple of 8: the last XCD's share of the bags is shorter
+    # B not a multiple of 256: the last block of bags is shorter
     ("C4", dict(T=3, B=4099, rows_scale=0.02), dict()),
     # 16-bit gradients, int32 ids
     ("C4", dict(T=3, B=8192, rows_scale=0.03), dict(io="bf16", index_dtype=torch.int32)),
