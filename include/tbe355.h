@@ -60,7 +60,8 @@ typedef enum { TBE_IO_F32 = 0, TBE_IO_F16 = 1, TBE_IO_BF16 = 2 } tbe_io_dtype; /
 /* Describe the table set.  rows, D: HOST arrays of T entries.  Builds D_offsets / row_base / table
  * offsets on the current device.  One host thread at a time may make calls on a handle; calls on different
  * streams may overlap on the device as long as they do not share a workspace or write the same tables (all they
- * share in the handle is read-only metadata and the sticky invalid-id flag). */
+ * share in the handle is read-only metadata, the sticky invalid-id flag and the hot-row hint, which may be rewritten
+ * while it is read: see tbe_set_tunable). */
 tbe_status tbe_create(int32_t T, const int64_t* rows, const int32_t* D, tbe_dtype weight_dtype, tbe_handle** out);
 tbe_status tbe_destroy(tbe_handle* h);
 

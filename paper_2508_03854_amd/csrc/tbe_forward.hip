@@ -248,6 +248,8 @@ __global__ __launch_bounds__(kHotThreads, 8) void forward_hot_kernel(
     __shared__ raw_t s_rows[kHotRowBytes / 16];
     __shared__ uint32_t s_tab_id[kHotTab];
     __shared__ uint16_t s_tab_slot[kHotTab];
+    __shared__ uint32_t s_ids[kHotRows];
+    __shared__ uint32_t s_n;
     __shared__ uint32_t s_cold[kHotWaves][kWave];
     __shared__ uint16_t s_hot[kHotWaves][kWave];
     const int lane = lane_id();
@@ -266,15 +268,18 @@ __global__ __launch_bounds__(kHotThreads, 8) void forward_hot_kernel(
     const int64_t R = row_base[t + 1] - row_base[t];
     const WT* table = weights + w_off[t];
     const bool col_on = lc < D;
-    // ---- the table's hot rows: id table, then the rows themselves (one lane group per row)
-    int nh = (int)hot_n[t];
+    // ---- the table's hot rows: id table, then the rows themselves (one lane group per row).  The list's length and
+    // each listed id are read once, for both: a backward call over other tables of this shape may rewrite the list meanwhile,
+    // and an id table that named one row where another, or none, was copied would give wrong sums.
     const int cap = (kHotRowBytes / 16) >> lpr_log2;
-    nh = nh > kHotRows ? kHotRows : nh;
-    nh = nh > cap ? cap : nh;
+    if (threadIdx.x == 0) s_n = hot_n[t];
     for (int k = threadIdx.x; k < kHotTab; k += kHotThreads) s_tab_id[k] = kHotEmpty;
     __syncthreads();
+    int nh = s_n < (uint32_t)kHotRows ? (int)s_n : kHotRows;
+    nh = nh > cap ? cap : nh;
     if ((int)threadIdx.x < nh) {
         const uint32_t id = hot_ids[(size_t)t * kHotRows + threadIdx.x];
+        s_ids[threadIdx.x] = id;
         if ((int64_t)id < R) {
             uint32_t hsh = hot_hash(id);
             for (;;) {   // ends: the table is at most a quarter full
@@ -288,8 +293,9 @@ __global__ __launch_bounds__(kHotThreads, 8) void forward_hot_kernel(
             }
         }
     }
+    __syncthreads();
     for (int k = (int)(threadIdx.x >> lpr_log2); k < nh; k += kHotThreads >> lpr_log2) {
-        const uint32_t id = hot_ids[(size_t)t * kHotRows + k];
+        const uint32_t id = s_ids[k];
         s_rows[(k << lpr_log2) + li] = ((int64_t)id < R && col_on) ? RowIO<WT>::load_raw(table + (int64_t)id * D + lc)
                                                                      : RowIO<WT>::zero_raw();
     }

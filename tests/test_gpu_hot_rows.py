@@ -139,3 +139,42 @@ def test_hot_rows_do_not_change_results_beyond_summation_order(H):
         outs.append(a.cpu().numpy())
         tbe.close()
     H.assert_close(outs[0], outs[1], H.RTOL_F32, cfg.w_scale, "hot-row path against the plain path")
+
+
+def test_forward_while_a_backward_over_other_tables_rewrites_the_hint(H):
+    """One handle, two sets of tables: forwards over the first on one stream while backward calls over the second, on
+    another, list in turn the hot rows of two batches that share none.  The calls share the hint only, and it may change
+    nothing but the order of the additions."""
+    cfg = W.config("C4", T=4, B=1024, rows_scale=2e-3, c=1.0)
+    idx, off = W.make_batch(cfg, 0)
+    tables = [idx[int(off[t * cfg.B]): int(off[(t + 1) * cfg.B])] for t in range(cfg.T)]
+    half = [r // 2 for r in cfg.rows]
+    lo = torch.cat([x % n for x, n in zip(tables, half)]).cuda()
+    hi = torch.cat([x % n + n for x, n in zip(tables, half)]).cuda()
+    both = torch.where(torch.arange(lo.numel(), device="cuda") % 2 == 0, lo, hi)
+    d_off = off.cuda()
+    first = H.flat_from_tables(H.host_tables(cfg))
+    second = first.clone()
+    state = torch.zeros(cfg.total_rows, device="cuda")
+    grad = torch.randn(cfg.B, cfg.sum_D, device="cuda")
+    tbe = TBE(cfg.rows, cfg.D, cfg.weight_dtype)
+    tbe.set_tunable("hot_rows_min_workgroups", -1)
+    ref = tbe.forward(first, both, d_off, cfg.B, "sum").clone()
+    tbe.set_tunable("hot_rows_min_workgroups", 0)
+    assert tbe.debug_forward_kernels(cfg.B, both.numel()) & binding.FWD_HOT_ROWS
+    ws = tbe.alloc_workspace(cfg.B, both.numel())
+    side = torch.cuda.Stream()
+    side.wait_stream(torch.cuda.current_stream())
+    outs = [torch.empty_like(ref) for _ in range(80)]
+    torch.cuda.synchronize()
+    for i, out in enumerate(outs):
+        if i % 4 == 0:
+            with torch.cuda.stream(side):
+                tbe.backward_rowwise_adagrad(grad, lo if i % 8 == 0 else hi, d_off, cfg.B, second, state, ws,
+                                             pooling="sum", lr=cfg.lr, eps=cfg.eps)
+        tbe.forward(first, both, d_off, cfg.B, "sum", out=out)
+    torch.cuda.synchronize()
+    want = ref.cpu().numpy()
+    for out in outs:
+        H.assert_close(out.cpu().numpy(), want, H.RTOL_F32, cfg.w_scale, "forward next to a backward over other tables")
+    tbe.close()
