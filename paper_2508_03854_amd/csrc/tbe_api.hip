@@ -79,13 +79,16 @@ static int64_t most_parts(int64_t N) {
 // What the dense rows may make of a workspace.  A dense row leaves one partial sum per chunk of bags, so their area grows with
 // the columns of all tables whose gradient block is large, not with the lookups: a batch of few lookups per bag would pay
 // several times its other memory for it (32 tables of 128 columns, 16384 bags of one id: 20 + 58 MB).  So the layout with
-// dense rows takes at most 20 bytes per lookup (the five streams once more) over 20.5 bytes per lookup and n / 192 + 4096 +
-// 512 T partial sums of the widest row, and a batch that would fit the library's own scratch array by the latter does so with
-// dense rows as well; within that as many chunks as are useful.  Fewer chunks cost time only below about 512 workgroups
-// (measured: 64 tables, 4096 bags, 16 / 8 / 4 chunks 63 / 58 / 90 us; 12 tables, 8192 bags, 32 / 16 / 8 chunks 21 / 29 / 50 us).
+// dense rows takes at most 20 bytes per lookup (the five streams once more) and 16 MiB over 20.5 bytes per lookup and n / 192 +
+// 4096 + 512 T partial sums of the widest row, and a batch that would fit the library's own scratch array by the latter does
+// so with dense rows as well; within that as many chunks as are useful.  Fewer chunks cost time only below about 512 workgroups
+// (measured: 64 tables, 4096 bags, 16 / 8 / 4 chunks 63 / 58 / 90 us; 12 tables, 8192 bags, 32 / 16 / 8 chunks 21 / 29 / 50 us),
+// which is what small batches have: the 16 MiB, next to nothing of this memory, let 2 tables x 5399 bags x 256 columns (86 k
+// lookups) share their 22 blocks of bags out to 22 workgroups a table rather than 11, 33 -> 19 us, and 12 tables x 6478 bags
+// (909 k lookups) to 26 rather than 13, 35 -> 25 us.
 static size_t dense_allowance(const tbe_handle* h, size_t n) {
     const size_t lean = 41 * n / 2 + 4 * (n / 192 + 4096 + 512 * (size_t)h->T) * (size_t)h->maxD;
-    const size_t full = lean + 20 * n;
+    const size_t full = lean + 20 * n + ((size_t)16 << 20);
     return lean <= (size_t)TBE_STATIC_SCRATCH_BYTES ? std::min(full, (size_t)TBE_STATIC_SCRATCH_BYTES) : full;
 }
 
