@@ -5,18 +5,22 @@
 // a long row's partial sums), so weights and moments have a single writer and the result does not depend
 // on scheduling.  A row of D floats is covered by LPR = D/4 lanes (one float4 each), which leaves
 // G = 64/LPR lane groups per wavefront.  Rows are binned by the number of lookups that hit them:
-//   - short  (a run of <= G consecutive rows with <= 64 lookups in total): one row per lane group, the
-//     lookups' bag ids arrive with one coalesced load and are handed out with cross-lane reads;
+//   - short  (a run of <= G consecutive rows of one table with <= 64 lookups in total): one row per lane group, the
+//     lookups' bag ids arrive in windows of 64 with one coalesced load and are handed out with cross-lane reads;
 //   - medium (65 .. long_min lookups): the whole wavefront walks the row, groups interleaved;
 //   - long   (> long_min lookups): listed by tbe_lists.hip; the hottest of a large gradient block go through the matrix
 //     cores (tbe_dense.hip), the others are cut into parts that wavefronts of the kernels here reduce into partial sums.
-// Row metadata (segment bounds, key, table, moment) is fetched for up to 64 rows at a time, one row per lane.
+// Row metadata (segment bounds, key, table, moment) is fetched for up to 16 rows at a time, one row per lane.
 #include "tbe_rows.h"
 
 namespace tbe {
 
 constexpr int kSegThreads = 256;
-constexpr int kSegBlocks = 2048;  // persistent grids: waves stride over blocks of 64 unique rows, or over rows
+// Rows of one wavefront pass.  Measured at 64 / 32 / 16 / 8: 64 tables, 4096 bags of 31 ids, bfloat16 gradients 721 / 724 / 702 /
+// 722 us for the row updates; 12 tables x 8192 bags of 20 uniform ids, 128 fp32 columns 520 / 502 / 507 / 528; lognormal bags of
+// 32 tables 300 / 299 / 276 / 275 (64 rows a pass leave 2 to 4 passes per wavefront there, the last round half empty).
+constexpr uint32_t kPassRows = 16;
+constexpr int kSegBlocks = 2048;  // persistent grids: waves stride over passes of 16 unique rows, or over rows
 // Gradient fragments in flight per lane while a row is reduced: as many as the registers of the variant allow
 // without spilling at the WAVES wavefronts per SIMD its kernel is compiled for.  Measured at the largest workload with
 // 32-bit gradients: 2 / 4 / 6 / 8 in flight give 21.6 / 20.4 / 20.2 / 19.8 ms for the row updates; 8 needs more than
@@ -24,7 +28,7 @@ constexpr int kSegBlocks = 2048;  // persistent grids: waves stride over blocks 
 // the size.
 template <int NC, bool MEAN, typename GT, int WAVES>
 __device__ __host__ constexpr int seg_unroll() {
-    return NC > 1 ? 4 : (sizeof(GT) == 4 ? (WAVES < 8 ? (MEAN ? 6 : 8) : (MEAN ? 4 : 6)) : 8);
+    return NC > 1 ? 4 : (sizeof(GT) == 4 ? (WAVES < 8 ? (MEAN ? 6 : 8) : (MEAN ? 4 : 6)) : (MEAN ? 6 : 8));
 }
 
 
@@ -55,14 +59,15 @@ __device__ __forceinline__ float bag_scale(const OffsetWords offsets, uint32_t b
 // Where the upstream gradient of a lookup of table t lives: element base + (row - row0) * pitch (+ column).
 // Pooled: row = bag id, one [B, sum(D)] matrix.  Non-pooled: row = original position, one [n_t, D_t] block per table.
 struct GradAddr {
-    int64_t base, pitch, row0;
+    int64_t base;
+    uint32_t pitch, row0;   // (a 32-bit pitch: one 32 x 32 + 64 bit multiply-add per address instead of a 64-bit product)
 };
 __device__ __forceinline__ GradAddr grad_addr(const SegArgs& a, const int t, const int D) {
     GradAddr ga;
     if (a.seq) {
-        ga.base = a.seq_gbase[t]; ga.pitch = D; ga.row0 = 0;
+        ga.base = a.seq_gbase[t]; ga.pitch = (uint32_t)D; ga.row0 = 0u;
     } else {
-        ga.base = a.D_off[t]; ga.pitch = a.sumD; ga.row0 = (int64_t)t * a.B;
+        ga.base = a.D_off[t]; ga.pitch = (uint32_t)a.sumD; ga.row0 = (uint32_t)t * (uint32_t)a.B;
     }
     return ga;
 }
@@ -72,7 +77,7 @@ __device__ __forceinline__ GradAddr grad_addr(const SegArgs& a, const int t, con
 // fold_groups() completes the sum.  NC = 256-column chunks per row.
 template <int NC, bool MEAN, typename GT, int WAVES = 8>
 __device__ __forceinline__ void segment_reduce(float (&acc)[NC][4], const RowGeom& g, const GT* __restrict__ gcol,
-                                               const int64_t sumD, const int64_t bag0,
+                                               const uint32_t pitch, const uint32_t row0,
                                                const uint32_t* __restrict__ bag_sorted, const OffsetWords offsets,
                                                const uint32_t s, const uint32_t e) {
     constexpr int kSegUnroll = seg_unroll<NC, MEAN, GT, WAVES>();
@@ -83,7 +88,7 @@ __device__ __forceinline__ void segment_reduce(float (&acc)[NC][4], const RowGeo
         float my_s = 1.f;
         if (lane < n) {
             const uint32_t bag = bag_sorted[base + lane];
-            my_b = (uint32_t)((int64_t)bag - bag0);
+            my_b = bag - row0;
             my_s = bag_scale<MEAN>(offsets, bag);
         }
         for (int k0 = 0; k0 < n; k0 += kSegUnroll * g.G) {
@@ -98,7 +103,7 @@ __device__ __forceinline__ void segment_reduce(float (&acc)[NC][4], const RowGeo
 #pragma unroll
                 for (int c = 0; c < NC; ++c) {
                     const int col = g.lc + c * kWave * 4;
-                    x[u][c] = (on && col < g.D) ? GradIO<GT>::load(gcol + (int64_t)b * sumD + col) : GradIO<GT>::zero();
+                    x[u][c] = (on && col < g.D) ? GradIO<GT>::load(gcol + (uint64_t)b * pitch + col) : GradIO<GT>::zero();
                 }
             }
 #pragma unroll
@@ -148,10 +153,10 @@ __device__ __forceinline__ float adagrad_step(const float v_new, const float lr,
 //   v <- v + ||g||^2 ;  w <- w - lr / (sqrt(v / c) + eps) * g      (updated v; v stored unscaled)
 // Lanes with write == true store their 4 columns; the lane with lc == 0 among them stores the moment.
 // With sgd == true the step is plain SGD instead, w <- w - lr * g, and the moment is neither read nor written.
-template <typename WT, int NC>
-__device__ __forceinline__ void adagrad_row(const float (&acc)[NC][4], const RowGeom& g, WT* __restrict__ wrow,
-                                            float* __restrict__ vptr, const float v_old, const bool write,
-                                            const float lr, const float eps, const float inv_c, const bool sgd = false) {
+template <int NC>
+__device__ __forceinline__ float row_step(const float (&acc)[NC][4], const RowGeom& g, float* __restrict__ vptr,
+                                          const float v_old, const bool write, const float lr, const float eps,
+                                          const float inv_c, const bool sgd) {   // the moment; returns the step size
     float sq = 0.f;
 #pragma unroll
     for (int c = 0; c < NC; ++c) {
@@ -163,21 +168,104 @@ __device__ __forceinline__ void adagrad_row(const float (&acc)[NC][4], const Row
     }
     sq = group_sum(sq, g.LPR);  // within the LPR lanes that cover the row
     const float v_new = v_old + sq;
-    const float step = sgd ? lr : adagrad_step(v_new, lr, eps, inv_c);
-    if (write) {
+    if (write && g.lc == 0 && !sgd) *vptr = v_new;
+    return sgd ? lr : adagrad_step(v_new, lr, eps, inv_c);
+}
+template <typename WT, int NC>
+__device__ __forceinline__ void adagrad_row(const float (&acc)[NC][4], const RowGeom& g, WT* __restrict__ wrow,
+                                            float* __restrict__ vptr, const float v_old, const bool write,
+                                            const float lr, const float eps, const float inv_c, const bool sgd = false) {
+    const float step = row_step<NC>(acc, g, vptr, v_old, write, lr, eps, inv_c, sgd);
+    if (!write) return;
 #pragma unroll
-        for (int c = 0; c < NC; ++c) {
-            const int col = g.lc + c * kWave * 4;
-            if (col < g.D) {
-                float w[4];
-                RowIO<WT>::load4(wrow + col, w);
+    for (int c = 0; c < NC; ++c) {
+        const int col = g.lc + c * kWave * 4;
+        if (col < g.D) {
+            float w[4];
+            RowIO<WT>::load4(wrow + col, w);
 #pragma unroll
-                for (int v = 0; v < 4; ++v) w[v] = fmaf(-step, acc[c][v], w[v]);
-                RowIO<WT>::store4(wrow + col, w);
-            }
+            for (int v = 0; v < 4; ++v) w[v] = fmaf(-step, acc[c][v], w[v]);
+            RowIO<WT>::store4(wrow + col, w);
         }
-        if (g.lc == 0 && !sgd) *vptr = v_new;
     }
+}
+// ... of a row of at most 256 columns whose weights are in registers already
+template <typename WT>
+__device__ __forceinline__ void adagrad_row_loaded(const float (&acc)[1][4], const RowGeom& g, WT* __restrict__ wrow,
+                                                   const typename RowIO<WT>::raw4_t wraw, float* __restrict__ vptr,
+                                                   const float v_old, const bool write, const float lr, const float eps,
+                                                   const float inv_c, const bool sgd) {
+    const float step = row_step<1>(acc, g, vptr, v_old, write, lr, eps, inv_c, sgd);
+    if (write && g.lc < g.D) {
+        float w[4];
+        RowIO<WT>::unpack4(wraw, w);
+#pragma unroll
+        for (int v = 0; v < 4; ++v) w[v] = fmaf(-step, acc[0][v], w[v]);
+        RowIO<WT>::store4(wrow + g.lc, w);
+    }
+}
+
+// ---- short rows ---------------------------------------------------------------------------------------------------
+// Most rows of a batch have one or two lookups, and their bookkeeping is vector-ALU work: before the three things below the row
+// updates of 64 tables x 4096 bags of 31 ids (Zipf 1.1, bfloat16 gradients) issued 32183 vector instructions per wavefront in
+// 800 us, now 21746 in 702.  A round has as many slots as its longest row needs (1, 2, 4 or the variant's unroll, not always the
+// last); the bag ids of 64 lookups serve all the rounds they cover; a round's rows are of one table, so that its addresses start
+// from scalars and each costs one 32 x 32 + 64 bit multiply-add.  12 tables x 8192 bags of 20 uniform ids, 128 columns: 544 ->
+// 507 us.  The weights are loaded behind the gradients: ahead of them 507 -> 612 us there (the read and the write of a row then
+// lie further apart), 702 -> 727 us above.  Only the variant with the longest chain per row, 32-bit gradients of wide binary16
+// rows, gains by it (64 tables x 32768 bags of 31 ids: 4201 -> 4172 us; before all this 4188).
+//
+// NS lookups of short rows, of every lane group its own: number q0 .. q0+NS-1 of the group's glen, which lie in lanes off, off+1,
+// ... of (my_b, my_s).  UNIFORM: one group, so that all of this is the same in all lanes and stays on the scalar unit.
+template <int NS, bool UNIFORM, bool MEAN, typename GT>
+__device__ __forceinline__ void add_lookups(float (&acc)[1][4], const GT* __restrict__ gcol, const uint32_t pitch,
+                                            const uint32_t lane_col, const uint32_t my_b, const float my_s, const uint32_t off,
+                                            const uint32_t q0, const uint32_t glen) {
+    typename GradIO<GT>::raw_t x[NS];
+    float sc[NS];
+#pragma unroll
+    for (int u = 0; u < NS; ++u) {
+        const int src = (int)((off + q0 + (uint32_t)u) & (kWave - 1));
+        uint32_t b;
+        if (UNIFORM) {
+            b = bcast_lane(my_b, src);
+            sc[u] = MEAN ? bcast_lane(my_s, src) : 1.f;
+            const GT* row = gcol + (uint64_t)b * pitch;
+            x[u] = q0 + u < glen ? GradIO<GT>::load(row + lane_col) : GradIO<GT>::zero();
+        } else {
+            b = __shfl(my_b, src, kWave);
+            sc[u] = MEAN ? __shfl(my_s, src, kWave) : 1.f;
+            x[u] = q0 + u < glen ? GradIO<GT>::load(gcol + lane_col + (uint64_t)b * pitch) : GradIO<GT>::zero();
+        }
+    }
+#pragma unroll
+    for (int u = 0; u < NS; ++u) {
+        const float4 f = GradIO<GT>::to_float(x[u]);
+        if (MEAN) {
+            acc[0][0] = fmaf(sc[u], f.x, acc[0][0]);
+            acc[0][1] = fmaf(sc[u], f.y, acc[0][1]);
+            acc[0][2] = fmaf(sc[u], f.z, acc[0][2]);
+            acc[0][3] = fmaf(sc[u], f.w, acc[0][3]);
+        } else {
+            acc[0][0] += f.x;
+            acc[0][1] += f.y;
+            acc[0][2] += f.z;
+            acc[0][3] += f.w;
+        }
+    }
+}
+// all lookups of short rows, lmax of the longest: as many slots a round as are needed
+template <int NS, bool UNIFORM, bool MEAN, typename GT>
+__device__ __forceinline__ void add_short(float (&acc)[1][4], const GT* __restrict__ gcol, const uint32_t pitch,
+                                          const uint32_t lane_col, const uint32_t my_b, const float my_s, const uint32_t off,
+                                          const uint32_t lmax, const uint32_t glen) {
+    uint32_t q0 = 0;
+    for (; q0 + 4u < lmax; q0 += NS) add_lookups<NS, UNIFORM, MEAN, GT>(acc, gcol, pitch, lane_col, my_b, my_s, off, q0, glen);
+    if (q0 >= lmax) return;
+    const uint32_t left = lmax - q0;
+    if (left == 1u) add_lookups<1, UNIFORM, MEAN, GT>(acc, gcol, pitch, lane_col, my_b, my_s, off, q0, glen);
+    else if (left == 2u) add_lookups<2, UNIFORM, MEAN, GT>(acc, gcol, pitch, lane_col, my_b, my_s, off, q0, glen);
+    else add_lookups<4, UNIFORM, MEAN, GT>(acc, gcol, pitch, lane_col, my_b, my_s, off, q0, glen);
 }
 
 // ---- parts of long rows ----------------------------------------------------------------------------------------
@@ -238,30 +326,42 @@ static_assert(kHotRows <= kSegThreads, "one thread per listed row");
 template <typename WT, bool MEAN, typename GT, int kSegWaves>
 __global__ __launch_bounds__(kSegThreads, kSegWaves) void seg_update_kernel(const SegArgs a) {
     constexpr int kSegUnroll = seg_unroll<1, MEAN, GT, kSegWaves>();
+    constexpr bool kAhead = kSegWaves < 8;   // a row's weights are loaded ahead of its gradients (see the short rows above)
     const int lane = lane_id();
     copy_hint(a);
     if (a.counters[4] != 0u) return;
     reduce_parts<false, MEAN, GT, kSegWaves>(a);
     const uint32_t U = a.counters[0];
     const uint32_t nwaves = gridDim.x * (kSegThreads / kWave);
-    // rows per wavefront pass: 64 when there is plenty of work, fewer when the batch touches so few rows that
-    // whole wavefronts would otherwise go idle while others walk 64 rows one round after the other - down to as many as
+    // rows per wavefront pass: 16 when there is plenty of work, fewer when the batch touches so few rows that
+    // whole wavefronts would otherwise go idle while others walk 16 rows one round after the other - down to as many as
     // the widest table's rows a wavefront takes side by side
-    uint32_t rpw = kWave;
+    uint32_t rpw = kPassRows;
     while (rpw > (1u << a.min_rows_log2) && U / rpw < 2u * nwaves) rpw >>= 1;
     const uint32_t nblk = (U + rpw - 1) / rpw;
+    // Spans of consecutive passes go to the dies in turn, and a die's wavefronts take the passes of its spans in order: spans of
+    // one workgroup's passes, or long ones, so that a die reads the gradient blocks of a few tables only (die_spans).
+    const uint32_t per_wg = kSegThreads / kWave;
+    const uint32_t span = a.die_spans > 0 ? (nblk + kDies * (uint32_t)a.die_spans - 1u) / (kDies * (uint32_t)a.die_spans) : per_wg;
+    const uint32_t die = blockIdx.x & (kDies - 1u);
     WT* tables = static_cast<WT*>(a.tables);
-    for (uint32_t blk = blockIdx.x * (kSegThreads / kWave) + (threadIdx.x >> 6); blk < nblk; blk += nwaves) {
+    for (uint32_t i = (blockIdx.x / kDies) * per_wg + (threadIdx.x >> 6);; i += nwaves / kDies) {
+        const uint32_t first = (i / span * kDies + die) * span;   // of the span
+        if (first >= nblk) break;
+        const uint32_t blk = first + i % span;
+        if (blk >= nblk) continue;
+        const uint32_t u0 = blk * rpw;
         // ---- one row per lane: bounds, key, table, width, moment
-        const uint32_t u = (uint32_t)lane < rpw ? blk * rpw + lane : U;
+        const uint32_t last = U - u0 < rpw ? U - u0 : rpw;   // rows of the pass
+        const uint32_t u = u0 + lane;
         uint32_t s = 0, e = 0, key = 0;
-        if (u < U) {
+        if ((uint32_t)lane < last) {
             s = a.seg_start[u];
             e = a.seg_start[u + 1];
             key = a.keys_unique[u];
         }
         const uint32_t len = e - s;
-        bool live = (u < U) && len >= 1 && len <= a.long_min && key < a.total_rows;
+        bool live = (uint32_t)lane < last && len >= 1 && len <= a.long_min && key < a.total_rows;
         int t = 0, D = 4;
         float v = 0.f;
         if (live) {
@@ -274,8 +374,21 @@ __global__ __launch_bounds__(kSegThreads, kSegWaves) void seg_update_kernel(cons
                 v = a.state ? a.state[key] : 0.f;
             }
         }
+        // a window of 64 lookups of one table, lane's lookup win + lane: loaded once for all the short rows that lie in it
+        const uint32_t e_blk = bcast_lane(e, (int)last - 1);   // end of the block's lookups
+        uint32_t win = 0, my_b = 0;
+        int win_t = -1;
+        float my_s = 1.f;
+        auto load_window = [&](const uint32_t s0, const int t_w, const uint32_t row0) {
+            win = s0;
+            win_t = t_w;
+            const uint32_t at = s0 + (uint32_t)lane;
+            const uint32_t bag = a.bag_sorted[at < e_blk ? at : e_blk - 1u];
+            my_b = bag - row0;
+            my_s = bag_scale<MEAN>(a.offsets, bag);
+        };
         int r = 0;
-        while (r < (int)rpw) {
+        while (r < (int)last) {
             if (!bcast_lane((int)live, r)) {
                 ++r;
                 continue;
@@ -298,65 +411,35 @@ __global__ __launch_bounds__(kSegThreads, kSegWaves) void seg_update_kernel(cons
                 ++r;
                 continue;
             }
+            // ---- short rows: rows r .. r+k-1 share the table of row r and have at most 64 lookups in total
+            const int t_r = bcast_lane(t, r);
+            const GradAddr ga = grad_addr(a, t_r, g.D);
+            const GT* const gcol = static_cast<const GT*>(a.grad_out) + ga.base;
+            WT* const wtab = tables + a.w_off[t_r];
+            const uint32_t rb = (uint32_t)a.row_base[t_r];
+            const bool col_on = g.lc < g.D;
+            const uint32_t lane_col = col_on ? (uint32_t)g.lc : 0u;   // (what other lanes sum is not used)
             if (g.G == 1) {
-                // ---- a short row as wide as the wavefront (more than 128 columns): one row per round, so its
-                // bookkeeping is the same in all lanes and stays on the scalar unit (key, table, bag ids, addresses)
+                // a row as wide as the wavefront (more than 128 columns): one row per round, so its bookkeeping is the same in
+                // all lanes and stays on the scalar unit (key, bag ids, addresses)
                 const uint32_t key_r = bcast_lane(key, r);
-                const int t_r = bcast_lane(t, r);
                 const float v_r = bcast_lane(v, r);
-                uint32_t my_bag = 0;
-                float my_s = 1.f;
-                if ((uint32_t)lane < len_r) {
-                    my_bag = a.bag_sorted[s_r + lane];
-                    my_s = bag_scale<MEAN>(a.offsets, my_bag);
-                }
-                const bool col_on = g.lc < g.D;
-                const GradAddr ga = grad_addr(a, t_r, g.D);
-                const GT* gcol = static_cast<const GT*>(a.grad_out) + ga.base + g.lc;
+                if (win_t != t_r || s_r + len_r - win > (uint32_t)kWave) load_window(s_r, t_r, ga.row0);
+                WT* const wrow = wtab + (uint64_t)(key_r - rb) * (uint32_t)g.D;
+                typename RowIO<WT>::raw4_t wraw;
+                if constexpr (kAhead) wraw = RowIO<WT>::load4_raw(wrow + lane_col);
                 float acc[1][4] = {{0.f, 0.f, 0.f, 0.f}};
-                for (uint32_t q0 = 0; q0 < len_r; q0 += kSegUnroll) {
-                    typename GradIO<GT>::raw_t x[kSegUnroll];
-                    float sc[kSegUnroll];
-#pragma unroll
-                    for (int uu = 0; uu < kSegUnroll; ++uu) {
-                        const uint32_t qi = q0 + uu;                                  // < 64 wherever it is used
-                        const uint32_t bag = bcast_lane(my_bag, (int)(qi & (kWave - 1)));
-                        sc[uu] = MEAN ? bcast_lane(my_s, (int)(qi & (kWave - 1))) : 1.f;
-                        const bool on = qi < len_r && col_on;
-                        x[uu] = on ? GradIO<GT>::load(gcol + ((int64_t)bag - ga.row0) * ga.pitch) : GradIO<GT>::zero();
-                    }
-#pragma unroll
-                    for (int uu = 0; uu < kSegUnroll; ++uu) {
-                        const float4 f = GradIO<GT>::to_float(x[uu]);
-                        if (MEAN) {
-                            acc[0][0] = fmaf(sc[uu], f.x, acc[0][0]);
-                            acc[0][1] = fmaf(sc[uu], f.y, acc[0][1]);
-                            acc[0][2] = fmaf(sc[uu], f.z, acc[0][2]);
-                            acc[0][3] = fmaf(sc[uu], f.w, acc[0][3]);
-                        } else {
-                            acc[0][0] += f.x;
-                            acc[0][1] += f.y;
-                            acc[0][2] += f.z;
-                            acc[0][3] += f.w;
-                        }
-                    }
-                }
-                WT* wrow = tables + a.w_off[t_r] + ((int64_t)key_r - a.row_base[t_r]) * g.D;
-                adagrad_row<WT, 1>(acc, g, wrow, a.state + key_r, v_r, true, a.lr, a.eps, a.inv_c, a.state == nullptr);
+                add_short<kSegUnroll, true, MEAN, GT>(acc, gcol, ga.pitch, lane_col, my_b, my_s, s_r - win, len_r, len_r);
+                if constexpr (kAhead)
+                    adagrad_row_loaded<WT>(acc, g, wrow, wraw, a.state + key_r, v_r, true, a.lr, a.eps, a.inv_c, a.state == nullptr);
+                else adagrad_row<WT, 1>(acc, g, wrow, a.state + key_r, v_r, true, a.lr, a.eps, a.inv_c, a.state == nullptr);
                 ++r;
                 continue;
             }
-            // ---- short rows: rows r .. r+k-1 share the width of row r and have at most 64 lookups in total
-            const bool q = live && D == g.D && lane >= r && lane < r + g.G && (e - s_r) <= (uint32_t)kWave;
+            const bool q = live && t == t_r && lane >= r && lane < r + g.G && (e - s_r) <= (uint32_t)kWave;
             const uint64_t m = __ballot(q) >> r;                       // bit j: row r+j qualifies
             const int k = (~m == 0ull) ? kWave : (__ffsll((unsigned long long)(~m)) - 1);  // trailing ones, >= 1
-            const uint32_t tot = bcast_lane(e, r + k - 1) - s_r;   // lookups of the k rows, <= 64
-            uint32_t my_bag = 0;
-            float my_s = 1.f;
-            if ((uint32_t)lane < tot) {
-                my_bag = a.bag_sorted[s_r + lane];
-                my_s = bag_scale<MEAN>(a.offsets, my_bag);
-            }
+            if (win_t != t_r || bcast_lane(e, r + k - 1) - win > (uint32_t)kWave) load_window(s_r, t_r, ga.row0);
             // this lane group's row
             const bool gon = g.sub < k;
             const int gi = (r + g.sub) & (kWave - 1);
@@ -365,48 +448,11 @@ __global__ __launch_bounds__(kSegThreads, kSegWaves) void seg_update_kernel(cons
             const uint32_t glen_any = __shfl(len, gi, kWave);
             const uint32_t glen = gon ? glen_any : 0u;
             const uint32_t gkey = __shfl(key, gi, kWave);
-            const int gt = __shfl(t, gi, kWave);
             const float gv = __shfl(v, gi, kWave);
-            const int goff = (int)(gs - s_r);
-            const bool col_on = g.lc < g.D;
-            const GradAddr ga = grad_addr(a, gt, g.D);
-            const GT* gcol = static_cast<const GT*>(a.grad_out) + ga.base + g.lc;
-            const int64_t bag0 = ga.row0;
-            WT* wrow = tables + a.w_off[gt] + ((int64_t)gkey - a.row_base[gt]) * g.D;
-            uint32_t lmax = glen;  // longest row of the round (wave-uniform loop bound)
-            for (int o = g.LPR; o < kWave; o <<= 1) {
-                const uint32_t other = __shfl_xor(lmax, o, kWave);
-                lmax = other > lmax ? other : lmax;
-            }
+            WT* const wrow = wtab + (uint64_t)(gkey - rb) * (uint32_t)g.D;
+            const uint32_t lmax = (uint32_t)wave_max_i32((int)glen);   // longest row of the round (wave-uniform loop bound)
             float acc[1][4] = {{0.f, 0.f, 0.f, 0.f}};
-            for (uint32_t q0 = 0; q0 < lmax; q0 += kSegUnroll) {
-                typename GradIO<GT>::raw_t x[kSegUnroll];
-                float sc[kSegUnroll];
-#pragma unroll
-                for (int uu = 0; uu < kSegUnroll; ++uu) {
-                    const uint32_t qi = q0 + uu;
-                    const int src = (goff + (int)qi) & (kWave - 1);
-                    const uint32_t bag = __shfl(my_bag, src, kWave);
-                    sc[uu] = MEAN ? __shfl(my_s, src, kWave) : 1.f;
-                    const bool on = qi < glen && col_on;
-                    x[uu] = on ? GradIO<GT>::load(gcol + ((int64_t)bag - bag0) * ga.pitch) : GradIO<GT>::zero();
-                }
-#pragma unroll
-                for (int uu = 0; uu < kSegUnroll; ++uu) {
-                    const float4 f = GradIO<GT>::to_float(x[uu]);
-                    if (MEAN) {
-                        acc[0][0] = fmaf(sc[uu], f.x, acc[0][0]);
-                        acc[0][1] = fmaf(sc[uu], f.y, acc[0][1]);
-                        acc[0][2] = fmaf(sc[uu], f.z, acc[0][2]);
-                        acc[0][3] = fmaf(sc[uu], f.w, acc[0][3]);
-                    } else {
-                        acc[0][0] += f.x;
-                        acc[0][1] += f.y;
-                        acc[0][2] += f.z;
-                        acc[0][3] += f.w;
-                    }
-                }
-            }
+            add_short<kSegUnroll, false, MEAN, GT>(acc, gcol, ga.pitch, lane_col, my_b, my_s, gs - win, lmax, glen);
             adagrad_row<WT, 1>(acc, g, wrow, a.state + gkey, gv, gon, a.lr, a.eps, a.inv_c, a.state == nullptr);
             r += k;
         }
@@ -639,6 +685,7 @@ SegArgs seg_args(const tbe_handle* h, const Workspace& w, char* ws, const void* 
     a.hint_n = hint ? h->d_hot_n : nullptr;
     // side by side: 64 / (lanes per row) rows of the widest table up to 256 columns
     a.min_rows_log2 = h->maxD > 128 ? 0 : (h->maxD > 64 ? 1 : (h->maxD > 32 ? 2 : 3));
+    a.die_spans = 0;
     const bool dense = w.dense && !seq;
     a.dense_n = dense ? reinterpret_cast<uint32_t*>(ws + w.dense_n) : nullptr;
     a.dense_rows = reinterpret_cast<uint32_t*>(ws + w.dense_rows);
@@ -661,6 +708,15 @@ hipError_t launch_segment_update(const tbe_handle* h, const Workspace& w, char* 
     a.inv_c = 1.0f / c;
     a.tables = tables;
     a.state = state;
+    // The row updates gather a table's gradient block at random, and every die that works on the table reads it through its own
+    // L2.  Where the blocks are small enough to stay there next to the rows themselves (1.5 MiB of 4), a die takes two long spans
+    // of rows; from 16 tables on, so that the spans, equal in rows, are about equal in lookups too.  Row updates without / with
+    // it, us: 26 tables x 4096 bags x 64 fp32 columns (1 MiB) 83.5 / 71.6; 55 tables x 2306 bags x 149 columns binary16 188 /
+    // 162; 31 x 1699 x 224 fp32 (1.5 MB) 62 / 52; 57 x 1410 x 128 fp32 143 / 125; but 64 tables x 4096 bags x 224 bfloat16
+    // (1.8 MB) 702 / 706, 12 tables x 1548 x 224 binary16 39.1 / 41.5, and at 16384 x 149 fp32 (9.8 MB) 288 / 310.  One span
+    // per die gains as much and loses more where tables differ; four gain half.
+    const uint64_t block = (uint64_t)B * (uint64_t)h->sumD * (grad_io == 0 ? 4u : 2u);   // of all tables
+    if (!seq && h->T >= 16 && block <= (uint64_t)h->T * (3u << 19)) a.die_spans = 2;
     const bool mean = pooling == TBE_MEAN;
     if (a.dense_n) {
         LaunchTimer tm(h, s, "seg_dense_partial");

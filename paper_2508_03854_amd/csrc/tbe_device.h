@@ -231,6 +231,9 @@ struct RowIO<float> {
     }
     // 4-element fragment used by the optimizer step (one lane owns 4 columns)
     static __device__ __forceinline__ void load4(const float* p, float (&x)[4]) { load(p, x); }
+    using raw4_t = float4;   // ... as it sits in registers between the load and its use
+    static __device__ __forceinline__ raw4_t load4_raw(const float* p) { return load_raw(p); }
+    static __device__ __forceinline__ void unpack4(const raw4_t& r, float (&x)[4]) { x[0] = r.x; x[1] = r.y; x[2] = r.z; x[3] = r.w; }
     static __device__ __forceinline__ void store4(float* p, const float (&x)[4]) {
         *reinterpret_cast<float4*>(p) = make_float4(x[0], x[1], x[2], x[3]);
     }
@@ -262,8 +265,10 @@ struct RowIO<__half> {
             x[2 * i + 1] = __half2float(__ushort_as_half((unsigned short)(w[i] >> 16)));
         }
     }
-    static __device__ __forceinline__ void load4(const __half* p, float (&x)[4]) {
-        const uint2 raw = *reinterpret_cast<const uint2*>(p);
+    using raw4_t = uint2;
+    static __device__ __forceinline__ raw4_t load4_raw(const __half* p) { return *reinterpret_cast<const uint2*>(p); }
+    static __device__ __forceinline__ void load4(const __half* p, float (&x)[4]) { unpack4(load4_raw(p), x); }
+    static __device__ __forceinline__ void unpack4(const raw4_t& raw, float (&x)[4]) {
         x[0] = __half2float(__ushort_as_half((unsigned short)(raw.x & 0xFFFFu)));
         x[1] = __half2float(__ushort_as_half((unsigned short)(raw.x >> 16)));
         x[2] = __half2float(__ushort_as_half((unsigned short)(raw.y & 0xFFFFu)));

@@ -18,6 +18,9 @@ struct OffsetWords {
 
 constexpr uint32_t kDenseFlag = 0x80000000u;   // long_list entry: the dense-row kernel reduces the row
 
+// Dies of the chip, each with an L2 of its own; workgroup i of a launch runs on die i % kDies.
+constexpr uint32_t kDies = 8;
+
 struct SegArgs {
     const uint32_t* keys_unique;  // unique_rows
     const uint32_t* seg_start;
@@ -48,6 +51,7 @@ struct SegArgs {
     uint32_t* hot_n;              // [T]
     uint32_t* hint_ids;           // the handle's hint (null: not kept)
     uint32_t* hint_n;
+    int die_spans;                // seg_update: long spans of rows that each die takes; 0: the passes of a workgroup in turn
     int min_rows_log2;            // seg_update: a wavefront takes at least 2^this consecutive rows
     // dense rows (tbe_dense.hip); null dense_n: no table can have any
     uint32_t* dense_n;            // [T] number of dense rows
