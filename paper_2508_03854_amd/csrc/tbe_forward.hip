@@ -17,8 +17,10 @@ constexpr int kFwdThreads = 256;
 // more bags share a wavefront, the more lanes one long bag keeps waiting, so the bound falls with the lanes per row
 // (measured at lognormal bag lengths, 8 bags per wavefront: 2.28 ms without, 2.07 / 2.01 / 1.94 / 1.86 ms at 96 / 64 /
 // 48 / 32; a bound below the typical length would send ordinary bags the slower way).
-__device__ __host__ __forceinline__ int long_bag_min(const int lanes_per_row) {
-    return lanes_per_row > 16 ? 64 : (lanes_per_row > 8 ? 48 : 32);
+// `floor` raises the bound for batches whose ordinary bags are that long themselves (long_bag_floor).
+__device__ __forceinline__ int long_bag_min(const int lanes_per_row, const int floor) {
+    const int bound = lanes_per_row > 16 ? 64 : (lanes_per_row > 8 ? 48 : 32);
+    return bound > floor ? bound : floor;
 }
 
 // NC = number of 64-lane column chunks a row needs (1 when D <= 64 * kVec); U = rows in flight per group.
@@ -144,7 +146,7 @@ template <typename WT, int U, bool MEAN>
 __global__ __launch_bounds__(kFwdThreads, 8) void forward_groups_kernel(
     const WT* __restrict__ weights, const IdxView indices, const IdxView offsets,
     const int32_t* __restrict__ D_off, const int64_t* __restrict__ w_off, const int64_t* __restrict__ row_base,
-    const int32_t* __restrict__ tables_of_class, const int32_t n_tables, const int lpr_log2, const int32_t B,
+    const int32_t* __restrict__ tables_of_class, const int32_t n_tables, const int lpr_log2, const int long_floor, const int32_t B,
     const int64_t nnz, const int32_t sumD, void* __restrict__ out, const int out_io, int32_t* err) {
     constexpr int V = RowIO<WT>::kVec;
     using raw_t = typename RowIO<WT>::raw_t;
@@ -176,7 +178,7 @@ __global__ __launch_bounds__(kFwdThreads, 8) void forward_groups_kernel(
     const int full_len = (int)((end - start) < (int64_t)0x7FFFFFFF ? (end - start) : (int64_t)0x7FFFFFFF);
     // a bag far longer than its neighbours would keep the other groups of the wavefront waiting: such bags are left to
     // forward_long_bags_kernel, where a whole wavefront walks one bag
-    const bool is_long = full_len > long_bag_min(LPR);
+    const bool is_long = full_len > long_bag_min(LPR, long_floor);
     const int len = is_long ? 0 : full_len;
     const int maxlen = wave_max_i32(len);   // longest bag of the wavefront: the loop bounds below are wave-uniform
     float acc[V];
@@ -240,7 +242,7 @@ template <typename WT, int U, bool MEAN>
 __global__ __launch_bounds__(kHotThreads, 8) void forward_hot_kernel(
     const WT* __restrict__ weights, const IdxView indices, const IdxView offsets,
     const int32_t* __restrict__ D_off, const int64_t* __restrict__ w_off, const int64_t* __restrict__ row_base,
-    const int32_t* __restrict__ tables_of_class, const int32_t n_tables, const int lpr_log2, const int32_t B,
+    const int32_t* __restrict__ tables_of_class, const int32_t n_tables, const int lpr_log2, const int long_floor, const int32_t B,
     const int64_t nnz, const int32_t sumD, void* __restrict__ out, const int out_io, int32_t* err,
     const uint32_t* __restrict__ hot_ids, const uint32_t* __restrict__ hot_n, const int32_t chunks_per_table) {
     constexpr int V = RowIO<WT>::kVec;
@@ -318,7 +320,7 @@ __global__ __launch_bounds__(kHotThreads, 8) void forward_hot_kernel(
             end = end < start ? start : (end > nnz ? nnz : end);
         }
         const int full_len = (int)((end - start) < (int64_t)0x7FFFFFFF ? (end - start) : (int64_t)0x7FFFFFFF);
-        const bool is_long = full_len > long_bag_min(LPR);   // left to forward_long_bags_kernel
+        const bool is_long = full_len > long_bag_min(LPR, long_floor);   // left to forward_long_bags_kernel
         const int len = is_long ? 0 : full_len;
         const int maxlen = wave_max_i32(len);
         float acc[V];
@@ -391,20 +393,20 @@ __global__ __launch_bounds__(kHotThreads, 8) void forward_hot_kernel(
     }
 }
 
-// The long bags of the lane-group classes.  A wavefront looks at kLongScan x 64 consecutive bags of one table, 64 at
+// The long bags of the lane-group classes.  A wavefront looks at 2^scan_log2 consecutive bags of one table, at most 64 at
 // a time with one bag per lane, and walks every bag with more than long_bag_min ids with all of its lanes
 // (forward_bag, as for wide rows).  A kernel of its own: inside the lane-group kernel the second phase pushed the
 // binary16 variant over its 64 registers (8.0 -> 9.3 ms at the largest workload).
-constexpr int kLongScan = 4;
 template <typename WT, bool MEAN>
 __global__ __launch_bounds__(kFwdThreads, 4) void forward_long_bags_kernel(
     const WT* __restrict__ weights, const IdxView indices, const IdxView offsets,
     const int32_t* __restrict__ D_off, const int64_t* __restrict__ w_off, const int64_t* __restrict__ row_base,
-    const int32_t* __restrict__ tables_of_class, const int32_t n_tables, const int32_t B, const int64_t nnz,
-    const int32_t sumD, void* __restrict__ out, const int out_io, int32_t* err) {
+    const int32_t* __restrict__ tables_of_class, const int32_t n_tables, const int scan_log2, const int long_floor, const int32_t B,
+    const int64_t nnz, const int32_t sumD, void* __restrict__ out, const int out_io, int32_t* err) {
     constexpr int V = RowIO<WT>::kVec;
     const int lane = lane_id();
-    const int64_t per_table = ((int64_t)B + kLongScan * kWave - 1) / (kLongScan * kWave);   // wavefronts per table
+    const int64_t scan = (int64_t)1 << scan_log2;
+    const int64_t per_table = ((int64_t)B + scan - 1) >> scan_log2;   // wavefronts per table
     const int64_t wid = (int64_t)blockIdx.x * (kFwdThreads / kWave) + (threadIdx.x >> 6);
     const int64_t i = wid / per_table;
     if (i >= n_tables) return;
@@ -413,13 +415,13 @@ __global__ __launch_bounds__(kFwdThreads, 4) void forward_long_bags_kernel(
     const int D = D_off[t + 1] - d0;
     // the bound of the table's class: lanes per row as the host classifies them (power of two, at least 4)
     const int nl = (D + V - 1) / V;
-    const int bound = long_bag_min(nl > 16 ? 32 : (nl > 8 ? 16 : (nl > 4 ? 8 : 4)));
-    for (int q = 0; q < kLongScan; ++q) {
-        const int64_t b0 = ((wid - i * per_table) * kLongScan + q) * kWave;   // first bag of this round (wave-uniform)
-        if (b0 >= B) break;
+    const int bound = long_bag_min(nl > 16 ? 32 : (nl > 8 ? 16 : (nl > 4 ? 8 : 4)), long_floor);
+    const int64_t first = (wid - i * per_table) << scan_log2;
+    const int64_t last = first + scan < (int64_t)B ? first + scan : (int64_t)B;
+    for (int64_t b0 = first; b0 < last; b0 += kWave) {   // (wave-uniform)
         const int64_t b = b0 + lane;
         int64_t start = 0, end = 0;
-        if (b < B) {   // clamped as in the lane-group kernel
+        if (b < last) {   // clamped as in the lane-group kernel
             const int64_t bag = (int64_t)t * B + b;
             start = offsets[bag];
             end = offsets[bag + 1];
@@ -474,6 +476,25 @@ static int hot_chunks(const tbe_handle* h, const int c, const int32_t B) {
     const int cpt = (int)(((int64_t)B + bags_per_wg - 1) / bags_per_wg);
     return h->d_hot_ids && h->hot_min_workgroups >= 0 && (int64_t)h->fwd_count[c] * cpt >= h->hot_min_workgroups ? cpt : 0;
 }
+// Twice the batch's mean bag length, up to kLongFloorMax ids: a lane group walks an ordinary bag whatever its length, and only
+// bags far above their neighbours are left to whole wavefronts.  With the class bounds alone, us (before -> with this and the
+// shorter runs below): 17000 bags of 40 ids, 32 fp32 columns 443 -> 13.5; 26 tables x 4096 bags, 1 + Poisson(30) ids, 64 binary16
+// columns 282 -> 40; of 100 ids, 128 fp32 columns 2627 -> 309.
+constexpr int kLongFloorMax = 128;
+static int long_bag_floor(const tbe_handle* h, const int32_t B, const int64_t nnz) {
+    const int64_t twice = 2 * nnz / ((int64_t)h->T * B);
+    return (int)(twice < kLongFloorMax ? twice : kLongFloorMax);
+}
+// Bags that a wavefront of forward_long_bags_kernel looks at: 256 where that fills the chip, fewer (down to 4) in smaller
+// batches, where long bags would wait for one another in a few wavefronts.  Lognormal bags of 35 ids on average, us, 256 bags a
+// wavefront -> this: 26 tables x 4096 bags x 32 fp32 columns 324 -> 82, 16 tables x 32768 bags 470 -> 347; where no bag is long
+// the launch takes 4.4 us either way.
+constexpr int64_t kLongScanWaves = 4096;
+static int long_scan_log2(const int64_t bags) {
+    int l = 2;
+    while (l < 8 && (bags >> (l + 1)) >= kLongScanWaves) ++l;
+    return l;
+}
 unsigned forward_kernels(const tbe_handle* h, const int32_t B, const int64_t nnz) {
     unsigned m = h->fwd_count[5] + h->fwd_count[6] > 0 ? TBE_FWD_WAVEFRONT_PER_BAG : 0u;
     if (forward_small(h, B, nnz)) return h->fwd_first[5] > 0 ? m | TBE_FWD_WAVEFRONT_PER_BAG : m;
@@ -507,6 +528,7 @@ static void launch_forward_groups(const tbe_handle* h, const void* tables, const
                                   hipStream_t s) {
     const WT* w = static_cast<const WT*>(tables);
     const int wpb = kFwdThreads / kWave;
+    const int long_floor = long_bag_floor(h, B, nnz);
     for (int c = 1; c < 5; ++c) {
         const int n = h->fwd_count[c];
         if (n == 0) continue;
@@ -521,33 +543,34 @@ static void launch_forward_groups(const tbe_handle* h, const void* tables, const
             const dim3 hgrid((unsigned)((int64_t)n * cpt));
             if (mean)
                 forward_hot_kernel<WT, 8, true><<<hgrid, kHotThreads, 0, s>>>(
-                    w, indices, offsets, d_D_off, h->d_w_off, h->d_row_base, list, n, lpr_log2, B, nnz, h->sumD, out, out_io,
+                    w, indices, offsets, d_D_off, h->d_w_off, h->d_row_base, list, n, lpr_log2, long_floor, B, nnz, h->sumD, out, out_io,
                     h->d_err, h->d_hot_ids, h->d_hot_n, cpt);
             else
                 forward_hot_kernel<WT, 8, false><<<hgrid, kHotThreads, 0, s>>>(
-                    w, indices, offsets, d_D_off, h->d_w_off, h->d_row_base, list, n, lpr_log2, B, nnz, h->sumD, out, out_io,
+                    w, indices, offsets, d_D_off, h->d_w_off, h->d_row_base, list, n, lpr_log2, long_floor, B, nnz, h->sumD, out, out_io,
                     h->d_err, h->d_hot_ids, h->d_hot_n, cpt);
             continue;
         }
         if (mean)
             forward_groups_kernel<WT, 8, true><<<grid, kFwdThreads, 0, s>>>(
-                w, indices, offsets, d_D_off, h->d_w_off, h->d_row_base, list, n, lpr_log2, B, nnz, h->sumD, out, out_io, h->d_err);
+                w, indices, offsets, d_D_off, h->d_w_off, h->d_row_base, list, n, lpr_log2, long_floor, B, nnz, h->sumD, out, out_io, h->d_err);
         else
             forward_groups_kernel<WT, 8, false><<<grid, kFwdThreads, 0, s>>>(
-                w, indices, offsets, d_D_off, h->d_w_off, h->d_row_base, list, n, lpr_log2, B, nnz, h->sumD, out, out_io, h->d_err);
+                w, indices, offsets, d_D_off, h->d_w_off, h->d_row_base, list, n, lpr_log2, long_floor, B, nnz, h->sumD, out, out_io, h->d_err);
     }
     // the bags those launches left out (the four classes' tables follow one another in the list)
     const int n_all = h->fwd_count[1] + h->fwd_count[2] + h->fwd_count[3] + h->fwd_count[4];
     if (n_all > 0) {
-        const int64_t waves = (int64_t)n_all * (((int64_t)B + kLongScan * kWave - 1) / (kLongScan * kWave));
+        const int scan_log2 = long_scan_log2((int64_t)n_all * B);
+        const int64_t waves = (int64_t)n_all * (((int64_t)B + (1 << scan_log2) - 1) >> scan_log2);
         const dim3 grid((unsigned)((waves + wpb - 1) / wpb));
         const int32_t* list = h->d_fwd_tables + h->fwd_first[1];
         if (mean)
             forward_long_bags_kernel<WT, true><<<grid, kFwdThreads, 0, s>>>(
-                w, indices, offsets, d_D_off, h->d_w_off, h->d_row_base, list, n_all, B, nnz, h->sumD, out, out_io, h->d_err);
+                w, indices, offsets, d_D_off, h->d_w_off, h->d_row_base, list, n_all, scan_log2, long_floor, B, nnz, h->sumD, out, out_io, h->d_err);
         else
             forward_long_bags_kernel<WT, false><<<grid, kFwdThreads, 0, s>>>(
-                w, indices, offsets, d_D_off, h->d_w_off, h->d_row_base, list, n_all, B, nnz, h->sumD, out, out_io, h->d_err);
+                w, indices, offsets, d_D_off, h->d_w_off, h->d_row_base, list, n_all, scan_log2, long_floor, B, nnz, h->sumD, out, out_io, h->d_err);
     }
 }
 

@@ -1,0 +1,56 @@
+"""Long bags of the lane-group forward classes: the bound that follows the batch's mean bag length, and wavefronts that look at 4
+to 128 bags."""
+import pytest
+import torch
+
+pytestmark = pytest.mark.gpu
+
+
+@pytest.mark.parametrize("dtype", ["f32", "f16"])
+@pytest.mark.parametrize("T,B,mean", [
+    (5, 3500, 15),     # the class bounds hold (32 / 48 / 64), 4 bags per wavefront, tables that end inside one
+    (5, 3501, 36),     # a bound of 72 for every class
+    (1, 16390, 90),    # the highest bound (128)
+    (6, 11000, 3),     # 16 bags per wavefront
+    (5, 105000, 2),    # 128 bags per wavefront: two rounds of 64
+])
+def test_bags_on_both_sides_of_the_bound(dtype, T, B, mean):
+    if not torch.cuda.is_available():
+        pytest.skip("no GPU")
+    from paper_2508_03854_amd import TBE, binding
+    v = 8 if dtype == "f16" else 4
+    D = [v * w for w in (1, 8, 13, 32, 3, 16)][:T]        # 1 to 32 lanes per row
+    R = 400
+    g = torch.Generator().manual_seed(B)
+    lens = torch.randint(0, 2 * mean + 1, (T * B,), generator=g)
+    twice = 2 * int(lens.sum()) // (T * B)
+    special = [0, 1] + [b + d for b in (32, 48, 64, 128, twice) for d in (-1, 0, 1)] + [300]
+    for t in range(T):   # the first and last bags of every table, and some in between
+        at = torch.cat([torch.arange(40), torch.arange(B - 40, B), torch.randperm(B - 80, generator=g)[:40] + 40]) + t * B
+        lens[at] = torch.tensor(special * 8)[torch.randperm(120, generator=g)].clamp(min=0)
+    off = torch.zeros(T * B + 1, dtype=torch.int64)
+    off[1:] = torch.cumsum(lens, 0)
+    idx = torch.randint(0, R, (int(off[-1]),), generator=g)
+    tbe = TBE([R] * T, D, dtype)
+    tbe.set_tunable("hot_rows_min_workgroups", -1)
+    assert tbe.debug_forward_kernels(B, idx.numel()) == binding.FWD_LANE_GROUPS | binding.FWD_LONG_BAGS
+    tabs = torch.empty(tbe.total_elems).uniform_(-0.01, 0.01, generator=g).to(tbe.torch_dtype).cuda()
+    args = (idx.cuda(), off.cuda(), B, "sum")
+    out = tbe.forward(tabs, *args)
+    d0 = w0 = 0
+    for t, d in enumerate(D):
+        o = off[t * B:(t + 1) * B + 1]
+        bag = torch.repeat_interleave(torch.arange(B), o[1:] - o[:-1])
+        want = torch.zeros(B, d, dtype=torch.float64)
+        want.index_add_(0, bag, tabs[w0:w0 + R * d].cpu().view(R, d).double()[idx[int(o[0]):int(o[-1])]])
+        # a 32-bit sum of L values of at most 0.01: at most (L - 1) * 2^-24 * L * 0.01
+        L = (o[1:] - o[:-1]).double()[:, None]
+        assert ((out[:, d0:d0 + d].cpu().double() - want).abs() <= 2.0 ** -24 * 0.01 * L * L).all(), (t, d)
+        d0 += d
+        w0 += R * d
+    # the kernel with hot rows, none listed yet, makes the same additions in the same order
+    tbe.set_tunable("hot_rows_min_workgroups", 1)
+    assert tbe.debug_forward_kernels(B, idx.numel()) == binding.FWD_HOT_ROWS | binding.FWD_LONG_BAGS
+    assert torch.equal(tbe.forward(tabs, *args), out)
+    assert not tbe.poll_index_error()
+    tbe.close()
