@@ -470,11 +470,24 @@ static bool forward_small(const tbe_handle* h, const int32_t B, const int64_t nn
 static bool forward_small_long(const tbe_handle* h, const int32_t B, const int64_t nnz) {
     return h->fwd_count[2] + h->fwd_count[3] + h->fwd_count[4] == 0 && nnz >= (int64_t)24 * h->T * B;
 }
+// Workgroups from which the lane-group classes 1 (32 lanes per row) and 2 (16) keep hot rows in LDS where no tunable says so:
+// 512 of its large workgroups run at a time, so a launch needs some rounds of them before LDS hits outweigh the last, part-filled
+// one and the copying of the rows.  Plain lane groups against hot rows, us (Zipf 1.2, the list filled by a backward call):
+//   128 fp32 columns, 1 + Poisson(30) ids   416 workgroups 92 101   640 132 137   768 189 173   1664 361 296
+//   256 binary16 columns, the same          416 121 126             640 173 174   768 229 198   1664 442 377
+//   64 fp32 columns, the same               384 94 108              832 200 199
+//   64 fp32 columns, 1 + Poisson(10) ids    384 44 53               832 100 99    3840 488 388
+//   128 binary16 columns, the same          384 52 69               832 147 146   3840 640 520
+// Rows of at most 8 lanes gain nothing at any size (1 + Poisson(10) ids): 32 fp32 columns 416 workgroups 51 69, 1920 278 275; 64
+// binary16 columns 416 58 94, 1920 359 359.
+constexpr int64_t kHotWorkgroups[2] = {768, 1024};
 // workgroups per table with which the lane-group class c keeps hot rows in LDS; 0: it does not
 static int hot_chunks(const tbe_handle* h, const int c, const int32_t B) {
+    if (!h->d_hot_ids || h->hot_min_workgroups < 0) return 0;
+    if (!h->hot_min_set && c > 2) return 0;
     const int64_t bags_per_wg = (int64_t)kHotPasses * kHotWaves * (kWave >> (6 - c));
     const int cpt = (int)(((int64_t)B + bags_per_wg - 1) / bags_per_wg);
-    return h->d_hot_ids && h->hot_min_workgroups >= 0 && (int64_t)h->fwd_count[c] * cpt >= h->hot_min_workgroups ? cpt : 0;
+    return (int64_t)h->fwd_count[c] * cpt >= (h->hot_min_set ? h->hot_min_workgroups : kHotWorkgroups[c - 1]) ? cpt : 0;
 }
 // Twice the batch's mean bag length, up to kLongFloorMax ids: a lane group walks an ordinary bag whatever its length, and only
 // bags far above their neighbours are left to whole wavefronts.  With the class bounds alone, us (before -> with this and the
