@@ -715,8 +715,11 @@ hipError_t launch_segment_update(const tbe_handle* h, const Workspace& w, char* 
     // 162; 31 x 1699 x 224 fp32 (1.5 MB) 62 / 52; 57 x 1410 x 128 fp32 143 / 125; but 64 tables x 4096 bags x 224 bfloat16
     // (1.8 MB) 702 / 706, 12 tables x 1548 x 224 binary16 39.1 / 41.5, and at 16384 x 149 fp32 (9.8 MB) 288 / 310.  One span
     // per die gains as much and loses more where tables differ; four gain half.
+    // Tables of very different width leave the dies with unequal work (16 tables x 650 bags, 8 to 520 columns, 26.0 / 31.9), so the
+    // widest may have twice the mean width.
     const uint64_t block = (uint64_t)B * (uint64_t)h->sumD * (grad_io == 0 ? 4u : 2u);   // of all tables
-    if (!seq && h->T >= 16 && block <= (uint64_t)h->T * (3u << 19)) a.die_spans = 2;
+    const bool level = (int64_t)h->maxD * h->T <= 2 * (int64_t)h->sumD;
+    if (!seq && h->T >= 16 && level && block <= (uint64_t)h->T * (3u << 19)) a.die_spans = 2;
     const bool mean = pooling == TBE_MEAN;
     if (a.dense_n) {
         LaunchTimer tm(h, s, "seg_dense_partial");
