@@ -476,7 +476,7 @@ __global__ __launch_bounds__(kSegThreads, 4) void seg_update_wide_kernel(const S
         if (e - s > a.long_min) continue;   // long rows are reduced part by part
         const int t = table_of_row(a, s, key);
         const int d0 = a.D_off[t];
-        if (a.D_off[t + 1] - d0 <= 256) continue;   // done by the 64-rows-per-wavefront kernel
+        if (a.D_off[t + 1] - d0 <= 256) continue;   // done by seg_update_kernel
         const RowGeom g = row_geom(a.D_off[t + 1] - d0);
         WT* wrow = tables + a.w_off[t] + ((int64_t)key - a.row_base[t]) * g.D;
         float acc[4][4];
