@@ -25,10 +25,11 @@ constexpr int kSegBlocks = 2048;  // persistent grids: waves stride over passes 
 // without spilling at the WAVES wavefronts per SIMD its kernel is compiled for.  Measured at the largest workload with
 // 32-bit gradients: 2 / 4 / 6 / 8 in flight give 21.6 / 20.4 / 20.2 / 19.8 ms for the row updates; 8 needs more than
 // the 64 registers of 8 wavefronts per SIMD, which is why seg_update runs 7 (6: 20.7 ms); 16-bit fragments are half
-// the size.
+// the size: 8 in flight with mean pooling too, row updates with 6 / 8, us: 32 tables x 8192 bags of 21 ids, 128 and 256 binary16
+// columns, bfloat16 gradients 518 / 505; 26 tables x 8192 bags, 64 binary16 columns, binary16 gradients 219 / 214.
 template <int NC, bool MEAN, typename GT, int WAVES>
 __device__ __host__ constexpr int seg_unroll() {
-    return NC > 1 ? 4 : (sizeof(GT) == 4 ? (WAVES < 8 ? (MEAN ? 6 : 8) : (MEAN ? 4 : 6)) : (MEAN ? 6 : 8));
+    return NC > 1 ? 4 : (sizeof(GT) == 4 ? (WAVES < 8 ? (MEAN ? 6 : 8) : (MEAN ? 4 : 6)) : 8);
 }
 
 
