@@ -21,6 +21,9 @@ constexpr int kSegThreads = 256;
 // 32 tables 300 / 299 / 276 / 275 (64 rows a pass leave 2 to 4 passes per wavefront there, the last round half empty).
 constexpr uint32_t kPassRows = 16;
 constexpr int kSegBlocks = 2048;  // persistent grids: waves stride over passes of 16 unique rows, or over rows
+constexpr int kSegBlocks7 = 1792;   // ... of the variants of 7 wavefronts per SIMD
+// Long spans count a die's wavefronts as an eighth of the grid: a pass would be left out or taken twice otherwise.
+static_assert(kSegBlocks % kDies == 0 && kSegBlocks7 % kDies == 0, "as many workgroups on every die");
 // Gradient fragments in flight per lane while a row is reduced: as many as the registers of the variant allow
 // without spilling at the WAVES wavefronts per SIMD its kernel is compiled for.  Measured at the largest workload with
 // 32-bit gradients: 2 / 4 / 6 / 8 in flight give 21.6 / 20.4 / 20.2 / 19.8 ms for the row updates; 8 needs more than
@@ -340,20 +343,29 @@ __global__ __launch_bounds__(kSegThreads, kSegWaves) void seg_update_kernel(cons
     uint32_t rpw = kPassRows;
     while (rpw > (1u << a.min_rows_log2) && U / rpw < 2u * nwaves) rpw >>= 1;
     const uint32_t nblk = (U + rpw - 1) / rpw;
-    // Spans of consecutive passes go to the dies in turn, and a die's wavefronts take the passes of its spans in order: spans of
-    // one workgroup's passes, or long ones, so that a die reads the gradient blocks of a few tables only (die_spans).
-    const uint32_t per_wg = kSegThreads / kWave;
-    const uint32_t span = a.die_spans > 0 ? (nblk + kDies * (uint32_t)a.die_spans - 1u) / (kDies * (uint32_t)a.die_spans) : per_wg;
-    const uint32_t die = blockIdx.x & (kDies - 1u);
+    // The wavefronts of the chip take the passes in turn.  With long spans those of a die take the passes of its two spans in turn
+    // instead, so that a die reads the gradient blocks of a few tables only: pass first + i of the first span, i < n1, then again + i
+    // of the second.  All of it is the same for the whole wavefront and stays on the scalar unit; with two divisions by the length of
+    // a span in every pass, and more scalar registers spilled than now, small batches paid 0.5 to 2 us (34 tables x 40 bags x 32
+    // columns 14.0 us, now 12.1; one table x 512 bags x 64 columns 8.8, now 8.1).
+    const uint32_t wave = (uint32_t)__builtin_amdgcn_readfirstlane((int)(threadIdx.x >> 6));
+    uint32_t i = blockIdx.x * (kSegThreads / kWave) + wave, step = nwaves, n1 = nblk, n = nblk, first = 0, again = 0;
+    if (a.long_spans) {
+        const uint32_t die = blockIdx.x & (kDies - 1u), span = (nblk + 2u * kDies - 1u) / (2u * kDies);
+        const uint32_t b0 = umin(die * span, nblk), b1 = umin(b0 + span, nblk);
+        const uint32_t b2 = umin((die + kDies) * span, nblk), b3 = umin(b2 + span, nblk);
+        i = (blockIdx.x / kDies) * (kSegThreads / kWave) + wave;
+        step = nwaves / kDies;
+        n1 = b1 - b0;
+        n = n1 + (b3 - b2);
+        first = b0;
+        again = b2 - n1;
+    }
     WT* tables = static_cast<WT*>(a.tables);
-    for (uint32_t i = (blockIdx.x / kDies) * per_wg + (threadIdx.x >> 6);; i += nwaves / kDies) {
-        const uint32_t first = (i / span * kDies + die) * span;   // of the span
-        if (first >= nblk) break;
-        const uint32_t blk = first + i % span;
-        if (blk >= nblk) continue;
-        const uint32_t u0 = blk * rpw;
+    for (; i < n; i += step) {
+        const uint32_t u0 = (i + (i < n1 ? first : again)) * rpw;
         // ---- one row per lane: bounds, key, table, width, moment
-        const uint32_t last = U - u0 < rpw ? U - u0 : rpw;   // rows of the pass
+        const uint32_t last = umin(U - u0, rpw);   // rows of the pass
         const uint32_t u = u0 + lane;
         uint32_t s = 0, e = 0, key = 0;
         if ((uint32_t)lane < last) {
@@ -615,11 +627,11 @@ static void launch_row_updates(const tbe_handle* h, const SegArgs& a, bool mean,
         // are as wide as the wavefront (measured: 20.2 -> 19.8 ms there, but 2.43 -> 2.55 ms on fp32 tables of the
         // same widths, which therefore keep 8)
         if (sizeof(GT) == 4 && !f32 && h->seg_mostly_wavefront_rows) {
-            const unsigned grid = 256u * 7u;
+            const unsigned grid = kSegBlocks7;
             if (mean) seg_update_kernel<__half, true, GT, 7><<<grid, kSegThreads, 0, s>>>(a);
             else seg_update_kernel<__half, false, GT, 7><<<grid, kSegThreads, 0, s>>>(a);
         } else {
-            const unsigned grid = 256u * 8u;
+            const unsigned grid = kSegBlocks;
             if (f32) {
                 if (mean) seg_update_kernel<float, true, GT, 8><<<grid, kSegThreads, 0, s>>>(a);
                 else seg_update_kernel<float, false, GT, 8><<<grid, kSegThreads, 0, s>>>(a);
@@ -686,7 +698,7 @@ SegArgs seg_args(const tbe_handle* h, const Workspace& w, char* ws, const void* 
     a.hint_n = hint ? h->d_hot_n : nullptr;
     // side by side: 64 / (lanes per row) rows of the widest table up to 256 columns
     a.min_rows_log2 = h->maxD > 128 ? 0 : (h->maxD > 64 ? 1 : (h->maxD > 32 ? 2 : 3));
-    a.die_spans = 0;
+    a.long_spans = 0;
     const bool dense = w.dense && !seq;
     a.dense_n = dense ? reinterpret_cast<uint32_t*>(ws + w.dense_n) : nullptr;
     a.dense_rows = reinterpret_cast<uint32_t*>(ws + w.dense_rows);
@@ -720,7 +732,7 @@ hipError_t launch_segment_update(const tbe_handle* h, const Workspace& w, char* 
     // widest may have twice the mean width.
     const uint64_t block = (uint64_t)B * (uint64_t)h->sumD * (grad_io == 0 ? 4u : 2u);   // of all tables
     const bool level = (int64_t)h->maxD * h->T <= 2 * (int64_t)h->sumD;
-    if (!seq && h->T >= 16 && level && block <= (uint64_t)h->T * (3u << 19)) a.die_spans = 2;
+    if (!seq && h->T >= 16 && level && block <= (uint64_t)h->T * (3u << 19)) a.long_spans = 1;
     const bool mean = pooling == TBE_MEAN;
     if (a.dense_n) {
         LaunchTimer tm(h, s, "seg_dense_partial");

@@ -14,6 +14,8 @@ __device__ __forceinline__ int lane_id() {
 
 __device__ __forceinline__ uint64_t lanemask_lt() { return (1ull << lane_id()) - 1ull; }
 
+__device__ __forceinline__ uint32_t umin(const uint32_t x, const uint32_t y) { return x < y ? x : y; }
+
 // smallest power of two >= x, for 1 <= x <= 64
 __device__ __forceinline__ int pow2ceil64(int x) {
     int p = 1;

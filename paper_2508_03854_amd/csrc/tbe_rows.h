@@ -51,7 +51,7 @@ struct SegArgs {
     uint32_t* hot_n;              // [T]
     uint32_t* hint_ids;           // the handle's hint (null: not kept)
     uint32_t* hint_n;
-    int die_spans;                // seg_update: long spans of rows that each die takes; 0: the passes of a workgroup in turn
+    int long_spans;               // seg_update: 1: each die takes two long spans of rows; 0: the whole chip takes all passes in turn
     int min_rows_log2;            // seg_update: a wavefront takes at least 2^this consecutive rows
     // dense rows (tbe_dense.hip); null dense_n: no table can have any
     uint32_t* dense_n;            // [T] number of dense rows

@@ -1,7 +1,9 @@
 """Row updates at the borders of their short-row rounds: rows of 1 to 9 lookups and around 64 next to each other, so that a
 round's slots, the windows of 64 lookups and the whole-wavefront path all start and end between and inside them; one row per
 wavefront and several, tables that end inside a pass, and 16 tables or more, whose rows the dies take in long spans - against the
-oracle, with the harness's tolerances."""
+oracle, with the harness's tolerances.  A wavefront takes a pass of as few rows as fill the chip, 1 to 8 in the small batches of
+the first test; passes of 16 rows, in which rounds share a window, and wavefronts of several passes need the many rows of the
+second."""
 import numpy as np
 import pytest
 import torch
@@ -18,11 +20,48 @@ COUNTS = [1, 1, 2, 3, 4, 5, 1, 6, 7, 8, 9, 1, 1, 1, 30, 33, 1, 62, 2, 63, 64, 65
     (1, 3000, [200], "f16", "mean", "f32"),           # ... lanes without a column
     (2, 1500, [136, 256], "f32", "mean", "bf16"),
     (3, 1111, [128, 20, 64], "f32", "sum", "f32"),
-    (16, 203, [64, 8, 256], "f16", "sum", "bf16"),    # long spans
+    (16, 203, [64, 8, 256], "f16", "sum", "bf16"),    # tables of too different widths for long spans
+    (18, 180, [64, 40, 128], "f32", "sum", "f32"),    # long spans
     (23, 97, [32, 128, 4], "f32", "mean", "f16"),
     (40, 13, [16, 136], "f16", "mean", "f16"),        # fewer rows than a pass takes
 ])
 def test_rows_of_few_lookups(T, rows, widths, dtype, pooling, io):
+    rep = _step(T, rows, widths, dtype, pooling, io, COUNTS)
+    assert rep["max_seg"] >= 64 or rows < 26
+
+
+# as many rows of 1 to 3 lookups as leave COUNTS a sixth of the rows
+FEW = [1, 1, 2, 1, 3] * 26 + COUNTS
+
+
+def _rows_per_pass(U, max_d, wavefronts):
+    """The rows of one pass of seg_update_kernel: 16, halved while wavefronts would have less than two passes, down to the rows of
+    the widest table that lie side by side in a wavefront."""
+    least = 1 if max_d > 128 else 2 if max_d > 64 else 4 if max_d > 32 else 8
+    rows = 16
+    while rows > least and U // rows < 2 * wavefronts:
+        rows //= 2
+    return rows
+
+
+@pytest.mark.parametrize("T,rows,widths,dtype,pooling,io,per_pass,spans", [
+    (1, 245000, [256], "f16", "sum", "f32", 16, False),          # 7 wavefronts per SIMD: the weights ahead of the gradients
+    (1, 245000, [200], "f16", "mean", "f32", 16, False),         # ... mean pooling, lanes without a column
+    (2, 133000, [256, 136], "f16", "mean", "bf16", 16, False),   # 8 wavefronts per SIMD, one row per round
+    (2, 133000, [128, 64], "f32", "mean", "f32", 16, False),     # 2 and 4 rows per round
+    (3, 88000, [20, 8, 4], "f32", "sum", "f16", 16, False),      # 8, 32 and 64
+    (17, 15700, [64, 64, 104], "f16", "sum", "bf16", 16, True),  # long spans that end inside tables
+    (16, 8500, [136, 256], "f32", "mean", "f32", 8, True),       # ... of passes of 8 rows
+])
+def test_passes_of_many_rows(T, rows, widths, dtype, pooling, io, per_pass, spans):
+    D = [widths[t % len(widths)] for t in range(T)]
+    seven = dtype == "f16" and io == "f32" and 2 * sum(r for r, d in zip([rows] * T, D) if d > 128) > rows * T
+    rep = _step(T, rows, widths, dtype, pooling, io, FEW)
+    assert _rows_per_pass(rep["U"], max(D), 7168 if seven else 8192) == per_pass
+    assert spans == (T >= 16 and max(D) * T <= 2 * sum(D) and 700 * sum(D) * (4 if io == "f32" else 2) <= T * (3 << 19))
+
+
+def _step(T, rows, widths, dtype, pooling, io, counts):
     if not torch.cuda.is_available():
         pytest.skip("no GPU")
     import gpu_harness as H
@@ -34,7 +73,7 @@ def test_rows_of_few_lookups(T, rows, widths, dtype, pooling, io):
     cfg.c, cfg.lr, cfg.eps = 2.0, 0.01, 1e-8
     ids, lens = [], []
     for R in cfg.rows:
-        of_table = np.repeat(np.arange(R), np.resize(np.roll(COUNTS, int(rng.integers(len(COUNTS)))), R))
+        of_table = np.repeat(np.arange(R), np.resize(np.roll(counts, int(rng.integers(len(counts)))), R))
         ids.append(rng.permutation(of_table))
         cuts = np.sort(rng.integers(0, len(of_table) + 1, size=B - 1))
         lens.append(np.diff(np.concatenate(([0], cuts, [len(of_table)]))))
@@ -49,5 +88,5 @@ def test_rows_of_few_lookups(T, rows, widths, dtype, pooling, io):
     ws = tbe.alloc_workspace(B, idx.numel())
     gout = torch.randn(B, cfg.sum_D, generator=torch.Generator().manual_seed(T))
     rep = H.check_step(cfg, tbe, flat, state, tabs, st, idx, off, gout, ws, io=io)
-    assert rep["max_seg"] >= 64 or rows < 26
     tbe.close()
+    return rep
