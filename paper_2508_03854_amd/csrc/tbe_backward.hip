@@ -10,17 +10,27 @@
 //   - medium (65 .. long_min lookups): the whole wavefront walks the row, groups interleaved;
 //   - long   (> long_min lookups): listed by tbe_lists.hip; the hottest of a large gradient block go through the matrix
 //     cores (tbe_dense.hip), the others are cut into parts that wavefronts of the kernels here reduce into partial sums.
-// Row metadata (segment bounds, key, table, moment) is fetched for up to 16 rows at a time, one row per lane.
+// Row metadata (segment bounds, key, table, moment) is fetched for up to 64 rows at a time, one row per lane.
 #include "tbe_rows.h"
 
 namespace tbe {
 
 constexpr int kSegThreads = 256;
-// Rows of one wavefront pass.  Measured at 64 / 32 / 16 / 8: 64 tables, 4096 bags of 31 ids, bfloat16 gradients 721 / 724 / 702 /
-// 722 us for the row updates; 12 tables x 8192 bags of 20 uniform ids, 128 fp32 columns 520 / 502 / 507 / 528; lognormal bags of
-// 32 tables 300 / 299 / 276 / 275 (64 rows a pass leave 2 to 4 passes per wavefront there, the last round half empty).
-constexpr uint32_t kPassRows = 16;
-constexpr int kSegBlocks = 2048;  // persistent grids: waves stride over passes of 16 unique rows, or over rows
+// Rows of one wavefront pass: 16 in batches of many rows, 32 from so many rows per wavefront on that the last round of passes does
+// not count.  Every pass starts with a chain of four dependent loads (bounds, first bag, table, moment) and one for its bag ids, which
+// longer passes do less often; shorter ones share out rows of unequal length better, and rows of many lookups lie together, in the
+// small tables of a handle.  Row updates with passes of 16 / 32 / 64 rows, ms: 256 tables x 32768 bags of 31 ids, 256 binary16 columns
+// (4500 rows per wavefront) 20.5 / 19.8 / 19.7; 64 such tables x 65536 bags (1400) 8.64 / 8.70 / 8.72, with mean pooling 9.36 / 9.39 /
+// 9.46, of half the bags (600) 2.47 / 2.58 / 2.62; 26 tables of 1000 to 1 M rows x 32768 bags, uniform, 128 columns (260) 1.25 / 1.54 /
+// 2.34.  Tables of at most 8 columns have 32 or 64 rows side by side, and a pass of 16 leaves lanes idle: 8 tables of 1 M rows x
+// 16384 bags of 20 uniform ids, 4 / 8 columns (270) 73 / 107 us with 16, 66 / 92 with 32; the 26 tables x 16384 bags at 4 columns
+// (180) 216 with 16, 240 with 32, 424 with 64.
+// Where registers allow (8 wavefronts per SIMD), the loads at the start serve as many of a wavefront's passes as 64 rows are: the same
+// 8 tables at 16 / 32 / 64 / 128 columns 131 / 187 / 330 / 615 us with the loads in every pass, 119 / 172 / 317 / 609 with this;
+// the variant of 7 wavefronts loses by it, 20.5 -> 21.2 ms at the first of the workloads above with passes of 16 rows.
+constexpr int kPassRowsLog2 = 4, kLongPassRowsLog2 = 5;
+constexpr uint32_t kLongPassNeed = 2048, kLongPassNeedNarrow = 128;   // rows per wavefront; tables of at most 8 columns
+constexpr int kSegBlocks = 2048;  // persistent grids: waves stride over passes of unique rows, or over rows
 constexpr int kSegBlocks7 = 1792;   // ... of the variants of 7 wavefronts per SIMD
 // Long spans count a die's wavefronts as an eighth of the grid: a pass would be left out or taken twice otherwise.
 static_assert(kSegBlocks % kDies == 0 && kSegBlocks7 % kDies == 0, "as many workgroups on every die");
@@ -330,6 +340,7 @@ static_assert(kHotRows <= kSegThreads, "one thread per listed row");
 template <typename WT, bool MEAN, typename GT, int kSegWaves>
 __global__ __launch_bounds__(kSegThreads, kSegWaves) void seg_update_kernel(const SegArgs a) {
     constexpr int kSegUnroll = seg_unroll<1, MEAN, GT, kSegWaves>();
+    constexpr bool kFetch = kSegWaves == 8;   // the start of a pass is loaded for several of them (see kPassRowsLog2)
     constexpr bool kAhead = kSegWaves < 8;   // a row's weights are loaded ahead of its gradients (see the short rows above)
     const int lane = lane_id();
     copy_hint(a);
@@ -337,17 +348,18 @@ __global__ __launch_bounds__(kSegThreads, kSegWaves) void seg_update_kernel(cons
     reduce_parts<false, MEAN, GT, kSegWaves>(a);
     const uint32_t U = a.counters[0];
     const uint32_t nwaves = gridDim.x * (kSegThreads / kWave);
-    // rows per wavefront pass: 16 when there is plenty of work, fewer when the batch touches so few rows that
-    // whole wavefronts would otherwise go idle while others walk 16 rows one round after the other - down to as many as
-    // the widest table's rows a wavefront takes side by side
-    uint32_t rpw = kPassRows;
-    while (rpw > (1u << a.min_rows_log2) && U / rpw < 2u * nwaves) rpw >>= 1;
-    const uint32_t nblk = (U + rpw - 1) / rpw;
+    // rows per pass: 2^lg (see kPassRowsLog2), fewer where the batch touches so few rows that whole wavefronts would go idle while
+    // others walk a pass one round after the other - down to as many as the widest table's rows a wavefront takes side by side
+    int lg = kPassRowsLog2;
+    if (U / nwaves >= a.long_pass_need) lg = kLongPassRowsLog2;
+    else while (lg > a.min_rows_log2 && (U >> lg) < 2u * nwaves) --lg;
+    const uint32_t nblk = (U + (1u << lg) - 1u) >> lg;
+    const uint32_t e_all = a.seg_start[U];   // lookups in all
     // The wavefronts of the chip take the passes in turn.  With long spans those of a die take the passes of its two spans in turn
     // instead, so that a die reads the gradient blocks of a few tables only: pass first + i of the first span, i < n1, then again + i
     // of the second.  All of it is the same for the whole wavefront and stays on the scalar unit; with two divisions by the length of
     // a span in every pass, and more scalar registers spilled than now, small batches paid 0.5 to 2 us (34 tables x 40 bags x 32
-    // columns 14.0 us, now 12.1; one table x 512 bags x 64 columns 8.8, now 8.1).
+    // columns 14.1 us, now 12.5; one table x 512 bags x 64 columns 8.8, now 8.1).
     const uint32_t wave = (uint32_t)__builtin_amdgcn_readfirstlane((int)(threadIdx.x >> 6));
     uint32_t i = blockIdx.x * (kSegThreads / kWave) + wave, step = nwaves, n1 = nblk, n = nblk, first = 0, again = 0;
     if (a.long_spans) {
@@ -362,19 +374,19 @@ __global__ __launch_bounds__(kSegThreads, kSegWaves) void seg_update_kernel(cons
         again = b2 - n1;
     }
     WT* tables = static_cast<WT*>(a.tables);
-    for (; i < n; i += step) {
-        const uint32_t u0 = (i + (i < n1 ? first : again)) * rpw;
-        // ---- one row per lane: bounds, key, table, width, moment
-        const uint32_t last = umin(U - u0, rpw);   // rows of the pass
-        const uint32_t u = u0 + lane;
-        uint32_t s = 0, e = 0, key = 0;
-        if ((uint32_t)lane < last) {
+    const int fetch_log2 = kFetch ? 6 : lg;
+    for (; i < n; i += step << (fetch_log2 - lg)) {
+        // ---- one row per lane, of the next pass or (kFetch) the next 64 / 2^lg: bounds, key, table, width, moment
+        const uint32_t i_l = i + ((uint32_t)lane >> lg) * step;
+        const uint32_t u = ((i_l + (i_l < n1 ? first : again)) << lg) + ((uint32_t)lane & ((1u << lg) - 1u));
+        const bool row_on = i_l < n && u < U && lane >> fetch_log2 == 0;
+        uint32_t s = 0, e = e_all, key = 0;
+        if (row_on) {
             s = a.seg_start[u];
             e = a.seg_start[u + 1];
             key = a.keys_unique[u];
         }
-        const uint32_t len = e - s;
-        bool live = (uint32_t)lane < last && len >= 1 && len <= a.long_min && key < a.total_rows;
+        bool live = row_on && e != s && e - s <= a.long_min && key < a.total_rows;
         int t = 0, D = 4;
         float v = 0.f;
         if (live) {
@@ -388,27 +400,24 @@ __global__ __launch_bounds__(kSegThreads, kSegWaves) void seg_update_kernel(cons
             }
         }
         // a window of 64 lookups of one table, lane's lookup win + lane: loaded once for all the short rows that lie in it
-        const uint32_t e_blk = bcast_lane(e, (int)last - 1);   // end of the block's lookups
         uint32_t win = 0, my_b = 0;
         int win_t = -1;
         float my_s = 1.f;
-        auto load_window = [&](const uint32_t s0, const int t_w, const uint32_t row0) {
+        auto load_window = [&](const int r, const uint32_t s0, const int t_w, const uint32_t row0) {
             win = s0;
             win_t = t_w;
             const uint32_t at = s0 + (uint32_t)lane;
-            const uint32_t bag = a.bag_sorted[at < e_blk ? at : e_blk - 1u];
+            const uint32_t end = bcast_lane(e, r | ((1 << lg) - 1));   // of the lookups of row r's pass
+            const uint32_t bag = a.bag_sorted[at < end ? at : end - 1u];
             my_b = bag - row0;
             my_s = bag_scale<MEAN>(a.offsets, bag);
         };
-        int r = 0;
-        while (r < (int)last) {
-            if (!bcast_lane((int)live, r)) {
-                ++r;
-                continue;
-            }
+        uint64_t todo = __ballot(live);
+        while (todo != 0ull) {
+            const int r = __ffsll((unsigned long long)todo) - 1;
             const RowGeom g = row_geom(bcast_lane(D, r));   // r is the same in all lanes: scalar reads
             const uint32_t s_r = bcast_lane(s, r);
-            const uint32_t len_r = bcast_lane(len, r);
+            const uint32_t len_r = bcast_lane(e, r) - s_r;
             if (len_r > (uint32_t)kWave) {
                 // ---- medium row: the whole wavefront reduces it
                 const uint32_t key_r = bcast_lane(key, r);
@@ -421,10 +430,10 @@ __global__ __launch_bounds__(kSegThreads, kSegWaves) void seg_update_kernel(cons
                 fold_groups<1>(acc, g);
                 WT* wrow = tables + a.w_off[t_r] + ((int64_t)key_r - a.row_base[t_r]) * g.D;
                 adagrad_row<WT, 1>(acc, g, wrow, a.state + key_r, v_r, g.sub == 0, a.lr, a.eps, a.inv_c, a.state == nullptr);
-                ++r;
+                todo &= todo - 1ull;
                 continue;
             }
-            // ---- short rows: rows r .. r+k-1 share the table of row r and have at most 64 lookups in total
+            // ---- short rows: rows r .. r+k-1 of one pass share the table of row r and have at most 64 lookups in total
             const int t_r = bcast_lane(t, r);
             const GradAddr ga = grad_addr(a, t_r, g.D);
             const GT* const gcol = static_cast<const GT*>(a.grad_out) + ga.base;
@@ -437,7 +446,7 @@ __global__ __launch_bounds__(kSegThreads, kSegWaves) void seg_update_kernel(cons
                 // all lanes and stays on the scalar unit (key, bag ids, addresses)
                 const uint32_t key_r = bcast_lane(key, r);
                 const float v_r = bcast_lane(v, r);
-                if (win_t != t_r || s_r + len_r - win > (uint32_t)kWave) load_window(s_r, t_r, ga.row0);
+                if (win_t != t_r || s_r + len_r - win > (uint32_t)kWave) load_window(r, s_r, t_r, ga.row0);
                 WT* const wrow = wtab + (uint64_t)(key_r - rb) * (uint32_t)g.D;
                 typename RowIO<WT>::raw4_t wraw;
                 if constexpr (kAhead) wraw = RowIO<WT>::load4_raw(wrow + lane_col);
@@ -446,19 +455,19 @@ __global__ __launch_bounds__(kSegThreads, kSegWaves) void seg_update_kernel(cons
                 if constexpr (kAhead)
                     adagrad_row_loaded<WT>(acc, g, wrow, wraw, a.state + key_r, v_r, true, a.lr, a.eps, a.inv_c, a.state == nullptr);
                 else adagrad_row<WT, 1>(acc, g, wrow, a.state + key_r, v_r, true, a.lr, a.eps, a.inv_c, a.state == nullptr);
-                ++r;
+                todo &= todo - 1ull;
                 continue;
             }
-            const bool q = live && t == t_r && lane >= r && lane < r + g.G && (e - s_r) <= (uint32_t)kWave;
+            const bool q = live && t == t_r && lane >= r && lane < r + g.G && (lane ^ r) >> lg == 0 && (e - s_r) <= (uint32_t)kWave;
             const uint64_t m = __ballot(q) >> r;                       // bit j: row r+j qualifies
-            const int k = (~m == 0ull) ? kWave : (__ffsll((unsigned long long)(~m)) - 1);  // trailing ones, >= 1
-            if (win_t != t_r || bcast_lane(e, r + k - 1) - win > (uint32_t)kWave) load_window(s_r, t_r, ga.row0);
+            const int k = __ffsll((unsigned long long)(~m)) - 1;       // trailing ones, 1 .. 2^lg
+            if (win_t != t_r || bcast_lane(e, r + k - 1) - win > (uint32_t)kWave) load_window(r, s_r, t_r, ga.row0);
             // this lane group's row
             const bool gon = g.sub < k;
             const int gi = (r + g.sub) & (kWave - 1);
             const uint32_t gs = __shfl(s, gi, kWave);
             // cross-lane reads stay outside any lane-dependent condition: a lane that sits out cannot be read from
-            const uint32_t glen_any = __shfl(len, gi, kWave);
+            const uint32_t glen_any = __shfl(e, gi, kWave) - gs;
             const uint32_t glen = gon ? glen_any : 0u;
             const uint32_t gkey = __shfl(key, gi, kWave);
             const float gv = __shfl(v, gi, kWave);
@@ -467,7 +476,7 @@ __global__ __launch_bounds__(kSegThreads, kSegWaves) void seg_update_kernel(cons
             float acc[1][4] = {{0.f, 0.f, 0.f, 0.f}};
             add_short<kSegUnroll, false, MEAN, GT>(acc, gcol, ga.pitch, lane_col, my_b, my_s, gs - win, lmax, glen);
             adagrad_row<WT, 1>(acc, g, wrow, a.state + gkey, gv, gon, a.lr, a.eps, a.inv_c, a.state == nullptr);
-            r += k;
+            todo &= ~(((1ull << k) - 1ull) << r);
         }
     }
 }
@@ -698,6 +707,7 @@ SegArgs seg_args(const tbe_handle* h, const Workspace& w, char* ws, const void* 
     a.hint_n = hint ? h->d_hot_n : nullptr;
     // side by side: 64 / (lanes per row) rows of the widest table up to 256 columns
     a.min_rows_log2 = h->maxD > 128 ? 0 : (h->maxD > 64 ? 1 : (h->maxD > 32 ? 2 : 3));
+    a.long_pass_need = h->maxD <= 8 ? kLongPassNeedNarrow : kLongPassNeed;
     a.long_spans = 0;
     const bool dense = w.dense && !seq;
     a.dense_n = dense ? reinterpret_cast<uint32_t*>(ws + w.dense_n) : nullptr;

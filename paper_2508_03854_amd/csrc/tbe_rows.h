@@ -52,7 +52,8 @@ struct SegArgs {
     uint32_t* hint_ids;           // the handle's hint (null: not kept)
     uint32_t* hint_n;
     int long_spans;               // seg_update: 1: each die takes two long spans of rows; 0: the whole chip takes all passes in turn
-    int min_rows_log2;            // seg_update: a wavefront takes at least 2^this consecutive rows
+    uint32_t long_pass_need;      // seg_update: rows per wavefront from which a pass has 32 rows
+    int min_rows_log2;            // seg_update: a pass has at least 2^this consecutive rows
     // dense rows (tbe_dense.hip); null dense_n: no table can have any
     uint32_t* dense_n;            // [T] number of dense rows
     uint32_t* dense_rows;         // [T][kDenseRows] their positions in long_list, longest first

@@ -35,8 +35,10 @@ FEW = [1, 1, 2, 1, 3] * 26 + COUNTS
 
 
 def _rows_per_pass(U, max_d, wavefronts):
-    """The rows of one pass of seg_update_kernel: 16, halved while wavefronts would have less than two passes, down to the rows of
-    the widest table that lie side by side in a wavefront."""
+    """The rows of one pass of seg_update_kernel: 32 in batches of very many rows or narrow ones, else 16, halved while wavefronts
+    would have less than two passes, down to the rows of the widest table that lie side by side in a wavefront."""
+    if U // wavefronts >= (128 if max_d <= 8 else 2048):
+        return 32
     least = 1 if max_d > 128 else 2 if max_d > 64 else 4 if max_d > 32 else 8
     rows = 16
     while rows > least and U // rows < 2 * wavefronts:
@@ -50,6 +52,7 @@ def _rows_per_pass(U, max_d, wavefronts):
     (2, 133000, [256, 136], "f16", "mean", "bf16", 16, False),   # 8 wavefronts per SIMD, one row per round
     (2, 133000, [128, 64], "f32", "mean", "f32", 16, False),     # 2 and 4 rows per round
     (3, 88000, [20, 8, 4], "f32", "sum", "f16", 16, False),      # 8, 32 and 64
+    (3, 350500, [8, 4, 8], "f32", "sum", "f32", 32, False),      # passes of 32 rows, 32 and 64 side by side
     (17, 15700, [64, 64, 104], "f16", "sum", "bf16", 16, True),  # long spans that end inside tables
     (16, 8500, [136, 256], "f32", "mean", "f32", 8, True),       # ... of passes of 8 rows
 ])
@@ -59,6 +62,50 @@ def test_passes_of_many_rows(T, rows, widths, dtype, pooling, io, per_pass, span
     rep = _step(T, rows, widths, dtype, pooling, io, FEW)
     assert _rows_per_pass(rep["U"], max(D), 7168 if seven else 8192) == per_pass
     assert spans == (T >= 16 and max(D) * T <= 2 * sum(D) and 700 * sum(D) * (4 if io == "f32" else 2) <= T * (3 << 19))
+
+
+@pytest.mark.parametrize("D,dtype,wavefronts", [
+    (136, "f16", 7168),   # one row per round, the variant of fewer wavefronts: one pass at a time
+    (12, "f32", 8192),    # 16 rows per round, two passes at a time
+])
+def test_passes_of_very_many_rows(D, dtype, wavefronts):
+    """Passes of 32 rows, against the step in 64 bits: every row once, every seventh a second time."""
+    if not torch.cuda.is_available():
+        pytest.skip("no GPU")
+    from paper_2508_03854_amd import TBE
+    R, B, lr, eps, c = 2048 * wavefronts + 77, 1000, 0.01, 1e-8, 2.0
+    assert _rows_per_pass(R, D, wavefronts) == 32
+    g = torch.Generator(device="cuda").manual_seed(D)
+    idx = torch.cat([torch.arange(R, device="cuda"), torch.arange(0, R, 7, device="cuda")])
+    idx = idx[torch.randperm(idx.numel(), generator=g, device="cuda")]
+    off = (torch.arange(B + 1, device="cuda", dtype=torch.int64) * idx.numel()) // B
+    tbe = TBE([R], [D], dtype)
+    tables = torch.empty(R * D, device="cuda").uniform_(-0.01, 0.01, generator=g).to(tbe.torch_dtype)
+    state = torch.rand(R, generator=g, device="cuda") + 1.0
+    grad = torch.randn(B, D, generator=g, device="cuda")
+    w0, v0 = tables.view(R, D).clone(), state.clone()
+    tbe.backward_rowwise_adagrad(grad, idx, off, B, tables, state, tbe.alloc_workspace(B, idx.numel()), pooling="sum", lr=lr, eps=eps,
+                                 momentum_scale=c)
+    assert not tbe.poll_index_error()
+    order = torch.sort(idx, stable=True).indices
+    bag = torch.searchsorted(off, order, right=True) - 1
+    per_row = torch.ones(R, dtype=torch.int64, device="cuda")
+    per_row[::7] = 2
+    start = torch.cumsum(per_row, 0) - per_row
+    g64, w1 = grad.double(), tables.view(R, D)
+    for lo in range(0, R, 1 << 20):
+        r = slice(lo, min(R, lo + (1 << 20)))
+        two = per_row[r] == 2
+        s = g64[bag[start[r]]]
+        s[two] += g64[bag[start[r][two] + 1]]
+        v = v0[r].double() + (s * s).sum(1)
+        step = lr / (torch.sqrt(v / c) + eps)
+        want = w0[r].double() - step[:, None] * s
+        # moments: a sum of D squares in 32 bits; weights: 1e-5 of the row's step and the rounding to the table's type
+        assert ((state[r].double() - v).abs() <= D * 2.0 ** -24 * v).all()
+        bound = 1e-5 * step[:, None] * s.abs().amax(1, keepdim=True) + (2.0 ** -23 if dtype == "f32" else 2.0 ** -11) * want.abs() + 2.0 ** -25
+        assert ((w1[r].double() - want).abs() <= bound).all()
+    tbe.close()
 
 
 def _step(T, rows, widths, dtype, pooling, io, counts):
