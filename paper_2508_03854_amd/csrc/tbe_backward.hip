@@ -363,9 +363,10 @@ __global__ __launch_bounds__(kSegThreads, kSegWaves) void seg_update_kernel(cons
     const uint32_t wave = (uint32_t)__builtin_amdgcn_readfirstlane((int)(threadIdx.x >> 6));
     uint32_t i = blockIdx.x * (kSegThreads / kWave) + wave, step = nwaves, n1 = nblk, n = nblk, first = 0, again = 0;
     if (a.long_spans) {
-        const uint32_t die = blockIdx.x & (kDies - 1u), span = (nblk + 2u * kDies - 1u) / (2u * kDies);
-        const uint32_t b0 = umin(die * span, nblk), b1 = umin(b0 + span, nblk);
-        const uint32_t b2 = umin((die + kDies) * span, nblk), b3 = umin(b2 + span, nblk);
+        const uint32_t die = blockIdx.x & (kDies - 1u);
+        const uint32_t* const border = a.counters + kSpanWord + die;
+        const uint32_t b0 = border[0] >> lg, b1 = border[1] >> lg, b2 = border[kDies] >> lg;
+        const uint32_t b3 = die + 1u < kDies ? border[kDies + 1u] >> lg : nblk;
         i = (blockIdx.x / kDies) * (kSegThreads / kWave) + wave;
         step = nwaves / kDies;
         n1 = b1 - b0;
@@ -731,18 +732,7 @@ hipError_t launch_segment_update(const tbe_handle* h, const Workspace& w, char* 
     a.inv_c = 1.0f / c;
     a.tables = tables;
     a.state = state;
-    // The row updates gather a table's gradient block at random, and every die that works on the table reads it through its own
-    // L2.  Where the blocks are small enough to stay there next to the rows themselves (1.5 MiB of 4), a die takes two long spans
-    // of rows; from 16 tables on, so that the spans, equal in rows, are about equal in lookups too.  Row updates without / with
-    // it, us: 26 tables x 4096 bags x 64 fp32 columns (1 MiB) 83.5 / 71.6; 55 tables x 2306 bags x 149 columns binary16 188 /
-    // 162; 31 x 1699 x 224 fp32 (1.5 MB) 62 / 52; 57 x 1410 x 128 fp32 143 / 125; but 64 tables x 4096 bags x 224 bfloat16
-    // (1.8 MB) 702 / 706, 12 tables x 1548 x 224 binary16 39.1 / 41.5, and at 16384 x 149 fp32 (9.8 MB) 288 / 310.  One span
-    // per die gains as much and loses more where tables differ; four gain half.
-    // Tables of very different width leave the dies with unequal work (16 tables x 650 bags, 8 to 520 columns, 26.0 / 31.9), so the
-    // widest may have twice the mean width.
-    const uint64_t block = (uint64_t)B * (uint64_t)h->sumD * (grad_io == 0 ? 4u : 2u);   // of all tables
-    const bool level = (int64_t)h->maxD * h->T <= 2 * (int64_t)h->sumD;
-    if (!seq && h->T >= 16 && level && block <= (uint64_t)h->T * (3u << 19)) a.long_spans = 1;
+    a.long_spans = long_spans(h, B, seq, grad_io == 0 ? 4u : 2u);
     const bool mean = pooling == TBE_MEAN;
     if (a.dense_n) {
         LaunchTimer tm(h, s, "seg_dense_partial");

@@ -26,14 +26,13 @@ constexpr int kListThreads = 1024;
 constexpr uint32_t kListRank = 1024;   // long rows of one table that are ranked; of more, the kHotRows longest are found first
 static_assert(kDenseRows <= kHotRows && kHotRows <= (int)kListRank && kListRank <= (uint32_t)kListThreads, "one thread per ranked row");
 
-// first i in [0, n) with rows[i].y >= x, or n; a whole wavefront, 64 probes per round
-__device__ __forceinline__ uint32_t wave_lower_bound_key(const uint2* __restrict__ rows, const uint32_t n, const int64_t x) {
-    uint32_t lo = 0, hi = n;
+// first i in [lo, hi) with ge(i), which is false before some i and true from it on, or hi; a whole wavefront, 64 probes per round
+template <typename F>
+__device__ __forceinline__ uint32_t wave_first(uint32_t lo, uint32_t hi, F ge) {
     while (lo < hi) {
         const uint32_t step = (hi - lo + kWave - 1) / kWave;
         const uint64_t i = lo + (uint64_t)(lane_id() + 1) * step - 1;
-        const bool ge = i < hi ? (int64_t)rows[i].y >= x : true;
-        const uint64_t m = __ballot(ge);
+        const uint64_t m = __ballot(i < hi ? ge((uint32_t)i) : true);
         if (m == 0ull) return hi;
         const uint32_t f = (uint32_t)__ffsll((unsigned long long)m) - 1u;
         const uint64_t i_f = lo + (uint64_t)(f + 1u) * step - 1;
@@ -282,7 +281,77 @@ __device__ __forceinline__ void list_table(const SegArgs& a, ListLds* S, const i
     }
 }
 
-// grid: one workgroup per table, and in non-pooled mode one more for the gradient blocks
+// Where each of the kSpans long spans of rows starts that the dies take (seg_update_kernel), so that all of them hold the same work: a
+// row counts kSpanRow lookups besides its own, those of long rows not at all, which are reduced elsewhere.  Spans of equally many rows
+// were level only where tables of all sizes alternate: of 26 tables of 1000 to 1 M rows in ascending order, uniform ids, one die had 3.1
+// times the mean's lookups.  Row updates without long spans / with equally many rows / with these, us (tables in mixed, ascending and
+// descending order of size): 26 tables x 4096 bags of 11 ids x 64 columns 82 77 72, 87 80 75, 84 80 74; uniform ids 174 162 164,
+// 174 180 166, 176 173 169; 57 tables x 1410 bags of 21 ids x 128 columns 195 160 161, 199 180 157, 189 164 153; 40 tables x 4096 bags
+// of 20 ids, Zipf 1.2, x 64 columns 154 125 129, 143 148 132, 147 138 123.  With 4 / 8 / 24 lookups a row: uniform ids gain (ascending
+// 153 / 155 / 166), but many lookups of one row cost less than those of many, and skewed ids lose: the 57 tables in mixed order 178 /
+// 166 / 160.
+// One workgroup: the weight before every long row into LDS, then a wavefront per border finds the long row it lies before, and its
+// place between that row and the one before.  Five dependent loads, no more than the lists of a table take, beside which it runs
+// (measured: 0.2 us of the launch's 10).
+constexpr uint32_t kSpanRow = 16;
+constexpr uint32_t kSpanChunk = 2 * kListThreads;   // long rows in LDS at a time
+__device__ __forceinline__ void span_borders(const SegArgs& a) {
+    __shared__ uint64_t s_weight[kSpanChunk];                         // of the rows before a long row
+    __shared__ uint32_t s_row[kSpanChunk], s_long[kSpanChunk];        // its number; lookups of the long rows up to and with it
+    __shared__ uint32_t s_scan[kListThreads / kWave];
+    const uint32_t tid = threadIdx.x;
+    const uint32_t U = a.counters[0], nlong = a.counters[1] < a.cap_long ? a.counters[1] : a.cap_long;
+    const uint32_t N = a.seg_start[U];
+    auto load_chunk = [&](const uint32_t k0, const uint32_t carry) {   // returns the lookups of its rows
+        uint32_t u[2], s0[2], len[2];
+#pragma unroll
+        for (int j = 0; j < 2; ++j) u[j] = k0 + 2u * tid + j < nlong ? a.long_rows[k0 + 2u * tid + j].x : U;
+#pragma unroll
+        for (int j = 0; j < 2; ++j) {
+            s0[j] = a.seg_start[u[j]];
+            len[j] = u[j] < U ? a.seg_start[u[j] + 1] - s0[j] : 0u;
+        }
+        uint32_t tot;
+        uint32_t before = carry + block_excl_scan<kListThreads>(len[0] + len[1], s_scan, &tot);
+#pragma unroll
+        for (int j = 0; j < 2; ++j) {
+            s_weight[2u * tid + j] = (uint64_t)kSpanRow * u[j] + (s0[j] - before);
+            before += len[j];
+            s_row[2u * tid + j] = u[j];
+            s_long[2u * tid + j] = before;
+        }
+        __syncthreads();
+        return tot;
+    };
+    uint32_t all = 0;
+    for (uint32_t k0 = 0; k0 < nlong; k0 += kSpanChunk) {
+        all += load_chunk(k0, all);
+        __syncthreads();
+    }
+    const uint64_t whole = (uint64_t)kSpanRow * U + (N - all);
+    const uint32_t q = tid >> 6;
+    const uint64_t x = whole * q / kSpans;   // the border's weight
+    uint32_t lo = 0, hi = U, before = 0, carry = 0;
+    for (uint32_t k0 = 0; k0 < nlong; k0 += kSpanChunk) {
+        const uint32_t n = umin(nlong - k0, kSpanChunk);
+        if (nlong > kSpanChunk) carry += load_chunk(k0, carry);
+        if (hi == U) {   // (no long row so far has the border's weight before it)
+            const uint32_t i = wave_first(0u, n, [&](const uint32_t k) { return s_weight[k] >= x; });
+            if (i < n) hi = s_row[i];
+            if (i > 0u) {
+                lo = s_row[i - 1u] + 1u;
+                before = s_long[i - 1u];
+            }
+        }
+        __syncthreads();
+    }
+    if (q >= kSpans) return;
+    const uint32_t border = wave_first(lo, hi, [&](const uint32_t u) { return (uint64_t)kSpanRow * u + (a.seg_start[u] - before) >= x; });
+    if (lane_id() == 0) a.counters[kSpanWord + q] = border;
+}
+static_assert(kSpans <= kListThreads / kWave, "a wavefront per border");
+
+// grid: one workgroup per table, and one more for the gradient blocks (non-pooled mode) or the borders of long spans
 template <typename IT>
 __global__ __launch_bounds__(kListThreads) void list_rows_kernel(const SegArgs a, const IT* __restrict__ offsets,
                                                                  const int64_t nnz, const int64_t grad_elems,
@@ -291,13 +360,15 @@ __global__ __launch_bounds__(kListThreads) void list_rows_kernel(const SegArgs a
     __shared__ uint32_t s_range[2];
     const int t = blockIdx.x;
     if (t == a.T) {
-        seq_blocks<IT>(a, offsets, nnz, grad_elems, err);
+        if (a.seq) seq_blocks<IT>(a, offsets, nnz, grad_elems, err);
+        else span_borders(a);
         return;
     }
     const uint32_t nlong = a.counters[1] < a.cap_long ? a.counters[1] : a.cap_long;
     const uint32_t tid = threadIdx.x;
     if (tid < 2 * kWave) {
-        const uint32_t i = wave_lower_bound_key(a.long_rows, nlong, a.row_base[t + (int)(tid >> 6)]);
+        const int64_t x = a.row_base[t + (int)(tid >> 6)];
+        const uint32_t i = wave_first(0u, nlong, [&](const uint32_t k) { return (int64_t)a.long_rows[k].y >= x; });
         if ((tid & (kWave - 1)) == 0) s_range[tid >> 6] = i;
     }
     if (tid == 0) {
@@ -317,8 +388,9 @@ template <typename IT>
 __global__ __launch_bounds__(kListThreads) void list_rows_flat_kernel(const SegArgs a, const IT* __restrict__ offsets,
                                                                       const int64_t nnz, const int64_t grad_elems,
                                                                       int32_t* __restrict__ err) {
-    if (a.seq && blockIdx.x == gridDim.x - 1) {
-        seq_blocks<IT>(a, offsets, nnz, grad_elems, err);
+    if ((a.seq || a.long_spans) && blockIdx.x == gridDim.x - 1) {
+        if (a.seq) seq_blocks<IT>(a, offsets, nnz, grad_elems, err);
+        else span_borders(a);
         return;
     }
     const uint32_t nlong = a.counters[1] < a.cap_long ? a.counters[1] : a.cap_long;
@@ -392,16 +464,18 @@ __global__ __launch_bounds__(256) void dense_index_kernel(const SegArgs a) {
 
 hipError_t launch_lists(const tbe_handle* h, const Workspace& w, char* ws, const void* offsets, int idx32, int32_t B, int seq,
                         int64_t grad_elems, hipStream_t s) {
-    const SegArgs a = seg_args(h, w, ws, offsets, idx32, B, seq);
+    SegArgs a = seg_args(h, w, ws, offsets, idx32, B, seq);
+    a.long_spans = long_spans(h, B, seq, 2);   // (the gradient's type is not known yet: where any type would take them)
+    const unsigned more = seq || a.long_spans ? 1u : 0u;
     LaunchTimer tm(h, s, "seg_long_list");
     const int64_t nnz = w.n;
     if (h->T <= kMaxSortSegments) {
-        const unsigned grid = (unsigned)(h->T + (seq ? 1 : 0));
+        const unsigned grid = (unsigned)h->T + more;
         if (idx32) list_rows_kernel<int32_t><<<grid, kListThreads, 0, s>>>(a, static_cast<const int32_t*>(offsets), nnz, grad_elems, h->d_err);
         else list_rows_kernel<int64_t><<<grid, kListThreads, 0, s>>>(a, static_cast<const int64_t*>(offsets), nnz, grad_elems, h->d_err);
         if (a.dense_n) dense_index_kernel<<<(unsigned)(h->T * kIndexSplit), 256, 0, s>>>(a);
     } else {
-        const unsigned grid = (unsigned)((w.cap_long + kListThreads - 1) / kListThreads + (seq ? 1 : 0));
+        const unsigned grid = (unsigned)((w.cap_long + kListThreads - 1) / kListThreads) + more;
         if (idx32) list_rows_flat_kernel<int32_t><<<grid, kListThreads, 0, s>>>(a, static_cast<const int32_t*>(offsets), nnz, grad_elems, h->d_err);
         else list_rows_flat_kernel<int64_t><<<grid, kListThreads, 0, s>>>(a, static_cast<const int64_t*>(offsets), nnz, grad_elems, h->d_err);
     }

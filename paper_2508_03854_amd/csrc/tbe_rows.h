@@ -20,12 +20,15 @@ constexpr uint32_t kDenseFlag = 0x80000000u;   // long_list entry: the dense-row
 
 // Dies of the chip, each with an L2 of its own; workgroup i of a launch runs on die i % kDies.
 constexpr uint32_t kDies = 8;
+constexpr uint32_t kSpans = 2 * kDies;   // long spans of rows that the row updates may share out to the dies, two each
+constexpr uint32_t kSpanWord = 16;       // counters[kSpanWord + k]: first row of span k
+static_assert(kSpanWord + kSpans <= (uint32_t)kCounterWords, "borders among the counters");
 
 struct SegArgs {
     const uint32_t* keys_unique;  // unique_rows
     const uint32_t* seg_start;
     uint32_t* counters;           // [0] unique rows, [1] long rows, [2] dense partials, [3] work units, [4] != 0: apply nothing,
-                                  // [5] tables with dense rows
+                                  // [5] tables with dense rows, [kSpanWord ..] first rows of the long spans
     const uint32_t* bag_sorted;   // the sorted payload: linear bag id of every sorted lookup
     OffsetWords offsets;
     const void* grad_out;         // [B, sum(D)] float / binary16 / bfloat16, per the kernel's GT (or the sequence layout)
@@ -51,7 +54,8 @@ struct SegArgs {
     uint32_t* hot_n;              // [T]
     uint32_t* hint_ids;           // the handle's hint (null: not kept)
     uint32_t* hint_n;
-    int long_spans;               // seg_update: 1: each die takes two long spans of rows; 0: the whole chip takes all passes in turn
+    int long_spans;               // seg_update: 1: each die takes two long spans of rows (counters[kSpanWord ..]); 0: the whole chip
+                                  // takes all passes in turn
     uint32_t long_pass_need;      // seg_update: rows per wavefront from which a pass has 32 rows
     int min_rows_log2;            // seg_update: a pass has at least 2^this consecutive rows
     // dense rows (tbe_dense.hip); null dense_n: no table can have any
@@ -64,6 +68,20 @@ struct SegArgs {
     uint32_t dense_chunks;        // partial sums per dense row: runs of dense_per_chunk blocks
     uint32_t dense_per_chunk;
 };
+
+// Whether the row updates share long spans of rows out to the dies, for gradient elements of so many bytes.
+// They gather a table's gradient block at random, and every die that works on the table reads it through its own L2.  Where the blocks
+// are small enough to stay there next to the rows themselves (1.5 MiB of 4), a die takes two long spans of rows, equal in work
+// (span_borders); from 16 tables on, so that a span is no small part of one table.  Row updates without / with them, us: 26 tables x
+// 4096 bags x 64 fp32 columns (1 MiB) 82 / 72; 31 x 1699 x 224 fp32 (1.5 MB) 201 / 182; 57 x 1410 x 128 fp32 195 / 161; but 64 tables x
+// 4096 bags x 224 bfloat16 (1.8 MB) 702 / 706, 12 tables x 1548 x 224 binary16 39.1 / 41.5, and at 16384 x 149 fp32 (9.8 MB) 288 / 310.
+// Tables of more than 256 columns have rows in a span but no work for seg_update_kernel, and a row's lookups cost what its width says;
+// the widest may have twice the mean width (16 tables x 650 bags, 8 to 520 columns, as spans of equally many rows 26.0 / 31.9 us).
+inline int long_spans(const tbe_handle* h, const int32_t B, const int seq, const unsigned elem_bytes) {
+    const uint64_t block = (uint64_t)B * (uint64_t)h->sumD * elem_bytes;   // of all tables
+    const bool level = (int64_t)h->maxD * h->T <= 2 * (int64_t)h->sumD;
+    return !seq && h->T >= 16 && level && block <= (uint64_t)h->T * (3u << 19) ? 1 : 0;
+}
 
 // Dense rows exist only where a table's gradient block is large, 2 MiB at four bytes per element (half an L2: a block that fits
 // one is gathered from at L2 speed), and has enough bags to share out.  The lists are made before the gradient's type is known,

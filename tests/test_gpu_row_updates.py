@@ -4,6 +4,8 @@ wavefront and several, tables that end inside a pass, and 16 tables or more, who
 oracle, with the harness's tolerances.  A wavefront takes a pass of as few rows as fill the chip, 1 to 8 in the small batches of
 the first test; passes of 16 rows, in which rounds share a window, and wavefronts of several passes need the many rows of the
 second."""
+import ctypes
+
 import numpy as np
 import pytest
 import torch
@@ -137,3 +139,44 @@ def _step(T, rows, widths, dtype, pooling, io, counts):
     rep = H.check_step(cfg, tbe, flat, state, tabs, st, idx, off, gout, ws, io=io)
     tbe.close()
     return rep
+
+
+@pytest.mark.parametrize("T,B,rows,lookups,hot", [
+    (16, 100, (50, 4000), 2500, 0),           # ascending sizes, no long row
+    (26, 300, (20000, 30), 9000, 40),         # descending
+    (16, 200, (150, 9000), 20000, 145),       # more long rows than lie in LDS at a time
+    (20, 64, (3, 3), 10, 0),                  # fewer rows than a pass
+])
+def test_long_spans_of_equal_work(T, B, rows, lookups, hot):
+    """The borders of the long spans, as the batch's lists hold them: a row weighs 16 lookups and its own, long rows only the 16."""
+    if not torch.cuda.is_available():
+        pytest.skip("no GPU")
+    from paper_2508_03854_amd import TBE
+    rng = np.random.default_rng(T * B)
+    R = [round(rows[0] * (rows[1] / rows[0]) ** (t / (T - 1))) for t in range(T)]
+    ids = []
+    for r in R:
+        h = min(hot, r)
+        few = rng.integers(0, r, size=lookups - 130 * h)
+        ids.append(rng.permutation(np.concatenate([np.repeat(rng.permutation(r)[:h], 130), few])))
+    idx = torch.as_tensor(np.concatenate(ids)).cuda()
+    off = torch.cat([torch.arange(B) * lookups // B + t * lookups for t in range(T)] + [torch.tensor([T * lookups])]).cuda()
+    tbe = TBE(R, [64] * T, "f32")
+    ws = tbe.alloc_workspace(B, idx.numel())
+    tbe.backward_prepare(idx, off, B, ws)
+    n = idx.numel()
+    dev = tbe.debug_sorted_device(ws, B, n)
+    ptrs = [ctypes.c_void_p() for _ in range(5)]
+    assert tbe._lib.tbe_debug_sorted(tbe._h, ws.data_ptr(), B, n, *[ctypes.byref(p) for p in ptrs]) == 0
+    at = ptrs[4].value - ws.data_ptr()   # the number of unique rows heads the counters: borders from word 16 on
+    words = ws[at:at + 128].view(torch.int32).cpu().numpy().astype(np.int64)
+    U = int(words[0])
+    start = dev["seg_start"].cpu().numpy()
+    length = np.diff(start)
+    long_min = 64 if n <= 1 << 17 else 128 if n <= 3 << 17 else 256
+    if hot:
+        assert (length > long_min).sum() >= hot * T * 0.9
+    weight = np.concatenate(([0], np.cumsum(16 + np.where(length > long_min, 0, length))))
+    want = [int(np.searchsorted(weight, weight[-1] * q // 16)) for q in range(16)]
+    assert words[16:32].tolist() == want
+    tbe.close()
