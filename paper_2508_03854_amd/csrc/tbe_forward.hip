@@ -6,6 +6,8 @@
 // lane; the groups walk the bag in an interleaved fashion, four rows per group in flight, and a
 // butterfly over the groups folds the partial sums at the end.  The bag's ids are read with one
 // coalesced 64-wide load and handed to the groups with cross-lane reads.
+#include <type_traits>
+
 #include "tbe_device.h"
 #include "tbe_internal.h"
 
@@ -17,12 +19,28 @@ constexpr int kFwdThreads = 256;
 // more bags share a wavefront, the more lanes one long bag keeps waiting, so the bound falls with the lanes per row
 // (measured at lognormal bag lengths, 8 bags per wavefront: 2.28 ms without, 2.07 / 2.01 / 1.94 / 1.86 ms at 96 / 64 /
 // 48 / 32; a bound below the typical length would send ordinary bags the slower way).
-// `floor` raises the bound for batches whose ordinary bags are that long themselves (long_bag_floor).
-__device__ __forceinline__ int long_bag_min(const int lanes_per_row, const int floor) {
-    const int bound = lanes_per_row > 16 ? 64 : (lanes_per_row > 8 ? 48 : 32);
-    return bound > floor ? bound : floor;
+__device__ __forceinline__ int long_bag_min(const int lanes_per_row) {
+    return lanes_per_row > 16 ? 64 : (lanes_per_row > 8 ? 48 : 32);
 }
-
+// `floor` raises the bound for batches whose ordinary bags are that long themselves (long_bag_floor).
+// first position and ids of bag b of table t (0 ids from bag B on), clamped so that a malformed offsets array can never take a read
+// outside indices[0, nnz); positions are below 2^32
+struct BagSpan {
+    uint32_t start;
+    int len;
+};
+__device__ __forceinline__ BagSpan bag_span(const IdxView offsets, const int32_t t, const int32_t B, const int32_t b, const int64_t nnz) {
+    BagSpan r{0u, 0};
+    if (b < B) {
+        const int64_t bag = (int64_t)t * B + b;
+        int64_t start = offsets[bag], end = offsets[bag + 1];
+        start = start < 0 ? 0 : (start > nnz ? nnz : start);
+        end = end < start ? start : (end > nnz ? nnz : end);
+        r.start = (uint32_t)start;
+        r.len = (int)((end - start) < (int64_t)0x7FFFFFFF ? (end - start) : (int64_t)0x7FFFFFFF);
+    }
+    return r;
+}
 // NC = number of 64-lane column chunks a row needs (1 when D <= 64 * kVec); U = rows in flight per group.
 // The pooled value that is stored: the sum, or for mean pooling sum / L - the product with the reciprocal, corrected
 // once by its exact residual (the usual refinement step of a division), so that a mean that is exactly representable
@@ -138,6 +156,68 @@ __global__ __launch_bounds__(kFwdThreads, NC * U <= 4 ? 8 : 4) void forward_kern
     forward_bag<WT, NC, U, MEAN>(weights + w_off[t], D, R, indices, start, end, out, out_io, (int64_t)b * sumD + d0, err);
 }
 
+// Bags of more than long_bag_min ids that a lane group walks all the same: a single running sum of up to 128 terms would have up to
+// 2.5 times the error of the 2 to 16 interleaved ones of a whole wavefront, so such a bag's sum is moved to a 64-bit total every
+// 8 ids, or 16 of rows of 32 lanes.  Wavefronts without such a bag take the loop without totals.  rms error of fp32 rows (normal
+// values, units of 2^-24), one running sum / a whole wavefront / this: 40 ids of 32 columns 12.5 / 7.0 / 6.6, 62 of 64 19.2 / 11.2 /
+// 8.1, 100 of 8 30.6 / 11.9 / 8.1, 100 of 128 30.8 / 22.4 / 13.4.  The totals cost 3 to 15 % of launches of such bags: 26 tables x 4096
+// bags, 1 + Poisson(30) ids, 64 binary16 columns 40.1 -> 42.3 us, 17000 bags of 40 ids, 32 columns 13.1 -> 13.5; nothing elsewhere.
+__device__ __forceinline__ bool split_run_ends(const int k, const int lpr_log2) {   // k ids of a round of 2^lpr_log2 are summed
+    return (k & (lpr_log2 >= 5 ? 15 : 7)) == 0;
+}
+template <bool SPLIT, int V>
+struct Totals {
+    __device__ __forceinline__ void add(float (&)[V], bool) {}
+    __device__ __forceinline__ void finish(float (&)[V], bool) {}
+};
+template <int V>
+struct Totals<true, V> {
+    double sum[V];
+    __device__ __forceinline__ Totals() {
+#pragma unroll
+        for (int v = 0; v < V; ++v) sum[v] = 0.0;
+    }
+    __device__ __forceinline__ void add(float (&acc)[V], const bool split) {   // `split`: of this lane's bag
+#pragma unroll
+        for (int v = 0; v < V; ++v) {
+            sum[v] += split ? (double)acc[v] : 0.0;
+            acc[v] = split ? 0.f : acc[v];
+        }
+    }
+    __device__ __forceinline__ void finish(float (&acc)[V], const bool split) const {
+#pragma unroll
+        for (int v = 0; v < V; ++v) acc[v] = split ? (float)sum[v] : acc[v];
+    }
+};
+
+// ... in LDS, for a kernel that can spare it: [V][threads of the workgroup]
+template <bool SPLIT, int V>
+struct LdsTotals {
+    __device__ __forceinline__ LdsTotals(double (*)[kFwdThreads]) {}
+    __device__ __forceinline__ void add(float (&)[V], bool) {}
+    __device__ __forceinline__ void finish(float (&)[V], bool) {}
+};
+template <int V>
+struct LdsTotals<true, V> {
+    double (*sum)[kFwdThreads];
+    __device__ __forceinline__ LdsTotals(double (*s)[kFwdThreads]) : sum(s) {
+#pragma unroll
+        for (int v = 0; v < V; ++v) sum[v][threadIdx.x] = 0.0;
+    }
+    __device__ __forceinline__ void add(float (&acc)[V], const bool split) {
+        if (!split) return;
+#pragma unroll
+        for (int v = 0; v < V; ++v) {
+            __hip_atomic_fetch_add(&sum[v][threadIdx.x], (double)acc[v], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
+            acc[v] = 0.f;
+        }
+    }
+    __device__ __forceinline__ void finish(float (&acc)[V], const bool split) const {
+#pragma unroll
+        for (int v = 0; v < V; ++v) acc[v] = split ? (float)sum[v][threadIdx.x] : acc[v];
+    }
+};
+
 // Narrow rows (at most 16 lanes per row): every lane group of the wavefront takes a bag of its own, G = 64 / LPR
 // consecutive bags of one table per wavefront.  A bag of a dozen narrow rows is a few hundred bytes; with one
 // wavefront per bag the step is bound by the latency of the offsets -> ids -> rows chain, not by bandwidth.
@@ -157,60 +237,66 @@ __global__ __launch_bounds__(kFwdThreads, 8) void forward_groups_kernel(
     const int64_t wid = (int64_t)blockIdx.x * (kFwdThreads / kWave) + (threadIdx.x >> 6);
     const int64_t i = wid / per_table;
     if (i >= n_tables) return;
-    const int32_t t = tables_of_class[i];
+    const int32_t t = __builtin_amdgcn_readfirstlane(tables_of_class[i]);   // (the same for the wavefront: its table's numbers stay scalar)
     const int sub = lane >> lpr_log2;
     const int li = lane & (LPR - 1);        // lane inside its group
     const int lc = li * V;
-    const int64_t b = (wid - i * per_table) * G + sub;
+    const int32_t b = (int32_t)((wid - i * per_table) * G) + sub;
     const bool has_bag = b < B;
     const int32_t d0 = D_off[t];
     const int D = D_off[t + 1] - d0;
     const int64_t R = row_base[t + 1] - row_base[t];
     const WT* table = weights + w_off[t];
-    int64_t start = 0, end = 0;
-    if (has_bag) {   // clamped so that a malformed offsets array can never take a read outside indices[0, nnz)
-        const int64_t bag = (int64_t)t * B + b;
-        start = offsets[bag];
-        end = offsets[bag + 1];
-        start = start < 0 ? 0 : (start > nnz ? nnz : start);
-        end = end < start ? start : (end > nnz ? nnz : end);
-    }
-    const int full_len = (int)((end - start) < (int64_t)0x7FFFFFFF ? (end - start) : (int64_t)0x7FFFFFFF);
+    const BagSpan bag = bag_span(offsets, t, B, b, nnz);
+    const int full_len = bag.len;
     // a bag far longer than its neighbours would keep the other groups of the wavefront waiting: such bags are left to
     // forward_long_bags_kernel, where a whole wavefront walks one bag
-    const bool is_long = full_len > long_bag_min(LPR, long_floor);
+    bool split = full_len > long_bag_min(LPR), is_long = false;
+    if (__any(split)) {
+        is_long = split && full_len > long_floor;
+        split = split && !is_long;
+    }
     const int len = is_long ? 0 : full_len;
     const int maxlen = wave_max_i32(len);   // longest bag of the wavefront: the loop bounds below are wave-uniform
+    __shared__ double s_total[V][kFwdThreads];
     float acc[V];
 #pragma unroll
     for (int v = 0; v < V; ++v) acc[v] = 0.f;
     const bool col_on = lc < D;
-    for (int base = 0; base < maxlen; base += LPR) {
-        int32_t my = -1;
-        if (base + li < len) {
-            const int64_t id = indices[start + base + li];
-            if (id >= 0 && id < R) my = (int32_t)id;
-            else atomicOr(err, 1);
-        }
-        const int nk = maxlen - base < LPR ? maxlen - base : LPR;
-        for (int k0 = 0; k0 < nk; k0 += U) {
-            raw_t x[U];
-#pragma unroll
-            for (int u = 0; u < U; ++u) {
-                // cross-lane read outside any lane-dependent condition; lanes of a finished bag read -1
-                const int32_t id = __shfl(my, (sub << lpr_log2) + ((k0 + u) & (LPR - 1)), kWave);
-                const bool on = (k0 + u) < nk && id >= 0 && col_on;
-                x[u] = on ? RowIO<WT>::load_raw(table + (int64_t)id * D + lc) : RowIO<WT>::zero_raw();
+    auto walk = [&](auto split_c) {
+        constexpr bool kSplit = decltype(split_c)::value;
+        LdsTotals<kSplit, V> total(s_total);
+        for (int base = 0; base < maxlen; base += LPR) {
+            int32_t my = -1;
+            if (base + li < len) {
+                const int64_t id = indices[(int64_t)bag.start + base + li];
+                if (id >= 0 && id < R) my = (int32_t)id;
+                else atomicOr(err, 1);
             }
+            const int nk = maxlen - base < LPR ? maxlen - base : LPR;
+            for (int k0 = 0; k0 < nk; k0 += U) {
+                raw_t x[U];
 #pragma unroll
-            for (int u = 0; u < U; ++u) RowIO<WT>::accumulate(x[u], acc);
+                for (int u = 0; u < U; ++u) {
+                    // cross-lane read outside any lane-dependent condition; lanes of a finished bag read -1
+                    const int32_t id = __shfl(my, (sub << lpr_log2) + ((k0 + u) & (LPR - 1)), kWave);
+                    const bool on = (k0 + u) < nk && id >= 0 && col_on;
+                    x[u] = on ? RowIO<WT>::load_raw(table + (int64_t)id * D + lc) : RowIO<WT>::zero_raw();
+                }
+#pragma unroll
+                for (int u = 0; u < U; ++u) RowIO<WT>::accumulate(x[u], acc);
+                if (kSplit && (split_run_ends(k0 + U, lpr_log2) || k0 + U >= nk)) total.add(acc, split);
+            }
         }
-    }
+        total.finish(acc, split);
+    };
+    if (__any(split)) walk(std::true_type{});
+    else walk(std::false_type{});
     const float lenf = (float)len;
     float scale = 1.f;
     if (MEAN) scale = len > 0 ? 1.f / lenf : 0.f;
     if (has_bag && col_on && !is_long) {
-        const int64_t out_elem = b * (int64_t)sumD + d0 + lc;
+        const int64_t out_elem = (int64_t)b * sumD + d0 + lc;
 #pragma unroll
         for (int v4 = 0; v4 < V; v4 += 4)
             store4_from_float(out, out_io, out_elem + v4, pooled<MEAN>(acc[v4], lenf, scale),
@@ -308,82 +394,87 @@ __global__ __launch_bounds__(kHotThreads, 8) void forward_hot_kernel(
     uint32_t* const cold = &s_cold[wv][sub << lpr_log2];
     uint16_t* const hot = &s_hot[wv][sub << lpr_log2];
     for (int pass = 0; pass < kHotPasses; ++pass) {
-        const int64_t b = (((int64_t)chunk * kHotPasses + pass) * kHotWaves + wv) * G + sub;
-        if ((((int64_t)chunk * kHotPasses + pass) * kHotWaves + wv) * G >= B) break;   // (the same for all lanes)
+        const int32_t b0 = ((chunk * kHotPasses + pass) * kHotWaves + wv) * G, b = b0 + sub;
+        if (b0 >= B) break;   // (the same for all lanes)
         const bool has_bag = b < B;
-        int64_t start = 0, end = 0;
-        if (has_bag) {   // clamped so that a malformed offsets array can never take a read outside indices[0, nnz)
-            const int64_t bag = (int64_t)t * B + b;
-            start = offsets[bag];
-            end = offsets[bag + 1];
-            start = start < 0 ? 0 : (start > nnz ? nnz : start);
-            end = end < start ? start : (end > nnz ? nnz : end);
-        }
-        const int full_len = (int)((end - start) < (int64_t)0x7FFFFFFF ? (end - start) : (int64_t)0x7FFFFFFF);
-        const bool is_long = full_len > long_bag_min(LPR, long_floor);   // left to forward_long_bags_kernel
+        const BagSpan bag = bag_span(offsets, t, B, b, nnz);
+        const int full_len = bag.len;
+        bool split = full_len > long_bag_min(LPR);
+        const bool is_long = split && full_len > long_floor;   // left to forward_long_bags_kernel
+        split = split && !is_long;
         const int len = is_long ? 0 : full_len;
         const int maxlen = wave_max_i32(len);
         float acc[V];
 #pragma unroll
         for (int v = 0; v < V; ++v) acc[v] = 0.f;
-        for (int base = 0; base < maxlen; base += LPR) {
-            int32_t my = -1;
-            if (base + li < len) {
-                const int64_t id = indices[start + base + li];
-                if (id >= 0 && id < R) my = (int32_t)id;
-                else atomicOr(err, 1);
-            }
-            int slot = -1;
-            if (my >= 0 && nh > 0) {
-                uint32_t hsh = hot_hash((uint32_t)my);
-                for (;;) {
-                    const uint32_t tid = s_tab_id[hsh];
-                    if (tid == kHotEmpty) break;
-                    if (tid == (uint32_t)my) {
-                        slot = (int)s_tab_slot[hsh];
-                        break;
+        auto walk = [&](auto split_c) {
+            constexpr bool kSplit = decltype(split_c)::value;
+            constexpr int kU = kSplit ? (V == 8 ? 2 : 4) : U;   // the totals take the registers of the other rows   // rows in flight: the totals take the registers of the others
+            Totals<kSplit, V> total;
+            for (int base = 0; base < maxlen; base += LPR) {
+                int32_t my = -1;
+                if (base + li < len) {
+                    const int64_t id = indices[(int64_t)bag.start + base + li];
+                    if (id >= 0 && id < R) my = (int32_t)id;
+                    else atomicOr(err, 1);
+                }
+                int slot = -1;
+                if (my >= 0 && nh > 0) {
+                    uint32_t hsh = hot_hash((uint32_t)my);
+                    for (;;) {
+                        const uint32_t tid = s_tab_id[hsh];
+                        if (tid == kHotEmpty) break;
+                        if (tid == (uint32_t)my) {
+                            slot = (int)s_tab_slot[hsh];
+                            break;
+                        }
+                        hsh = (hsh + 1u) & (kHotTab - 1u);
                     }
-                    hsh = (hsh + 1u) & (kHotTab - 1u);
                 }
-            }
-            // this lane group's cold ids and hot slots, each list in bag order
-            const bool is_cold = my >= 0 && slot < 0, is_hot = slot >= 0;
-            const uint32_t mc = (uint32_t)(__ballot(is_cold) >> (sub << lpr_log2)) & gmask;
-            const uint32_t mh = (uint32_t)(__ballot(is_hot) >> (sub << lpr_log2)) & gmask;
-            if (is_cold) cold[__popc(mc & below)] = (uint32_t)my;
-            if (is_hot) hot[__popc(mh & below)] = (uint16_t)slot;
-            __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
-            const int nc = __popc(mc), nhh = __popc(mh);
-            const int ncmax = wave_max_i32(nc), nhmax = wave_max_i32(nhh);
-            for (int k0 = 0; k0 < ncmax; k0 += U) {
-                raw_t x[U];
+                // this lane group's cold ids and hot slots, each list in bag order
+                const bool is_cold = my >= 0 && slot < 0, is_hot = slot >= 0;
+                const uint32_t mc = (uint32_t)(__ballot(is_cold) >> (sub << lpr_log2)) & gmask;
+                const uint32_t mh = (uint32_t)(__ballot(is_hot) >> (sub << lpr_log2)) & gmask;
+                if (is_cold) cold[__popc(mc & below)] = (uint32_t)my;
+                if (is_hot) hot[__popc(mh & below)] = (uint16_t)slot;
+                __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
+                const int nc = __popc(mc), nhh = __popc(mh);
+                const int ncmax = wave_max_i32(nc), nhmax = wave_max_i32(nhh);
+                for (int k0 = 0; k0 < ncmax; k0 += kU) {
+                    raw_t x[kU];
 #pragma unroll
-                for (int u = 0; u < U; ++u) {
-                    const uint32_t id = cold[(k0 + u) & (LPR - 1)];
-                    const bool on = (k0 + u) < nc && col_on;
-                    x[u] = on ? RowIO<WT>::load_raw(table + (int64_t)id * D + lc) : RowIO<WT>::zero_raw();
+                    for (int u = 0; u < kU; ++u) {
+                        const uint32_t id = cold[(k0 + u) & (LPR - 1)];
+                        const bool on = (k0 + u) < nc && col_on;
+                        x[u] = on ? RowIO<WT>::load_raw(table + (int64_t)id * D + lc) : RowIO<WT>::zero_raw();
+                    }
+#pragma unroll
+                    for (int u = 0; u < kU; ++u) RowIO<WT>::accumulate(x[u], acc);
+                    if (kSplit && (split_run_ends(k0 + kU, lpr_log2) || k0 + kU >= ncmax)) total.add(acc, split);
                 }
+                for (int k0 = 0; k0 < nhmax; k0 += 4) {
+                    raw_t x[4];
 #pragma unroll
-                for (int u = 0; u < U; ++u) RowIO<WT>::accumulate(x[u], acc);
-            }
-            for (int k0 = 0; k0 < nhmax; k0 += 4) {
-                raw_t x[4];
+                    for (int u = 0; u < 4; ++u) {
+                        const int sl = hot[(k0 + u) & (LPR - 1)];
+                        const bool on = (k0 + u) < nhh;
+                        x[u] = on ? s_rows[(sl << lpr_log2) + li] : RowIO<WT>::zero_raw();
+                    }
 #pragma unroll
-                for (int u = 0; u < 4; ++u) {
-                    const int sl = hot[(k0 + u) & (LPR - 1)];
-                    const bool on = (k0 + u) < nhh;
-                    x[u] = on ? s_rows[(sl << lpr_log2) + li] : RowIO<WT>::zero_raw();
+                    for (int u = 0; u < 4; ++u) RowIO<WT>::accumulate(x[u], acc);
+                    if (kSplit && (split_run_ends(k0 + 4, lpr_log2) || k0 + 4 >= nhmax)) total.add(acc, split);
                 }
-#pragma unroll
-                for (int u = 0; u < 4; ++u) RowIO<WT>::accumulate(x[u], acc);
+                __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");   // the lists are free for the next round
             }
-            __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");   // the lists are free for the next round
-        }
+            total.finish(acc, split);
+        };
+        if (__any(split)) walk(std::true_type{});
+        else walk(std::false_type{});
         const float lenf = (float)len;
         float scale = 1.f;
         if (MEAN) scale = len > 0 ? 1.f / lenf : 0.f;
         if (has_bag && col_on && !is_long) {
-            const int64_t out_elem = b * (int64_t)sumD + d0 + lc;
+            const int64_t out_elem = (int64_t)b * sumD + d0 + lc;
 #pragma unroll
             for (int v4 = 0; v4 < V; v4 += 4)
                 store4_from_float(out, out_io, out_elem + v4, pooled<MEAN>(acc[v4], lenf, scale),
@@ -410,12 +501,13 @@ __global__ __launch_bounds__(kFwdThreads, 4) void forward_long_bags_kernel(
     const int64_t wid = (int64_t)blockIdx.x * (kFwdThreads / kWave) + (threadIdx.x >> 6);
     const int64_t i = wid / per_table;
     if (i >= n_tables) return;
-    const int32_t t = tables_of_class[i];
+    const int32_t t = __builtin_amdgcn_readfirstlane(tables_of_class[i]);   // (the same for the wavefront: its table's numbers stay scalar)
     const int32_t d0 = D_off[t];
     const int D = D_off[t + 1] - d0;
     // the bound of the table's class: lanes per row as the host classifies them (power of two, at least 4)
     const int nl = (D + V - 1) / V;
-    const int bound = long_bag_min(nl > 16 ? 32 : (nl > 8 ? 16 : (nl > 4 ? 8 : 4)), long_floor);
+    const int least = long_bag_min(nl > 16 ? 32 : (nl > 8 ? 16 : (nl > 4 ? 8 : 4)));
+    const int bound = least > long_floor ? least : long_floor;
     const int64_t first = (wid - i * per_table) << scan_log2;
     const int64_t last = first + scan < (int64_t)B ? first + scan : (int64_t)B;
     for (int64_t b0 = first; b0 < last; b0 += kWave) {   // (wave-uniform)

@@ -54,3 +54,53 @@ def test_bags_on_both_sides_of_the_bound(dtype, T, B, mean):
     assert torch.equal(tbe.forward(tabs, *args), out)
     assert not tbe.poll_index_error()
     tbe.close()
+
+
+def _sum_by_wavefront(x, lanes):
+    """fp32 sum over dim 1 as a whole wavefront makes it: 64 / lanes groups take the rows in turn and are folded pairwise."""
+    G = 64 // lanes
+    acc = torch.zeros(x.shape[0], G, x.shape[2])
+    for k in range(x.shape[1]):
+        acc[:, k % G] += x[:, k]
+    while acc.shape[1] > 1:
+        acc = acc[:, 0::2] + acc[:, 1::2]
+    return acc[:, 0]
+
+
+def _sum_by_lane_group(x, lanes):
+    """... as a lane group makes it above the class bound: runs of 8 rows (16 of rows of 32 lanes, 4 of rows of at most 4) in fp32,
+    their sums in 64 bits."""
+    run = 16 if lanes == 32 else min(8, max(4, lanes))
+    total = torch.zeros(x.shape[0], x.shape[2], dtype=torch.float64)
+    for k0 in range(0, x.shape[1], run):
+        acc = torch.zeros(x.shape[0], x.shape[2])
+        for k in range(k0, min(k0 + run, x.shape[1])):
+            acc += x[:, k]
+        total += acc.double()
+    return total.float()
+
+
+@pytest.mark.parametrize("D,L", [(8, 100), (16, 40), (32, 40), (32, 100), (64, 62), (128, 100)])
+def test_error_above_the_class_bounds(D, L):
+    """A lane group that walks a bag above its class bound is no further from the sum in 64 bits than a whole wavefront is."""
+    if not torch.cuda.is_available():
+        pytest.skip("no GPU")
+    from paper_2508_03854_amd import TBE, binding
+    T, B, R = 6, 3000, 700
+    g = torch.Generator().manual_seed(D + L)
+    w = torch.randn(T, R, D, generator=g)
+    idx = torch.randint(0, R, (T, B, L), generator=g)
+    tbe = TBE([R] * T, [D] * T, "f32")
+    assert tbe.debug_forward_kernels(B, idx.numel()) == binding.FWD_LANE_GROUPS | binding.FWD_LONG_BAGS
+    out = tbe.forward(w.view(-1).cuda(), idx.view(-1).cuda(), torch.arange(T * B + 1, dtype=torch.int64).cuda() * L, B, "sum").cpu()
+    lanes = 1 << ((D + 3) // 4 - 1).bit_length()
+    err = err_wave = 0.0
+    for t in range(T):
+        x = w[t][idx[t]]
+        want = x.double().sum(1)
+        got = out[:, t * D:(t + 1) * D]
+        assert torch.equal(got, _sum_by_lane_group(x, lanes))
+        err += float(((got.double() - want) ** 2).sum())
+        err_wave += float(((_sum_by_wavefront(x, lanes).double() - want) ** 2).sum())
+    assert err <= err_wave
+    tbe.close()
