@@ -22,7 +22,26 @@ constexpr int kFwdThreads = 256;
 __device__ __forceinline__ int long_bag_min(const int lanes_per_row) {
     return lanes_per_row > 16 ? 64 : (lanes_per_row > 8 ? 48 : 32);
 }
-// `floor` raises the bound for batches whose ordinary bags are that long themselves (long_bag_floor).
+// Of a table whose ordinary bags are that long themselves a lane group walks them all the same: only bags of more than twice the
+// table's mean length are long, and those of more than kLongBagMax ids.  The mean is the table's own: one table of bags of 100 ids among
+// 25 of 5, 32 fp32 columns, us, class bounds alone / twice the mean of the whole batch / of the table: 4096 bags 908 / 71 / 28, 65536
+// bags 1145 / 1153 / 189.  Class bounds alone against this: 17000 bags of 40 ids, 32 fp32 columns 444 / 13; 26 tables x 4096 bags,
+// 1 + Poisson(30) ids, 64 binary16 columns 283 / 43; of 100 ids, 128 fp32 columns 2625 / 318 (part of that by the shorter runs of
+// long_scan_log2).  Bags of 200 ids with the limit at 128 / 512: 17000 bags, 32 columns 37 / 53 us, 16 tables x 32768 bags 1084 / 715.
+constexpr int kLongBagMax = 128;
+// len: of a bag above long_bag_min; lookups: ids of its table (of a malformed offsets array any number, and any answer will do)
+__device__ __forceinline__ bool long_bag(const int len, const int64_t lookups, const int32_t B) {
+    return len > kLongBagMax || (uint64_t)(uint32_t)len * (uint32_t)B > 2u * (uint64_t)lookups;
+}
+// the same as a bound, for a kernel that needs it before it has seen a bag
+__device__ __forceinline__ int long_bag_bound(const int lanes_per_row, const int64_t lookups, const int32_t B) {
+    int mean2 = 0;   // the largest number up to kLongBagMax that is at most twice the mean
+#pragma unroll
+    for (int step = kLongBagMax; step > 0; step >>= 1)
+        if (mean2 + step <= kLongBagMax && (uint64_t)(uint32_t)(mean2 + step) * (uint32_t)B <= 2u * (uint64_t)lookups) mean2 += step;
+    const int least = long_bag_min(lanes_per_row);
+    return least > mean2 ? least : mean2;
+}
 // first position and ids of bag b of table t (0 ids from bag B on), clamped so that a malformed offsets array can never take a read
 // outside indices[0, nnz); positions are below 2^32
 struct BagSpan {
@@ -41,6 +60,10 @@ __device__ __forceinline__ BagSpan bag_span(const IdxView offsets, const int32_t
     }
     return r;
 }
+__device__ __forceinline__ int64_t table_lookups(const IdxView offsets, const int32_t t, const int32_t B) {
+    return offsets[(int64_t)(t + 1) * B] - offsets[(int64_t)t * B];
+}
+
 // NC = number of 64-lane column chunks a row needs (1 when D <= 64 * kVec); U = rows in flight per group.
 // The pooled value that is stored: the sum, or for mean pooling sum / L - the product with the reciprocal, corrected
 // once by its exact residual (the usual refinement step of a division), so that a mean that is exactly representable
@@ -226,7 +249,7 @@ template <typename WT, int U, bool MEAN>
 __global__ __launch_bounds__(kFwdThreads, 8) void forward_groups_kernel(
     const WT* __restrict__ weights, const IdxView indices, const IdxView offsets,
     const int32_t* __restrict__ D_off, const int64_t* __restrict__ w_off, const int64_t* __restrict__ row_base,
-    const int32_t* __restrict__ tables_of_class, const int32_t n_tables, const int lpr_log2, const int long_floor, const int32_t B,
+    const int32_t* __restrict__ tables_of_class, const int32_t n_tables, const int lpr_log2, const int32_t B,
     const int64_t nnz, const int32_t sumD, void* __restrict__ out, const int out_io, int32_t* err) {
     constexpr int V = RowIO<WT>::kVec;
     using raw_t = typename RowIO<WT>::raw_t;
@@ -253,7 +276,7 @@ __global__ __launch_bounds__(kFwdThreads, 8) void forward_groups_kernel(
     // forward_long_bags_kernel, where a whole wavefront walks one bag
     bool split = full_len > long_bag_min(LPR), is_long = false;
     if (__any(split)) {
-        is_long = split && full_len > long_floor;
+        is_long = split && long_bag(full_len, table_lookups(offsets, t, B), B);
         split = split && !is_long;
     }
     const int len = is_long ? 0 : full_len;
@@ -328,7 +351,7 @@ template <typename WT, int U, bool MEAN>
 __global__ __launch_bounds__(kHotThreads, 8) void forward_hot_kernel(
     const WT* __restrict__ weights, const IdxView indices, const IdxView offsets,
     const int32_t* __restrict__ D_off, const int64_t* __restrict__ w_off, const int64_t* __restrict__ row_base,
-    const int32_t* __restrict__ tables_of_class, const int32_t n_tables, const int lpr_log2, const int long_floor, const int32_t B,
+    const int32_t* __restrict__ tables_of_class, const int32_t n_tables, const int lpr_log2, const int32_t B,
     const int64_t nnz, const int32_t sumD, void* __restrict__ out, const int out_io, int32_t* err,
     const uint32_t* __restrict__ hot_ids, const uint32_t* __restrict__ hot_n, const int32_t chunks_per_table) {
     constexpr int V = RowIO<WT>::kVec;
@@ -338,6 +361,7 @@ __global__ __launch_bounds__(kHotThreads, 8) void forward_hot_kernel(
     __shared__ uint16_t s_tab_slot[kHotTab];
     __shared__ uint32_t s_ids[kHotRows];
     __shared__ uint32_t s_n;
+    __shared__ int64_t s_lookups;
     __shared__ uint32_t s_cold[kHotWaves][kWave];
     __shared__ uint16_t s_hot[kHotWaves][kWave];
     const int lane = lane_id();
@@ -361,6 +385,7 @@ __global__ __launch_bounds__(kHotThreads, 8) void forward_hot_kernel(
     // and an id table that named one row where another, or none, was copied would give wrong sums.
     const int cap = (kHotRowBytes / 16) >> lpr_log2;
     if (threadIdx.x == 0) s_n = hot_n[t];
+    if (threadIdx.x == kWave) s_lookups = table_lookups(offsets, t, B);
     for (int k = threadIdx.x; k < kHotTab; k += kHotThreads) s_tab_id[k] = kHotEmpty;
     __syncthreads();
     int nh = s_n < (uint32_t)kHotRows ? (int)s_n : kHotRows;
@@ -400,7 +425,7 @@ __global__ __launch_bounds__(kHotThreads, 8) void forward_hot_kernel(
         const BagSpan bag = bag_span(offsets, t, B, b, nnz);
         const int full_len = bag.len;
         bool split = full_len > long_bag_min(LPR);
-        const bool is_long = split && full_len > long_floor;   // left to forward_long_bags_kernel
+        const bool is_long = split && long_bag(full_len, s_lookups, B);   // left to forward_long_bags_kernel
         split = split && !is_long;
         const int len = is_long ? 0 : full_len;
         const int maxlen = wave_max_i32(len);
@@ -492,8 +517,8 @@ template <typename WT, bool MEAN>
 __global__ __launch_bounds__(kFwdThreads, 4) void forward_long_bags_kernel(
     const WT* __restrict__ weights, const IdxView indices, const IdxView offsets,
     const int32_t* __restrict__ D_off, const int64_t* __restrict__ w_off, const int64_t* __restrict__ row_base,
-    const int32_t* __restrict__ tables_of_class, const int32_t n_tables, const int scan_log2, const int long_floor, const int32_t B,
-    const int64_t nnz, const int32_t sumD, void* __restrict__ out, const int out_io, int32_t* err) {
+    const int32_t* __restrict__ tables_of_class, const int32_t n_tables, const int scan_log2, const int32_t B, const int64_t nnz,
+    const int32_t sumD, void* __restrict__ out, const int out_io, int32_t* err) {
     constexpr int V = RowIO<WT>::kVec;
     const int lane = lane_id();
     const int64_t scan = (int64_t)1 << scan_log2;
@@ -506,8 +531,7 @@ __global__ __launch_bounds__(kFwdThreads, 4) void forward_long_bags_kernel(
     const int D = D_off[t + 1] - d0;
     // the bound of the table's class: lanes per row as the host classifies them (power of two, at least 4)
     const int nl = (D + V - 1) / V;
-    const int least = long_bag_min(nl > 16 ? 32 : (nl > 8 ? 16 : (nl > 4 ? 8 : 4)));
-    const int bound = least > long_floor ? least : long_floor;
+    const int bound = long_bag_bound(nl > 16 ? 32 : (nl > 8 ? 16 : (nl > 4 ? 8 : 4)), table_lookups(offsets, t, B), B);
     const int64_t first = (wid - i * per_table) << scan_log2;
     const int64_t last = first + scan < (int64_t)B ? first + scan : (int64_t)B;
     for (int64_t b0 = first; b0 < last; b0 += kWave) {   // (wave-uniform)
@@ -581,15 +605,6 @@ static int hot_chunks(const tbe_handle* h, const int c, const int32_t B) {
     const int cpt = (int)(((int64_t)B + bags_per_wg - 1) / bags_per_wg);
     return (int64_t)h->fwd_count[c] * cpt >= (h->hot_min_set ? h->hot_min_workgroups : kHotWorkgroups[c - 1]) ? cpt : 0;
 }
-// Twice the batch's mean bag length, up to kLongFloorMax ids: a lane group walks an ordinary bag whatever its length, and only
-// bags far above their neighbours are left to whole wavefronts.  With the class bounds alone, us (before -> with this and the
-// shorter runs below): 17000 bags of 40 ids, 32 fp32 columns 443 -> 13.5; 26 tables x 4096 bags, 1 + Poisson(30) ids, 64 binary16
-// columns 282 -> 40; of 100 ids, 128 fp32 columns 2627 -> 309.
-constexpr int kLongFloorMax = 128;
-static int long_bag_floor(const tbe_handle* h, const int32_t B, const int64_t nnz) {
-    const int64_t twice = 2 * nnz / ((int64_t)h->T * B);
-    return (int)(twice < kLongFloorMax ? twice : kLongFloorMax);
-}
 // Bags that a wavefront of forward_long_bags_kernel looks at: 256 where that fills the chip, fewer (down to 4) in smaller
 // batches, where long bags would wait for one another in a few wavefronts.  Lognormal bags of 35 ids on average, us, 256 bags a
 // wavefront -> this: 26 tables x 4096 bags x 32 fp32 columns 324 -> 82, 16 tables x 32768 bags 470 -> 347; where no bag is long
@@ -633,7 +648,6 @@ static void launch_forward_groups(const tbe_handle* h, const void* tables, const
                                   hipStream_t s) {
     const WT* w = static_cast<const WT*>(tables);
     const int wpb = kFwdThreads / kWave;
-    const int long_floor = long_bag_floor(h, B, nnz);
     for (int c = 1; c < 5; ++c) {
         const int n = h->fwd_count[c];
         if (n == 0) continue;
@@ -648,20 +662,20 @@ static void launch_forward_groups(const tbe_handle* h, const void* tables, const
             const dim3 hgrid((unsigned)((int64_t)n * cpt));
             if (mean)
                 forward_hot_kernel<WT, 8, true><<<hgrid, kHotThreads, 0, s>>>(
-                    w, indices, offsets, d_D_off, h->d_w_off, h->d_row_base, list, n, lpr_log2, long_floor, B, nnz, h->sumD, out, out_io,
+                    w, indices, offsets, d_D_off, h->d_w_off, h->d_row_base, list, n, lpr_log2, B, nnz, h->sumD, out, out_io,
                     h->d_err, h->d_hot_ids, h->d_hot_n, cpt);
             else
                 forward_hot_kernel<WT, 8, false><<<hgrid, kHotThreads, 0, s>>>(
-                    w, indices, offsets, d_D_off, h->d_w_off, h->d_row_base, list, n, lpr_log2, long_floor, B, nnz, h->sumD, out, out_io,
+                    w, indices, offsets, d_D_off, h->d_w_off, h->d_row_base, list, n, lpr_log2, B, nnz, h->sumD, out, out_io,
                     h->d_err, h->d_hot_ids, h->d_hot_n, cpt);
             continue;
         }
         if (mean)
             forward_groups_kernel<WT, 8, true><<<grid, kFwdThreads, 0, s>>>(
-                w, indices, offsets, d_D_off, h->d_w_off, h->d_row_base, list, n, lpr_log2, long_floor, B, nnz, h->sumD, out, out_io, h->d_err);
+                w, indices, offsets, d_D_off, h->d_w_off, h->d_row_base, list, n, lpr_log2, B, nnz, h->sumD, out, out_io, h->d_err);
         else
             forward_groups_kernel<WT, 8, false><<<grid, kFwdThreads, 0, s>>>(
-                w, indices, offsets, d_D_off, h->d_w_off, h->d_row_base, list, n, lpr_log2, long_floor, B, nnz, h->sumD, out, out_io, h->d_err);
+                w, indices, offsets, d_D_off, h->d_w_off, h->d_row_base, list, n, lpr_log2, B, nnz, h->sumD, out, out_io, h->d_err);
     }
     // the bags those launches left out (the four classes' tables follow one another in the list)
     const int n_all = h->fwd_count[1] + h->fwd_count[2] + h->fwd_count[3] + h->fwd_count[4];
@@ -672,10 +686,10 @@ static void launch_forward_groups(const tbe_handle* h, const void* tables, const
         const int32_t* list = h->d_fwd_tables + h->fwd_first[1];
         if (mean)
             forward_long_bags_kernel<WT, true><<<grid, kFwdThreads, 0, s>>>(
-                w, indices, offsets, d_D_off, h->d_w_off, h->d_row_base, list, n_all, scan_log2, long_floor, B, nnz, h->sumD, out, out_io, h->d_err);
+                w, indices, offsets, d_D_off, h->d_w_off, h->d_row_base, list, n_all, scan_log2, B, nnz, h->sumD, out, out_io, h->d_err);
         else
             forward_long_bags_kernel<WT, false><<<grid, kFwdThreads, 0, s>>>(
-                w, indices, offsets, d_D_off, h->d_w_off, h->d_row_base, list, n_all, scan_log2, long_floor, B, nnz, h->sumD, out, out_io, h->d_err);
+                w, indices, offsets, d_D_off, h->d_w_off, h->d_row_base, list, n_all, scan_log2, B, nnz, h->sumD, out, out_io, h->d_err);
     }
 }
 

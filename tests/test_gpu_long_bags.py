@@ -104,3 +104,38 @@ def test_error_above_the_class_bounds(D, L):
         err_wave += float(((_sum_by_wavefront(x, lanes).double() - want) ** 2).sum())
     assert err <= err_wave
     tbe.close()
+
+
+@pytest.mark.parametrize("D,long,short", [(32, 100, 5), (64, 70, 3), (128, 128, 1)])
+def test_bound_follows_the_tables_own_mean(D, long, short):
+    """One table of long bags among tables of short ones: its ordinary bags are summed by lane groups and not by whole wavefronts,
+    and a bag of the same length among the short ones by a whole wavefront."""
+    if not torch.cuda.is_available():
+        pytest.skip("no GPU")
+    from paper_2508_03854_amd import TBE, binding
+    T, B, R = 9, 2100, 500
+    g = torch.Generator().manual_seed(D)
+    lens = torch.full((T, B), short)
+    lens[4] = long
+    lens[2, ::100] = long
+    lens[4, ::70] = 2 * long + 1
+    off = torch.zeros(T * B + 1, dtype=torch.int64)
+    off[1:] = torch.cumsum(lens.view(-1), 0)
+    w = torch.randn(T, R, D, generator=g)
+    idx = torch.randint(0, R, (int(off[-1]),), generator=g)
+    tbe = TBE([R] * T, [D] * T, "f32")
+    assert tbe.debug_forward_kernels(B, idx.numel()) == binding.FWD_LANE_GROUPS | binding.FWD_LONG_BAGS
+    lanes = D // 4
+    for it in (torch.int64, torch.int32):
+        out = tbe.forward_ex(w.view(-1).cuda(), idx.cuda().to(it), off.cuda().to(it), B, "sum").cpu()
+
+        def check(t, bags, sums):
+            at = off[t * B + bags]
+            x = w[t][idx[at[:, None] + torch.arange(int(lens[t, bags[0]]))]]
+            assert torch.equal(out[bags, t * D:(t + 1) * D], sums(x, lanes)), (it, t)
+
+        every = torch.arange(B)
+        check(4, every[every % 70 != 0], _sum_by_lane_group)
+        check(4, every[::70], _sum_by_wavefront)
+        check(2, every[::100], _sum_by_wavefront)
+    tbe.close()
