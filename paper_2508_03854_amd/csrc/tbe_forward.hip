@@ -48,9 +48,9 @@ struct BagSpan {
     uint32_t start;
     int len;
 };
-__device__ __forceinline__ BagSpan bag_span(const IdxView offsets, const int32_t t, const int32_t B, const int32_t b, const int64_t nnz) {
+__device__ __forceinline__ BagSpan bag_span(const IdxView offsets, const int32_t t, const int32_t B, const uint32_t b, const int64_t nnz) {
     BagSpan r{0u, 0};
-    if (b < B) {
+    if (b < (uint32_t)B) {
         const int64_t bag = (int64_t)t * B + b;
         int64_t start = offsets[bag], end = offsets[bag + 1];
         start = start < 0 ? 0 : (start > nnz ? nnz : start);
@@ -264,8 +264,8 @@ __global__ __launch_bounds__(kFwdThreads, 8) void forward_groups_kernel(
     const int sub = lane >> lpr_log2;
     const int li = lane & (LPR - 1);        // lane inside its group
     const int lc = li * V;
-    const int32_t b = (int32_t)((wid - i * per_table) * G) + sub;
-    const bool has_bag = b < B;
+    const uint32_t b = (uint32_t)((wid - i * per_table) * G) + (uint32_t)sub;   // (below 2^31 + 64)
+    const bool has_bag = b < (uint32_t)B;
     const int32_t d0 = D_off[t];
     const int D = D_off[t + 1] - d0;
     const int64_t R = row_base[t + 1] - row_base[t];
@@ -419,9 +419,9 @@ __global__ __launch_bounds__(kHotThreads, 8) void forward_hot_kernel(
     uint32_t* const cold = &s_cold[wv][sub << lpr_log2];
     uint16_t* const hot = &s_hot[wv][sub << lpr_log2];
     for (int pass = 0; pass < kHotPasses; ++pass) {
-        const int32_t b0 = ((chunk * kHotPasses + pass) * kHotWaves + wv) * G, b = b0 + sub;
-        if (b0 >= B) break;   // (the same for all lanes)
-        const bool has_bag = b < B;
+        const uint32_t b0 = (uint32_t)((chunk * kHotPasses + pass) * kHotWaves + wv) * (uint32_t)G, b = b0 + (uint32_t)sub;
+        if (b0 >= (uint32_t)B) break;   // (the same for all lanes)
+        const bool has_bag = b < (uint32_t)B;
         const BagSpan bag = bag_span(offsets, t, B, b, nnz);
         const int full_len = bag.len;
         bool split = full_len > long_bag_min(LPR);
