@@ -245,9 +245,10 @@ tbe_status tbe_poll_index_error(tbe_handle* h);
  *   TBE_TUNE_HOT_ROWS_MIN_WORKGROUPS  The forward keeps, for every table, a copy of the rows that had the most lookups
  *       (at least 513) in the LAST backward call on this handle in on-chip memory (the handle remembers their ids: a hint, the
  *       pooled sums are the same whatever it holds) and serves their lookups from there.  That path runs for a group
- *       of tables of one width when it fills at least `value` workgroups (until set: 768 for rows of 257 to 512 bytes, 1024 for
- *       129 to 256, never for narrower ones; 0: whenever the width allows it, also for batches so small that they would
- *       otherwise take one wavefront per bag; negative: never). */
+ *       of tables of one width when it fills at least `value` workgroups (0: whenever the width allows it, also for batches so
+ *       small that they would otherwise take one wavefront per bag; negative: never).  TBE_TUNE_AUTO, which a handle starts
+ *       with: 768 for rows of 257 to 512 bytes, 1024 for 129 to 256, never for narrower ones. */
+#define TBE_TUNE_AUTO INT64_MIN
 typedef enum { TBE_TUNE_HOT_ROWS_MIN_WORKGROUPS = 0 } tbe_tunable;
 tbe_status tbe_set_tunable(tbe_handle* h, tbe_tunable which, int64_t value);
 

@@ -21,6 +21,7 @@ I64, I32 = 0, 1                       # tbe_index_dtype
 IO_F32, IO_F16, IO_BF16 = 0, 1, 2     # tbe_io_dtype
 FWD_WAVEFRONT_PER_BAG, FWD_LANE_GROUPS, FWD_HOT_ROWS, FWD_LONG_BAGS = 1, 2, 4, 8   # TBE_FWD_*
 TUNABLES = {"hot_rows_min_workgroups": 0}   # tbe_tunable
+TUNE_AUTO = -(1 << 63)                 # TBE_TUNE_AUTO
 _IDX = {torch.int64: I64, torch.int32: I32}
 _IO = {torch.float32: IO_F32, torch.float16: IO_F16, torch.bfloat16: IO_BF16}
 

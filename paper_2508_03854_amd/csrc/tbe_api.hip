@@ -630,7 +630,7 @@ tbe_status tbe_replica_mean(tbe_handle* h, void* const* replicas, int32_t M, siz
 tbe_status tbe_set_tunable(tbe_handle* h, tbe_tunable which, int64_t value) {
     if (!h) return TBE_EINVAL;
     switch (which) {
-        case TBE_TUNE_HOT_ROWS_MIN_WORKGROUPS: h->hot_min_workgroups = value; h->hot_min_set = true; return TBE_OK;
+        case TBE_TUNE_HOT_ROWS_MIN_WORKGROUPS: h->hot_min_workgroups = value; return TBE_OK;
     }
     return TBE_EINVAL;
 }

@@ -599,11 +599,11 @@ static bool forward_small_long(const tbe_handle* h, const int32_t B, const int64
 constexpr int64_t kHotWorkgroups[2] = {768, 1024};
 // workgroups per table with which the lane-group class c keeps hot rows in LDS; 0: it does not
 static int hot_chunks(const tbe_handle* h, const int c, const int32_t B) {
-    if (!h->d_hot_ids || h->hot_min_workgroups < 0) return 0;
-    if (!h->hot_min_set && c > 2) return 0;
+    const bool by_class = h->hot_min_workgroups == TBE_TUNE_AUTO;
+    if (!h->d_hot_ids || (by_class ? c > 2 : h->hot_min_workgroups < 0)) return 0;
     const int64_t bags_per_wg = (int64_t)kHotPasses * kHotWaves * (kWave >> (6 - c));
     const int cpt = (int)(((int64_t)B + bags_per_wg - 1) / bags_per_wg);
-    return (int64_t)h->fwd_count[c] * cpt >= (h->hot_min_set ? h->hot_min_workgroups : kHotWorkgroups[c - 1]) ? cpt : 0;
+    return (int64_t)h->fwd_count[c] * cpt >= (by_class ? kHotWorkgroups[c - 1] : h->hot_min_workgroups) ? cpt : 0;
 }
 // Bags that a wavefront of forward_long_bags_kernel looks at: 256 where that fills the chip, fewer (down to 4) in smaller
 // batches, where long bags would wait for one another in a few wavefronts.  Lognormal bags of 35 ids on average, us, 256 bags a

@@ -67,10 +67,9 @@ struct tbe_handle {
     // the same forward result; null when the handle has too many tables to keep one.
     uint32_t* d_hot_ids = nullptr;    // [T][kHotRows]
     uint32_t* d_hot_n = nullptr;      // [T]
-    // The forward stages hot rows in LDS when a width class fills this many workgroups; < 0: never.  Until the tunable is set the
-    // line follows the class instead (hot_chunks).
-    int64_t hot_min_workgroups = 256;
-    bool hot_min_set = false;
+    // The forward stages hot rows in LDS when a width class fills this many workgroups; < 0: never, except TBE_TUNE_AUTO, where the
+    // line follows the class (hot_chunks).
+    int64_t hot_min_workgroups = TBE_TUNE_AUTO;
     int fwd_first[7] = {0, 0, 0, 0, 0, 0, 0};
     int fwd_count[7] = {0, 0, 0, 0, 0, 0, 0};
     // timing

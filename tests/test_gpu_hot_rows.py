@@ -178,3 +178,25 @@ def test_forward_while_a_backward_over_other_tables_rewrites_the_hint(H):
     for out in outs:
         H.assert_close(out.cpu().numpy(), want, H.RTOL_F32, cfg.w_scale, "forward next to a backward over other tables")
     tbe.close()
+
+
+@pytest.mark.parametrize("dtype", ["f32", "f16"])
+@pytest.mark.parametrize("lanes,bags_per_workgroup,line", [(32, 256, 768), (16, 512, 1024), (8, 1024, None), (4, 2048, None)])
+def test_line_of_a_handle_without_tunable(dtype, lanes, bags_per_workgroup, line):
+    """Hot rows from 768 / 1024 workgroups on, never for rows of at most 8 lanes; TUNE_AUTO brings that back after another value.
+    (The query launches nothing.)"""
+    if not torch.cuda.is_available():
+        pytest.skip("no GPU")
+    D = lanes * (4 if dtype == "f32" else 8)
+    for T in ((line or 1024) - 1, line or 1024, 4000):
+        for B in (bags_per_workgroup, 3 * bags_per_workgroup + 1):
+            tbe = TBE([100] * T, [D] * T, dtype)
+            workgroups = T * ((B + bags_per_workgroup - 1) // bags_per_workgroup)
+            own = line is not None and workgroups >= line
+            for value, hot in ((None, own), (1, True), (binding.TUNE_AUTO, own), (-1, False), (workgroups + 1, False),
+                               (workgroups, True), (binding.TUNE_AUTO, own)):
+                if value is not None:
+                    tbe.set_tunable("hot_rows_min_workgroups", value)
+                kernels = tbe.debug_forward_kernels(B, 10 * T * B)
+                assert kernels == binding.FWD_LONG_BAGS | (binding.FWD_HOT_ROWS if hot else binding.FWD_LANE_GROUPS), (T, B, value)
+            tbe.close()
