@@ -364,9 +364,11 @@ __global__ __launch_bounds__(kSegThreads, kSegWaves) void seg_update_kernel(cons
     uint32_t i = blockIdx.x * (kSegThreads / kWave) + wave, step = nwaves, n1 = nblk, n = nblk, first = 0, again = 0;
     if (a.long_spans) {
         const uint32_t die = blockIdx.x & (kDies - 1u);
-        const uint32_t* const border = a.counters + kSpanWord + die;
-        const uint32_t b0 = border[0] >> lg, b1 = border[1] >> lg, b2 = border[kDies] >> lg;
-        const uint32_t b3 = die + 1u < kDies ? border[kDies + 1u] >> lg : nblk;
+        auto border = [&](const uint32_t k) {   // (as a scalar: it came from a vector load)
+            return (uint32_t)__builtin_amdgcn_readfirstlane((int)a.counters[kSpanWord + k]) >> lg;
+        };
+        const uint32_t b0 = border(die), b1 = border(die + 1u), b2 = border(die + kDies);
+        const uint32_t b3 = die + 1u < kDies ? border(die + kDies + 1u) : nblk;
         i = (blockIdx.x / kDies) * (kSegThreads / kWave) + wave;
         step = nwaves / kDies;
         n1 = b1 - b0;
