@@ -340,6 +340,9 @@ static_assert(kHotRows <= kSegThreads, "one thread per listed row");
 template <typename WT, bool MEAN, typename GT, int kSegWaves>
 __global__ __launch_bounds__(kSegThreads, kSegWaves) void seg_update_kernel(const SegArgs a) {
     constexpr int kSegUnroll = seg_unroll<1, MEAN, GT, kSegWaves>();
+    // ... of rows side by side: 8 would spill registers where every fragment comes with its bag's scale (ten tables of odd widths,
+    // 777 bags, binary16 gradients, the step with 8 / 6: 108.4 / 107.2 us; 32 tables x 8192 bags, 128 and 256 columns 497 / 492)
+    constexpr int kSideUnroll = MEAN && sizeof(GT) == 2 ? 6 : kSegUnroll;
     constexpr bool kFetch = kSegWaves == 8;   // the start of a pass is loaded for several of them (see kPassRowsLog2)
     constexpr bool kAhead = kSegWaves < 8;   // a row's weights are loaded ahead of its gradients (see the short rows above)
     const int lane = lane_id();
@@ -477,7 +480,7 @@ __global__ __launch_bounds__(kSegThreads, kSegWaves) void seg_update_kernel(cons
             WT* const wrow = wtab + (uint64_t)(gkey - rb) * (uint32_t)g.D;
             const uint32_t lmax = (uint32_t)wave_max_i32((int)glen);   // longest row of the round (wave-uniform loop bound)
             float acc[1][4] = {{0.f, 0.f, 0.f, 0.f}};
-            add_short<kSegUnroll, false, MEAN, GT>(acc, gcol, ga.pitch, lane_col, my_b, my_s, gs - win, lmax, glen);
+            add_short<kSideUnroll, false, MEAN, GT>(acc, gcol, ga.pitch, lane_col, my_b, my_s, gs - win, lmax, glen);
             adagrad_row<WT, 1>(acc, g, wrow, a.state + gkey, gv, gon, a.lr, a.eps, a.inv_c, a.state == nullptr);
             todo &= ~(((1ull << k) - 1ull) << r);
         }
