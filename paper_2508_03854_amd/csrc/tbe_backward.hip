@@ -226,8 +226,9 @@ __device__ __forceinline__ void adagrad_row_loaded(const float (&acc)[1][4], con
 // last); the bag ids of 64 lookups serve all the rounds they cover; a round's rows are of one table, so that its addresses start
 // from scalars and each costs one 32 x 32 + 64 bit multiply-add.  12 tables x 8192 bags of 20 uniform ids, 128 columns: 544 ->
 // 507 us.  The weights are loaded behind the gradients: ahead of them 507 -> 612 us there (the read and the write of a row then
-// lie further apart), 702 -> 727 us above.  Only the variant with the longest chain per row, 32-bit gradients of wide binary16
-// rows, gains by it (64 tables x 32768 bags of 31 ids: 4201 -> 4172 us; before all this 4188).
+// lie further apart), 702 -> 727 us above.  The variant of 7 wavefronts per SIMD, 32-bit gradients of wide binary16 rows, has them
+// ahead: 64 tables x 32768 bags of 31 ids 4271 -> 4242 us, half of the bags with mean pooling 2604 -> 2582, but 12 tables x 8192
+// bags of 20 uniform ids 833 -> 837 and x 4096 299 -> 302.
 //
 // NS lookups of short rows, of every lane group its own: number q0 .. q0+NS-1 of the group's glen, which lie in lanes off, off+1,
 // ... of (my_b, my_s).  UNIFORM: one group, so that all of this is the same in all lanes and stays on the scalar unit.
@@ -744,7 +745,7 @@ hipError_t launch_segment_update(const tbe_handle* h, const Workspace& w, char* 
         launch_dense(a, grad_io, mean, s);
         tm.done();
     }
-    // Rows of tables up to 256 columns wide go to the kernel that keeps 64 rows per wavefront, rows of wider tables
+    // Rows of tables up to 256 columns wide go to the kernel that takes them in passes of up to 32, rows of wider tables
     // to the one-wavefront-per-row kernel; a handle that holds both kinds runs both, each skipping the other's rows.
     const bool narrow = h->minD <= 256;
     const bool wide = h->maxD > 256;

@@ -728,7 +728,8 @@ hipError_t launch_forward(const tbe_handle* h, const void* tables, const int32_t
 // ---- non-pooled lookup -------------------------------------------------------------------------------------
 // out block of table t = [n_t, D_t], row i = W_t[indices[offsets[t] + i]]; the blocks follow one another.
 // A wavefront takes 64 consecutive positions: every lane resolves one lookup (table, source row, destination),
-// then the 16-byte fragments of all 64 rows are copied lane-parallel, four in flight per lane.
+// then the 16-byte fragments of all 64 rows are copied lane-parallel, one after the other in every lane: each is stored under its
+// lane's condition before the next is loaded.
 __device__ __forceinline__ int64_t wave_sum_i64(int64_t v) {
     for (int o = 1; o < kWave; o <<= 1) {
         const uint32_t lo = __shfl_xor((uint32_t)(v & 0xFFFFFFFFll), o, kWave);

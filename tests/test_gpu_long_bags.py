@@ -1,5 +1,5 @@
-"""Long bags of the lane-group forward classes: the bound that follows the batch's mean bag length, and wavefronts that look at 4
-to 128 bags."""
+"""Long bags of the lane-group forward classes: the bound that follows a table's mean bag length, the error of the bags that lane
+groups walk below it, and wavefronts that look at 4 to 128 bags."""
 import pytest
 import torch
 
@@ -138,4 +138,37 @@ def test_bound_follows_the_tables_own_mean(D, long, short):
         check(4, every[every % 70 != 0], _sum_by_lane_group)
         check(4, every[::70], _sum_by_wavefront)
         check(2, every[::100], _sum_by_wavefront)
+    tbe.close()
+
+
+@pytest.mark.parametrize("dtype", ["f32", "f16"])
+@pytest.mark.parametrize("hot", [-1, 0])
+def test_mean_pooling_on_both_sides_of_the_bound(dtype, hot):
+    if not torch.cuda.is_available():
+        pytest.skip("no GPU")
+    from paper_2508_03854_amd import TBE
+    v = 8 if dtype == "f16" else 4
+    D = [v * lanes for lanes in (2, 8, 13, 32)]
+    B, R = 4100, 300   # (more bags than one wavefront each takes)
+    g = torch.Generator().manual_seed(3)
+    lens = torch.randint(0, 90, (4 * B,), generator=g)     # twice the mean is 89
+    lens[::50] = torch.tensor([0, 31, 33, 47, 49, 63, 65, 88, 91, 127, 129, 260]).repeat(50)[:len(lens[::50])]
+    off = torch.zeros(4 * B + 1, dtype=torch.int64)
+    off[1:] = torch.cumsum(lens, 0)
+    idx = torch.randint(0, R, (int(off[-1]),), generator=g)
+    tbe = TBE([R] * 4, D, dtype)
+    tbe.set_tunable("hot_rows_min_workgroups", hot)
+    w = torch.empty(tbe.total_elems).uniform_(-1, 1, generator=g).to(tbe.torch_dtype)
+    out = tbe.forward(w.cuda(), idx.cuda(), off.cuda(), B, "mean").cpu().double()
+    d0 = w0 = 0
+    for t, d in enumerate(D):
+        o = off[t * B:(t + 1) * B + 1]
+        L = (o[1:] - o[:-1]).double()[:, None]
+        want = torch.zeros(B, d, dtype=torch.float64)
+        want.index_add_(0, torch.repeat_interleave(torch.arange(B), o[1:] - o[:-1]), w[w0:w0 + R * d].view(R, d).double()[idx[int(o[0]):int(o[-1])]])
+        want /= L.clamp(min=1.0)
+        # a 32-bit sum of L values of at most 1 and one division: at most (L - 1 + 1) * 2^-24
+        assert ((out[:, d0:d0 + d] - want).abs() <= 2.0 ** -24 * L).all(), (t, d)
+        d0 += d
+        w0 += R * d
     tbe.close()
