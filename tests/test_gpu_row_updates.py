@@ -146,6 +146,7 @@ def _step(T, rows, widths, dtype, pooling, io, counts):
     (26, 300, (20000, 30), 9000, 40),         # descending
     (16, 200, (150, 9000), 20000, 145),       # more long rows than lie in LDS at a time
     (20, 64, (3, 3), 10, 0),                  # fewer rows than a pass
+    (4100, 7, (30, 20), 24, 0),               # more tables than the lists take one by one
 ])
 def test_long_spans_of_equal_work(T, B, rows, lookups, hot):
     """The borders of the long spans, as the batch's lists hold them: a row weighs 16 lookups and its own, long rows only the 16."""
