@@ -99,11 +99,7 @@ __device__ __forceinline__ int64_t wave_upper_bound_i64(const IT* __restrict__ a
 // Inclusive running maximum across a block of kRsThreads threads (smem: kRsWaves words, free again on return).
 __device__ __forceinline__ uint32_t block_incl_max(uint32_t v, uint32_t* smem) {
     const int l = lane_id();
-#pragma unroll
-    for (int o = 1; o < kWave; o <<= 1) {
-        const uint32_t n = __shfl_up(v, o, kWave);
-        if (l >= o) v = n > v ? n : v;
-    }
+    v = wave_incl_max(v);
     const int w = threadIdx.x >> 6;
     if (l == kWave - 1) smem[w] = v;
     __syncthreads();
@@ -215,12 +211,7 @@ __device__ __forceinline__ void tile_owners(const IT* __restrict__ offsets, cons
         }
 #pragma unroll
         for (int k = 1; k < ITEMS; ++k) run[k] = run[k] > run[k - 1] ? run[k] : run[k - 1];
-        int32_t top = run[ITEMS - 1];
-#pragma unroll
-        for (int d = 1; d < kWave; d <<= 1) {
-            const int32_t up = __shfl_up(top, d, kWave);
-            if (lane >= d) top = up > top ? up : top;
-        }
+        const int32_t top = (int32_t)wave_incl_max((uint32_t)run[ITEMS - 1]);   // (places among the tile's bags: not negative)
         int32_t prev = __shfl_up(top, 1, kWave);
         if (lane == 0) prev = 0;
         if (lane == kWave - 1) o->wmax[w] = top;
