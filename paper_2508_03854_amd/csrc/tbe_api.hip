@@ -30,6 +30,22 @@ static size_t hist_cap(int64_t N, int nseg) {
 SortShape sort_shape(const tbe_handle* h, int64_t N) {
     SortShape sh;
     sh.nseg = h->segmented ? h->T : 1;
+    // One launch where keys are local to their segment and reading a segment once per range of it costs less than two launches a
+    // pass.  That grows with the square of a segment: of one table 16384 ids of 3 rows 25 -> 29 us, of 100000 rows, Zipf 1.3, 38 ->
+    // 35, 32768 of them 48 -> 58.  The host knows no segment's length, only that all of them together are N: hence the average, and
+    // a bound on N for the batch that is one table's after all (60000 of 65000 ids in one of 26 tables 52 -> 80).  Very many tables
+    // have a workgroup of 1024 threads each for a few ids: 1000 tables x 10 and x 60 ids 48 -> 50 and 51 -> 60, 300 x 1 35 -> 24.
+    sh.small = (h->segmented || h->T == 1) && sh.nseg <= kSmallTables && (N <= kSmallMax || (N <= kSmallMaxMany && N <= kSmallSegment * sh.nseg));
+    if (sh.small) {
+        sh.passes = 1;
+        sh.bits = h->sort_bits;
+        sh.bins = 0;
+        sh.hist_bytes = 0;
+        sh.self_scan = true;
+        sh.chunk = sh.tile = kSmallChunk;
+        sh.max_chunks = (int)((N + kSmallChunk - 1) / kSmallChunk) + sh.nseg;
+        return sh;
+    }
     sh.self_scan = N <= kSelfScanMax;
     const int64_t few = kSelfScanChunks * sh.nseg;   // chunks in all
     if (sh.self_scan && N <= 32 * 4096 && N <= few * 1024) sh.tile = 1024;
@@ -143,7 +159,9 @@ Workspace carve(const tbe_handle* h, int32_t B, int64_t N) {
     w.seq_gbase = take(8 * (size_t)h->T);
     const size_t parts = 4 * (size_t)w.cap_main * (size_t)h->maxD;
     w.rle_blocks = (int)(((int64_t)n + kRleTile - 1) / kRleTile);
-    const size_t front = align256(4 * (n + 1)) + align256(8 * (size_t)w.rle_blocks);   // spare keys, run-length counts
+    // spare keys and run-length counts; or the ranges of a small batch and their counts
+    const size_t ranges = (std::min(n, (size_t)kSmallMaxMany) + kSmallChunk - 1) / kSmallChunk + (size_t)w.sort.nseg;
+    const size_t front = std::max(align256(4 * (n + 1)) + align256(8 * (size_t)w.rle_blocks), align256(32 * ranges) + align256(8 * ranges));
     const size_t base = off + std::max(front, align256(parts));
     size_t reserve = base;
     // Dense rows: for the tables whose gradient block is large.  Enough chunks for about a thousand workgroups in all, at most
@@ -179,8 +197,13 @@ Workspace carve(const tbe_handle* h, int32_t B, int64_t N) {
         }
     }
     const size_t shared = off;
-    w.keys[sorted ^ 1] = take(4 * (n + 1));
-    w.rle_counts = take(8 * (size_t)w.rle_blocks);
+    if (w.sort.small) {
+        w.chunk_desc = take(32 * ranges);
+        w.rle_counts = take(8 * ranges);
+    } else {
+        w.keys[sorted ^ 1] = take(4 * (n + 1));
+        w.rle_counts = take(8 * (size_t)w.rle_blocks);
+    }
     w.partial = shared;
     w.dense_partial = shared + parts;   // (a multiple of 16)
     w.total = reserve;   // (covers both uses: at least base, and with dense rows no less than what they were fitted into)
@@ -447,11 +470,8 @@ static tbe_status backward_impl(const tbe_handle* h, const void* grad_out, tbe_i
     hipStream_t s = static_cast<hipStream_t>(hip_stream);
     const int idx32 = index_dtype == TBE_I32;
     hipError_t e = hipSuccess;
-    const int buf = w.sort.passes & 1;  // every pass flips the double buffer, starting from 0
     if (prep) {
         e = launch_sort(h, w, ws, indices, offsets, idx32, B, nnz, seq != 0, s);
-        if (e != hipSuccess) return TBE_EHIP;
-        e = launch_run_lengths(h, w, ws, buf, nnz, s);
         if (e != hipSuccess) return TBE_EHIP;
         e = launch_lists(h, w, ws, offsets, idx32, B, seq, grad_elems, s);
         if (e != hipSuccess) return TBE_EHIP;

@@ -15,6 +15,11 @@ constexpr int kRadixTile = 4096;  // elements per radix-sort tile (256 threads x
 constexpr int kRadixMaxBlocks = 8192;  // large batches: each radix block owns one contiguous slice of the input
 constexpr int kRleTile = 2048;  // elements per run-length tile (at most 4096: one wavefront scans its runs of 64)
 constexpr int64_t kRleOneBlock = 32768;  // batches up to this size are segmented by one workgroup
+// Batches that are sorted in one launch (tbe_sort_small.hip): of at most kSmallMax lookups, or of at most kSmallMaxMany that are no
+// more than kSmallSegment per table on average; of at most kSmallTables tables.
+constexpr int kSmallTables = 512;
+constexpr int64_t kSmallMax = 12288, kSmallMaxMany = 65536, kSmallSegment = 8192;
+constexpr int kSmallChunk = 512;         // places of the sorted order that a workgroup owns
 constexpr int kMaxParts = 1024;          // parts that a long row is cut into at most
 constexpr int kMaxSortSegments = 4096;  // tables beyond this are sorted as one segment on the linearised key
 constexpr int kDenseRows = 128;  // rows per table that the dense-row kernel reduces at most (multiple of 32)
@@ -83,6 +88,7 @@ namespace tbe {
 // How the keys of a batch of N lookups are sorted (see tbe_sort.hip).
 struct SortShape {
     int nseg;          // sort segments
+    bool small;        // one launch for the whole sort; of what follows the chunks alone are used, its workgroups' ranges
     int passes, bits;  // radix passes, digit bits of each
     size_t hist_bytes; // chunk histograms
     int bins;          // 256, 1024 or 2048: histogram width of the kernels that run
@@ -130,10 +136,9 @@ unsigned forward_kernels(const tbe_handle* h, int32_t B, int64_t nnz);
 hipError_t launch_replica_mean(const tbe_handle* h, void* const* replicas, int M, size_t count, bool f32, hipStream_t s);
 // Sorts the batch's ids, segment by segment, into (linearised row key, payload) pairs; the payload is the lookup's bag, or
 // its position when seq is set.  The result lies in buffer pair w.sort.passes & 1 of the workspace.
+// Then the run lengths: vals of the other pair receive unique_rows.
 hipError_t launch_sort(const tbe_handle* h, const Workspace& w, char* ws, const void* indices, const void* offsets, int idx32,
                        int32_t B, int64_t N, bool seq, hipStream_t s);
-// `sorted` is the buffer index (0/1) that holds the sorted pairs; vals of the other pair receive unique_rows
-hipError_t launch_run_lengths(const tbe_handle* h, const Workspace& w, char* ws, int sorted, int64_t N, hipStream_t s);
 struct SegArgs;
 SegArgs seg_args(const tbe_handle* h, const Workspace& w, char* ws, const void* offsets, int idx32, int32_t B, int seq);
 // lists the long rows of the sorted batch (and, seq != 0, the gradient blocks of the non-pooled layout)
