@@ -85,6 +85,13 @@ __device__ __forceinline__ void nt_store16(void* p, const uint4 v) {
     __builtin_nontemporal_store(x, static_cast<u32x4_t*>(p));
 }
 
+__device__ __forceinline__ void nt_store8(void* p, const uint2 v) {
+    typedef uint32_t u32x2_t __attribute__((ext_vector_type(2)));
+    u32x2_t x;
+    x.x = v.x; x.y = v.y;
+    __builtin_nontemporal_store(x, static_cast<u32x2_t*>(p));
+}
+
 // ---- ids and offsets: int64 or int32 at the boundary --------------------------------------------------
 struct IdxView {
     const void* p;
@@ -139,10 +146,14 @@ struct GradIO<bf16_t> {
     }
 };
 
-// store four consecutive elements; io = 0 float, 1 binary16, 2 bfloat16 (one rounding to nearest even)
+// store four consecutive elements; io = 0 float, 1 binary16, 2 bfloat16 (one rounding to nearest even).  NT: as a stream, which pays
+// where a wavefront writes whole lines and costs where it leaves parts of them to be filled by a later store
+template <bool NT = false>
 __device__ __forceinline__ void store4_from_float(void* base, int io, int64_t elem, float a, float b, float c, float d) {
     if (io == 0) {
-        *reinterpret_cast<float4*>(static_cast<float*>(base) + elem) = make_float4(a, b, c, d);
+        float* const p = static_cast<float*>(base) + elem;
+        if (NT) nt_store16(p, make_uint4(__float_as_uint(a), __float_as_uint(b), __float_as_uint(c), __float_as_uint(d)));
+        else *reinterpret_cast<float4*>(p) = make_float4(a, b, c, d);
     } else {
         unsigned short h0, h1, h2, h3;
         if (io == 1) {
@@ -151,9 +162,24 @@ __device__ __forceinline__ void store4_from_float(void* base, int io, int64_t el
         } else {
             h0 = float_to_bf16_rn(a); h1 = float_to_bf16_rn(b); h2 = float_to_bf16_rn(c); h3 = float_to_bf16_rn(d);
         }
-        *reinterpret_cast<uint2*>(static_cast<unsigned short*>(base) + elem) =
-            make_uint2((uint32_t)h0 | ((uint32_t)h1 << 16), (uint32_t)h2 | ((uint32_t)h3 << 16));
+        const uint2 v = make_uint2((uint32_t)h0 | ((uint32_t)h1 << 16), (uint32_t)h2 | ((uint32_t)h3 << 16));
+        unsigned short* const p = static_cast<unsigned short*>(base) + elem;
+        if (NT) nt_store8(p, v);
+        else *reinterpret_cast<uint2*>(p) = v;
     }
+}
+// ... and eight into a 16-bit type
+template <bool NT = false>
+__device__ __forceinline__ void store8_from_float(void* base, int io, int64_t elem, const float (&x)[8]) {
+    uint32_t w[4];
+#pragma unroll
+    for (int i = 0; i < 4; ++i)
+        w[i] = io == 1 ? (uint32_t)__half_as_ushort(__float2half_rn(x[2 * i])) | (uint32_t)__half_as_ushort(__float2half_rn(x[2 * i + 1])) << 16
+                       : (uint32_t)float_to_bf16_rn(x[2 * i]) | (uint32_t)float_to_bf16_rn(x[2 * i + 1]) << 16;
+    unsigned short* const p = static_cast<unsigned short*>(base) + elem;
+    const uint4 v = make_uint4(w[0], w[1], w[2], w[3]);
+    if (NT) nt_store16(p, v);
+    else *reinterpret_cast<uint4*>(p) = v;
 }
 
 // ---- 16-byte row fragments ---------------------------------------------------------------------
@@ -219,6 +245,10 @@ __device__ __forceinline__ float bcast_lane(const float x, const int src) {
     return __int_as_float(__builtin_amdgcn_readlane(__float_as_int(x), src));
 }
 
+__device__ __forceinline__ int64_t lane_i64(const int64_t x, const int src) {   // (src: the same in all lanes)
+    return (int64_t)(((uint64_t)bcast_lane((uint32_t)((uint64_t)x >> 32), src) << 32) | bcast_lane((uint32_t)(uint64_t)x, src));
+}
+
 // One digit count into a histogram.  When every active lane holds the same digit (the common case for the high digits,
 // because ids arrive grouped by table) one lane adds the whole count instead of 64 lanes queueing on one LDS word.
 __device__ __forceinline__ void hist_add(uint32_t* __restrict__ hw, const uint32_t d, const bool valid) {
@@ -245,10 +275,8 @@ struct RowIO<float> {
     static __device__ __forceinline__ void accumulate(const raw_t& r, float (&acc)[4]) {
         acc[0] += r.x; acc[1] += r.y; acc[2] += r.z; acc[3] += r.w;
     }
-    static __device__ __forceinline__ void load(const float* p, float (&x)[4]) {
-        const float4 v = *reinterpret_cast<const float4*>(p);
-        x[0] = v.x; x[1] = v.y; x[2] = v.z; x[3] = v.w;
-    }
+    static __device__ __forceinline__ void unpack(const raw_t& r, float (&x)[4]) { x[0] = r.x; x[1] = r.y; x[2] = r.z; x[3] = r.w; }
+    static __device__ __forceinline__ void load(const float* p, float (&x)[4]) { unpack(load_raw(p), x); }
     // 4-element fragment used by the optimizer step (one lane owns 4 columns)
     static __device__ __forceinline__ void load4(const float* p, float (&x)[4]) { load(p, x); }
     using raw4_t = float4;   // ... as it sits in registers between the load and its use
@@ -276,8 +304,7 @@ struct RowIO<__half> {
             asm("v_fma_mix_f32 %0, %1, 1.0, %0 op_sel:[1,0,0] op_sel_hi:[1,0,0]" : "+v"(acc[2 * i + 1]) : "v"(w[i]));
         }
     }
-    static __device__ __forceinline__ void load(const __half* p, float (&x)[8]) {
-        const uint4 raw = *reinterpret_cast<const uint4*>(p);
+    static __device__ __forceinline__ void unpack(const raw_t& raw, float (&x)[8]) {
         const uint32_t w[4] = {raw.x, raw.y, raw.z, raw.w};
 #pragma unroll
         for (int i = 0; i < 4; ++i) {
@@ -285,6 +312,7 @@ struct RowIO<__half> {
             x[2 * i + 1] = __half2float(__ushort_as_half((unsigned short)(w[i] >> 16)));
         }
     }
+    static __device__ __forceinline__ void load(const __half* p, float (&x)[8]) { unpack(load_raw(p), x); }
     using raw4_t = uint2;
     static __device__ __forceinline__ raw4_t load4_raw(const __half* p) { return *reinterpret_cast<const uint2*>(p); }
     static __device__ __forceinline__ void load4(const __half* p, float (&x)[4]) { unpack4(load4_raw(p), x); }

@@ -727,9 +727,18 @@ hipError_t launch_forward(const tbe_handle* h, const void* tables, const int32_t
 
 // ---- non-pooled lookup -------------------------------------------------------------------------------------
 // out block of table t = [n_t, D_t], row i = W_t[indices[offsets[t] + i]]; the blocks follow one another.
-// A wavefront takes 64 consecutive positions: every lane resolves one lookup (table, source row, destination),
-// then the 16-byte fragments of all 64 rows are copied lane-parallel, one after the other in every lane: each is stored under its
-// lane's condition before the next is loaded.
+// A wavefront takes 64 consecutive positions.  As a rule they lie in one table: then its lanes look at 64 tables at a time, each lane
+// with one id finds its row, and what the wavefront writes is one contiguous run of 64 * D_t elements, which its lanes fill fragment
+// after fragment, kSeqInFlight of them under way before the first is converted and stored.  Only a fragment's row goes from lane to
+// lane.  Positions of several tables, or of an offsets array that does not add up, take the general path below, where every lane
+// resolves its own position and finds out for every fragment whose row it is.
+// Bound: the gather of the rows and the stream of the output, which is written past the caches: nothing here reads it again, and the
+// rows stay in the L2.  With a search per lane, a division and five cross-lane reads per fragment and one of them in flight / this with
+// plain stores / this, us: 14 tables of 100 k rows x 32 and 2 of 2 M x 128 fp32 columns, 3.1 M positions, Zipf 1.3, bfloat16 out 143 /
+// 110 / 66; 8 tables of 300 k rows, 1.3 M positions, Zipf 1.1: 64 fp32 columns 121 / 111 / 67, 256 fp32 430 / 412 / 359, 256 binary16
+// into fp32 433 / 378 / 255, into bfloat16 260 / 224 / 139, 32 fp32 into bfloat16 35 / 27 / 26; 8 in flight instead of 4 0 to 30 % slower.
+constexpr int kSeqInFlight = 4;
+
 __device__ __forceinline__ int64_t wave_sum_i64(int64_t v) {
     for (int o = 1; o < kWave; o <<= 1) {
         const uint32_t lo = __shfl_xor((uint32_t)(v & 0xFFFFFFFFll), o, kWave);
@@ -739,32 +748,43 @@ __device__ __forceinline__ int64_t wave_sum_i64(int64_t v) {
     return v;
 }
 
-template <typename WT>
-__device__ __forceinline__ void copy_fragment(const WT* __restrict__ src, void* __restrict__ out, const int out_io,
-                                              const int64_t elem, const bool zero) {
-    constexpr int V = RowIO<WT>::kVec;
-    float x[V];
-    if (zero) {
-#pragma unroll
-        for (int v = 0; v < V; ++v) x[v] = 0.f;
-    } else {
-        RowIO<WT>::load(src, x);
+// What a lane copies at a time: a 16-byte piece of a row, or where binary16 rows go into fp32 an 8-byte one, so that neighbouring
+// lanes' stores are 16 bytes next to each other.
+template <typename WT, int IO>
+struct SeqFragment {
+    static constexpr int kElems = RowIO<WT>::kVec;
+    using raw_t = typename RowIO<WT>::raw_t;
+    static __device__ __forceinline__ raw_t load(const WT* p) { return RowIO<WT>::load_raw(p); }
+    static __device__ __forceinline__ raw_t zero() { return RowIO<WT>::zero_raw(); }
+    static __device__ __forceinline__ void store(const raw_t raw, void* __restrict__ out, const int64_t elem) {
+        float x[kElems];
+        RowIO<WT>::unpack(raw, x);
+        if constexpr (IO != 0 && kElems == 8) store8_from_float<true>(out, IO, elem, x);
+        else store4_from_float<true>(out, IO, elem, x[0], x[1], x[2], x[3]);
     }
-#pragma unroll
-    for (int v4 = 0; v4 < V; v4 += 4) store4_from_float(out, out_io, elem + v4, x[v4], x[v4 + 1], x[v4 + 2], x[v4 + 3]);
-}
+};
+template <>
+struct SeqFragment<__half, 0> {
+    static constexpr int kElems = 4;
+    using raw_t = uint2;
+    static __device__ __forceinline__ raw_t load(const __half* p) { return RowIO<__half>::load4_raw(p); }
+    static __device__ __forceinline__ raw_t zero() { return make_uint2(0u, 0u); }
+    static __device__ __forceinline__ void store(const raw_t raw, void* __restrict__ out, const int64_t elem) {
+        float x[4];
+        RowIO<__half>::unpack4(raw, x);
+        store4_from_float<true>(out, 0, elem, x[0], x[1], x[2], x[3]);
+    }
+};
 
-// IT: int64 or int32 ids and offsets, compiled apart: the search below is a chain of loads that differs from lane to lane, and
-// with the width as a run-time flag every step of it branches around two loads.
-template <typename WT, typename IT>
-__global__ __launch_bounds__(kFwdThreads, 8) void lookup_seq_kernel(
+// The general path: every position by itself.
+template <typename WT, typename IT, int IO>
+__device__ __forceinline__ void lookup_seq_rows(
     const WT* __restrict__ weights, const IT* __restrict__ indices, const IT* __restrict__ offsets, const int32_t* __restrict__ D_off,
-    const int64_t* __restrict__ w_off, const int64_t* __restrict__ row_base, const int T, const int64_t nnz,
-    void* __restrict__ out, const int out_io, const int64_t out_elems, int32_t* err) {
-    constexpr int V = RowIO<WT>::kVec;
+    const int64_t* __restrict__ w_off, const int64_t* __restrict__ row_base, const int T, const int64_t p0, const int64_t nnz,
+    void* __restrict__ out, const int64_t out_elems, int32_t* err) {
+    using F4 = SeqFragment<WT, IO>;
+    constexpr uint32_t kF = F4::kElems;
     const int lane = lane_id();
-    const int64_t p0 = ((int64_t)blockIdx.x * (kFwdThreads / kWave) + (threadIdx.x >> 6)) * kWave;
-    if (p0 >= nnz) return;
     const int64_t p = p0 + lane;
     const bool valid = p < nnz;
     // table of the position: the last t with offsets[t] <= p (empty tables are skipped by construction)
@@ -807,43 +827,95 @@ __global__ __launch_bounds__(kFwdThreads, 8) void lookup_seq_kernel(
         atomicOr(err, 1);
         dst_elem = -1;
     }
-    const int n = (int)((nnz - p0) < (int64_t)kWave ? (nnz - p0) : (int64_t)kWave);
-    const int F = D / V;  // fragments per row
-    const bool uniform = __all(!valid || D == __shfl(D, 0, kWave));
-    if (uniform) {
-        const int F0 = __shfl(F, 0, kWave);
-        const int total = n * F0;
-        for (int q0 = 0; q0 < total; q0 += 4 * kWave) {
+    // all fragments of the rows, one behind the other: a row's first is number `first`
+    const uint32_t F = valid && dst_elem >= 0 ? (uint32_t)D / kF : 0u, behind = wave_incl_scan(F), first = behind - F;
+    const uint32_t total = bcast_lane(behind, kWave - 1);
+    const int64_t src = bad ? -1 : src_elem;
+    const uint32_t F0 = bcast_lane(F, 0);   // (of the first position, which exists)
+    const uint32_t inv = __all(!valid || F == F0) && F0 > 0u ? ((1u << 31) + F0 - 1u) / F0 : 0u;   // all the same: as in one table
+    for (uint32_t q0 = (uint32_t)lane; q0 - (uint32_t)lane < total; q0 += kSeqInFlight * kWave) {
+        typename F4::raw_t x[kSeqInFlight];
+        int64_t to[kSeqInFlight];
 #pragma unroll
-            for (int u = 0; u < 4; ++u) {
-                const int q = q0 + u * kWave + lane;
-                const int k = q / F0, f = q - k * F0;
-                const int ks = k < n ? k : 0;
-                const uint32_t s_lo = __shfl((uint32_t)(src_elem & 0xFFFFFFFFll), ks, kWave);
-                const uint32_t s_hi = __shfl((uint32_t)((uint64_t)src_elem >> 32), ks, kWave);
-                const uint32_t d_lo = __shfl((uint32_t)(dst_elem & 0xFFFFFFFFll), ks, kWave);
-                const uint32_t d_hi = __shfl((uint32_t)((uint64_t)dst_elem >> 32), ks, kWave);
-                const int zb = __shfl((int)bad, ks, kWave);
-                const int64_t d0 = (int64_t)(((uint64_t)d_hi << 32) | d_lo);
-                if (q < total && d0 >= 0) {
-                    const int64_t se = (int64_t)(((uint64_t)s_hi << 32) | s_lo) + (int64_t)f * V;
-                    copy_fragment<WT>(weights + se, out, out_io, d0 + (int64_t)f * V, zb != 0);
-                }
+        for (int u = 0; u < kSeqInFlight; ++u) {
+            const uint32_t q = q0 + (uint32_t)u * kWave;
+            int k = 0;   // the last row whose first fragment is q or one before it
+            if (inv != 0u) {
+                k = (int)umin(__umulhi(2u * q, inv), kWave - 1u);
+            } else {
+#pragma unroll
+                for (int step = kWave / 2; step > 0; step >>= 1) k += (uint32_t)__shfl(first, k + step, kWave) <= q ? step : 0;
             }
+            const int64_t f = (int64_t)(q - (uint32_t)__shfl(first, k, kWave)) * kF;
+            const int64_t from = (int64_t)(((uint64_t)(uint32_t)__shfl((int)((uint64_t)src >> 32), k, kWave) << 32) | (uint32_t)__shfl((int)(uint64_t)src, k, kWave));
+            to[u] = f + (int64_t)(((uint64_t)(uint32_t)__shfl((int)((uint64_t)dst_elem >> 32), k, kWave) << 32) | (uint32_t)__shfl((int)(uint64_t)dst_elem, k, kWave));
+            x[u] = q < total && from >= 0 ? F4::load(weights + from + f) : F4::zero();
         }
-    } else {  // a table boundary inside the 64 positions: row by row
-        for (int k = 0; k < n; ++k) {
-            const uint32_t s_lo = __shfl((uint32_t)(src_elem & 0xFFFFFFFFll), k, kWave);
-            const uint32_t s_hi = __shfl((uint32_t)((uint64_t)src_elem >> 32), k, kWave);
-            const uint32_t d_lo = __shfl((uint32_t)(dst_elem & 0xFFFFFFFFll), k, kWave);
-            const uint32_t d_hi = __shfl((uint32_t)((uint64_t)dst_elem >> 32), k, kWave);
-            const int zb = __shfl((int)bad, k, kWave);
-            const int Fk = __shfl(F, k, kWave);
-            const int64_t d0 = (int64_t)(((uint64_t)d_hi << 32) | d_lo);
-            for (int f = lane; f < Fk && d0 >= 0; f += kWave) {
-                const int64_t se = (int64_t)(((uint64_t)s_hi << 32) | s_lo) + (int64_t)f * V;
-                copy_fragment<WT>(weights + se, out, out_io, d0 + (int64_t)f * V, zb != 0);
-            }
+#pragma unroll
+        for (int u = 0; u < kSeqInFlight; ++u)
+            if (q0 + (uint32_t)u * kWave < total) F4::store(x[u], out, to[u]);
+    }
+}
+
+// IT: int64 or int32 ids and offsets, compiled apart: with the width as a run-time flag every step of a search branches around two
+// loads.
+template <typename WT, typename IT, int IO>
+__global__ __launch_bounds__(kFwdThreads, 8) void lookup_seq_kernel(
+    const WT* __restrict__ weights, const IT* __restrict__ indices, const IT* __restrict__ offsets, const int32_t* __restrict__ D_off,
+    const int64_t* __restrict__ w_off, const int64_t* __restrict__ row_base, const int T, const int64_t nnz,
+    void* __restrict__ out, const int64_t out_elems, int32_t* err) {
+    const int lane = lane_id();
+    const int64_t p0 = ((int64_t)blockIdx.x * (kFwdThreads / kWave) + (threadIdx.x >> 6)) * kWave;
+    if (p0 >= nnz) return;
+    const int n = (int)((nnz - p0) < (int64_t)kWave ? (nnz - p0) : (int64_t)kWave);
+    const int64_t my_id = (int64_t)indices[p0 + (lane < n ? lane : n - 1)];
+    // the first table that ends behind p0, all that is needed of it, and the elements of the blocks before its own; 64 tables a round
+    int t = -1, D = 0;
+    int64_t part = 0, start = 0, end = 0, R = 0, w0 = 0;
+    for (int t0 = 0; t0 < T; t0 += kWave) {
+        const bool on = t0 + lane < T;
+        const int tt = on ? t0 + lane : T - 1;
+        const int64_t s = (int64_t)offsets[tt], e = (int64_t)offsets[tt + 1], rows = row_base[tt + 1] - row_base[tt], w = w_off[tt];
+        const int cols = D_off[tt + 1] - D_off[tt];
+        const uint64_t m = __ballot(on && e > p0);
+        const int f = m != 0ull ? __ffsll((unsigned long long)m) - 1 : kWave;
+        if (on && lane < f && e > s) part += (e - s) * (int64_t)cols;
+        if (m != 0ull) {
+            t = t0 + f;
+            start = lane_i64(s, f);
+            end = lane_i64(e, f);
+            R = lane_i64(rows, f);
+            w0 = lane_i64(w, f);
+            D = bcast_lane(cols, f);
+            break;
+        }
+    }
+    const int64_t dst = wave_sum_i64(part) + (p0 - start) * D;
+    if (t < 0 || start < 0 || start > p0 || end < p0 + n || dst < 0 || dst + (int64_t)n * D > out_elems) {
+        lookup_seq_rows<WT, IT, IO>(weights, indices, offsets, D_off, w_off, row_base, T, p0, nnz, out, out_elems, err);
+        return;
+    }
+    const WT* const table = weights + w0;
+    const bool ok = my_id >= 0 && my_id < R;
+    if (!ok) atomicOr(err, 1);   // as in the pooled forward: flagged, and the row reads as zeros
+    const int row = ok ? (int)my_id : -1;   // (tables have fewer than 2^31 rows)
+    using F4 = SeqFragment<WT, IO>;
+    constexpr uint32_t kF = F4::kElems;
+    const uint32_t F = (uint32_t)D / kF, total = (uint32_t)n * F;   // fragments per row, in all
+    const uint32_t inv = ((1u << 31) + F - 1u) / F;   // q / F by a multiplication: exact, as q * F stays below 2^31
+    for (uint32_t q0 = (uint32_t)lane; q0 - (uint32_t)lane < total; q0 += kSeqInFlight * kWave) {
+        typename F4::raw_t x[kSeqInFlight];
+#pragma unroll
+        for (int u = 0; u < kSeqInFlight; ++u) {
+            const uint32_t q = q0 + (uint32_t)u * kWave;
+            const uint32_t k = __umulhi(2u * q, inv), f = q - k * F;
+            const int r = __shfl(row, (int)(k < (uint32_t)n ? k : 0u), kWave);
+            x[u] = r >= 0 && q < total ? F4::load(table + (int64_t)r * D + f * kF) : F4::zero();
+        }
+#pragma unroll
+        for (int u = 0; u < kSeqInFlight; ++u) {
+            const uint32_t q = q0 + (uint32_t)u * kWave;
+            if (q < total) F4::store(x[u], out, dst + (int64_t)q * kF);
         }
     }
 }
@@ -851,9 +923,14 @@ __global__ __launch_bounds__(kFwdThreads, 8) void lookup_seq_kernel(
 template <typename WT, typename IT>
 static void launch_lookup_seq_as(const tbe_handle* h, const dim3 grid, const void* tables, const void* indices, const void* offsets,
                                  int64_t nnz, void* out, int out_io, int64_t out_elems, hipStream_t s) {
-    lookup_seq_kernel<WT, IT><<<grid, kFwdThreads, 0, s>>>(static_cast<const WT*>(tables), static_cast<const IT*>(indices),
-                                                           static_cast<const IT*>(offsets), h->d_D_off, h->d_w_off, h->d_row_base,
-                                                           h->T, nnz, out, out_io, out_elems, h->d_err);
+    auto go = [&](auto io) {
+        lookup_seq_kernel<WT, IT, decltype(io)::value><<<grid, kFwdThreads, 0, s>>>(
+            static_cast<const WT*>(tables), static_cast<const IT*>(indices), static_cast<const IT*>(offsets), h->d_D_off, h->d_w_off,
+            h->d_row_base, h->T, nnz, out, out_elems, h->d_err);
+    };
+    if (out_io == 0) go(std::integral_constant<int, 0>{});
+    else if (out_io == 1) go(std::integral_constant<int, 1>{});
+    else go(std::integral_constant<int, 2>{});
 }
 
 hipError_t launch_lookup_seq(const tbe_handle* h, const void* tables, const void* indices, const void* offsets,
