@@ -30,6 +30,13 @@ constexpr int kSegThreads = 256;
 // the variant of 7 wavefronts loses by it, 20.5 -> 21.2 ms at the first of the workloads above with passes of 16 rows.
 constexpr int kPassRowsLog2 = 4, kLongPassRowsLog2 = 5;
 constexpr uint32_t kLongPassNeed = 2048, kLongPassNeedNarrow = 128;   // rows per wavefront; tables of at most 8 columns
+// Rows of few lookups are read and written past the caches (as streams) where the batch's rows and its gradients together are more
+// than the Infinity Cache holds: the gradients, which are gathered again and again, stay there instead.  Where everything fits, the next
+// forward finds the rows in it.  Whole steps without / with this, us: 12 tables x 8192 bags of 20 uniform ids, 128 fp32 columns (928 MB
+// of rows + 50 MB) 591 / 547; 64 tables x 4096 bags of 31 ids, bfloat16 gradients (663 + 117) 1261 / 1245; 16 tables x 16384 bags of 21
+// ids (271 + 151) 766 / 754; but where it all fits 26 tables x 4096 bags of 11 ids (56 + 27) 162 / 165, sequences of 3.1 M events (34 + 275)
+// 343 / 361.  The reads or the writes alone: 561 and 576 of the first 577.
+constexpr uint64_t kInfinityCacheBytes = (uint64_t)256 << 20;
 constexpr int kSegBlocks = 2048;  // persistent grids: waves stride over passes of unique rows, or over rows
 constexpr int kSegBlocks7 = 1792;   // ... of the variants of 7 wavefronts per SIMD
 // Long spans count a die's wavefronts as an eighth of the grid: a pass would be left out or taken twice otherwise.
@@ -188,7 +195,8 @@ __device__ __forceinline__ float row_step(const float (&acc)[NC][4], const RowGe
 template <typename WT, int NC>
 __device__ __forceinline__ void adagrad_row(const float (&acc)[NC][4], const RowGeom& g, WT* __restrict__ wrow,
                                             float* __restrict__ vptr, const float v_old, const bool write,
-                                            const float lr, const float eps, const float inv_c, const bool sgd = false) {
+                                            const float lr, const float eps, const float inv_c, const bool sgd = false,
+                                            const bool stream = false) {
     const float step = row_step<NC>(acc, g, vptr, v_old, write, lr, eps, inv_c, sgd);
     if (!write) return;
 #pragma unroll
@@ -196,10 +204,11 @@ __device__ __forceinline__ void adagrad_row(const float (&acc)[NC][4], const Row
         const int col = g.lc + c * kWave * 4;
         if (col < g.D) {
             float w[4];
-            RowIO<WT>::load4(wrow + col, w);
+            RowIO<WT>::unpack4(stream ? RowIO<WT>::template load4_raw<true>(wrow + col) : RowIO<WT>::load4_raw(wrow + col), w);
 #pragma unroll
             for (int v = 0; v < 4; ++v) w[v] = fmaf(-step, acc[c][v], w[v]);
-            RowIO<WT>::store4(wrow + col, w);
+            if (stream) RowIO<WT>::template store4<true>(wrow + col, w);
+            else RowIO<WT>::store4(wrow + col, w);
         }
     }
 }
@@ -208,14 +217,15 @@ template <typename WT>
 __device__ __forceinline__ void adagrad_row_loaded(const float (&acc)[1][4], const RowGeom& g, WT* __restrict__ wrow,
                                                    const typename RowIO<WT>::raw4_t wraw, float* __restrict__ vptr,
                                                    const float v_old, const bool write, const float lr, const float eps,
-                                                   const float inv_c, const bool sgd) {
+                                                   const float inv_c, const bool sgd, const bool stream) {
     const float step = row_step<1>(acc, g, vptr, v_old, write, lr, eps, inv_c, sgd);
     if (write && g.lc < g.D) {
         float w[4];
         RowIO<WT>::unpack4(wraw, w);
 #pragma unroll
         for (int v = 0; v < 4; ++v) w[v] = fmaf(-step, acc[0][v], w[v]);
-        RowIO<WT>::store4(wrow + g.lc, w);
+        if (stream) RowIO<WT>::template store4<true>(wrow + g.lc, w);
+        else RowIO<WT>::store4(wrow + g.lc, w);
     }
 }
 
@@ -351,6 +361,7 @@ __global__ __launch_bounds__(kSegThreads, kSegWaves) void seg_update_kernel(cons
     if (a.counters[4] != 0u) return;
     reduce_parts<false, MEAN, GT, kSegWaves>(a);
     const uint32_t U = a.counters[0];
+    const bool stream = (uint64_t)U * a.row_bytes > a.stream_from;
     const uint32_t nwaves = gridDim.x * (kSegThreads / kWave);
     // rows per pass: 2^lg (see kPassRowsLog2), fewer where the batch touches so few rows that whole wavefronts would go idle while
     // others walk a pass one round after the other - down to as many as the widest table's rows a wavefront takes side by side
@@ -456,12 +467,12 @@ __global__ __launch_bounds__(kSegThreads, kSegWaves) void seg_update_kernel(cons
                 if (win_t != t_r || s_r + len_r - win > (uint32_t)kWave) load_window(r, s_r, t_r, ga.row0);
                 WT* const wrow = wtab + (uint64_t)(key_r - rb) * (uint32_t)g.D;
                 typename RowIO<WT>::raw4_t wraw;
-                if constexpr (kAhead) wraw = RowIO<WT>::load4_raw(wrow + lane_col);
+                if constexpr (kAhead) wraw = stream ? RowIO<WT>::template load4_raw<true>(wrow + lane_col) : RowIO<WT>::load4_raw(wrow + lane_col);
                 float acc[1][4] = {{0.f, 0.f, 0.f, 0.f}};
                 add_short<kSegUnroll, true, MEAN, GT>(acc, gcol, ga.pitch, lane_col, my_b, my_s, s_r - win, len_r, len_r);
                 if constexpr (kAhead)
-                    adagrad_row_loaded<WT>(acc, g, wrow, wraw, a.state + key_r, v_r, true, a.lr, a.eps, a.inv_c, a.state == nullptr);
-                else adagrad_row<WT, 1>(acc, g, wrow, a.state + key_r, v_r, true, a.lr, a.eps, a.inv_c, a.state == nullptr);
+                    adagrad_row_loaded<WT>(acc, g, wrow, wraw, a.state + key_r, v_r, true, a.lr, a.eps, a.inv_c, a.state == nullptr, stream);
+                else adagrad_row<WT, 1>(acc, g, wrow, a.state + key_r, v_r, true, a.lr, a.eps, a.inv_c, a.state == nullptr, stream);
                 todo &= todo - 1ull;
                 continue;
             }
@@ -482,7 +493,7 @@ __global__ __launch_bounds__(kSegThreads, kSegWaves) void seg_update_kernel(cons
             const uint32_t lmax = (uint32_t)wave_max_i32((int)glen);   // longest row of the round (wave-uniform loop bound)
             float acc[1][4] = {{0.f, 0.f, 0.f, 0.f}};
             add_short<kSideUnroll, false, MEAN, GT>(acc, gcol, ga.pitch, lane_col, my_b, my_s, gs - win, lmax, glen);
-            adagrad_row<WT, 1>(acc, g, wrow, a.state + gkey, gv, gon, a.lr, a.eps, a.inv_c, a.state == nullptr);
+            adagrad_row<WT, 1>(acc, g, wrow, a.state + gkey, gv, gon, a.lr, a.eps, a.inv_c, a.state == nullptr, stream);
             todo &= ~(((1ull << k) - 1ull) << r);
         }
     }
@@ -698,6 +709,8 @@ SegArgs seg_args(const tbe_handle* h, const Workspace& w, char* ws, const void* 
     a.sumD = h->sumD;
     a.maxD = h->maxD;
     a.total_rows = (uint32_t)h->total_rows;
+    a.stream_from = 0;
+    a.row_bytes = (uint32_t)(h->total_elems / h->total_rows) * (h->dtype == TBE_F32 ? 4u : 2u);
     a.lr = a.eps = a.inv_c = 0.f;
     a.tables = nullptr;
     a.state = nullptr;
@@ -738,6 +751,8 @@ hipError_t launch_segment_update(const tbe_handle* h, const Workspace& w, char* 
     a.inv_c = 1.0f / c;
     a.tables = tables;
     a.state = state;
+    const uint64_t grad_bytes = (uint64_t)B * (uint64_t)h->sumD * (grad_io == 0 ? 4u : 2u);   // (of sequences next to nothing: they are read once)
+    a.stream_from = grad_bytes < kInfinityCacheBytes ? kInfinityCacheBytes - grad_bytes : 0u;
     a.long_spans = long_spans(h, B, seq, grad_io == 0 ? 4u : 2u);
     const bool mean = pooling == TBE_MEAN;
     if (a.dense_n) {

@@ -73,7 +73,7 @@ __device__ __forceinline__ uint32_t block_excl_scan(uint32_t v, uint32_t* smem, 
     return wbase + inc - v;
 }
 
-// ---- streaming (non-temporal) 16-byte accesses: data that is used once should not displace what a cache is kept for
+// ---- streaming (non-temporal) accesses: data that is used once should not displace what a cache is kept for
 typedef uint32_t u32x4_t __attribute__((ext_vector_type(4)));
 __device__ __forceinline__ uint4 nt_load16(const void* p) {
     const u32x4_t v = __builtin_nontemporal_load(static_cast<const u32x4_t*>(p));
@@ -85,8 +85,12 @@ __device__ __forceinline__ void nt_store16(void* p, const uint4 v) {
     __builtin_nontemporal_store(x, static_cast<u32x4_t*>(p));
 }
 
+typedef uint32_t u32x2_t __attribute__((ext_vector_type(2)));
+__device__ __forceinline__ uint2 nt_load8(const void* p) {
+    const u32x2_t v = __builtin_nontemporal_load(static_cast<const u32x2_t*>(p));
+    return make_uint2(v.x, v.y);
+}
 __device__ __forceinline__ void nt_store8(void* p, const uint2 v) {
-    typedef uint32_t u32x2_t __attribute__((ext_vector_type(2)));
     u32x2_t x;
     x.x = v.x; x.y = v.y;
     __builtin_nontemporal_store(x, static_cast<u32x2_t*>(p));
@@ -277,13 +281,19 @@ struct RowIO<float> {
     }
     static __device__ __forceinline__ void unpack(const raw_t& r, float (&x)[4]) { x[0] = r.x; x[1] = r.y; x[2] = r.z; x[3] = r.w; }
     static __device__ __forceinline__ void load(const float* p, float (&x)[4]) { unpack(load_raw(p), x); }
-    // 4-element fragment used by the optimizer step (one lane owns 4 columns)
-    static __device__ __forceinline__ void load4(const float* p, float (&x)[4]) { load(p, x); }
+    // 4-element fragment used by the optimizer step (one lane owns 4 columns); NT: past the caches
     using raw4_t = float4;   // ... as it sits in registers between the load and its use
-    static __device__ __forceinline__ raw4_t load4_raw(const float* p) { return load_raw(p); }
+    template <bool NT = false>
+    static __device__ __forceinline__ raw4_t load4_raw(const float* p) {
+        if (!NT) return load_raw(p);
+        const uint4 v = nt_load16(p);
+        return make_float4(__uint_as_float(v.x), __uint_as_float(v.y), __uint_as_float(v.z), __uint_as_float(v.w));
+    }
     static __device__ __forceinline__ void unpack4(const raw4_t& r, float (&x)[4]) { x[0] = r.x; x[1] = r.y; x[2] = r.z; x[3] = r.w; }
+    template <bool NT = false>
     static __device__ __forceinline__ void store4(float* p, const float (&x)[4]) {
-        *reinterpret_cast<float4*>(p) = make_float4(x[0], x[1], x[2], x[3]);
+        if (NT) nt_store16(p, make_uint4(__float_as_uint(x[0]), __float_as_uint(x[1]), __float_as_uint(x[2]), __float_as_uint(x[3])));
+        else *reinterpret_cast<float4*>(p) = make_float4(x[0], x[1], x[2], x[3]);
     }
 };
 
@@ -314,8 +324,8 @@ struct RowIO<__half> {
     }
     static __device__ __forceinline__ void load(const __half* p, float (&x)[8]) { unpack(load_raw(p), x); }
     using raw4_t = uint2;
-    static __device__ __forceinline__ raw4_t load4_raw(const __half* p) { return *reinterpret_cast<const uint2*>(p); }
-    static __device__ __forceinline__ void load4(const __half* p, float (&x)[4]) { unpack4(load4_raw(p), x); }
+    template <bool NT = false>
+    static __device__ __forceinline__ raw4_t load4_raw(const __half* p) { return NT ? nt_load8(p) : *reinterpret_cast<const uint2*>(p); }
     static __device__ __forceinline__ void unpack4(const raw4_t& raw, float (&x)[4]) {
         x[0] = __half2float(__ushort_as_half((unsigned short)(raw.x & 0xFFFFu)));
         x[1] = __half2float(__ushort_as_half((unsigned short)(raw.x >> 16)));
@@ -323,11 +333,13 @@ struct RowIO<__half> {
         x[3] = __half2float(__ushort_as_half((unsigned short)(raw.y >> 16)));
     }
     // one rounding, to nearest even, from the fp32 result to the stored binary16
+    template <bool NT = false>
     static __device__ __forceinline__ void store4(__half* p, const float (&x)[4]) {
         uint2 raw;
         raw.x = (uint32_t)__half_as_ushort(__float2half_rn(x[0])) | ((uint32_t)__half_as_ushort(__float2half_rn(x[1])) << 16);
         raw.y = (uint32_t)__half_as_ushort(__float2half_rn(x[2])) | ((uint32_t)__half_as_ushort(__float2half_rn(x[3])) << 16);
-        *reinterpret_cast<uint2*>(p) = raw;
+        if (NT) nt_store8(p, raw);
+        else *reinterpret_cast<uint2*>(p) = raw;
     }
 };
 

@@ -39,6 +39,8 @@ struct SegArgs {
     const int64_t* w_off;
     int32_t T, B, sumD, maxD;
     uint32_t total_rows;
+    uint32_t row_bytes;           // of the handle's mean row
+    uint64_t stream_from;         // bytes of unique rows from which they are read and written past the caches
     float lr, eps, inv_c;
     void* tables;
     float* state;          // nullptr: plain SGD step, no moments
