@@ -280,7 +280,6 @@ struct RowIO<float> {
         acc[0] += r.x; acc[1] += r.y; acc[2] += r.z; acc[3] += r.w;
     }
     static __device__ __forceinline__ void unpack(const raw_t& r, float (&x)[4]) { x[0] = r.x; x[1] = r.y; x[2] = r.z; x[3] = r.w; }
-    static __device__ __forceinline__ void load(const float* p, float (&x)[4]) { unpack(load_raw(p), x); }
     // 4-element fragment used by the optimizer step (one lane owns 4 columns); NT: past the caches
     using raw4_t = float4;   // ... as it sits in registers between the load and its use
     template <bool NT = false>
@@ -322,7 +321,6 @@ struct RowIO<__half> {
             x[2 * i + 1] = __half2float(__ushort_as_half((unsigned short)(w[i] >> 16)));
         }
     }
-    static __device__ __forceinline__ void load(const __half* p, float (&x)[8]) { unpack(load_raw(p), x); }
     using raw4_t = uint2;
     template <bool NT = false>
     static __device__ __forceinline__ raw4_t load4_raw(const __half* p) { return NT ? nt_load8(p) : *reinterpret_cast<const uint2*>(p); }

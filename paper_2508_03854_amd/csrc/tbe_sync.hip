@@ -18,34 +18,66 @@ struct ReplicaPtrs {
     void* p[kMaxReplicas];
 };
 
-// 16 bytes per thread and iteration: the sum runs over the replicas in index order, in fp32, and is divided by M
+__device__ __forceinline__ uint4 pack(const float (&x)[4]) {
+    return make_uint4(__float_as_uint(x[0]), __float_as_uint(x[1]), __float_as_uint(x[2]), __float_as_uint(x[3]));
+}
+__device__ __forceinline__ uint4 pack(const float (&x)[8]) {   // binary16, to nearest even
+    uint32_t w[4];
+#pragma unroll
+    for (int i = 0; i < 4; ++i)
+        w[i] = (uint32_t)__half_as_ushort(__float2half_rn(x[2 * i])) | (uint32_t)__half_as_ushort(__float2half_rn(x[2 * i + 1])) << 16;
+    return make_uint4(w[0], w[1], w[2], w[3]);
+}
+
+// 16 bytes per thread and replica, or two such pieces: the sum runs over the replicas in index order, in fp32, and is divided by M
 // (a true division, so the result is the correctly rounded quotient of the fp32 sum).
-template <typename WT>
+// Bound: the stream, read once and written once.  The means are written past the caches, and replicas that together are much more than
+// the Infinity Cache holds (LARGE) read past them too, two pieces in flight; smaller ones find part of themselves there, and have the
+// workgroups to fill the chip at once instead.  Plain accesses / LARGE / the other, us: 4 x 60 M fp32 (960 MB) 378 / 354 / 379; 8 x
+// 10 M fp32 (320 MB) 105 / 113 / 94; 2 x 40 M fp32 (320) 109 / 111 / 105; 4 x 20 M binary16 (160) 48 / 55 / 46.
+constexpr size_t kLargeReplicas = (size_t)512 << 20;   // bytes of all of them
+template <typename WT, bool LARGE>
 __global__ __launch_bounds__(256) void replica_mean_kernel(const ReplicaPtrs r, const int M, const size_t nvec,
                                                            const size_t count) {
     constexpr int V = RowIO<WT>::kVec;
+    constexpr int U = LARGE ? 2 : 1;
+    using raw_t = typename RowIO<WT>::raw_t;
     const float fm = (float)M;
-    const size_t stride = (size_t)gridDim.x * blockDim.x;
-    for (size_t i = (size_t)blockIdx.x * blockDim.x + threadIdx.x; i < nvec; i += stride) {
-        float sum[V];
+    const size_t stride = (size_t)gridDim.x * blockDim.x * U;
+    for (size_t i0 = (size_t)blockIdx.x * blockDim.x * U + threadIdx.x; i0 < nvec; i0 += stride) {
+        float sum[U][V];
 #pragma unroll
-        for (int v = 0; v < V; ++v) sum[v] = 0.f;
+        for (int u = 0; u < U; ++u)
+#pragma unroll
+            for (int v = 0; v < V; ++v) sum[u][v] = 0.f;
         for (int m = 0; m < M; ++m) {
-            float x[V];
-            RowIO<WT>::load(static_cast<const WT*>(r.p[m]) + i * V, x);
+            raw_t raw[U];
 #pragma unroll
-            for (int v = 0; v < V; ++v) sum[v] += x[v];
-        }
+            for (int u = 0; u < U; ++u) {
+                const size_t i = i0 + u * blockDim.x < nvec ? i0 + u * blockDim.x : nvec - 1;
+                const WT* const src = static_cast<const WT*>(r.p[m]) + i * V;
+                if (LARGE) raw[u] = __builtin_bit_cast(raw_t, nt_load16(src));
+                else raw[u] = RowIO<WT>::load_raw(src);
+            }
 #pragma unroll
-        for (int v = 0; v < V; ++v) sum[v] /= fm;
-        for (int m = 0; m < M; ++m) {
-            WT* dst = static_cast<WT*>(r.p[m]) + i * V;
+            for (int u = 0; u < U; ++u) {
+                float x[V];
+                RowIO<WT>::unpack(raw[u], x);
 #pragma unroll
-            for (int v4 = 0; v4 < V; v4 += 4) {
-                const float q[4] = {sum[v4], sum[v4 + 1], sum[v4 + 2], sum[v4 + 3]};
-                RowIO<WT>::store4(dst + v4, q);
+                for (int v = 0; v < V; ++v) sum[u][v] += x[v];
             }
         }
+        uint4 mean[U];
+#pragma unroll
+        for (int u = 0; u < U; ++u) {
+#pragma unroll
+            for (int v = 0; v < V; ++v) sum[u][v] /= fm;
+            mean[u] = pack(sum[u]);
+        }
+        for (int m = 0; m < M; ++m)
+#pragma unroll
+            for (int u = 0; u < U; ++u)
+                if (i0 + u * blockDim.x < nvec) nt_store16(static_cast<WT*>(r.p[m]) + (i0 + u * blockDim.x) * V, mean[u]);
     }
     // the last count % V elements, one thread each
     const size_t tail0 = nvec * V;
@@ -58,17 +90,23 @@ __global__ __launch_bounds__(256) void replica_mean_kernel(const ReplicaPtrs r, 
     }
 }
 
+template <typename WT>
+static void launch_mean(const ReplicaPtrs& r, int M, size_t count, hipStream_t s) {
+    const size_t nvec = count / RowIO<WT>::kVec;
+    if ((size_t)M * count * sizeof(WT) > kLargeReplicas) {
+        replica_mean_kernel<WT, true><<<256 * 8, 256, 0, s>>>(r, M, nvec, count);
+    } else {
+        const size_t need = nvec / 256 + 1;   // (at least one workgroup, for the last few elements)
+        replica_mean_kernel<WT, false><<<(unsigned)(need < 16384 ? need : 16384), 256, 0, s>>>(r, M, nvec, count);
+    }
+}
+
 hipError_t launch_replica_mean(const tbe_handle* h, void* const* replicas, int M, size_t count, bool f32, hipStream_t s) {
     ReplicaPtrs r;
     for (int m = 0; m < kMaxReplicas; ++m) r.p[m] = m < M ? replicas[m] : nullptr;
     LaunchTimer tm(h, s, "replica_mean");
-    if (f32) {
-        const size_t nvec = count / RowIO<float>::kVec;
-        replica_mean_kernel<float><<<256 * 8, 256, 0, s>>>(r, M, nvec, count);
-    } else {
-        const size_t nvec = count / RowIO<__half>::kVec;
-        replica_mean_kernel<__half><<<256 * 8, 256, 0, s>>>(r, M, nvec, count);
-    }
+    if (f32) launch_mean<float>(r, M, count, s);
+    else launch_mean<__half>(r, M, count, s);
     tm.done();
     return hipGetLastError();
 }

@@ -1,0 +1,32 @@
+"""The replica mean on either side of the size from which it reads past the caches, and around its workgroups' pieces - against
+the sum in index order in fp32, one division, one rounding, bit for bit."""
+import pytest
+import torch
+
+pytestmark = pytest.mark.gpu
+
+
+@pytest.mark.parametrize("M,count,dtype", [
+    (2, 1, "f32"), (2, 7, "f16"), (3, 1023, "f32"), (3, 1025, "f32"), (2, 2049, "f16"), (16, 4097, "f16"),
+    (2, (1 << 26) + 1027, "f32"),                                 # just above 512 MB together, a ragged end
+    (4, (1 << 26) + 8 * 300 + 5, "f16"),
+    (2, (1 << 26), "f32"),                                        # just not: one round of 16384 workgroups is not enough
+    (5, 33_600_003, "f32"),
+])
+def test_mean_of_every_size(M, count, dtype):
+    if not torch.cuda.is_available():
+        pytest.skip("no GPU")
+    from paper_2508_03854_amd import TBE
+    dt = torch.float32 if dtype == "f32" else torch.float16
+    g = torch.Generator(device="cuda").manual_seed(M + count)
+    reps = [torch.empty(count + 16, dtype=dt, device="cuda").uniform_(-1, 1, generator=g) for _ in range(M)]
+    want = reps[0].float()
+    for r in reps[1:]:
+        want += r.float()
+    want /= M
+    tails = [r[count:].clone() for r in reps]
+    tbe = TBE([16], [8], dtype)
+    tbe.replica_mean([r[:count] for r in reps])
+    for r, tail in zip(reps, tails):
+        assert torch.equal(r[:count], want[:count].to(dt)) and torch.equal(r[count:], tail)
+    tbe.close()
