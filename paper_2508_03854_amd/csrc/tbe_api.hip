@@ -79,15 +79,31 @@ static size_t most_chunks(const tbe_handle* h, int64_t N) {
 // A row with more than this many lookups is long, i.e. shared out to several wavefronts in parts of this size.  A wavefront
 // walks 512 lookups of a wide row in about 60 us, so small batches, whose row updates take less than that, cut finer; the
 // borders follow from the memory of the partial sums (at most 2 n / part slots): never more than n / 48 plus a constant.
-static uint32_t long_min_of(int64_t N) {
-    return N <= ((int64_t)1 << 17) ? 64u : (N <= ((int64_t)3 << 17) ? 128u : (N <= ((int64_t)3 << 19) ? 256u : 512u));
+// The smallest batches are a matter of the longest chain of loads.  Where rows take a wavefront each they cut finer still, as long as
+// few lookups of a table keep the one workgroup that lists its long rows from becoming that chain.  Parts of 64 / 32 / 16, backward us: ten tables x 777 bags of 6 ids,
+// 8 to 1024 columns 70 / 59 / 59; 10 tables x 1200 lookups of 64, 256, 1024 columns 33.5 33.4 49.9 / 33.1 32.5 46.7 / 32.4 31.9 42.6;
+// one table x 12000 42.3 44.4 63.8 / 44.0 44.1 57.9 / 47.3 47.0 62.0; x 24000 53 55 93 / 57 58 94 / 63 62 96.
+struct PartSteps {
+    int64_t top[6];      // batches of at most so many lookups
+    uint32_t part[6];
+};
+static PartSteps part_steps(const tbe_handle* h) {
+    const int64_t T = h->T;
+    return {{h->maxD > 256 ? std::min((int64_t)32768, 4096 * T) : 0, h->maxD > 128 ? std::min((int64_t)65536, 8192 * T) : 0, (int64_t)1 << 17, (int64_t)3 << 17,
+             (int64_t)3 << 19, INT64_MAX},
+            {16, 32, 64, 128, 256, 512}};
 }
-// per_part(N / part) with the parts of this batch or of any smaller one: ascending in N
-static int64_t most_parts(int64_t N) {
+static uint32_t long_min_of(const PartSteps& p, int64_t N) {
+    int i = 0;
+    while (N > p.top[i]) ++i;
+    return p.part[i];
+}
+// N / part with the parts of this batch or of any smaller one: ascending in N
+static int64_t most_parts(const PartSteps& p, int64_t N) {
     int64_t m = 0;
-    for (const int64_t top : {(int64_t)1 << 17, (int64_t)3 << 17, (int64_t)3 << 19, N}) {
+    for (const int64_t top : p.top) {
         const int64_t n = top < N ? top : N;
-        m = std::max(m, n / (int64_t)long_min_of(n) + 1);
+        m = std::max(m, n / (int64_t)long_min_of(p, n) + 1);
     }
     return m;
 }
@@ -147,8 +163,9 @@ Workspace carve(const tbe_handle* h, int32_t B, int64_t N) {
         w.chunk_desc += shift;
     }
     w.counters = take(4 * kCounterWords);
-    w.long_min = long_min_of((int64_t)n);
-    w.cap_long = most_parts((int64_t)n);           // at most n / (long_min + 1) rows are long
+    const PartSteps steps = part_steps(h);
+    w.long_min = long_min_of(steps, (int64_t)n);
+    w.cap_long = most_parts(steps, (int64_t)n);           // at most n / (long_min + 1) rows are long
     w.cap_main = 2 * w.cap_long + 1;               // ceil(len / part) slots for a row of len > part lookups
     w.long_rows = take(8 * (size_t)w.cap_long);
     w.long_list = take(16 * (size_t)w.cap_long);

@@ -24,6 +24,7 @@ namespace tbe {
 
 constexpr int kListThreads = 1024;
 constexpr uint32_t kListRank = 1024;   // long rows of one table that are ranked; of more, the kHotRows longest are found first
+constexpr uint32_t kDenseMinLen = 64;  // dense rows have more lookups than this
 static_assert(kDenseRows <= kHotRows && kHotRows <= (int)kListRank && kListRank <= (uint32_t)kListThreads, "one thread per ranked row");
 
 // first i in [lo, hi) with ge(i), which is false before some i and true from it on, or hi; a whole wavefront, 64 probes per round
@@ -213,7 +214,7 @@ __device__ __forceinline__ void list_table(const SegArgs& a, ListLds* S, const i
                 rank += (l > my_len || (l == my_len && j < tid)) ? 1u : 0u;
             }
             if (a.hot_ids && rank < (uint32_t)kHotRows && my_len > kHotMin) a.hot_ids[(size_t)t * kHotRows + rank] = a.long_rows[i0 + my_k].y - rb;
-            if (rank < (uint32_t)kDenseRows) atomicAdd(&S->sum, my_len < 0x01000000u ? my_len : 0x01000000u);
+            if (rank < (uint32_t)kDenseRows && my_len > kDenseMinLen) atomicAdd(&S->sum, my_len < 0x01000000u ? my_len : 0x01000000u);
         }
         const uint32_t hot = (uint32_t)__syncthreads_count(my_len > kHotMin);
         if (a.hot_n && tid == 0) a.hot_n[t] = hot < (uint32_t)kHotRows ? hot : (uint32_t)kHotRows;
@@ -223,6 +224,10 @@ __device__ __forceinline__ void list_table(const SegArgs& a, ListLds* S, const i
         const bool filled = !MANY || (uint32_t)a.T * a.dense_chunks * ((D + 255u) / 256u) >= 128u;
         if (a.dense_n && filled && dense_block((uint32_t)a.B, D) && S->sum >= 2u * (uint32_t)a.B)
             nd = nc < (uint32_t)kDenseRows ? nc : (uint32_t)kDenseRows;
+        if (a.long_min < kDenseMinLen) {   // (the same for all) parts cut finer than dense rows are looked for
+            const uint32_t many = (uint32_t)__syncthreads_count(tid < nc && my_len > kDenseMinLen);
+            nd = nd < many ? nd : many;
+        }
     }
     // ---- parts of the rows that are not dense: their number, then the table's place in the unit list, and the dense rows'
     // places (which tables come first decides the order in which units are worked on, and addresses, nothing else)
