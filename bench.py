@@ -73,7 +73,8 @@ def algorithmic_bytes(cfg, nnz, U_t, ib=8, eb=4):
         "forward_pool": rows_bytes + nnz * ib + nb * ib + dense,
         "radix_hist": nnz * 4,
         "radix_scatter": nnz * 16,                                  # (key, bag id) in and out (pass 0: ids in)
-        "radix_binscan": 0,
+        "radix_scan": 0,
+        "sort_small": nnz * (ib + 8) + nb * ib,                     # ids in, (key, bag id) out
         "rle_count": nnz * 4,
         "rle_scan": 0,
         "rle_write": nnz * 4 + U * 8,

@@ -150,16 +150,14 @@ Workspace carve(const tbe_handle* h, int32_t B, int64_t N) {
         const size_t chunks = most_chunks(h, (int64_t)n);
         const size_t hist8 = (size_t)(w.sort.self_scan ? 2 : 4) * 256 * (chunks + 1);
         w.radix_hist = take(std::max(std::max(w.sort.hist_bytes, hist_cap((int64_t)n, w.sort.nseg)), hist8));
-        w.bin_tot = take(w.sort.self_scan ? 0 : 4 * 256 * (size_t)w.sort.nseg);
-        w.seg_chunk0 = take(w.sort.self_scan ? 0 : 4 * (size_t)(w.sort.nseg + 1));
+        w.nchunks = take(w.sort.self_scan ? 0 : 4);
         w.chunk_desc = take(32 * chunks);
         const size_t need = off - at;
         off = at;
         w.seg_start = take(std::max(4 * (n + 1), need));
         const size_t shift = off - at - need;
         w.radix_hist += shift;
-        w.bin_tot += shift;
-        w.seg_chunk0 += shift;
+        w.nchunks += shift;
         w.chunk_desc += shift;
     }
     w.counters = take(4 * kCounterWords);

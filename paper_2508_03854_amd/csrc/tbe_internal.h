@@ -105,7 +105,7 @@ struct Workspace {
     // (pooled calls) or its position (non-pooled calls), so vals[sorted] is the per-lookup stream the gradient
     // kernels read.  After the sort vals[spare] receives unique_rows.
     size_t keys[2], vals[2], seg_start, counters, long_rows, long_list, unit_list, hot_ids, hot_n, seq_gbase, dense_n, dense_tab,
-        dense_rows, dense_index, radix_hist, bin_tot, seg_chunk0, chunk_desc, rle_counts, partial, dense_partial, total;
+        dense_rows, dense_index, radix_hist, nchunks, chunk_desc, rle_counts, partial, dense_partial, total;
     SortShape sort;
     int rle_blocks;
     uint32_t long_min;    // a row with more lookups is long: it is cut into parts of about that many

@@ -23,16 +23,15 @@ struct SortArgs {
     const void* offsets;     // flag costs every load of the divergent searches a branch around two forms of it)
     const int64_t* row_base;
     ChunkDesc* desc;
-    uint32_t* chunk0;        // [nseg + 1] first chunk of every segment (large batches)
-    void* ghist;             // self-scan: uint16 [chunk][NB] (a chunk is one tile); else uint32 [digit][G]
-    uint32_t* bin_tot;       // [nseg][256] (large batches)
+    uint32_t* nchunks;       // chunks of all segments (large batches; else null)
+    void* ghist;             // self-scan: uint16 [chunk][NB] (a chunk is one tile); else uint32 at hist_word(chunk, digit)
     const uint32_t* keys_in;
     const uint32_t* vals_in;
     uint32_t* keys_out;
     uint32_t* vals_out;
     int32_t* err;
     int64_t N, chunk, nbags;
-    int32_t B, nseg, G, max_chunks;
+    int32_t B, nseg, max_chunks;
     int32_t shift;
     uint32_t mask, invalid_key;
     int32_t by_table;        // keys are table-local (a single table counts as such)
@@ -88,7 +87,7 @@ __device__ __forceinline__ uint32_t block_incl_max(uint32_t v, uint32_t* smem) {
 
 // Which chunk is this workgroup's?  Segment borders are offsets[t * B], forced into [0, N] and made ascending, so that
 // the chunks always tile [0, N) exactly, whatever the offsets array holds.  NT segments (the workgroup's threads) per round; every round
-// scans borders and chunk counts.  Workgroup 0 also leaves chunk0 for the binscan, if there is one.
+// scans borders and chunk counts.  Workgroup 0 also leaves the number of chunks for the scan of the histograms, if there is one.
 template <typename IT, int NT>
 __device__ __forceinline__ ChunkDesc find_chunk(const SortArgs& a, const uint32_t c, uint32_t* smem, ChunkDesc* s_desc) {
     if (threadIdx.x == 0) *s_desc = ChunkDesc{0, 0, 0, 0, 0, 0, 0, 0};
@@ -97,10 +96,7 @@ __device__ __forceinline__ ChunkDesc find_chunk(const SortArgs& a, const uint32_
         if (threadIdx.x == 0) {
             const int64_t s = (int64_t)c * a.chunk, n = (a.N + a.chunk - 1) / a.chunk;
             if (s < a.N) *s_desc = ChunkDesc{(uint32_t)s, (uint32_t)(s + a.chunk < a.N ? s + a.chunk : a.N), 0, 0, (uint32_t)n, 0, (uint32_t)a.N, 0};
-            if (c == 0 && a.chunk0) {
-                a.chunk0[0] = 0;
-                a.chunk0[1] = (uint32_t)n;
-            }
+            if (c == 0 && a.nchunks) *a.nchunks = (uint32_t)n;
         }
         __syncthreads();
         return *s_desc;
@@ -129,13 +125,10 @@ __device__ __forceinline__ ChunkDesc find_chunk(const SortArgs& a, const uint32_
             const int64_t e = s + a.chunk < (int64_t)b1 ? s + a.chunk : (int64_t)b1;
             *s_desc = ChunkDesc{(uint32_t)s, (uint32_t)e, (uint32_t)t, f, n, b0, b1, 0};
         }
-        if (c == 0 && a.chunk0) {
-            if (t < a.nseg) a.chunk0[t] = f;
-            if (t == a.nseg - 1) a.chunk0[a.nseg] = f + n;
-        }
+        if (c == 0 && a.nchunks && t == a.nseg - 1) *a.nchunks = f + n;
         carry_b = last;
         carry_c += tot;
-        if (carry_c > c && !(c == 0 && a.chunk0)) break;   // (the same for all threads) found
+        if (carry_c > c && !(c == 0 && a.nchunks)) break;   // (the same for all threads) found
     }
     __syncthreads();
     return *s_desc;

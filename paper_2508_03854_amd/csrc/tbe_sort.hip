@@ -11,7 +11,7 @@ namespace tbe {
 // positions; a chunk never crosses a segment border.  One workgroup owns one chunk in every pass:
 //   hist    : counts the digits of its chunk (pass 0: of the keys it makes from the ids, and leaves the chunk's
 //             descriptor for the kernels that follow)
-//   binscan : large batches only - block d turns ghist[d][*] into an exclusive scan per segment
+//   scan    : large batches only - adds up the chunks' histograms
 //   scatter : ranks the chunk tile by tile and writes (key, payload) to its final place inside the segment
 // Chunk k precedes chunk k+1, and the scatter ranks elements in input order, so the sort is stable.  The last pass
 // turns table-local keys into linearised ones as it writes them.
@@ -23,7 +23,7 @@ namespace tbe {
 //
 // Digits: up to 11 bits in batches of at most kSelfScanMax lookups, 8 bits beyond.  A small batch's time is its chain of
 // launches (about 4 us each), so it takes wide digits (fewer passes) and lets every scatter workgroup add up the
-// histograms of its segment's chunks by itself (no binscan launch).  In a large batch 2048 bins would leave runs of two
+// histograms of its segment's chunks by itself (no launch for the scan).  In a large batch 2048 bins would leave runs of two
 // keys per tile and bin to write, and the chunk histograms would be too many to add up per workgroup.
 //
 // Bound: launches and latency in small batches, the streams and the ranking beyond.  Measured, whole training step, against
@@ -110,6 +110,13 @@ __device__ __forceinline__ void load_ids(const IT* __restrict__ indices, const i
     for (int k = 0; k < ITEMS; ++k) id[k] = indices[first + k * kWave < p1 ? first + k * kWave : p1 - 1];
 }
 
+// Chunk histograms of a large batch: [group of kScanDigits digits][chunk][digit of the group], max_chunks + 1 chunks.  A workgroup of the
+// scan reads one group from end to end, a chunk's workgroups in pieces of 32 bytes.
+constexpr int kScanDigits = 8;
+__device__ __forceinline__ size_t hist_word(const SortArgs& a, const uint32_t chunk, const uint32_t d) {
+    return ((size_t)(d / kScanDigits) * ((uint32_t)a.max_chunks + 1u) + chunk) * kScanDigits + d % kScanDigits;
+}
+
 // Private histograms: lanes are spread over kCopies of them, which divides the number of lanes that meet on one LDS word
 // or bank (the kernel is bound by these LDS additions, not by the key stream: 1.04 ms with one copy per wavefront, 0.83 ms
 // with two, for the three passes of the largest workload).
@@ -177,41 +184,72 @@ __global__ __launch_bounds__(kRsThreads) void radix_hist_kernel(const SortArgs a
 #pragma unroll
         for (int q = 0; q < kCopies; ++q) c += h[q][d];
         if (SELF) static_cast<uint16_t*>(a.ghist)[(size_t)blockIdx.x * NB + d] = (uint16_t)c;
-        else static_cast<uint32_t*>(a.ghist)[(size_t)d * a.G + blockIdx.x] = c;
+        else static_cast<uint32_t*>(a.ghist)[hist_word(a, blockIdx.x, d)] = c;
     }
 }
 
-// grid = nbins blocks; block d scans row d of ghist in place: first over all chunks, then every segment's part is
-// re-based to start at zero; bin_tot[segment][d] = number of keys with digit d in the segment
-__global__ __launch_bounds__(kRsThreads) void radix_binscan_kernel(const SortArgs a) {
-    __shared__ uint32_t smem[kRsWaves];
-    __shared__ uint32_t s_b0[kMaxSortSegments];
-    uint32_t* row = static_cast<uint32_t*>(a.ghist) + (size_t)blockIdx.x * a.G;
-    const int nchunks = (int)a.chunk0[a.nseg];   // < G
-    uint32_t carry = 0;
-    for (int base = 0; base <= nchunks; base += 4 * kRsThreads) {   // four counts per thread and round
-        const int i = base + 4 * (int)threadIdx.x;
-        uint32_t v[4];
-#pragma unroll
-        for (int q = 0; q < 4; ++q) v[q] = (i + q < nchunks) ? row[i + q] : 0u;
-        uint32_t tot;
-        uint32_t run = carry + block_excl_scan<kRsThreads>(v[0] + v[1] + v[2] + v[3], smem, &tot);
-#pragma unroll
-        for (int q = 0; q < 4; ++q) {
-            if (i + q <= nchunks) row[i + q] = run;     // row[nchunks] = total
-            run += v[q];
-        }
-        carry += tot;
+// Large batches: every chunk's count of a digit becomes the sum of those of all chunks before it, chunk nchunks gets the sum of all; a
+// chunk's place within its segment is the difference to the segment's first.  A workgroup takes kScanDigits digits of all chunks, a
+// thread one of them in a run of consecutive chunks, held in registers.
+// Bound: latency.  All histograms, scans and scatters of a step with a row of all chunks per digit (256 scattered words for every
+// chunk's workgroups) / a row of all digits per chunk (every scan workgroup reads all of it) / this, us: 32 tables,
+// 26 M lookups 124 + 58 + 301 / 98 + 98 + 287 / 101 + 54 + 289; 16 tables, 5.5 M 45 + 24 + 92 / 39 + 28 + 89 / 39 + 19 + 89; 64 tables, 65 M
+// 301 + 72 + 851 / 274 + 110 + 844 / 284 + 57 + 851.
+constexpr int kScanThreads = 1024, kScanParts = kScanThreads / kScanDigits;
+// exclusive prefix of the threads' sums over the parts of a digit
+__device__ __forceinline__ uint32_t scan_parts(uint32_t (&s_part)[kScanDigits][kScanParts], const uint32_t dl, const uint32_t part, const uint32_t sum) {
+    s_part[dl][part] = sum;
+    __syncthreads();
+    if (threadIdx.x < kScanDigits * kWave) {   // a wavefront per digit: two parts per lane
+        uint2* const p = reinterpret_cast<uint2*>(s_part[threadIdx.x / kWave]) + lane_id();
+        const uint2 v = *p;
+        const uint32_t before = wave_incl_scan(v.x + v.y) - v.x - v.y;
+        *p = make_uint2(before, before + v.x);
     }
     __syncthreads();
-    for (int t = threadIdx.x; t < a.nseg; t += kRsThreads) {
-        const uint32_t b0 = row[a.chunk0[t]], b1 = row[a.chunk0[t + 1]];
-        s_b0[t] = b0;
-        a.bin_tot[(size_t)t * 256 + blockIdx.x] = b1 - b0;
-    }
-    __syncthreads();
-    for (int i = threadIdx.x; i < nchunks; i += kRsThreads) row[i] -= s_b0[a.desc[i].seg];
+    return s_part[dl][part];
 }
+template <int HELD>
+__device__ __forceinline__ void scan_held(uint32_t (&s_part)[kScanDigits][kScanParts], const uint32_t dl, const uint32_t part, uint32_t* const col,
+                                          const uint32_t r0, const uint32_t r1, const uint32_t rows, const uint32_t nchunks) {
+    uint32_t v[HELD], sum = 0;
+#pragma unroll
+    for (int u = 0; u < HELD; ++u) v[u] = col[(size_t)umin(r0 + u, nchunks - 1u) * kScanDigits];
+#pragma unroll
+    for (int u = 0; u < HELD; ++u) sum += r0 + u < r1 ? v[u] : 0u;
+    uint32_t run = scan_parts(s_part, dl, part, sum);
+#pragma unroll
+    for (int u = 0; u < HELD; ++u) {
+        if (r0 + u < r1 || (r0 + u == nchunks && (uint32_t)u < rows)) col[(size_t)(r0 + u) * kScanDigits] = run;   // (the part's own rows alone)
+        run += r0 + u < r1 ? v[u] : 0u;
+    }
+}
+__global__ __launch_bounds__(kScanThreads) void radix_scan_kernel(const SortArgs a) {
+    __shared__ uint32_t s_part[kScanDigits][kScanParts];
+    const uint32_t nchunks = *a.nchunks;   // at most max_chunks
+    const uint32_t dl = threadIdx.x & (kScanDigits - 1), part = threadIdx.x / kScanDigits;
+    uint32_t* const col = static_cast<uint32_t*>(a.ghist) + hist_word(a, 0u, blockIdx.x * kScanDigits + dl);
+    const uint32_t rows = (nchunks + kScanParts) / kScanParts;   // of every part: nchunks + 1 of them in all
+    const uint32_t r0 = part * rows, r1 = umin(r0 + rows, nchunks);
+    if (rows <= 12u) {
+        scan_held<12>(s_part, dl, part, col, r0, r1, rows, nchunks);
+    } else if (rows <= 32u) {
+        scan_held<32>(s_part, dl, part, col, r0, r1, rows, nchunks);
+    } else if (rows <= 66u) {
+        scan_held<66>(s_part, dl, part, col, r0, r1, rows, nchunks);
+    } else {
+        uint32_t sum = 0;
+        for (uint32_t r = r0; r < r1; ++r) sum += col[(size_t)r * kScanDigits];
+        uint32_t run = scan_parts(s_part, dl, part, sum);
+        for (uint32_t r = r0; r < r1; ++r) {
+            const uint32_t v = col[(size_t)r * kScanDigits];
+            col[(size_t)r * kScanDigits] = run;
+            run += v;
+        }
+        if (nchunks >= r0 && nchunks < r0 + rows) col[(size_t)nchunks * kScanDigits] = run;
+    }
+}
+static_assert(kScanParts == 2 * kWave && kScanDigits * kWave <= kScanThreads, "two parts per lane, a wavefront per digit");
 
 template <int NB, int ITEMS>
 struct ScatterLds {
@@ -383,8 +421,10 @@ __global__ __launch_bounds__(kRsThreads, NB == 256 && !FIRST ? 4 : 1) void radix
                     }
             }
         } else {
-            tot[0] = (uint32_t)tid <= a.mask ? a.bin_tot[(size_t)ds.seg * 256 + tid] : 0u;
-            pre[0] = (uint32_t)tid <= a.mask ? static_cast<const uint32_t*>(a.ghist)[(size_t)tid * a.G + chunk] : 0u;
+            const uint32_t* const q = static_cast<const uint32_t*>(a.ghist);
+            const uint32_t first = q[hist_word(a, ds.first, tid)];
+            tot[0] = q[hist_word(a, ds.first + ds.count, tid)] - first;
+            pre[0] = q[hist_word(a, chunk, tid)] - first;
         }
 #pragma unroll
         for (int j = 0; j < K; ++j) sum += tot[j];
@@ -421,8 +461,8 @@ static void launch_pass(const tbe_handle* h, const SortArgs& a, const SortShape&
         tm.done();
     }
     if (!SELF) {
-        LaunchTimer tm(h, s, "radix_binscan");
-        radix_binscan_kernel<<<a.mask + 1u, kRsThreads, 0, s>>>(a);
+        LaunchTimer tm(h, s, "radix_scan");
+        radix_scan_kernel<<<256 / kScanDigits, kScanThreads, 0, s>>>(a);
         tm.done();
     }
     LaunchTimer tm(h, s, "radix_scatter");
@@ -581,16 +621,14 @@ hipError_t launch_sort(const tbe_handle* h, const Workspace& w, char* ws, const 
     a.offsets = offsets;
     a.row_base = h->d_row_base;
     a.desc = reinterpret_cast<ChunkDesc*>(ws + w.chunk_desc);
-    a.chunk0 = sh.self_scan ? nullptr : reinterpret_cast<uint32_t*>(ws + w.seg_chunk0);
+    a.nchunks = sh.self_scan ? nullptr : reinterpret_cast<uint32_t*>(ws + w.nchunks);
     a.ghist = ws + w.radix_hist;
-    a.bin_tot = reinterpret_cast<uint32_t*>(ws + w.bin_tot);
     a.err = h->d_err;
     a.N = N;
     a.chunk = sh.chunk;
     a.nbags = (int64_t)h->T * B;
     a.B = B;
     a.nseg = sh.nseg;
-    a.G = sh.max_chunks + 1;
     a.max_chunks = sh.max_chunks;
     a.mask = (1u << sh.bits) - 1u;
     a.invalid_key = (uint32_t)h->total_rows;

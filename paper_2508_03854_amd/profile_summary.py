@@ -42,9 +42,9 @@ XCDS = 8   # GRBM_GUI_ACTIVE comes back summed over the chip's 8 dies (8 x 2.3e9
 RECORD = {
     "forward_kernel": "forward_pool", "forward_groups_kernel": "forward_pool", "forward_hot_kernel": "forward_pool",
     "forward_long_bags_kernel": "forward_pool",
-    "radix_hist_kernel": "radix_hist", "radix_binscan_kernel": "radix_binscan", "radix_scatter_kernel": "radix_scatter",
+    "radix_hist_kernel": "radix_hist", "radix_scan_kernel": "radix_scan", "radix_scatter_kernel": "radix_scatter",
     "rle_count_kernel": "rle_count", "rle_scan_kernel": "rle_scan", "rle_write_kernel": "rle_write",
-    "rle_one_block_kernel": "rle_write", "list_rows_kernel": "seg_long_list", "list_rows_flat_kernel": "seg_long_list",
+    "sort_small_kernel": "sort_small", "rle_small_kernel": "rle_write", "rle_one_block_kernel": "rle_write", "list_rows_kernel": "seg_long_list", "list_rows_flat_kernel": "seg_long_list",
     "dense_index_kernel": "seg_long_list", "seg_dense_kernel": "seg_dense_partial", "seg_update_kernel": "seg_update",
     "seg_update_wide_kernel": "seg_update", "seg_long_update_kernel": "seg_long_update",
 }
