@@ -213,17 +213,18 @@ struct Totals<true, V> {
     }
 };
 
+constexpr int kGroupThreads = 256;   // of the kernel of plain lane groups
 // ... in LDS, for a kernel that can spare it: [V][threads of the workgroup]
 template <bool SPLIT, int V>
 struct LdsTotals {
-    __device__ __forceinline__ LdsTotals(double (*)[kFwdThreads]) {}
+    __device__ __forceinline__ LdsTotals(double (*)[kGroupThreads]) {}
     __device__ __forceinline__ void add(float (&)[V], bool) {}
     __device__ __forceinline__ void finish(float (&)[V], bool) {}
 };
 template <int V>
 struct LdsTotals<true, V> {
-    double (*sum)[kFwdThreads];
-    __device__ __forceinline__ LdsTotals(double (*s)[kFwdThreads]) : sum(s) {
+    double (*sum)[kGroupThreads];
+    __device__ __forceinline__ LdsTotals(double (*s)[kGroupThreads]) : sum(s) {
 #pragma unroll
         for (int v = 0; v < V; ++v) sum[v][threadIdx.x] = 0.0;
     }
@@ -241,58 +242,118 @@ struct LdsTotals<true, V> {
     }
 };
 
-// Narrow rows (at most 16 lanes per row): every lane group of the wavefront takes a bag of its own, G = 64 / LPR
-// consecutive bags of one table per wavefront.  A bag of a dozen narrow rows is a few hundred bytes; with one
-// wavefront per bag the step is bound by the latency of the offsets -> ids -> rows chain, not by bandwidth.
-// A group reads LPR ids with one coalesced load, then walks them U rows at a time.
-template <typename WT, int U, bool MEAN>
-__global__ __launch_bounds__(kFwdThreads, 8) void forward_groups_kernel(
+// Narrow rows (at most 32 lanes per row): every lane group of the wavefront takes a bag of its own, G = 64 / LPR bags of one table per
+// wavefront.  A bag of a dozen narrow rows is a few hundred bytes; with one wavefront per bag the step is bound by the latency of the
+// offsets -> ids -> rows chain, not by bandwidth.  A group reads LPR ids with one coalesced load, then walks them U rows at a time.
+// BY_LENGTH: the workgroup hands its bags out by length, longest first, so that those that share a wavefront are of a length: a
+// wavefront walks as far as the longest of its bags.  Consecutive bags / this, us: 32 tables x 65536 bags, lognormal of 12 ids on
+// average, 2 of 128 and 30 of 32 fp32 columns 482 / 410; 16 tables x 32768 bags: 8 fp32 columns, lognormal of 12 and 35 ids 98 213 / 85
+// 180; 32 fp32 123 308 / 110 267, 1 + Poisson(30) 136 / 127, fixed 40 158 / 157; 64 binary16, lognormal 164 351 / 156 328.  Several such
+// rounds per workgroup level the lengths further (the first 372 with 8) but spread the workgroups that run at a time over more tables:
+// fixed 40 of 32 fp32 columns 169, 179, 190 with 2, 4, 8 of them; workgroups of 512 threads 432 at the first.
+constexpr uint32_t kLongBag = 255u;                      // in place of a length above kLongBagMax: the bag is left to another kernel
+struct BagOrder {
+    uint32_t start[kGroupThreads / 4], bin[kLongBagMax + 1];   // (at least 4 lanes per bag)
+    uint8_t len[kGroupThreads / 4], bag[kGroupThreads / 4];    // by place in the table; the places by length
+};
+static_assert(kLongBagMax < (int)kLongBag && kLongBagMax < 3 * kWave && kLongBagMax < kGroupThreads && kGroupThreads / 4 <= 256,
+              "lengths and places in a byte, three lengths per lane");
+template <typename WT, int U, bool MEAN, bool BY_LENGTH>
+__global__ __launch_bounds__(kGroupThreads, 8) void forward_groups_kernel(
     const WT* __restrict__ weights, const IdxView indices, const IdxView offsets,
     const int32_t* __restrict__ D_off, const int64_t* __restrict__ w_off, const int64_t* __restrict__ row_base,
     const int32_t* __restrict__ tables_of_class, const int32_t n_tables, const int lpr_log2, const int32_t B,
     const int64_t nnz, const int32_t sumD, void* __restrict__ out, const int out_io, int32_t* err) {
     constexpr int V = RowIO<WT>::kVec;
     using raw_t = typename RowIO<WT>::raw_t;
+    __shared__ double s_total[V][kGroupThreads];
+    __shared__ typename std::conditional<BY_LENGTH, BagOrder, int>::type S;
     const int lane = lane_id();
     const int LPR = 1 << lpr_log2;
     const int G = kWave >> lpr_log2;
-    const int64_t per_table = ((int64_t)B + G - 1) / G;   // wavefronts per table
-    const int64_t wid = (int64_t)blockIdx.x * (kFwdThreads / kWave) + (threadIdx.x >> 6);
-    const int64_t i = wid / per_table;
-    if (i >= n_tables) return;
-    const int32_t t = __builtin_amdgcn_readfirstlane(tables_of_class[i]);   // (the same for the wavefront: its table's numbers stay scalar)
     const int sub = lane >> lpr_log2;
     const int li = lane & (LPR - 1);        // lane inside its group
     const int lc = li * V;
-    const uint32_t b = (uint32_t)((wid - i * per_table) * G) + (uint32_t)sub;   // (below 2^31 + 64)
-    const bool has_bag = b < (uint32_t)B;
+    const int wv = (int)(threadIdx.x >> 6);
+    // ---- the table, and the first bag of this wavefront or (BY_LENGTH) workgroup
+    const int bags = BY_LENGTH ? kGroupThreads >> lpr_log2 : G;
+    const int64_t per_table = ((int64_t)B + bags - 1) / bags;   // wavefronts or workgroups per table
+    const int64_t wid = BY_LENGTH ? (int64_t)blockIdx.x : (int64_t)blockIdx.x * (kGroupThreads / kWave) + wv;
+    const int64_t i = wid / per_table;
+    if (i >= n_tables) return;
+    const int32_t t = __builtin_amdgcn_readfirstlane(tables_of_class[i]);   // (the same for the wavefront: its table's numbers stay scalar)
+    const uint32_t b0 = (uint32_t)((wid - i * per_table) * bags);   // (below 2^31)
     const int32_t d0 = D_off[t];
     const int D = D_off[t + 1] - d0;
     const int64_t R = row_base[t + 1] - row_base[t];
     const WT* table = weights + w_off[t];
-    const BagSpan bag = bag_span(offsets, t, B, b, nnz);
-    const int full_len = bag.len;
+    const bool col_on = lc < D;
     // a bag far longer than its neighbours would keep the other groups of the wavefront waiting: such bags are left to
     // forward_long_bags_kernel, where a whole wavefront walks one bag
-    bool split = full_len > long_bag_min(LPR), is_long = false;
-    if (__any(split)) {
-        is_long = split && long_bag(full_len, table_lookups(offsets, t, B), B);
-        split = split && !is_long;
+    const int long_min = long_bag_min(LPR);
+    uint32_t b = b0 + (uint32_t)sub, start;
+    int len;
+    bool is_long = false;
+    if constexpr (BY_LENGTH) {
+        const int64_t lookups = table_lookups(offsets, t, B);
+        const int k = (int)threadIdx.x;
+        if (k <= kLongBagMax) S.bin[k] = 0u;
+        __syncthreads();
+        uint32_t my_len = 0;
+        if (k < bags) {
+            const BagSpan bag = bag_span(offsets, t, B, b0 + (uint32_t)k, nnz);
+            const bool lng = bag.len > long_min && long_bag(bag.len, lookups, B);
+            my_len = lng ? 0u : (uint32_t)bag.len;
+            S.start[k] = bag.start;
+            S.len[k] = (uint8_t)(lng ? kLongBag : my_len);
+            atomicAdd(&S.bin[my_len], 1u);
+        }
+        __syncthreads();
+        if (wv == 0) {   // where each length begins, the longest first: three bins per lane
+            uint32_t c[3], sum = 0;
+#pragma unroll
+            for (int q = 0; q < 3; ++q) {
+                const int l = kLongBagMax - 3 * lane - q;
+                c[q] = l >= 0 ? S.bin[l] : 0u;
+                sum += c[q];
+            }
+            uint32_t at = wave_incl_scan(sum) - sum;
+#pragma unroll
+            for (int q = 0; q < 3; ++q) {
+                const int l = kLongBagMax - 3 * lane - q;
+                if (l >= 0) S.bin[l] = at;
+                at += c[q];
+            }
+        }
+        __syncthreads();
+        if (k < bags) S.bag[atomicAdd(&S.bin[my_len], 1u)] = (uint8_t)k;   // (a bag's sum does not depend on the bags beside it)
+        __syncthreads();
+        const int mine = S.bag[wv * G + sub];
+        b = b0 + (uint32_t)mine;
+        start = S.start[mine];
+        len = S.len[mine];
+        is_long = len == (int)kLongBag;
+        len = is_long ? 0 : len;
+    } else {
+        const BagSpan bag = bag_span(offsets, t, B, b, nnz);
+        start = bag.start;
+        len = bag.len;
+        if (__any(len > long_min)) is_long = len > long_min && long_bag(len, table_lookups(offsets, t, B), B);
+        len = is_long ? 0 : len;
     }
-    const int len = is_long ? 0 : full_len;
+    const bool split = len > long_min;
+    const bool has_bag = b < (uint32_t)B;
     const int maxlen = wave_max_i32(len);   // longest bag of the wavefront: the loop bounds below are wave-uniform
-    __shared__ double s_total[V][kFwdThreads];
     float acc[V];
 #pragma unroll
     for (int v = 0; v < V; ++v) acc[v] = 0.f;
-    const bool col_on = lc < D;
     auto walk = [&](auto split_c) {
         constexpr bool kSplit = decltype(split_c)::value;
         LdsTotals<kSplit, V> total(s_total);
         for (int base = 0; base < maxlen; base += LPR) {
             int32_t my = -1;
             if (base + li < len) {
-                const int64_t id = indices[(int64_t)bag.start + base + li];
+                const int64_t id = indices[(int64_t)start + base + li];
                 if (id >= 0 && id < R) my = (int32_t)id;
                 else atomicOr(err, 1);
             }
@@ -649,6 +710,10 @@ static void launch_forward_nc(const tbe_handle* h, int first, int n, const void*
                                                                       list, n, B, nnz, h->sumD, out, out_io, h->d_err);
 }
 
+// Workgroups from which a launch of lane groups hands bags out by length: as many as the chip holds at a time.  Smaller ones pay
+// 0.2 to 0.5 us for the four barriers and have nothing to fill the gaps with: 8 tables x 4096 bags, 1 + Poisson(10) ids, 8 fp32 columns
+// 15.0 -> 15.7 us, 64 binary16 15.4 -> 15.8, 64 fp32 16.1 -> 16.4.
+constexpr int64_t kByLengthWorkgroups = 2048;
 // the narrow-row classes: 32, 16, 8 and 4 lanes per row
 template <typename WT>
 static void launch_forward_groups(const tbe_handle* h, const void* tables, const int32_t* d_D_off, const IdxView indices,
@@ -662,7 +727,7 @@ static void launch_forward_groups(const tbe_handle* h, const void* tables, const
         const int lpr_log2 = 6 - c;              // 32, 16, 8, 4 lanes per row
         const int G = kWave >> lpr_log2;
         const int64_t waves = (int64_t)n * (((int64_t)B + G - 1) / G);
-        const dim3 grid((unsigned)((waves + wpb - 1) / wpb));
+        dim3 grid((unsigned)((waves + kGroupThreads / kWave - 1) / (kGroupThreads / kWave)));
         const int32_t* list = h->d_fwd_tables + h->fwd_first[c];
         // with a hot-row list in the handle, and enough bags per table to fill a workgroup's rounds
         const int cpt = hot_chunks(h, c, B);
@@ -678,12 +743,20 @@ static void launch_forward_groups(const tbe_handle* h, const void* tables, const
                     h->d_err, h->d_hot_ids, h->d_hot_n, cpt);
             continue;
         }
-        if (mean)
-            forward_groups_kernel<WT, 8, true><<<grid, kFwdThreads, 0, s>>>(
+        const int64_t bags = kGroupThreads >> lpr_log2;   // of a workgroup
+        const int64_t groups = (int64_t)n * (((int64_t)B + bags - 1) / bags);
+        auto go = [&](auto mean_c, auto by_length_c) {
+            forward_groups_kernel<WT, 8, decltype(mean_c)::value, decltype(by_length_c)::value><<<grid, kGroupThreads, 0, s>>>(
                 w, indices, offsets, d_D_off, h->d_w_off, h->d_row_base, list, n, lpr_log2, B, nnz, h->sumD, out, out_io, h->d_err);
-        else
-            forward_groups_kernel<WT, 8, false><<<grid, kFwdThreads, 0, s>>>(
-                w, indices, offsets, d_D_off, h->d_w_off, h->d_row_base, list, n, lpr_log2, B, nnz, h->sumD, out, out_io, h->d_err);
+        };
+        if (groups >= kByLengthWorkgroups) {
+            grid = dim3((unsigned)groups);
+            if (mean) go(std::true_type{}, std::true_type{});
+            else go(std::false_type{}, std::true_type{});
+        } else {
+            if (mean) go(std::true_type{}, std::false_type{});
+            else go(std::false_type{}, std::false_type{});
+        }
     }
     // the bags those launches left out (the four classes' tables follow one another in the list)
     const int n_all = h->fwd_count[1] + h->fwd_count[2] + h->fwd_count[3] + h->fwd_count[4];

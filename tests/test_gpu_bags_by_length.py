@@ -1,0 +1,46 @@
+"""The lane groups of large launches, which hand a workgroup's bags out by length: ragged ends, empty, ordinary, split and long bags,
+every class of row widths and output type, on both sides of the line - against 64-bit sums."""
+import pytest
+import torch
+
+pytestmark = pytest.mark.gpu
+
+
+@pytest.mark.parametrize("lanes,dtype,pooling,io", [
+    (4, "f32", "sum", torch.float32), (3, "f16", "mean", torch.float16), (8, "f32", "mean", torch.bfloat16), (7, "f16", "sum", torch.float32),
+    (16, "f32", "sum", torch.float16), (13, "f16", "sum", torch.bfloat16), (32, "f32", "mean", torch.float32), (25, "f16", "mean", torch.float16),
+])
+def test_bags_of_large_launches(lanes, dtype, pooling, io):
+    if not torch.cuda.is_available():
+        pytest.skip("no GPU")
+    from paper_2508_03854_amd import TBE, binding
+    T, R, dev = 3, 400, "cuda"
+    D = lanes * (8 if dtype == "f16" else 4)
+    per_wg = 256 // (4 if lanes <= 4 else 8 if lanes <= 8 else 16 if lanes <= 16 else 32)
+    line = max(2048 // T * per_wg, 5600)                           # 2046 workgroups of whole bags, then 2049 (8 bags each: 2100 on, smaller batches go another way)
+    tbe = TBE([R] * T, [D] * T, dtype)
+    tbe.set_tunable("hot_rows_min_workgroups", -1)                 # plain lane groups at every size
+    g = torch.Generator(device=dev).manual_seed(lanes)
+    w = torch.empty(tbe.total_elems, device=dev).uniform_(-1, 1, generator=g).to(tbe.torch_dtype)
+    for B in (line, line + 1, line + per_wg - 1):
+        lens = torch.round(torch.exp(1.2 + torch.randn(T * B, generator=g, device=dev))).long().clamp_(0, 127)
+        lens[::7] = 0
+        lens[5::1009] = torch.tensor([31, 33, 47, 49, 63, 65, 127, 128, 129, 255, 300], device=dev).repeat(len(lens[5::1009]) // 11 + 1)[:len(lens[5::1009])]
+        off = torch.zeros(T * B + 1, dtype=torch.int64, device=dev)
+        torch.cumsum(lens, 0, out=off[1:])
+        idx = torch.randint(0, R, (int(off[-1]),), generator=g, device=dev)
+        assert tbe.debug_forward_kernels(B, idx.numel()) == binding.FWD_LANE_GROUPS | binding.FWD_LONG_BAGS
+        out = tbe.forward_ex(w, idx.int(), off.int(), B, pooling, out=torch.full((B, T * D), 7.0, dtype=io, device=dev)).double()
+        assert not tbe.poll_index_error()
+        for t in range(T):
+            o = off[t * B:(t + 1) * B + 1]
+            L = (o[1:] - o[:-1]).double()[:, None]
+            rows = w[t * R * D:(t + 1) * R * D].view(R, D).double()[idx[int(o[0]):int(o[-1])]]
+            want = torch.zeros(B, D, dtype=torch.float64, device=dev)
+            want.index_add_(0, torch.repeat_interleave(torch.arange(B, device=dev), o[1:] - o[:-1]), rows)
+            if pooling == "mean":
+                want /= L.clamp(min=1.0)
+            # a 32-bit sum of L values of at most 1 (a mean: one L-th of that, and one division), rounded once to the output's type
+            err = 2.0 ** -24 * (L * L if pooling == "sum" else L + 1.0) + want.abs() * {torch.float32: 0.0, torch.float16: 2.0 ** -11, torch.bfloat16: 2.0 ** -8}[io] + 2.0 ** -24
+            assert ((out[:, t * D:(t + 1) * D] - want).abs() <= err).all(), (B, t)
+    tbe.close()
