@@ -25,12 +25,17 @@
 // Tables narrower than 256 columns give the spare wavefronts a share of the bags.  Two workgroups per compute unit (68 KB of
 // LDS, 128 accumulator registers) overlap each other's counting.  The partial sums of a row, one per workgroup, are added
 // in order by the kernel that applies the step, so the result does not depend on scheduling.
+// Tables of up to 64 columns have a form of their own (dense_run_narrow), for there the count table, whose size does not shrink with
+// the columns, is what takes the time: 30 tables x 65536 bags x 32 columns, long-tailed bags, Zipf 1.3, mean pooling, 277 -> 191 us,
+// bfloat16 250 -> 165; 16 x 32768 x 64, Zipf 1.1, binary16 gradients 76 -> 60, fp32 and mean pooling 85 -> 74.  Taken for 65 to 128
+// columns too (four groups, each turning all counts into bfloat16 again) 137 -> 145.
 // Bound: wide tables by the stream of the gradient block, at about half the copy rate (64 tables x 32768 bags, 48 of 256
-// columns: 1.9 GB in 0.67 ms), narrow ones by the count table, whose size does not shrink with the columns (32 tables x 65536
-// bags, 30 of 32 columns: 0.32 GB in 0.29 ms).  Measured, whole training step, against 16 dense rows on the vector units and
-// sweeps over the rest: the former 9.5 -> 8.2 ms, the latter, mean pooling, 2.5 -> 1.7 ms.  Of that, the loads ahead of the
-// matrix instructions 20 us of 690; the runs cost 85 us of 607 (and 8 of 296 at 32 columns).  All variants but the two of
-// 16-bit gradients under mean pooling (2 registers each) compile without spilled vector registers.
+// columns: 1.9 GB in 0.64 ms), narrow ones by the chain of searches, list loads and LDS additions that fills the count table (a block
+// of 256 bags takes 12 us, two at a time per compute unit, for about 4 us of instructions).
+// Measured, whole training step, against 16 dense rows on the vector units and sweeps over the rest: the former 9.5 -> 8.2 ms, the
+// latter, mean pooling, 2.5 -> 1.7 ms.  Of that, the loads ahead of the matrix instructions 20 us of 690; the runs cost 85 us of 607
+// (and 8 of 296 at 32 columns); the counting as a function of its own, whose registers the compiler then lays out apart, 690 -> 645.
+// Spilled vector registers: 7 to 9 under mean pooling, 1 with 16-bit gradients, none else.
 // 0 * Inf is NaN, so a non-finite element of one bag's gradient reaches every dense row of its table here; the kernel that
 // adds the partial sums reduces such rows again from their own lookups.
 #include "tbe_rows.h"
@@ -100,6 +105,71 @@ struct DenseLds {
     uint32_t lo[kDenseRows], pref[kDenseRows], scan[kDThreads / kWave], flags;
 };
 
+// The counts of a block of bags, in the table: ix0 and ix1 where the thread's dense row starts and ends in the block, L its bag's
+// length.  `round`: bags of more than 65535 ids are counted 65535 at a time.  Returns 0, or whether a bag of the block has more
+// ids than a byte counts (bit 0), or than a round does (bit 1).
+template <int MT, bool MEAN, int kU>
+__device__ __forceinline__ uint32_t count_block(const SegArgs& a, const uint32_t nd, const uint32_t ix0, const uint32_t ix1, const uint32_t L,
+                                                const int64_t bag0, const uint32_t b0, const uint32_t nb, const uint32_t round, DenseLds* S) {
+    const uint32_t tid = threadIdx.x;
+    uint16_t* const s_cnt = S->cnt;
+    uint32_t* const s_lo = S->lo;
+    uint32_t* const s_pref = S->pref;
+    uint32_t* const cnt32 = reinterpret_cast<uint32_t*>(s_cnt);
+    __syncthreads();   // the table is free (previous block, or pass)
+    // ---- counts of the block: zero, then one LDS addition per lookup of a dense row
+    for (uint32_t i = tid; i < MT * 32u * (kCntPitch / 8); i += kDThreads)
+        reinterpret_cast<uint4*>(s_cnt)[i] = make_uint4(0u, 0u, 0u, 0u);
+    const uint32_t n = ix1 - ix0;
+    if (tid < nd) s_lo[tid] = ix0;
+    if (tid == 0) S->flags = 0u;
+    if (MEAN) S->scale[tid] = L > 0u ? 1.f / (float)L : 0.f;
+    uint32_t all;
+    const uint32_t ex = block_excl_scan<kDThreads>(n, S->scan, &all);
+    if (tid < (uint32_t)kDenseRows) s_pref[tid] = tid < nd ? ex : 0xFFFFFFFFu;
+    if (L > 255u) atomicOr(&S->flags, L > 65535u ? 3u : 1u);   // (a count cannot exceed its bag's length)
+    __syncthreads();
+    const uint32_t flags = S->flags;
+    bool more = false;   // lookups left for a later round
+    // kU lookups in flight per thread: the searches and loads of one are a chain of LDS and L2 trips
+    for (uint32_t e0 = tid; e0 < all; e0 += kU * kDThreads) {
+        uint32_t row[kU], p[kU], bag[kU];
+#pragma unroll
+        for (int q = 0; q < kU; ++q) row[q] = 0u;
+#pragma unroll
+        for (uint32_t step = kDenseRows / 2; step > 0u; step >>= 1)   // the row: last h < nd with s_pref[h] <= e
+#pragma unroll
+            for (int q = 0; q < kU; ++q)
+                if (s_pref[row[q] + step] <= e0 + q * kDThreads) row[q] += step;   // (s_pref[nd ..] is above every e)
+#pragma unroll
+        for (int q = 0; q < kU; ++q) {
+            const uint32_t e = e0 + q * kDThreads;
+            p[q] = s_lo[row[q]] + (e - s_pref[row[q]]);
+            bag[q] = a.bag_sorted[e < all ? p[q] : s_lo[0]];
+        }
+#pragma unroll
+        for (int q = 0; q < kU; ++q) {
+            if (e0 + q * kDThreads >= all) continue;
+            bool take = true;
+            if (flags & 2u) {   // position among the row's lookups of this bag: 65535 of them per round
+                uint32_t q0 = s_lo[row[q]], q1 = p[q];   // first position in [q0, p] that holds this bag
+                while (q0 < q1) {
+                    const uint32_t mid = q0 + ((q1 - q0) >> 1);
+                    if (a.bag_sorted[mid] < bag[q]) q0 = mid + 1u;
+                    else q1 = mid;
+                }
+                const uint32_t r = (p[q] - q0) / 65535u;
+                take = r == round;
+                more |= r > round;
+            }
+            const uint32_t b = (uint32_t)((int64_t)bag[q] - bag0) - b0;
+            if (take && b < nb) atomicAdd(&cnt32[row[q] * (kCntPitch / 2) + (b >> 1)], 1u << (16u * (b & 1u)));
+        }
+    }
+    if (more) atomicOr(&S->flags, 8u);
+    return flags;
+}
+
 // MT: row tiles of 32 (compiled apart, so that the matrix instructions of a step are one straight run)
 template <int MT, bool MEAN, typename GT>
 __device__ __forceinline__ void dense_run(const SegArgs& a, const uint32_t cb, const uint32_t chunk, const int t,
@@ -109,8 +179,6 @@ __device__ __forceinline__ void dense_run(const SegArgs& a, const uint32_t cb, c
     constexpr int kPieces = kExact ? 1 : 3;
     using raw_t = typename Pair<GT>::raw_t;
     uint16_t* const s_cnt = S->cnt;
-    uint32_t* const s_lo = S->lo;
-    uint32_t* const s_pref = S->pref;
     const uint32_t tid = threadIdx.x;
     const int lane = lane_id();
     const int w = (int)(tid >> 6);
@@ -126,7 +194,6 @@ __device__ __forceinline__ void dense_run(const SegArgs& a, const uint32_t cb, c
     const uint32_t lane_col = (uint32_t)(col_on ? col : 0) * (uint32_t)sizeof(GT);
     const uint32_t B = (uint32_t)a.B;
     const int64_t bag0 = (int64_t)t * B;
-    uint32_t* const cnt32 = reinterpret_cast<uint32_t*>(s_cnt);
     const uint32_t* const my_ix = a.dense_index + ((size_t)tab.x * kDenseRows + (tid < nd ? tid : 0u)) * (a.dense_blocks + 1u);
     char* const sums = reinterpret_cast<char*>(a.dense_partial + (size_t)tab.y * 4u + (size_t)chunk * nd * (uint32_t)D);
     const uint32_t run = kRunBlocks * (uint32_t)splits;   // blocks that go into the accumulators before they are emptied
@@ -151,57 +218,7 @@ __device__ __forceinline__ void dense_run(const SegArgs& a, const uint32_t cb, c
             const uint32_t L = b0 + tid < B ? a.offsets.length(bag0 + b0 + tid) : 0u;   // this thread's bag's length
             for (uint32_t pass = 0;; ++pass) {   // pass 2r + d: counts' digit d (low, high byte) of round r
                 const uint32_t round = pass >> 1, digit = pass & 1u;
-                __syncthreads();   // the table is free (previous block, or pass)
-                // ---- counts of the block: zero, then one LDS addition per lookup of a dense row
-                for (uint32_t i = tid; i < MT * 32u * (kCntPitch / 8); i += kDThreads)
-                    reinterpret_cast<uint4*>(s_cnt)[i] = make_uint4(0u, 0u, 0u, 0u);
-                const uint32_t n = ix1 - ix0;
-                if (tid < nd) s_lo[tid] = ix0;
-                if (tid == 0) S->flags = 0u;
-                if (MEAN) S->scale[tid] = L > 0u ? 1.f / (float)L : 0.f;
-                uint32_t all;
-                const uint32_t ex = block_excl_scan<kDThreads>(n, S->scan, &all);
-                if (tid < (uint32_t)kDenseRows) s_pref[tid] = tid < nd ? ex : 0xFFFFFFFFu;
-                if (L > 255u) atomicOr(&S->flags, L > 65535u ? 3u : 1u);   // (a count cannot exceed its bag's length)
-                __syncthreads();
-                const uint32_t flags = S->flags;
-                bool more = false;   // lookups left for a later round
-                constexpr int kU = 8;   // lookups in flight per thread: the searches and loads of one are a chain of LDS and L2 trips
-                for (uint32_t e0 = tid; e0 < all; e0 += kU * kDThreads) {
-                    uint32_t row[kU], p[kU], bag[kU];
-#pragma unroll
-                    for (int q = 0; q < kU; ++q) row[q] = 0u;
-#pragma unroll
-                    for (uint32_t step = kDenseRows / 2; step > 0u; step >>= 1)   // the row: last h < nd with s_pref[h] <= e
-#pragma unroll
-                        for (int q = 0; q < kU; ++q)
-                            if (s_pref[row[q] + step] <= e0 + q * kDThreads) row[q] += step;   // (s_pref[nd ..] is above every e)
-#pragma unroll
-                    for (int q = 0; q < kU; ++q) {
-                        const uint32_t e = e0 + q * kDThreads;
-                        p[q] = s_lo[row[q]] + (e - s_pref[row[q]]);
-                        bag[q] = a.bag_sorted[e < all ? p[q] : s_lo[0]];
-                    }
-#pragma unroll
-                    for (int q = 0; q < kU; ++q) {
-                        if (e0 + q * kDThreads >= all) continue;
-                        bool take = true;
-                        if (flags & 2u) {   // position among the row's lookups of this bag: 65535 of them per round
-                            uint32_t q0 = s_lo[row[q]], q1 = p[q];   // first position in [q0, p] that holds this bag
-                            while (q0 < q1) {
-                                const uint32_t mid = q0 + ((q1 - q0) >> 1);
-                                if (a.bag_sorted[mid] < bag[q]) q0 = mid + 1u;
-                                else q1 = mid;
-                            }
-                            const uint32_t r = (p[q] - q0) / 65535u;
-                            take = r == round;
-                            more |= r > round;
-                        }
-                        const uint32_t b = (uint32_t)((int64_t)bag[q] - bag0) - b0;
-                        if (take && b < nb) atomicAdd(&cnt32[row[q] * (kCntPitch / 2) + (b >> 1)], 1u << (16u * (b & 1u)));
-                    }
-                }
-                if (more) atomicOr(&S->flags, 8u);
+                const uint32_t flags = count_block<MT, MEAN, 8>(a, nd, ix0, ix1, L, bag0, b0, nb, round, S);
                 __syncthreads();
                 bool big = false;
                 for (uint32_t i = tid; i < MT * 32u * (kCntPitch / 8); i += kDThreads) {
@@ -362,6 +379,196 @@ __device__ __forceinline__ void dense_run(const SegArgs& a, const uint32_t cb, c
     }
 }
 
+__device__ __forceinline__ float grad_float(const float x) { return x; }
+__device__ __forceinline__ float grad_float(const __half x) { return __half2float(x); }
+__device__ __forceinline__ float grad_float(const bf16_t x) { return bf16_to_float(__builtin_bit_cast(unsigned short, x)); }
+
+// Tables of up to 64 columns.  A lane holds one column, not two, so that 32 columns fill the matrix instructions and need half the
+// accumulators: the registers freed hold four steps of gradient rows, which are loaded, like the next block's list ends and bag
+// lengths, ahead of the counting and arrive during it.  A count is turned into bfloat16 where it is multiplied (once, or twice above
+// 32 columns), which saves a pass over the table and a barrier.
+template <int MT, bool MEAN, typename GT>
+__device__ __forceinline__ void dense_run_narrow(const SegArgs& a, const uint32_t chunk, const int t, const uint32_t nd, const uint2 tab,
+                                                 const int d0, const int D, DenseLds* S) {
+    constexpr bool kExact = !MEAN && sizeof(GT) == 2;
+    constexpr bool kF16 = kExact && __is_same(GT, __half);
+    constexpr int kPieces = kExact ? 1 : 3;
+    constexpr int kAhead = 4;   // steps whose gradient rows are in flight
+    uint16_t* const s_cnt = S->cnt;
+    const uint32_t tid = threadIdx.x;
+    const int lane = lane_id();
+    const int w = (int)(tid >> 6);
+    const int groups = D > 32 ? 2 : 1;                   // 32-column groups
+    const int cg = w & (groups - 1);
+    const int split = w / groups, splits = 4 / groups;
+    const int kh = lane >> 5;
+    const int col = cg * 32 + (lane & 31);
+    const bool col_on = col < D;                         // (other lanes read column 0 and store nothing)
+    const char* const gtab = static_cast<const char*>(a.grad_out) + (int64_t)(d0 + (col_on ? col : 0)) * (int)sizeof(GT);
+    const int64_t pitch = (int64_t)a.sumD * (int)sizeof(GT);
+    const uint32_t B = (uint32_t)a.B;
+    const int64_t bag0 = (int64_t)t * B;
+    const uint32_t* const my_ix = a.dense_index + ((size_t)tab.x * kDenseRows + (tid < nd ? tid : 0u)) * (a.dense_blocks + 1u);
+    float* const sums = a.dense_partial + (size_t)tab.y * 4u + (size_t)chunk * nd * (uint32_t)D;
+    const uint32_t run = kRunBlocks * (uint32_t)splits;
+    const uint32_t k_lo = chunk * a.dense_per_chunk;
+    const uint32_t k_hi = k_lo + a.dense_per_chunk < a.dense_blocks ? k_lo + a.dense_per_chunk : a.dense_blocks;
+    if (k_lo >= k_hi) return;
+    uint32_t next0 = my_ix[k_lo], next1 = my_ix[k_lo + 1u];   // the next block's
+    uint32_t nextL = k_lo * kDenseBags + tid < B ? a.offsets.length(bag0 + k_lo * kDenseBags + tid) : 0u;
+#pragma unroll 1
+    for (uint32_t k0 = k_lo; k0 < k_hi; k0 += run) {
+        const uint32_t k1 = k0 + run < k_hi ? k0 + run : k_hi;
+        f32x16 acc[MT];
+#pragma unroll
+        for (int m = 0; m < MT; ++m)
+#pragma unroll
+            for (int r = 0; r < 16; ++r) acc[m][r] = 0.f;
+#pragma unroll 1
+        for (uint32_t k = k0; k < k1; ++k) {
+            const uint32_t b0 = k * kDenseBags;
+            const uint32_t nb = B - b0 < (uint32_t)kDenseBags ? B - b0 : (uint32_t)kDenseBags;
+            const uint32_t ix0 = tid < nd ? next0 : 0u, ix1 = tid < nd ? next1 : 0u, L = nextL;
+            GT x[kAhead][8];
+            const char* const gblk = gtab + (int64_t)b0 * pitch;
+            auto load_step = [&](GT (&v)[8], const int j) {   // (a bag behind the batch's end has zero counts: the block's last will do)
+                uint32_t bag = (uint32_t)(j * 16 + kh * 8);
+                asm volatile("" : "+v"(bag));   // (or 16 addresses are computed ahead of the loops, and spilled)
+#pragma unroll
+                for (uint32_t i = 0; i < 8; ++i) {
+                    const uint32_t b = bag + i;
+                    v[i] = *reinterpret_cast<const GT*>(gblk + (uint64_t)(b < nb ? b : nb - 1u) * (uint32_t)pitch);
+                }
+            };
+#pragma unroll
+            for (int q = 0; q < kAhead; ++q) load_step(x[q], split + q * splits);
+            if (k + 1u < k_hi) {
+                next0 = next1;
+                next1 = my_ix[k + 2u];
+                nextL = b0 + kDenseBags + tid < B ? a.offsets.length(bag0 + b0 + kDenseBags + tid) : 0u;
+            }
+            for (uint32_t pass = 0;; ++pass) {
+                const uint32_t round = pass >> 1, digit = pass & 1u;
+                const uint32_t flags = count_block<MT, MEAN, 8>(a, nd, ix0, ix1, L, bag0, b0, nb, round, S);
+                __syncthreads();
+                const uint32_t keep = flags == 0u ? 0xFFFFFFFFu : (digit ? 0xFF00FF00u : 0x00FF00FFu);
+                uint32_t upper = 0;   // bits of counts above 255
+                auto multiply_step = [&](GT (&v)[8], const int j) {
+                    uint4 f[kPieces];
+                    if constexpr (kExact) {
+#pragma unroll
+                        for (int i = 0; i < 4; ++i)
+                            (&f[0].x)[i] = (uint32_t)__builtin_bit_cast(uint16_t, v[2 * i]) | (uint32_t)__builtin_bit_cast(uint16_t, v[2 * i + 1]) << 16;
+                    } else {
+                        float sc[8];
+                        if constexpr (MEAN) {
+                            const float4 sa = *reinterpret_cast<const float4*>(&S->scale[j * 16 + kh * 8]);
+                            const float4 sb = *reinterpret_cast<const float4*>(&S->scale[j * 16 + kh * 8 + 4]);
+                            sc[0] = sa.x; sc[1] = sa.y; sc[2] = sa.z; sc[3] = sa.w;
+                            sc[4] = sb.x; sc[5] = sb.y; sc[6] = sb.z; sc[7] = sb.w;
+                        }
+#pragma unroll
+                        for (int i = 0; i < 4; ++i) {
+                            float v0 = grad_float(v[2 * i]), v1 = grad_float(v[2 * i + 1]);
+                            if constexpr (MEAN) {
+                                v0 *= sc[2 * i];
+                                v1 *= sc[2 * i + 1];
+                            }
+#pragma unroll
+                            for (int p = 0; p < 3; ++p) {
+                                const uint32_t u0 = __float_as_uint(v0), u1 = __float_as_uint(v1);
+                                (&f[p].x)[i] = upper_halves(u0, u1);
+                                v0 -= __uint_as_float(u0 & 0xFFFF0000u);
+                                v1 -= __uint_as_float(u1 & 0xFFFF0000u);
+                            }
+                        }
+                    }
+#pragma unroll
+                    for (int m = 0; m < MT; ++m) {
+                        uint4 av = *reinterpret_cast<const uint4*>(&s_cnt[(m * 32 + (lane & 31)) * kCntPitch + j * 16 + kh * 8]);
+#pragma unroll
+                        for (int q = 0; q < 4; ++q) {
+                            uint32_t c = (&av.x)[q];
+                            upper |= c & 0xFF00FF00u;
+                            c &= keep;
+                            (&av.x)[q] = count_bits<kF16>(c & 0xFFFFu) | (count_bits<kF16>(c >> 16) << 16);
+                        }
+#pragma unroll
+                        for (int p = kPieces - 1; p >= 0; --p) acc[m] = mfma<kF16>(av, f[p], acc[m]);   // small pieces first
+                    }
+                };
+#pragma unroll 1
+                for (int j0 = split; j0 < kDenseBags / 16; j0 += kAhead * splits) {   // (all of a short block's: no counts, no branches)
+#pragma unroll
+                    for (int q = 0; q < kAhead; ++q) {
+                        multiply_step(x[q], j0 + q * splits);
+                        load_step(x[q], j0 + (q + kAhead) * splits);
+                        __builtin_amdgcn_sched_barrier(0);
+                    }
+                }
+                if (flags == 0u) break;
+                if (upper) atomicOr(&S->flags, 4u);
+                __syncthreads();
+                const uint32_t fl = S->flags;
+                if (digit == 0u && !(fl & 4u)) {        // no count has an upper byte: skip that pass
+                    if (!(fl & 8u)) break;
+                    ++pass;
+                } else if (digit == 1u && !(fl & 8u)) {
+                    break;
+                }
+#pragma unroll
+                for (int q = 0; q < kAhead; ++q) load_step(x[q], split + q * splits);
+            }
+        }
+        // ---- the wavefronts that shared a column group's bags, in order, then the rows' partial sums
+#pragma unroll 1
+        for (int sp = 1; sp < splits; ++sp) {
+            uint32_t rp = 32u * (uint32_t)groups;
+            asm volatile("" : "+s"(rp));
+            float* const red = reinterpret_cast<float*>(s_cnt) + 4u * (uint32_t)kh * rp + (uint32_t)(cg * 32 + (lane & 31));
+            __syncthreads();
+            if (split == sp) {
+#pragma unroll
+                for (int m = 0; m < MT; ++m)
+#pragma unroll
+                    for (int r = 0; r < 16; ++r) red[(uint32_t)(m * 32 + (r & 3) + 8 * (r >> 2)) * rp] = acc[m][r];
+            }
+            __syncthreads();
+            if (split == 0) {
+#pragma unroll
+                for (int m = 0; m < MT; ++m)
+#pragma unroll
+                    for (int r = 0; r < 16; ++r) acc[m][r] += red[(uint32_t)(m * 32 + (r & 3) + 8 * (r >> 2)) * rp];
+            }
+        }
+        if (split == 0 && col_on) {
+            const bool add = k0 > k_lo;
+            uint32_t row_floats = (uint32_t)D;
+            int left = (int)nd - 4 * kh;
+            asm volatile("" : "+s"(row_floats), "+v"(left));
+            uint32_t at = (uint32_t)(4 * kh) * row_floats + (uint32_t)col;
+#pragma unroll
+            for (int m = 0; m < MT; ++m, at += 32u * row_floats) {
+                if (add) {
+                    float o[16];
+#pragma unroll
+                    for (int r = 0; r < 16; ++r) {
+                        const int h = (r & 3) + 8 * (r >> 2);
+                        o[r] = sums[m * 32 + h < left ? at + (uint32_t)h * row_floats : (uint32_t)col];
+                    }
+#pragma unroll
+                    for (int r = 0; r < 16; ++r) acc[m][r] += o[r];
+                }
+#pragma unroll
+                for (int r = 0; r < 16; ++r) {
+                    const int h = (r & 3) + 8 * (r >> 2);
+                    if (m * 32 + h < left) sums[at + (uint32_t)h * row_floats] = acc[m][r];
+                }
+            }
+        }
+    }
+}
+
 template <bool MEAN, typename GT>
 __global__ __launch_bounds__(kDThreads, 2) void seg_dense_kernel(const SegArgs a, const uint32_t col_blocks) {
     __shared__ DenseLds S;
@@ -376,6 +583,13 @@ __global__ __launch_bounds__(kDThreads, 2) void seg_dense_kernel(const SegArgs a
     const int d0 = a.D_off[t];
     const int D = a.D_off[t + 1] - d0;
     if ((int)cb * 256 >= D) return;
+    if (D <= 64) {
+        if (nd > 96u) dense_run_narrow<4, MEAN, GT>(a, chunk, t, nd, tab, d0, D, &S);
+        else if (nd > 64u) dense_run_narrow<3, MEAN, GT>(a, chunk, t, nd, tab, d0, D, &S);
+        else if (nd > 32u) dense_run_narrow<2, MEAN, GT>(a, chunk, t, nd, tab, d0, D, &S);
+        else dense_run_narrow<1, MEAN, GT>(a, chunk, t, nd, tab, d0, D, &S);
+        return;
+    }
     if (nd > 96u) dense_run<4, MEAN, GT>(a, cb, chunk, t, nd, tab, d0, D, &S);
     else if (nd > 64u) dense_run<3, MEAN, GT>(a, cb, chunk, t, nd, tab, d0, D, &S);
     else if (nd > 32u) dense_run<2, MEAN, GT>(a, cb, chunk, t, nd, tab, d0, D, &S);
