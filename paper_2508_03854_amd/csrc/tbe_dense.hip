@@ -26,16 +26,16 @@
 // LDS, 128 accumulator registers) overlap each other's counting.  The partial sums of a row, one per workgroup, are added
 // in order by the kernel that applies the step, so the result does not depend on scheduling.
 // Tables of up to 64 columns have a form of their own (dense_run_narrow), for there the count table, whose size does not shrink with
-// the columns, is what takes the time: 30 tables x 65536 bags x 32 columns, long-tailed bags, Zipf 1.3, mean pooling, 277 -> 191 us,
-// bfloat16 250 -> 165; 16 x 32768 x 64, Zipf 1.1, binary16 gradients 76 -> 60, fp32 and mean pooling 85 -> 74.  Taken for 65 to 128
-// columns too (four groups, each turning all counts into bfloat16 again) 137 -> 145.
+// the columns, is what takes the time: 30 tables x 65536 bags x 32 columns, long-tailed bags, Zipf 1.3, mean pooling, 277 -> 175 us;
+// 16 x 32768 x 64, Zipf 1.1, binary16 gradients 76 -> 68, fp32 and mean pooling 85 -> 78.  Taken for 65 to 128 columns too (four
+// groups, each turning all counts into bfloat16 again) 137 -> 145.
 // Bound: wide tables by the stream of the gradient block, at about half the copy rate (64 tables x 32768 bags, 48 of 256
 // columns: 1.9 GB in 0.64 ms), narrow ones by the chain of searches, list loads and LDS additions that fills the count table (a block
-// of 256 bags takes 12 us, two at a time per compute unit, for about 4 us of instructions).
+// of 256 bags takes 11 us, two at a time per compute unit, for about 4 us of instructions).
 // Measured, whole training step, against 16 dense rows on the vector units and sweeps over the rest: the former 9.5 -> 8.2 ms, the
 // latter, mean pooling, 2.5 -> 1.7 ms.  Of that, the loads ahead of the matrix instructions 20 us of 690; the runs cost 85 us of 607
 // (and 8 of 296 at 32 columns); the counting as a function of its own, whose registers the compiler then lays out apart, 690 -> 645.
-// Spilled vector registers: 7 to 9 under mean pooling, 1 with 16-bit gradients, none else.
+// Spilled vector registers: 6 to 9 under mean pooling, 1 or 2 with 16-bit gradients, none else.
 // 0 * Inf is NaN, so a non-finite element of one bag's gradient reaches every dense row of its table here; the kernel that
 // adds the partial sums reduces such rows again from their own lookups.
 #include "tbe_rows.h"
@@ -387,20 +387,19 @@ __device__ __forceinline__ float grad_float(const bf16_t x) { return bf16_to_flo
 // accumulators: the registers freed hold four steps of gradient rows, which are loaded, like the next block's list ends and bag
 // lengths, ahead of the counting and arrive during it.  A count is turned into bfloat16 where it is multiplied (once, or twice above
 // 32 columns), which saves a pass over the table and a barrier.
-template <int MT, bool MEAN, typename GT>
+template <int MT, int GROUPS, bool MEAN, typename GT>
 __device__ __forceinline__ void dense_run_narrow(const SegArgs& a, const uint32_t chunk, const int t, const uint32_t nd, const uint2 tab,
                                                  const int d0, const int D, DenseLds* S) {
     constexpr bool kExact = !MEAN && sizeof(GT) == 2;
     constexpr bool kF16 = kExact && __is_same(GT, __half);
     constexpr int kPieces = kExact ? 1 : 3;
-    constexpr int kAhead = 4;   // steps whose gradient rows are in flight
+    constexpr int kAhead = GROUPS == 2 ? 2 : 4;   // steps whose gradient rows are in flight
     uint16_t* const s_cnt = S->cnt;
     const uint32_t tid = threadIdx.x;
     const int lane = lane_id();
     const int w = (int)(tid >> 6);
-    const int groups = D > 32 ? 2 : 1;                   // 32-column groups
-    const int cg = w & (groups - 1);
-    const int split = w / groups, splits = 4 / groups;
+    constexpr int splits = 4 / GROUPS;                   // wavefronts that share the bags of a 32-column group
+    const int cg = w & (GROUPS - 1), split = w / GROUPS;
     const int kh = lane >> 5;
     const int col = cg * 32 + (lane & 31);
     const bool col_on = col < D;                         // (other lanes read column 0 and store nothing)
@@ -410,7 +409,7 @@ __device__ __forceinline__ void dense_run_narrow(const SegArgs& a, const uint32_
     const int64_t bag0 = (int64_t)t * B;
     const uint32_t* const my_ix = a.dense_index + ((size_t)tab.x * kDenseRows + (tid < nd ? tid : 0u)) * (a.dense_blocks + 1u);
     float* const sums = a.dense_partial + (size_t)tab.y * 4u + (size_t)chunk * nd * (uint32_t)D;
-    const uint32_t run = kRunBlocks * (uint32_t)splits;
+    constexpr uint32_t run = 4 * kRunBlocks;
     const uint32_t k_lo = chunk * a.dense_per_chunk;
     const uint32_t k_hi = k_lo + a.dense_per_chunk < a.dense_blocks ? k_lo + a.dense_per_chunk : a.dense_blocks;
     if (k_lo >= k_hi) return;
@@ -419,11 +418,14 @@ __device__ __forceinline__ void dense_run_narrow(const SegArgs& a, const uint32_
 #pragma unroll 1
     for (uint32_t k0 = k_lo; k0 < k_hi; k0 += run) {
         const uint32_t k1 = k0 + run < k_hi ? k0 + run : k_hi;
-        f32x16 acc[MT];
+        f32x16 acc[MT], acc2[GROUPS == 2 ? MT : 1];
 #pragma unroll
         for (int m = 0; m < MT; ++m)
 #pragma unroll
-            for (int r = 0; r < 16; ++r) acc[m][r] = 0.f;
+            for (int r = 0; r < 16; ++r) {
+                acc[m][r] = 0.f;
+                if (GROUPS == 2) acc2[m][r] = 0.f;
+            }
 #pragma unroll 1
         for (uint32_t k = k0; k < k1; ++k) {
             const uint32_t b0 = k * kDenseBags;
@@ -453,7 +455,7 @@ __device__ __forceinline__ void dense_run_narrow(const SegArgs& a, const uint32_
                 __syncthreads();
                 const uint32_t keep = flags == 0u ? 0xFFFFFFFFu : (digit ? 0xFF00FF00u : 0x00FF00FFu);
                 uint32_t upper = 0;   // bits of counts above 255
-                auto multiply_step = [&](GT (&v)[8], const int j) {
+                auto multiply_step = [&](GT (&v)[8], const int j, f32x16* const to) {
                     uint4 f[kPieces];
                     if constexpr (kExact) {
 #pragma unroll
@@ -494,14 +496,14 @@ __device__ __forceinline__ void dense_run_narrow(const SegArgs& a, const uint32_
                             (&av.x)[q] = count_bits<kF16>(c & 0xFFFFu) | (count_bits<kF16>(c >> 16) << 16);
                         }
 #pragma unroll
-                        for (int p = kPieces - 1; p >= 0; --p) acc[m] = mfma<kF16>(av, f[p], acc[m]);   // small pieces first
+                        for (int p = kPieces - 1; p >= 0; --p) to[m] = mfma<kF16>(av, f[p], to[m]);   // small pieces first
                     }
                 };
 #pragma unroll 1
                 for (int j0 = split; j0 < kDenseBags / 16; j0 += kAhead * splits) {   // (all of a short block's: no counts, no branches)
 #pragma unroll
                     for (int q = 0; q < kAhead; ++q) {
-                        multiply_step(x[q], j0 + q * splits);
+                        multiply_step(x[q], j0 + q * splits, GROUPS == 2 && (q & 1) ? acc2 : acc);
                         load_step(x[q], j0 + (q + kAhead) * splits);
                         __builtin_amdgcn_sched_barrier(0);
                     }
@@ -521,9 +523,15 @@ __device__ __forceinline__ void dense_run_narrow(const SegArgs& a, const uint32_
             }
         }
         // ---- the wavefronts that shared a column group's bags, in order, then the rows' partial sums
+        if constexpr (GROUPS == 2) {
+#pragma unroll
+            for (int m = 0; m < MT; ++m)
+#pragma unroll
+                for (int r = 0; r < 16; ++r) acc[m][r] += acc2[m][r];
+        }
 #pragma unroll 1
         for (int sp = 1; sp < splits; ++sp) {
-            uint32_t rp = 32u * (uint32_t)groups;
+            uint32_t rp = 32u * (uint32_t)GROUPS;
             asm volatile("" : "+s"(rp));
             float* const red = reinterpret_cast<float*>(s_cnt) + 4u * (uint32_t)kh * rp + (uint32_t)(cg * 32 + (lane & 31));
             __syncthreads();
@@ -569,6 +577,15 @@ __device__ __forceinline__ void dense_run_narrow(const SegArgs& a, const uint32_
     }
 }
 
+template <int GROUPS, bool MEAN, typename GT>
+__device__ __forceinline__ void dense_any_narrow(const SegArgs& a, const uint32_t chunk, const int t, const uint32_t nd, const uint2 tab,
+                                                 const int d0, const int D, DenseLds* S) {
+    if (nd > 96u) dense_run_narrow<4, GROUPS, MEAN, GT>(a, chunk, t, nd, tab, d0, D, S);
+    else if (nd > 64u) dense_run_narrow<3, GROUPS, MEAN, GT>(a, chunk, t, nd, tab, d0, D, S);
+    else if (nd > 32u) dense_run_narrow<2, GROUPS, MEAN, GT>(a, chunk, t, nd, tab, d0, D, S);
+    else dense_run_narrow<1, GROUPS, MEAN, GT>(a, chunk, t, nd, tab, d0, D, S);
+}
+
 template <bool MEAN, typename GT>
 __global__ __launch_bounds__(kDThreads, 2) void seg_dense_kernel(const SegArgs a, const uint32_t col_blocks) {
     __shared__ DenseLds S;
@@ -583,13 +600,8 @@ __global__ __launch_bounds__(kDThreads, 2) void seg_dense_kernel(const SegArgs a
     const int d0 = a.D_off[t];
     const int D = a.D_off[t + 1] - d0;
     if ((int)cb * 256 >= D) return;
-    if (D <= 64) {
-        if (nd > 96u) dense_run_narrow<4, MEAN, GT>(a, chunk, t, nd, tab, d0, D, &S);
-        else if (nd > 64u) dense_run_narrow<3, MEAN, GT>(a, chunk, t, nd, tab, d0, D, &S);
-        else if (nd > 32u) dense_run_narrow<2, MEAN, GT>(a, chunk, t, nd, tab, d0, D, &S);
-        else dense_run_narrow<1, MEAN, GT>(a, chunk, t, nd, tab, d0, D, &S);
-        return;
-    }
+    if (D <= 32) return dense_any_narrow<1, MEAN, GT>(a, chunk, t, nd, tab, d0, D, &S);
+    if (D <= 64) return dense_any_narrow<2, MEAN, GT>(a, chunk, t, nd, tab, d0, D, &S);
     if (nd > 96u) dense_run<4, MEAN, GT>(a, cb, chunk, t, nd, tab, d0, D, &S);
     else if (nd > 64u) dense_run<3, MEAN, GT>(a, cb, chunk, t, nd, tab, d0, D, &S);
     else if (nd > 32u) dense_run<2, MEAN, GT>(a, cb, chunk, t, nd, tab, d0, D, &S);
