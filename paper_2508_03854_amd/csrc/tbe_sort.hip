@@ -21,14 +21,16 @@ namespace tbe {
 // Making the keys inside pass 0, twice, instead of storing them and their bags first costs one more read of the ids and
 // saves 8 bytes written and 4 read per lookup and two launches.
 //
+// The smallest batches have a sort of one launch instead (tbe_sort_small.hip; sort_shape draws the line).
+//
 // Digits: up to 11 bits in batches of at most kSelfScanMax lookups, 8 bits beyond.  A small batch's time is its chain of
 // launches (about 4 us each), so it takes wide digits (fewer passes) and lets every scatter workgroup add up the
 // histograms of its segment's chunks by itself (no launch for the scan).  In a large batch 2048 bins would leave runs of two
 // keys per tile and bin to write, and the chunk histograms would be too many to add up per workgroup.
 //
 // Bound: launches and latency in small batches, the streams and the ranking beyond.  Measured, whole training step, against
-// a sort that stored keys and bags first and took 8-bit digits throughout: one table, 10 k lookups 102 -> 67 us; 26 tables,
-// 1.2 M lookups 295 -> 254 us; 64 tables, 65 M lookups 9.50 -> 9.18 ms.
+// a sort that stored keys and bags first and took 8-bit digits throughout: 26 tables, 1.2 M lookups 295 -> 254 us; 64 tables, 65 M
+// lookups 9.50 -> 9.18 ms.
 // =================================================================================================
 constexpr int kRsWaves = kRsThreads / kWave;
 
