@@ -31,10 +31,12 @@ SortShape sort_shape(const tbe_handle* h, int64_t N) {
     SortShape sh;
     sh.nseg = h->segmented ? h->T : 1;
     // One launch where keys are local to their segment and reading a segment once per range of it costs less than two launches a
-    // pass.  That grows with the square of a segment: of one table 16384 ids of 3 rows 25 -> 29 us, of 100000 rows, Zipf 1.3, 38 ->
-    // 35, 32768 of them 48 -> 58.  The host knows no segment's length, only that all of them together are N: hence the average, and
-    // a bound on N for the batch that is one table's after all (60000 of 65000 ids in one of 26 tables 52 -> 80).  Very many tables
-    // have a workgroup of 1024 threads each for a few ids: 1000 tables x 10 and x 60 ids 48 -> 50 and 51 -> 60, 300 x 1 35 -> 24.
+    // pass.  That grows with the longest segment, of which the host knows only that all of them together are N: hence the bound on N for
+    // the batch that is one table's after all, and on the average, beyond which most batches have such a table.  Prepare calls with nearly
+    // all ids in one of 26 tables, passes / one launch, us: 48000 ids 36 to 65 / 24 to 61, 65536 ids of 100000 rows 39 to 74 / 28 to 76,
+    // and of tables of at most 2000 rows, which take one pass of wide digits, 30 to 44 / 33 to 52, where spread over the tables 23 to 28 /
+    // 17 to 22.  Very many tables have a workgroup of 1024 threads each for a few ids: 1000 tables x 10 and x 60 ids 48 -> 50 and 51 ->
+    // 60, 300 x 1 35 -> 24.
     sh.small = (h->segmented || h->T == 1) && sh.nseg <= kSmallTables && (N <= kSmallMax || (N <= kSmallMaxMany && N <= kSmallSegment * sh.nseg));
     if (sh.small) {
         sh.passes = 1;

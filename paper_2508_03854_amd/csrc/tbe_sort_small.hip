@@ -3,24 +3,28 @@
 // Passes over digits are a chain of launches, two each, that a small batch cannot fill.  Here a workgroup owns a range of at most
 // kSmallChunk places of one segment's SORTED order and finds the elements that belong there by itself, from the segment's ids
 // alone, so that nothing has to be exchanged between workgroups:
-//   1. the segment's keys are made from its ids (and kept in LDS, up to kSmallHeld of them);
+//   1. the segment's keys are made from its ids, once, and kept: 31 per thread in LDS, the others in registers;
 //   2. a radix selection, histograms of digits of up to ten bits from the top, finds the keys at the range's first and last place:
 //      their first digits, unless more elements than there are threads share those or lie between, then as many more as it takes;
-//   3. the elements from the one to the other are compacted in order of position;
+//   3. the elements from the one to the other become bits of masks, and the masks' bits positions, in order;
 //   4. a stable radix sort in LDS on what distinguishes them, up to six bits a pass, one element per thread;
 //   5. the payload (a binary search for the position's bag, most steps in LDS), and the range's heads and long rows counted.
 // What workgroups repeat is the reading of the segment and steps 2 and 3 on it.  It is the same for any distribution of the ids
 // over the segments and over the rows: a range has its places, whether they hold as many rows or one.
 //
-// Bound: latency, a chain of about ten barriers, and the instructions spent on the whole segment.  So a wavefront per border scans
-// the histograms and every wavefront the counts, and loops are kept rolled: instructions come from memory too, and the same steps
-// unrolled over up to 64 keys in registers took 23 us where this takes 11.6 (one table, 10240 uniform ids of 100000 rows: find the
-// range 1.6, keys and first histogram 1.6, borders 1.5, count and compact 2.4, sort 2.6, bags and output 1.0).  In ranges of 1024
-// places 14.6.
-// Against passes over digits, prepare call with run lengths and lists, us: one table, 100 / 2000 / 8000 / 12288 uniform ids of 100000
-// rows 24 26 28 31 / 16 17 18 19, of Zipf 1.3 24 30 33 35 / 16 21 26 31, of 3 rows (long runs everywhere) 19 20 22 23 / 17 18 22 24;
-// 10 tables x 6000 35 / 23, 26 x 2500 34 / 20, 64 x 1000 34 / 19, 200 x 300 39 / 27.  The whole step of one table, 512 bags of 20 ids,
-// 64 columns 44.4 / 34.0; of ten tables of odd widths x 777 bags 104 / 93.
+// Bound: latency, a chain of about ten barriers, and in long segments the instructions and LDS additions spent on the whole of them.  So
+// a wavefront per border scans the histograms and every wavefront the counts; loops are kept rolled, for instructions come from memory
+// too (keys in registers with these steps unrolled over them 23 us where rolled loops took 11.6; registers are read by number instead);
+// and no step branches on an element.  One table, 10240 uniform ids of 100000 rows, us: find the range 1.2, keys and first histogram 2.3,
+// borders 0.6, masks 0.4, positions 0.9, sort 2.5, bags and output 1.2.  In ranges of 1024 places 14.6.
+// Against passes over digits, prepare call with run lengths and lists, us: one table, 2000 / 10240 / 12288 uniform ids of 100000 rows 27
+// 31 32 / 16 18 18, of Zipf 1.3 30 36 36 / 19 25 26; 10 tables x 4662 30 / 17.5, 26 x 2307 34 / 18.5, 200 x 300 32 / 26, 512 x 128 34.5 /
+// 36.  With nearly all ids in one of several tables of 100000 rows, uniform, Zipf 1.1, Zipf 1.3, of 3 rows, of one row: 32000 ids 41 48 50
+// 47 59 / 19 32 37 33 46, 48000 ids 36 47 50 47 65 / 24 41 48 44 61, 65536 ids 39 50 55 52 74 / 28 49 57 54 76.  (Where keys beyond 32768
+// were made from the ids again in every step, and the lanes of one row added to one LDS word one after the other: 65000 ids 45 79 89 107
+// 154.)  The sort alone is then 30 us of 48000 ids: first histogram 7.5, second 6 to 9, masks 4.5.
+#include <type_traits>
+
 #include "tbe_sort.h"
 
 namespace tbe {
@@ -28,27 +32,32 @@ namespace tbe {
 constexpr int kSmallThreads = 1024;
 constexpr int kSmallWaves = kSmallThreads / kWave;
 constexpr int kSelBits = 10, kSelBins = 1 << kSelBits;   // 16 bins per lane in a wavefront's scan
-constexpr int kSmallHeld = 32 * kSmallThreads;           // keys in LDS; of larger segments they are made from the ids again
+constexpr int kSelPitch = kSelBins + 4;                  // of the copies of a histogram: one bin's lie in different banks
+constexpr int kSmallHeld = 31 * kSmallThreads;           // keys in LDS at most
+constexpr int kSmallRows = 32;                           // rows of 64 further ones in registers of a wavefront, and one more
 constexpr int kBagSteps = 2048;                          // offsets of a table in LDS: all, or every 2nd, 4th, ...
 static_assert(kSmallChunk <= kSmallThreads && kSelBins == 16 * kWave, "an element per thread, 16 bins per lane");
+static_assert(kSmallHeld / kSmallThreads % 2 == 1 && kSmallHeld / kSmallThreads < 32, "a thread's kept elements in 32 bits");
+static_assert(kSmallMax <= kSmallMaxMany && kSmallMaxMany <= kSmallHeld + (kSmallRows + 1) * kSmallThreads, "a batch may be one segment's");
 constexpr uint32_t kNoKey = 0xFFFFFFFFu;                 // (keys are below 2^31)
 // in a range's counts: it starts a segment with an id outside its table, or ends in one
 constexpr uint32_t kRangeStartsInvalid = 0x80000000u, kRangeEndsInvalid = 0x40000000u;
 
 struct SmallLds {
     union {
-        __align__(16) uint32_t hist[4][kSelBins];   // spread over the lanes at first, then one per border
+        __align__(16) uint32_t hist[4][kSelPitch];   // copies that the lanes are spread over; of two borders two each
         struct { uint32_t key[kSmallThreads], pos[kSmallThreads]; } buf[2];
     };
     uint32_t cnt[kSmallWaves][kWave];
     uint32_t off[kBagSteps];
-    uint4 taken[kSmallWaves], place[2];
+    uint4 place[2];
+    uint32_t borders[2 * kSmallWaves], taken[2 * kSmallWaves], none[kWave];
     uint32_t scan[kSmallWaves], total;
     ChunkDesc desc;
 };
 
 struct Place { uint32_t bin, before, count; };   // a bin, the elements in bins below, and in it
-// The bin of element number x (x below their sum) of a histogram, or of four that follow one another added up.  By one wavefront.
+// The bin of element number x (x below their sum) of a histogram's copies added up.  By one wavefront.
 template <int COPIES>
 __device__ __forceinline__ Place find_place(const uint32_t* h, const uint32_t x) {
     const int lane = lane_id();
@@ -57,7 +66,7 @@ __device__ __forceinline__ Place find_place(const uint32_t* h, const uint32_t x)
     for (int q = 0; q < COPIES; ++q)
 #pragma unroll
         for (int j = 0; j < 4; ++j) {   // (in an order that spreads the lanes over the banks)
-            const uint4 v = *reinterpret_cast<const uint4*>(h + q * kSelBins + 16 * lane + 4 * ((j + lane) & 3));
+            const uint4 v = *reinterpret_cast<const uint4*>(h + q * kSelPitch + 16 * lane + 4 * ((j + lane) & 3));
             sum += v.x + v.y + v.z + v.w;
         }
     const uint32_t incl = wave_incl_scan(sum);
@@ -66,7 +75,7 @@ __device__ __forceinline__ Place find_place(const uint32_t* h, const uint32_t x)
     const int bin = 16 * f + (lane & 15);
     uint32_t c = 0;
 #pragma unroll
-    for (int q = 0; q < COPIES; ++q) c += h[q * kSelBins + bin];
+    for (int q = 0; q < COPIES; ++q) c += h[q * kSelPitch + bin];
     uint32_t in_row = c;   // inclusive, within the 16 lanes of a row, which hold the same
     in_row += dpp_or_zero<0x111, 0xF>(in_row);
     in_row += dpp_or_zero<0x112, 0xF>(in_row);
@@ -95,10 +104,45 @@ __device__ __forceinline__ ChunkDesc find_range(const SortArgs& a, const uint32_
     return ChunkDesc{s, e, (uint32_t)seg, first, bcast_lane(n, seg), start, end, 0};
 }
 
+// E digits per lane into a histogram.  Lanes that all hold the same one, as where a segment's upper digits agree, would queue on one LDS
+// word: then one of them adds their number.  (Looked for only where the first digits agree.)
+template <uint32_t E>
+__device__ __forceinline__ void add_digits(uint32_t* const h, const uint32_t (&d)[E]) {
+    const uint32_t d0 = (uint32_t)__builtin_amdgcn_readfirstlane((int)d[0]);
+    if (__ballot(d[0] != d0) == 0ull) {
+        uint32_t other = 0;
+#pragma unroll
+        for (uint32_t u = 1; u < E; ++u) other |= d[u] ^ d0;
+        if (__ballot(other != 0u) == 0ull) {
+            if (lane_id() == 0) atomicAdd(&h[d0], E * (uint32_t)kWave);
+            return;
+        }
+    }
+#pragma unroll
+    for (uint32_t u = 0; u < E; ++u) atomicAdd(&h[d[u]], 1u);
+}
+
+// the set bits of m but the lowest q
+__device__ __forceinline__ uint64_t without_lowest(uint64_t m, const uint32_t q) {
+    if (q >= (uint32_t)__popcll(m)) return 0ull;
+    for (uint32_t i = 0; i < q; ++i) m &= m - 1ull;
+    return m;
+}
+
+// m = 2 m + (x <= y), m = 2 m + (x == y): a comparison and an addition with its carry
+__device__ __forceinline__ void push_le(uint32_t& m, const uint32_t x, const uint32_t y) {
+    asm("v_cmp_ge_u32_e32 vcc, %2, %1\n\tv_addc_co_u32_e32 %0, vcc, %0, %0, vcc" : "+v"(m) : "v"(x), "s"(y) : "vcc");
+}
+__device__ __forceinline__ void push_eq(uint32_t& m, const uint32_t x, const uint32_t y) {
+    asm("v_cmp_eq_u32_e32 vcc, %2, %1\n\tv_addc_co_u32_e32 %0, vcc, %0, %0, vcc" : "+v"(m) : "v"(x), "s"(y) : "vcc");
+}
+
+// held: keys that LDS has room for, an odd number of rounds of the workgroup
 template <typename IT>
-__global__ __launch_bounds__(kSmallThreads) void sort_small_kernel(const SortArgs a, uint2* __restrict__ counts, const uint32_t long_min) {
+__global__ __launch_bounds__(kSmallThreads) void sort_small_kernel(const SortArgs a, uint2* __restrict__ counts, const uint32_t long_min,
+                                                                   const uint32_t held) {
     __shared__ SmallLds S;
-    extern __shared__ uint32_t s_keys[];   // min(N, kSmallHeld), whole rounds of the workgroup
+    extern __shared__ __align__(16) uint32_t s_keys[];
     // (neighbouring ranges read the same ids: on one die.  The grid is a multiple of 8)
     const uint32_t chunk = (blockIdx.x & 7u) * (gridDim.x >> 3) + (blockIdx.x >> 3);
     if (chunk >= (uint32_t)a.max_chunks) return;
@@ -113,7 +157,9 @@ __global__ __launch_bounds__(kSmallThreads) void sort_small_kernel(const SortArg
     if (ds.e <= ds.s) return;
     const int64_t rb = a.row_base[ds.seg];
     const uint32_t R = (uint32_t)(a.row_base[ds.seg + 1] - rb);
-    reinterpret_cast<uint4*>(S.hist)[tid] = make_uint4(0u, 0u, 0u, 0u);
+    // (256 threads per copy, a uint4 each)
+    auto clear_hist = [&] { *reinterpret_cast<uint4*>(&S.hist[tid >> 8][4u * (tid & 255u)]) = make_uint4(0u, 0u, 0u, 0u); };
+    clear_hist();
     if (tid == 0) S.total = 0u;
     // ---- the table's offsets: every 2^bag_log2-th
     const IT* const offsets = static_cast<const IT*>(a.offsets) + (int64_t)ds.seg * a.B;
@@ -127,42 +173,35 @@ __global__ __launch_bounds__(kSmallThreads) void sort_small_kernel(const SortArg
         }
     }
     __syncthreads();
-    // ---- the segment's keys: element k of this lane is the segment's element number first + 64 k
+    // ---- the segment's elements.  The keys of the first `kept` stay in LDS, `per` that follow one another of each thread (an odd number,
+    // which spreads the lanes over the banks; from n on they are kNoKey).  Those behind stay in registers, in rows of 64, at most
+    // row_per to a wavefront.
     const uint32_t n = ds.seg_end - ds.seg_start;
-    const uint32_t per = (n + kSmallThreads - 1u) / kSmallThreads;   // elements per lane
-    const uint32_t first = w * per * kWave + (uint32_t)lane;
-    const bool held = n <= (uint32_t)kSmallHeld;
+    const uint32_t kept = umin(n, held), per = umin((n + kSmallThreads - 1u) / kSmallThreads | 1u, held / kSmallThreads);
+    const uint32_t rows = (n - kept + kWave - 1u) / kWave, row_per = (rows + kSmallWaves - 1u) / kSmallWaves;
+    const uint32_t row0 = umin(w * row_per, rows), my_rows = umin(row_per, rows - row0);
     const IT* const ids = static_cast<const IT*>(a.indices) + ds.seg_start;
-    bool bad = false;
-    auto from_ids = [&](auto f) {
-        constexpr uint32_t kU = 8;   // ids in flight
+    auto key_of = [&](const IT id) { return (sizeof(IT) == 8 ? (uint64_t)id < (uint64_t)R : (uint32_t)id < R) ? (uint32_t)id : R; };
+    typedef uint32_t rows_t __attribute__((ext_vector_type(kSmallRows)));
+    rows_t row = 0u;
+    uint32_t last_row = 0u;   // number kSmallRows
+    // of_kept(key) for this thread's kept elements, the last one first; of_row(key, the row's number among the wavefront's)
+    auto each = [&](auto of_kept, auto of_row) {
+        const uint32_t* mine = s_keys + tid * per + per - 1u;
+        uint32_t left = per;
 #pragma unroll 1
-        for (uint32_t k0 = 0; k0 < per; k0 += kU) {
-            IT id[kU];
-#pragma unroll
-            for (uint32_t u = 0; u < kU; ++u) id[u] = ids[umin(first + (k0 + u) * kWave, n - 1u)];
-#pragma unroll
-            for (uint32_t u = 0; u < kU; ++u) {
-                if (k0 + u >= per) break;
-                const bool in = first + (k0 + u) * kWave < n;
-                const bool ok = id[u] >= 0 && (int64_t)id[u] < (int64_t)R;
-                bad |= in && !ok;
-                f(in ? (ok ? (uint32_t)id[u] : R) : kNoKey, first + (k0 + u) * kWave);
-            }
-        }
-    };
-    auto each_key = [&](auto f) {
-        if (held) {
+        for (; (left & 3u) != 0u; --left) of_kept(*mine--);
 #pragma unroll 1
-            for (uint32_t k0 = 0; k0 < per; k0 += 2u) {
-                const uint32_t at = first + k0 * kWave, next = at + (k0 + 1u < per ? kWave : 0u);
-                const uint32_t x = s_keys[at], y = s_keys[next];
-                f(x, at);
-                f(k0 + 1u < per ? y : kNoKey, next);
-            }
-        } else {
-            from_ids(f);
+        for (; left > 0u; left -= 4u, mine -= 4) {
+            uint32_t k[4];
+#pragma unroll
+            for (int u = 0; u < 4; ++u) k[u] = mine[-u];
+#pragma unroll
+            for (int u = 0; u < 4; ++u) of_kept(k[u]);
         }
+#pragma unroll 1
+        for (uint32_t r = 0; r < umin(my_rows, kSmallRows); ++r) of_row(row[r], r);
+        if (my_rows > (uint32_t)kSmallRows) of_row(last_row, (uint32_t)kSmallRows);
     };
     // ---- the keys at places r0 and r0 + cnt - 1 (0: the lower border, 1: the upper one), digit by digit from the top
     const uint32_t r0 = ds.s - ds.seg_start, cnt = ds.e - ds.s;
@@ -172,12 +211,65 @@ __global__ __launch_bounds__(kSmallThreads) void sort_small_kernel(const SortArg
     uint32_t low = (levels - 1u) * width;   // bits below the digit
     {
         uint32_t* const h = S.hist[lane & 3];
-        from_ids([&](const uint32_t k, const uint32_t at) {
-            if (held) s_keys[at] = k;
-            if (k != kNoKey) atomicAdd(&h[k >> low], 1u);
+        bool bad = false;
+        constexpr uint32_t kU = 8;   // ids in flight, and as many more while these are used
+        IT id[kU];
+        // f(keys, number of the first) for elements first, first + stride, ...; from n on the segment's last
+        auto from_ids = [&](const uint32_t first, const uint32_t stride, const uint32_t rounds, auto f) {
+            auto load = [&](const uint32_t k0) {
+#pragma unroll
+                for (uint32_t u = 0; u < kU; ++u)
+                    if (u < 4u || k0 + 4u < rounds) id[u] = ids[umin(first + (k0 + u) * stride, n - 1u)];
+            };
+            load(0u);
+#pragma unroll 1
+            for (uint32_t k0 = 0; k0 < rounds; k0 += kU) {
+                uint32_t k[kU];
+#pragma unroll
+                for (uint32_t u = 0; u < kU; ++u) k[u] = key_of(id[u]);
+                if (k0 + kU < rounds) load(k0 + kU);
+                f(k, k0);
+            }
+        };
+        from_ids(tid, kSmallThreads, per, [&](uint32_t (&k)[kU], const uint32_t k0) {
+            uint32_t* const to = s_keys + tid + k0 * kSmallThreads;
+            if ((k0 + kU) * kSmallThreads <= kept) {   // (without a branch per element, which would take as long as the rest of it)
+#pragma unroll
+                for (uint32_t u = 0; u < kU; ++u) {
+                    bad |= k[u] == R;
+                    to[u * kSmallThreads] = k[u];
+                    k[u] >>= low;
+                }
+                add_digits(h, k);
+            } else {
+#pragma unroll
+                for (uint32_t u = 0; u < kU; ++u) {
+                    if (k0 + u >= per) break;
+                    bad |= k[u] == R;
+                    const bool in = tid + (k0 + u) * kSmallThreads < n;
+                    to[u * kSmallThreads] = in ? k[u] : kNoKey;
+                    atomicAdd(&h[k[u] >> low], in ? 1u : 0u);
+                }
+            }
         });
+        const uint32_t first = kept + row0 * kWave + (uint32_t)lane, most = umin(my_rows, kSmallRows);
+        auto add_row = [&](const uint32_t k, const uint32_t r) {   // returns what a row holds of it
+            bad |= k == R;
+            const bool in = first + r * kWave < n;
+            atomicAdd(&h[k >> low], in ? 1u : 0u);
+            return in ? k : kNoKey;
+        };
+        if (most > 0u)
+            from_ids(first, kWave, most, [&](const uint32_t (&k)[kU], const uint32_t r) {
+#pragma unroll
+                for (uint32_t u = 0; u < kU; ++u) {
+                    if (r + u >= most) break;
+                    row[r + u] = add_row(k[u], r + u);
+                }
+            });
+        if (my_rows > most) last_row = add_row(key_of(ids[umin(first + kSmallRows * kWave, n - 1u)]), kSmallRows);
+        if (bad) atomicOr(a.err, 1);
     }
-    if (bad) atomicOr(a.err, 1);
     __syncthreads();
     // (a wavefront per border; all of them reading the histogram would take as long as 16 of these in turn)
     if (w < 2u) {
@@ -200,16 +292,22 @@ __global__ __launch_bounds__(kSmallThreads) void sort_small_kernel(const SortArg
     while (low > 0u && between > (uint32_t)kSmallThreads) {
         const uint32_t high = low;
         low -= width;
-        if (tid < 2u * kSelBins / 4u) reinterpret_cast<uint4*>(S.hist)[tid] = make_uint4(0u, 0u, 0u, 0u);
+        clear_hist();
         __syncthreads();
-        each_key([&](const uint32_t k, uint32_t) {
+        const bool one = key0 == key1;
+        uint32_t* const h = one ? S.hist[lane & 3] : S.hist[lane & 1];
+        // (the upper border's histograms lie behind the lower one's; the other lanes add to a word of their own instead of branching)
+        const uint32_t upper = one ? 0u : 2u * kSelPitch;
+        auto add = [&](const uint32_t k) {
             const uint32_t d = k >> high;
-            if (d == key0) atomicAdd(&S.hist[0][(k >> low) & mask], 1u);
-            else if (d == key1) atomicAdd(&S.hist[1][(k >> low) & mask], 1u);
-        });
+            uint32_t* const to = &h[((k >> low) & mask) + (d == key1 ? upper : 0u)];
+            atomicAdd(((d == key0) | (d == key1)) ? to : &S.none[lane], 1u);
+        };
+        each(add, [&](const uint32_t k, uint32_t) { add(k); });
         __syncthreads();
         if (w < 2u) {
-            const Place p = find_place<1>(S.hist[key0 == key1 ? 0u : w], w == 0u ? r0 - before0 : r0 + cnt - 1u - before1);
+            const uint32_t x = w == 0u ? r0 - before0 : r0 + cnt - 1u - before1;
+            const Place p = one ? find_place<4>(S.hist[0], x) : find_place<2>(S.hist[2u * w], x);
             if (lane == 0) S.place[w] = make_uint4(p.bin, p.before, p.count, 0u);
         }
         __syncthreads();
@@ -220,65 +318,104 @@ __global__ __launch_bounds__(kSmallThreads) void sort_small_kernel(const SortArg
     // taken (and, if it is the upper one too, before a_hi), of the upper one's those before number b_hi.
     const bool whole = between <= (uint32_t)kSmallThreads, one_key = key0 == key1;
     const uint32_t base = key0 << low, top = ((key1 - key0 + 1u) << low) - 1u;
-    const uint32_t a_lo = r0 - before0, a_hi = one_key ? a_lo + cnt : kNoKey, b_hi = r0 + cnt - before1;
-    uint32_t nr = 0, na = 0, nb = 0;   // elements from border to border, of the lower border's key, of the upper one's
-    if (whole)
-        each_key([&](const uint32_t k, uint32_t) { nr += (uint32_t)__popcll(__ballot(k - base <= top)); });
-    else
-        each_key([&](const uint32_t k, uint32_t) {
-            nr += (uint32_t)__popcll(__ballot(k - base <= top));
-            na += (uint32_t)__popcll(__ballot(k == key0));
-            nb += (uint32_t)__popcll(__ballot(k == key1));
-        });
-    if (lane == 0) S.taken[w] = make_uint4(nr, na, nb, 0u);
-    __syncthreads();
-    {
-        const uint4 v = S.taken[lane & (kSmallWaves - 1)];
-        const bool before = (uint32_t)lane < w;
-        nr = bcast_lane(wave_incl_scan(before ? v.x : 0u), kWave - 1);
-        na = bcast_lane(wave_incl_scan(before ? v.y : 0u), kWave - 1);
-        nb = bcast_lane(wave_incl_scan(before ? v.z : 0u), kWave - 1);
-    }
     const uint64_t lt = lanemask_lt();
+    // masks of them: of the thread's kept elements, and of a row of the wavefront's others in each lane
+    uint32_t kept_sel = 0;
+    uint64_t row_sel = 0;
     if (whole) {
-        each_key([&](const uint32_t k, const uint32_t p) {
-            const bool on = k - base <= top;
-            const uint64_t mr = __ballot(on);
-            if (on) {
-                const uint32_t at = nr + (uint32_t)__popcll(mr & lt);
-                S.buf[0].key[at] = k - base;
-                S.buf[0].pos[at] = ds.seg_start + p;
-            }
-            nr += (uint32_t)__popcll(mr);
-        });
+        each([&](const uint32_t k) { push_le(kept_sel, k - base, top); },
+             [&](const uint32_t k, const uint32_t r) {
+                 const uint64_t m = __ballot(k - base <= top);
+                 row_sel = (uint32_t)lane == r ? m : row_sel;
+             });
     } else {
-        // the range's elements among the first r, x, y
-        auto place = [&](const uint32_t r, const uint32_t x, const uint32_t y) {
-            const uint32_t t = (x < a_lo ? a_lo : (x > a_hi ? a_hi : x)) - a_lo;
-            return one_key ? t : r - x - y + t + umin(y, b_hi);
+        uint32_t kept_a = 0, kept_b = 0;
+        uint64_t row_a = 0, row_b = 0;
+        if (one_key) {
+            each([&](const uint32_t k) { push_eq(kept_a, k, key0); },
+                 [&](const uint32_t k, const uint32_t r) {
+                     const uint64_t m = __ballot(k == key0);
+                     row_a = (uint32_t)lane == r ? m : row_a;
+                 });
+        } else {
+            each([&](const uint32_t k) {
+                     push_le(kept_sel, k - base, top);
+                     push_eq(kept_a, k, key0);
+                     push_eq(kept_b, k, key1);
+                 },
+                 [&](const uint32_t k, const uint32_t r) {
+                     const uint64_t m = __ballot(k - base <= top), ma = __ballot(k == key0), mb = __ballot(k == key1);
+                     if ((uint32_t)lane == r) {
+                         row_sel = m;
+                         row_a = ma;
+                         row_b = mb;
+                     }
+                 });
+        }
+        // the numbers of their first elements of either key: both in one word within a wavefront, which has at most 4096 elements of a kind
+        const uint32_t of_kept = (uint32_t)__popc(kept_a) | (uint32_t)__popc(kept_b) << 16;
+        const uint32_t of_row = (uint32_t)__popcll(row_a) | (uint32_t)__popcll(row_b) << 16;
+        const uint32_t in_kept = wave_incl_scan(of_kept), in_row = wave_incl_scan(of_row);
+        if (lane == kWave - 1) {
+            S.borders[w] = in_kept;
+            S.borders[kSmallWaves + w] = in_row;
+        }
+        __syncthreads();
+        const uint32_t v = lane < 2 * kSmallWaves ? S.borders[lane] : 0u, va = v & 0xFFFFu, vb = v >> 16;
+        const uint32_t xa = wave_incl_scan(va) - va, xb = wave_incl_scan(vb) - vb;
+        const uint32_t a_lo = r0 - before0, a_hi = a_lo + cnt, b_hi = r0 + cnt - before1;
+        auto from = [](const uint32_t number, const uint32_t first) { return number > first ? number - first : 0u; };
+        auto choose = [&](const uint64_t sel, const uint64_t ma, const uint64_t mb, const uint32_t before, const int wave) {
+            const uint32_t x = (before & 0xFFFFu) + bcast_lane(xa, wave), y = (before >> 16) + bcast_lane(xb, wave);
+            const uint64_t lower = without_lowest(ma, from(a_lo, x));
+            return one_key ? lower & ~without_lowest(ma, from(a_hi, x)) : (sel & ~ma & ~mb) | lower | (mb & ~without_lowest(mb, from(b_hi, y)));
         };
-        each_key([&](const uint32_t k, const uint32_t p) {
-            const uint64_t mr = __ballot(k - base <= top), ma = __ballot(k == key0), mb = __ballot(k == key1);
-            if (mr == 0ull) return;
-            const uint32_t x = na + (uint32_t)__popcll(ma & lt), y = nb + (uint32_t)__popcll(mb & lt);
-            const bool on = k == key0 ? x >= a_lo && x < a_hi : (k == key1 ? y < b_hi : k - base <= top);
-            if (on) {
-                const uint32_t at = place(nr + (uint32_t)__popcll(mr & lt), x, y);
-                S.buf[0].key[at] = k - base;
-                S.buf[0].pos[at] = ds.seg_start + p;
+        kept_sel = (uint32_t)choose(kept_sel, kept_a, kept_b, in_kept - of_kept, (int)w);
+        if (row_per > 0u) row_sel = choose(row_sel, row_a, row_b, in_row - of_row, kSmallWaves + (int)w);
+    }
+    {   // their positions
+        const uint32_t c = (uint32_t)__popc(kept_sel), in_kept = wave_incl_scan(c);
+        const uint32_t cr = (uint32_t)__popcll(row_sel), in_row = wave_incl_scan(cr);
+        if (lane == kWave - 1) {
+            S.taken[w] = in_kept;
+            S.taken[kSmallWaves + w] = in_row;
+        }
+        __syncthreads();
+        const uint32_t v = lane < 2 * kSmallWaves ? S.taken[lane] : 0u, xs = wave_incl_scan(v) - v;
+        // a lane its own, bit by bit, or where few lanes hold many, lane after lane
+        auto write = [&](uint64_t sel, uint32_t at, const uint32_t p0, const uint32_t count) {
+            uint64_t any = __ballot(sel != 0ull);
+            if (wave_max_i32((int)count) <= __popcll(any)) {
+                while (sel != 0ull) {
+                    S.buf[0].pos[at++] = p0 + (uint32_t)__ffsll((unsigned long long)sel) - 1u;
+                    sel &= sel - 1ull;
+                }
+            } else {
+                for (; any != 0ull; any &= any - 1ull) {
+                    const int r = __ffsll((unsigned long long)any) - 1;
+                    const uint64_t m = (uint64_t)lane_i64((int64_t)sel, r);
+                    const uint32_t first = bcast_lane(at, r), pr = bcast_lane(p0, r);
+                    if (m >> lane & 1ull) S.buf[0].pos[first + (uint32_t)__popcll(m & lt)] = pr + (uint32_t)lane;
+                }
             }
-            nr += (uint32_t)__popcll(mr);
-            na += (uint32_t)__popcll(ma);
-            nb += (uint32_t)__popcll(mb);
-        });
+        };
+        write(kept_sel, bcast_lane(xs, (int)w) + in_kept - c, ds.seg_start + tid * per, c);
+        if (row_per > 0u) write(row_sel, bcast_lane(xs, kSmallWaves + (int)w) + in_row - cr, ds.seg_start + kept + (row0 + (uint32_t)lane) * kWave, cr);
     }
     __syncthreads();
     // ---- sorted by what the keys differ in, stably; one element per thread, a digit's counts per wavefront
     const uint32_t m = whole ? between : cnt;
     const bool on = tid < m;
-    uint32_t my = S.buf[0].key[tid], pos = S.buf[0].pos[tid];
+    uint32_t my = 0, pos = 0;
+    if (on) {
+        pos = S.buf[0].pos[tid];
+        const uint32_t p = pos - ds.seg_start;
+        my = (p < held ? s_keys[p] : key_of(ids[p])) - base;
+    }
+    S.buf[0].key[tid] = my;   // (where all are of one key, this is what is read below)
     const int diff = top == 0u ? 0 : 32 - __clz((int)top);
     const int passes = (diff + 5) / 6, db = passes == 0 ? 0 : (diff + passes - 1) / passes;
+    if (passes == 0) __syncthreads();
     for (int ps = 0; ps < passes; ++ps) {
         const uint32_t d = (my >> (ps * db)) & ((1u << db) - 1u);
         uint32_t rank = 0;
@@ -317,7 +454,7 @@ __global__ __launch_bounds__(kSmallThreads) void sort_small_kernel(const SortArg
     if (tid >= o && tid < o + cnt) {
         // (where the range is not a part of all there is: the elements of the lower border's key before it, and the length of the run
         // of the upper one's that goes on behind it)
-        head = tid == 0u ? whole || a_lo == 0u : my != sorted[tid - 1u];
+        head = tid == 0u ? whole || r0 == before0 : my != sorted[tid - 1u];
         if (head && base + my < R)
             lng = tid + long_min < m ? sorted[tid + long_min] == my : !whole && my == top && r0 + tid + long_min < before1 + count1;
         uint32_t val = pos;
@@ -384,12 +521,13 @@ __global__ __launch_bounds__(kSmallRleThreads) void rle_small_kernel(const RleAr
 
 hipError_t launch_sort_small(const tbe_handle* h, const SortArgs& a, const RleArgs& r, int idx32, hipStream_t s) {
     const unsigned grid = ((unsigned)a.max_chunks + 7u) & ~7u;
-    const int64_t held = a.N < kSmallHeld ? a.N : (int64_t)kSmallHeld;
-    const size_t lds = 4 * (size_t)((held + kSmallThreads - 1) / kSmallThreads * kSmallThreads);
+    const int64_t rounds = ((a.N + kSmallThreads - 1) / kSmallThreads) | 1;
+    const int64_t held = rounds * kSmallThreads < kSmallHeld ? rounds * kSmallThreads : kSmallHeld;
+    const size_t lds = 4 * (size_t)held;
     {
         LaunchTimer tm(h, s, "sort_small");
-        if (idx32) sort_small_kernel<int32_t><<<grid, kSmallThreads, lds, s>>>(a, r.counts, r.long_min);
-        else sort_small_kernel<int64_t><<<grid, kSmallThreads, lds, s>>>(a, r.counts, r.long_min);
+        if (idx32) sort_small_kernel<int32_t><<<grid, kSmallThreads, lds, s>>>(a, r.counts, r.long_min, (uint32_t)held);
+        else sort_small_kernel<int64_t><<<grid, kSmallThreads, lds, s>>>(a, r.counts, r.long_min, (uint32_t)held);
         tm.done();
     }
     LaunchTimer tm(h, s, "rle_write");
