@@ -382,6 +382,8 @@ tbe_status tbe_create(int32_t T, const int64_t* rows, const int32_t* D, tbe_dtyp
             const int nl = (D[t] + vec - 1) / vec;
             const int c = nl > 128 ? 6 : (nl > 64 ? 5 : (nl > kFwdGroupMaxLanes ? 0 : (nl > 16 ? 1 : (nl > 8 ? 2 : (nl > 4 ? 3 : 4)))));
             lists[c].push_back(t);
+            h->fwd_columns[c] |= (uint32_t)D[t] | (uint32_t)h->D_off[t];
+            h->fwd_maxD[c] = std::max(h->fwd_maxD[c], (int)D[t]);
         }
         for (int c = 0; c < 7; ++c) {
             h->fwd_first[c] = (int)cls_tables.size();

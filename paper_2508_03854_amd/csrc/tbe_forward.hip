@@ -258,7 +258,7 @@ struct BagOrder {
 };
 static_assert(kLongBagMax < (int)kLongBag && kLongBagMax < 3 * kWave && kLongBagMax < kGroupThreads && kGroupThreads / 4 <= 256,
               "lengths and places in a byte, three lengths per lane");
-template <typename WT, int U, bool MEAN, bool BY_LENGTH>
+template <typename WT, int U, bool MEAN, bool BY_LENGTH, bool STREAM>
 __global__ __launch_bounds__(kGroupThreads, 8) void forward_groups_kernel(
     const WT* __restrict__ weights, const IdxView indices, const IdxView offsets,
     const int32_t* __restrict__ D_off, const int64_t* __restrict__ w_off, const int64_t* __restrict__ row_base,
@@ -381,15 +381,13 @@ __global__ __launch_bounds__(kGroupThreads, 8) void forward_groups_kernel(
     if (MEAN) scale = len > 0 ? 1.f / lenf : 0.f;
     if (has_bag && col_on && !is_long) {
         const int64_t out_elem = (int64_t)b * sumD + d0 + lc;
-        // (the output goes past the caches, which are left to the rows, where lanes write next to each other: 64 tables x 3001 bags of
-        // 31 ids, 128 and 256 binary16 columns into binary16 198 -> 192 us)
         float y[V];
 #pragma unroll
         for (int v = 0; v < V; ++v) y[v] = pooled<MEAN>(acc[v], lenf, scale);
         if constexpr (V == 4) {
-            store4_from_float<true>(out, out_io, out_elem, y[0], y[1], y[2], y[3]);
+            store4_from_float<STREAM>(out, out_io, out_elem, y[0], y[1], y[2], y[3]);
         } else if (out_io != 0) {
-            store8_from_float<true>(out, out_io, out_elem, y);
+            store8_from_float<STREAM>(out, out_io, out_elem, y);
         } else {
             store4_from_float(out, 0, out_elem, y[0], y[1], y[2], y[3]);
             store4_from_float(out, 0, out_elem + 4, y[4], y[5], y[6], y[7]);
@@ -714,6 +712,20 @@ static void launch_forward_nc(const tbe_handle* h, int first, int n, const void*
 // 0.2 to 0.5 us for the four barriers and have nothing to fill the gaps with: 8 tables x 4096 bags, 1 + Poisson(10) ids, 8 fp32 columns
 // 15.0 -> 15.7 us, 64 binary16 15.4 -> 15.8, 64 fp32 16.1 -> 16.4.
 constexpr int64_t kByLengthWorkgroups = 2048;
+// Do the lane groups of class c write their parts of the output past the caches, which are then left to the rows?  Not where that leaves
+// parts of 64-byte pieces to other workgroups, which are then fetched and written again: 26 tables x 32768 bags of one id, us, plain / past
+// the caches: 12 fp32 columns 33.5 / 51, 28 55 / 83, 4 and 8 columns into bfloat16 34 / 36; but 16 columns, 64 bytes, 33.5 / 33, of 5 and 10
+// ids 51 / 48 and 70 / 66.  And wider parts not where the output is small enough for its reader to find it in a cache: forward and one
+// kernel that reads its output, 14, 27, 54, 80, 109 MB of 64 to 512 bytes a part: 0.91 to 1.0, 0.96 to 1.0, 0.95 to 1.04, 0.99 to 1.04,
+// 0.98 to 1.06 times as fast (the forward alone 1.01 to 1.06, 1.01 to 1.05, 1.0 to 1.1, 1.0 to 1.2, 1.0 to 1.2; of 64 tables x 3001 bags of 31
+// ids, 128 and 256 binary16 columns into binary16, 86 MB, 198 -> 192 us).  Parts of 64 bytes gain both, 1.0 to 1.03, from the smallest on.
+constexpr size_t kLargeOutput = (size_t)48 << 20;   // bytes
+static bool stream_output(const tbe_handle* h, const int c, const int32_t B, const void* out, const int out_io) {
+    const size_t eb = out_io == 0 ? 4 : 2, pitch = (size_t)h->sumD * eb;
+    if (h->dtype == TBE_F16 && out_io == 0) return false;   // (a lane's eight elements are two stores)
+    if (((h->fwd_columns[c] * eb | pitch | reinterpret_cast<uintptr_t>(out)) & 63u) != 0u) return false;
+    return (size_t)B * pitch > kLargeOutput || (size_t)h->fwd_maxD[c] * eb == 64u;
+}
 // the narrow-row classes: 32, 16, 8 and 4 lanes per row
 template <typename WT>
 static void launch_forward_groups(const tbe_handle* h, const void* tables, const int32_t* d_D_off, const IdxView indices,
@@ -745,9 +757,15 @@ static void launch_forward_groups(const tbe_handle* h, const void* tables, const
         }
         const int64_t bags = kGroupThreads >> lpr_log2;   // of a workgroup
         const int64_t groups = (int64_t)n * (((int64_t)B + bags - 1) / bags);
+        const bool stream = stream_output(h, c, B, out, out_io);
+        auto launch = [&](auto mean_c, auto by_length_c, auto stream_c) {
+            forward_groups_kernel<WT, 8, decltype(mean_c)::value, decltype(by_length_c)::value, decltype(stream_c)::value>
+                <<<grid, kGroupThreads, 0, s>>>(w, indices, offsets, d_D_off, h->d_w_off, h->d_row_base, list, n, lpr_log2, B, nnz,
+                                                h->sumD, out, out_io, h->d_err);
+        };
         auto go = [&](auto mean_c, auto by_length_c) {
-            forward_groups_kernel<WT, 8, decltype(mean_c)::value, decltype(by_length_c)::value><<<grid, kGroupThreads, 0, s>>>(
-                w, indices, offsets, d_D_off, h->d_w_off, h->d_row_base, list, n, lpr_log2, B, nnz, h->sumD, out, out_io, h->d_err);
+            if (stream) launch(mean_c, by_length_c, std::true_type{});
+            else launch(mean_c, by_length_c, std::false_type{});
         };
         if (groups >= kByLengthWorkgroups) {
             grid = dim3((unsigned)groups);

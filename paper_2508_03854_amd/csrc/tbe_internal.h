@@ -77,6 +77,8 @@ struct tbe_handle {
     int64_t hot_min_workgroups = TBE_TUNE_AUTO;
     int fwd_first[7] = {0, 0, 0, 0, 0, 0, 0};
     int fwd_count[7] = {0, 0, 0, 0, 0, 0, 0};
+    uint32_t fwd_columns[7] = {0};   // of the class's tables: all bits of their numbers of columns and first columns
+    int fwd_maxD[7] = {0};           // ... and the most columns
     // timing
     bool timing = false;
     std::vector<tbe::TimingSlot> slots;  // pool of event pairs
