@@ -246,18 +246,30 @@ struct LdsTotals<true, V> {
 // wavefront.  A bag of a dozen narrow rows is a few hundred bytes; with one wavefront per bag the step is bound by the latency of the
 // offsets -> ids -> rows chain, not by bandwidth.  A group reads LPR ids with one coalesced load, then walks them U rows at a time.
 // BY_LENGTH: the workgroup hands its bags out by length, longest first, so that those that share a wavefront are of a length: a
-// wavefront walks as far as the longest of its bags.  Consecutive bags / this, us: 32 tables x 65536 bags, lognormal of 12 ids on
-// average, 2 of 128 and 30 of 32 fp32 columns 482 / 410; 16 tables x 32768 bags: 8 fp32 columns, lognormal of 12 and 35 ids 98 213 / 85
-// 180; 32 fp32 123 308 / 110 267, 1 + Poisson(30) 136 / 127, fixed 40 158 / 157; 64 binary16, lognormal 164 351 / 156 328.  Several such
-// rounds per workgroup level the lengths further (the first 372 with 8) but spread the workgroups that run at a time over more tables:
-// fixed 40 of 32 fp32 columns 169, 179, 190 with 2, 4, 8 of them; workgroups of 512 threads 432 at the first.
-constexpr uint32_t kLongBag = 255u;                      // in place of a length above kLongBagMax: the bag is left to another kernel
-struct BagOrder {
-    uint32_t start[kGroupThreads / 4], bin[kLongBagMax + 1];   // (at least 4 lanes per bag)
-    uint8_t len[kGroupThreads / 4], bag[kGroupThreads / 4];    // by place in the table; the places by length
-};
-static_assert(kLongBagMax < (int)kLongBag && kLongBagMax < 3 * kWave && kLongBagMax < kGroupThreads && kGroupThreads / 4 <= 256,
-              "lengths and places in a byte, three lengths per lane");
+// wavefront walks as far as the longest of its bags.  Every wavefront finds the order of all of them by itself, and none where they are of
+// one length, so that the workgroup's wavefronts never wait for each other (with counts in LDS and four barriers instead, bags of one to
+// five ids took 6 to 14 % longer than consecutive ones).  Consecutive bags / this, us: 32 tables x 65536 bags, lognormal of 12 ids on
+// average, 2 of 128 and 30 of 32 fp32 columns 481 / 414; 16 tables x 32768 bags: 8 fp32 columns, lognormal of 12 and 35 ids 94 201 / 82
+// 173; 32 fp32 122 297 / 111 258, 1 + Poisson(30) 133 / 126, fixed 5 and 40 36.6 156 / 36.7 156; 64 binary16, lognormal 171 344 / 162 324;
+// 8192 bags of 128 fp32, Poisson(3) 34.7 / 35.6, fixed 3 33.9 / 32.8.  Several such rounds per workgroup level the lengths further (the
+// first 372 with 8) but spread the workgroups that run at a time over more tables: fixed 40 of 32 fp32 columns 169, 179, 190 with 2, 4, 8
+// of them; workgroups of 512 threads 432 at the first.
+// Place of every lane's number, below 2^bits, among those of the lanes `in`, the largest first, equal ones by lane: a bit at a time from
+// the top, the lanes that agree so far and have a bit that this one lacks come before it.
+__device__ __forceinline__ uint32_t place_by_size(const uint32_t x, const int bits, const uint64_t in) {
+    uint32_t lo = (uint32_t)in, hi = (uint32_t)(in >> 32), place = 0;
+#pragma unroll 1
+    for (int b = bits - 1; b >= 0; --b) {
+        const uint32_t has = (uint32_t)__builtin_amdgcn_sbfe((int)x, b, 1);   // all ones or nothing
+        const uint64_t m = __builtin_amdgcn_uicmp(has, 0u, 33 /* != */);
+        const uint32_t before = (uint32_t)__popc(lo & (uint32_t)m) + (uint32_t)__popc(hi & (uint32_t)(m >> 32));
+        place += before & ~has;
+        lo = __builtin_amdgcn_bitop3_b32(lo, (uint32_t)m, has, 0x90);           // lo & ~(m ^ has)
+        hi = __builtin_amdgcn_bitop3_b32(hi, (uint32_t)(m >> 32), has, 0x90);
+    }
+    return place + __builtin_amdgcn_mbcnt_hi(hi, __builtin_amdgcn_mbcnt_lo(lo, 0u));
+}
+static_assert(kLongBagMax < 256 && kGroupThreads / 4 <= kWave, "a length in a byte, a workgroup's bags in the lanes of a wavefront");
 template <typename WT, int U, bool MEAN, bool BY_LENGTH, bool STREAM>
 __global__ __launch_bounds__(kGroupThreads, 8) void forward_groups_kernel(
     const WT* __restrict__ weights, const IdxView indices, const IdxView offsets,
@@ -267,7 +279,6 @@ __global__ __launch_bounds__(kGroupThreads, 8) void forward_groups_kernel(
     constexpr int V = RowIO<WT>::kVec;
     using raw_t = typename RowIO<WT>::raw_t;
     __shared__ double s_total[V][kGroupThreads];
-    __shared__ typename std::conditional<BY_LENGTH, BagOrder, int>::type S;
     const int lane = lane_id();
     const int LPR = 1 << lpr_log2;
     const int G = kWave >> lpr_log2;
@@ -295,45 +306,25 @@ __global__ __launch_bounds__(kGroupThreads, 8) void forward_groups_kernel(
     int len;
     bool is_long = false;
     if constexpr (BY_LENGTH) {
-        const int64_t lookups = table_lookups(offsets, t, B);
-        const int k = (int)threadIdx.x;
-        if (k <= kLongBagMax) S.bin[k] = 0u;
-        __syncthreads();
-        uint32_t my_len = 0;
-        if (k < bags) {
-            const BagSpan bag = bag_span(offsets, t, B, b0 + (uint32_t)k, nnz);
-            const bool lng = bag.len > long_min && long_bag(bag.len, lookups, B);
-            my_len = lng ? 0u : (uint32_t)bag.len;
-            S.start[k] = bag.start;
-            S.len[k] = (uint8_t)(lng ? kLongBag : my_len);
-            atomicAdd(&S.bin[my_len], 1u);
+        // every wavefront by itself, without a barrier: a lane per bag of the workgroup
+        const BagSpan bag = bag_span(offsets, t, B, b0 + umin((uint32_t)lane, (uint32_t)bags - 1u), nnz);
+        bool lng = false;
+        if (__any(bag.len > long_min)) lng = bag.len > long_min && long_bag(bag.len, table_lookups(offsets, t, B), B);
+        const uint32_t my_len = lng ? 0u : (uint32_t)bag.len;
+        uint32_t word = my_len | (lng ? 256u : 0u) | (uint32_t)lane << 16;
+        start = bag.start;
+        if (__ballot(my_len != (uint32_t)__builtin_amdgcn_readfirstlane((int)my_len)) != 0ull) {   // (a bag's sum does not depend on those beside it)
+            const uint64_t in = bags == kWave ? ~0ull : (1ull << bags) - 1ull;
+            const uint32_t place = place_by_size(my_len, 32 - __clz(wave_max_i32((int)my_len)), in);
+            const int to = 4 * (int)(lane < bags ? place : (uint32_t)lane);
+            word = (uint32_t)__builtin_amdgcn_ds_permute(to, (int)word);
+            start = (uint32_t)__builtin_amdgcn_ds_permute(to, (int)start);
         }
-        __syncthreads();
-        if (wv == 0) {   // where each length begins, the longest first: three bins per lane
-            uint32_t c[3], sum = 0;
-#pragma unroll
-            for (int q = 0; q < 3; ++q) {
-                const int l = kLongBagMax - 3 * lane - q;
-                c[q] = l >= 0 ? S.bin[l] : 0u;
-                sum += c[q];
-            }
-            uint32_t at = wave_incl_scan(sum) - sum;
-#pragma unroll
-            for (int q = 0; q < 3; ++q) {
-                const int l = kLongBagMax - 3 * lane - q;
-                if (l >= 0) S.bin[l] = at;
-                at += c[q];
-            }
-        }
-        __syncthreads();
-        if (k < bags) S.bag[atomicAdd(&S.bin[my_len], 1u)] = (uint8_t)k;   // (a bag's sum does not depend on the bags beside it)
-        __syncthreads();
-        const int mine = S.bag[wv * G + sub];
-        b = b0 + (uint32_t)mine;
-        start = S.start[mine];
-        len = S.len[mine];
-        is_long = len == (int)kLongBag;
-        len = is_long ? 0 : len;
+        word = __shfl(word, wv * G + sub, kWave);
+        start = __shfl(start, wv * G + sub, kWave);
+        b = b0 + (word >> 16);
+        len = (int)(word & 0xFFu);
+        is_long = (word & 256u) != 0u;
     } else {
         const BagSpan bag = bag_span(offsets, t, B, b, nnz);
         start = bag.start;
@@ -708,9 +699,9 @@ static void launch_forward_nc(const tbe_handle* h, int first, int n, const void*
                                                                       list, n, B, nnz, h->sumD, out, out_io, h->d_err);
 }
 
-// Workgroups from which a launch of lane groups hands bags out by length: as many as the chip holds at a time.  Smaller ones pay
-// 0.2 to 0.5 us for the four barriers and have nothing to fill the gaps with: 8 tables x 4096 bags, 1 + Poisson(10) ids, 8 fp32 columns
-// 15.0 -> 15.7 us, 64 binary16 15.4 -> 15.8, 64 fp32 16.1 -> 16.4.
+// Workgroups from which a launch of lane groups hands bags out by length: as many as the chip holds at a time.  Smaller ones gain nothing
+// by it that can be told from the noise: 8 tables x 4096 bags, 1 + Poisson(10) ids, 8 fp32 columns 13.9 / 14.0 us, 64 binary16 14.1 / 13.6,
+// 64 fp32 14.5 / 14.2; Poisson(3) 13.9 / 13.9, 13.4 / 13.5, 13.6 / 13.6.
 constexpr int64_t kByLengthWorkgroups = 2048;
 // Do the lane groups of class c write their parts of the output past the caches, which are then left to the rows?  Not where that leaves
 // parts of 64-byte pieces to other workgroups, which are then fetched and written again: 26 tables x 32768 bags of one id, us, plain / past

@@ -44,3 +44,27 @@ def test_bags_of_large_launches(lanes, dtype, pooling, io):
             err = 2.0 ** -24 * (L * L if pooling == "sum" else L + 1.0) + want.abs() * {torch.float32: 0.0, torch.float16: 2.0 ** -11, torch.bfloat16: 2.0 ** -8}[io] + 2.0 ** -24
             assert ((out[:, t * D:(t + 1) * D] - want).abs() <= err).all(), (B, t)
     tbe.close()
+
+
+@pytest.mark.parametrize("D,dtype", [(8, "f32"), (32, "f32"), (64, "f16"), (128, "f32")])
+@pytest.mark.parametrize("length,odd", [(0, 0), (5, 0), (5, 1), (128, 0), (64, 3)])
+def test_bags_of_one_length(D, dtype, length, odd):
+    """Workgroups whose bags are all of one length keep their order; one bag of another length is enough to give them one."""
+    if not torch.cuda.is_available():
+        pytest.skip("no GPU")
+    from paper_2508_03854_amd import TBE
+    R, B, dev = 50, 70_001, "cuda"
+    tbe = TBE([R], [D], dtype)
+    tbe.set_tunable("hot_rows_min_workgroups", -1)
+    g = torch.Generator(device=dev).manual_seed(D + length)
+    w = torch.randint(-2, 3, (R * D,), generator=g, device=dev).to(tbe.torch_dtype)   # exact sums in any order
+    lens = torch.full((B,), length, device=dev)
+    lens[17::500] += odd
+    off = torch.zeros(B + 1, dtype=torch.int64, device=dev)
+    torch.cumsum(lens, 0, out=off[1:])
+    idx = torch.randint(0, R, (int(off[-1]),), generator=g, device=dev)
+    out = tbe.forward(w, idx, off, B, "sum", out=torch.full((B, D), 7.0, device=dev))
+    counts = torch.zeros(B * R, device=dev)
+    counts.index_add_(0, torch.repeat_interleave(torch.arange(B, device=dev), lens) * R + idx, torch.ones(idx.numel(), device=dev))
+    assert torch.equal(out, counts.view(B, R) @ w.view(R, D).float())
+    tbe.close()
