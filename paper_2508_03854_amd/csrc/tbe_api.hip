@@ -78,36 +78,42 @@ static size_t most_chunks(const tbe_handle* h, int64_t N) {
     return (size_t)(std::max(std::max(small, middle), large) + 1 + (h->segmented ? h->T : 1));
 }
 
-// A row with more than this many lookups is long, i.e. shared out to several wavefronts in parts of this size.  A wavefront
+// A row with more than so many lookups is long, i.e. shared out to several wavefronts in parts.  A wavefront
 // walks 512 lookups of a wide row in about 60 us, so small batches, whose row updates take less than that, cut finer; the
-// borders follow from the memory of the partial sums (at most 2 n / part slots): never more than n / 48 plus a constant.
+// borders follow from the memory of the partial sums (at most n / part + n / min slots): never more than n / 48 plus a constant.
 // The smallest batches are a matter of the longest chain of loads.  Where rows take a wavefront each they cut finer still, as long as
-// few lookups of a table keep the one workgroup that lists its long rows from becoming that chain.  Parts of 64 / 32 / 16, backward us: ten tables x 777 bags of 6 ids,
-// 8 to 1024 columns 70 / 59 / 59; 10 tables x 1200 lookups of 64, 256, 1024 columns 33.5 33.4 49.9 / 33.1 32.5 46.7 / 32.4 31.9 42.6;
-// one table x 12000 42.3 44.4 63.8 / 44.0 44.1 57.9 / 47.3 47.0 62.0; x 24000 53 55 93 / 57 58 94 / 63 62 96.
+// few lookups of a table keep the one workgroup that lists its long rows from becoming that chain.  Parts of 64 / 32 / 16, backward us:
+// ten tables x 777 bags of 6 ids, 8 to 1024 columns 70 / 59 / 59; 10 tables x 1200 lookups of 64, 256, 1024 columns 33.5 33.4 49.9 / 33.1
+// 32.5 46.7 / 32.4 31.9 42.6; one table x 12000 42.3 44.4 63.8 / 44.0 44.1 57.9 / 47.3 47.0 62.0; x 24000 53 55 93 / 57 58 94 / 63 62 96.
+// But a batch that has any long row pays for it: its list 3 to 4 us, the parts 1.6, their sums 2 to 4.  So with fewer than 512 lookups per
+// table, where a row has hardly more than a wavefront walks in that time, rows of up to 64 stay whole.  Against parts of 64, rows of 17
+// and more cut / this: 59 tables x 33 lookups, 1024 columns 29.7 -> 40.6 / 30.0, 2 x 85 27 -> 37 / 27, 9 x 286 of 512 columns 35 -> 45 /
+// 35.6; the mean over 1394 random batches of up to 65536 lookups, tables of 129 to 1024 columns, is 5 % faster with either, 63 / 11 of
+// them more than 3 % slower than with the passes and parts that a batch of any size can have.
 struct PartSteps {
-    int64_t top[6];      // batches of at most so many lookups
-    uint32_t part[6];
+    int64_t top[8];             // batches of at most so many lookups
+    uint32_t min[8], part[8];   // ... cut rows of more than `min` of them into parts of `part`
+    int of(const int64_t N) const {
+        int i = 0;
+        while (N > top[i]) ++i;
+        return i;
+    }
+    // the most long rows, and slots for partial sums, that a batch of N lookups or fewer has: ascending in N
+    int64_t most(const int64_t N, const bool slots) const {
+        int64_t m = 0;
+        for (const int64_t t : top) {
+            const int64_t n = std::min(t, N), i = of(n);
+            m = std::max(m, n / (int64_t)min[i] + (slots ? n / (int64_t)part[i] : 0) + 1);
+        }
+        return m;
+    }
 };
 static PartSteps part_steps(const tbe_handle* h, const bool fine) {
-    const int64_t T = h->T;
-    return {{fine && h->maxD > 256 ? std::min((int64_t)32768, 4096 * T) : 0, fine && h->maxD > 128 ? std::min((int64_t)65536, 8192 * T) : 0,
-             (int64_t)1 << 17, (int64_t)3 << 17, (int64_t)3 << 19, INT64_MAX},
-            {16, 32, 64, 128, 256, 512}};
-}
-static uint32_t long_min_of(const PartSteps& p, int64_t N) {
-    int i = 0;
-    while (N > p.top[i]) ++i;
-    return p.part[i];
-}
-// N / part with the parts of this batch or of any smaller one: ascending in N
-static int64_t most_parts(const PartSteps& p, int64_t N) {
-    int64_t m = 0;
-    for (const int64_t top : p.top) {
-        const int64_t n = top < N ? top : N;
-        m = std::max(m, n / (int64_t)long_min_of(p, n) + 1);
-    }
-    return m;
+    const int64_t D = fine ? h->maxD : 0, T = h->T, least = (int64_t)1 << 15, less = (int64_t)1 << 16;
+    return {{D > 256 ? std::min(least, 512 * T) : 0, D > 256 ? std::min(least, 4096 * T) : 0, D > 128 ? std::min(less, 512 * T) : 0,
+             D > 128 ? std::min(less, 8192 * T) : 0, (int64_t)1 << 17, (int64_t)3 << 17, (int64_t)3 << 19, INT64_MAX},
+            {64, 16, 64, 32, 64, 128, 256, 512},
+            {16, 16, 32, 32, 64, 128, 256, 512}};
 }
 
 // What the dense rows may make of a workspace.  A dense row leaves one partial sum per chunk of bags, so their area grows with
@@ -162,9 +168,10 @@ static Workspace lay_out(const tbe_handle* h, int32_t B, int64_t N, const PartSt
         w.chunk_desc += shift;
     }
     w.counters = take(4 * kCounterWords);
-    w.long_min = long_min_of(steps, (int64_t)n);
-    w.cap_long = most_parts(steps, (int64_t)n);           // at most n / (long_min + 1) rows are long
-    w.cap_main = 2 * w.cap_long + 1;               // ceil(len / part) slots for a row of len > part lookups
+    w.long_min = steps.min[steps.of((int64_t)n)];
+    w.part = steps.part[steps.of((int64_t)n)];
+    w.cap_long = steps.most((int64_t)n, false);    // at most n / (long_min + 1) rows are long
+    w.cap_main = steps.most((int64_t)n, true) + 1; // ceil(len / part) slots for each of them
     w.long_rows = take(8 * (size_t)w.cap_long);
     w.long_list = take(16 * (size_t)w.cap_long);
     w.unit_list = take(8 * (size_t)w.cap_main);
@@ -232,12 +239,12 @@ static Workspace lay_out(const tbe_handle* h, int32_t B, int64_t N, const PartSt
 Workspace carve(const tbe_handle* h, int32_t B, int64_t N) {
     Workspace w = lay_out(h, B, N, part_steps(h, true));
     const PartSteps coarse = part_steps(h, false);
-    if (w.cap_long == most_parts(coarse, N > 0 ? N : 1)) return w;
+    if (w.cap_main == coarse.most(N > 0 ? N : 1, true) + 1) return w;
     Workspace c = lay_out(h, B, N, coarse);
     // (of all sizes up to this one: what the finer parts take, up to the array's end as long as the coarser ones fit into it)
     const size_t total = c.total <= (size_t)TBE_STATIC_SCRATCH_BYTES ? std::min(w.total, (size_t)TBE_STATIC_SCRATCH_BYTES) : w.total;
     const bool dense = N >= 2 * (int64_t)B;   // (no table has dense rows of fewer lookups)
-    if (w.total > total || w.long_min == c.long_min || (dense && w.dense_chunks < c.dense_chunks)) w = c;
+    if (w.total > total || w.part == c.part || (dense && w.dense_chunks < c.dense_chunks)) w = c;
     w.total = total;
     return w;
 }

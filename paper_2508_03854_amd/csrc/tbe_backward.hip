@@ -714,7 +714,8 @@ SegArgs seg_args(const tbe_handle* h, const Workspace& w, char* ws, const void* 
     a.lr = a.eps = a.inv_c = 0.f;
     a.tables = nullptr;
     a.state = nullptr;
-    a.long_min = a.part = w.long_min;
+    a.long_min = w.long_min;
+    a.part = w.part;
     a.cap_long = (uint32_t)w.cap_long;
     a.long_rows = reinterpret_cast<const uint2*>(ws + w.long_rows);
     a.long_list = reinterpret_cast<uint4*>(ws + w.long_list);

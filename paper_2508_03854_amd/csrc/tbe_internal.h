@@ -110,7 +110,7 @@ struct Workspace {
         dense_rows, dense_index, radix_hist, nchunks, chunk_desc, rle_counts, partial, dense_partial, total;
     SortShape sort;
     int rle_blocks;
-    uint32_t long_min;    // a row with more lookups is long: it is cut into parts of about that many
+    uint32_t long_min, part;      // a row with more lookups is long: it is cut into parts of about `part`
     int64_t cap_long, cap_main;   // long rows; partial-sum slots of their parts
     bool dense;           // dense rows are looked for; their sizes:
     uint32_t dense_blocks, dense_chunks, dense_per_chunk;
