@@ -817,9 +817,9 @@ hipError_t launch_forward(const tbe_handle* h, const void* tables, const int32_t
 
 // ---- non-pooled lookup -------------------------------------------------------------------------------------
 // out block of table t = [n_t, D_t], row i = W_t[indices[offsets[t] + i]]; the blocks follow one another.
-// A wavefront takes 64 consecutive positions.  As a rule they lie in one table: then its lanes look at 64 tables at a time, each lane
-// with one id finds its row, and what the wavefront writes is one contiguous run of 64 * D_t elements, which its lanes fill fragment
-// after fragment, kSeqInFlight of them under way before the first is converted and stored.  Only a fragment's row goes from lane to
+// A wavefront takes up to 64 consecutive positions.  As a rule they lie in one table: then its lanes look at 64 tables at a time, each
+// lane with one id finds its row, and what the wavefront writes is one contiguous run of rows, which its lanes fill fragment after
+// fragment, kSeqInFlight of them under way before the first is converted and stored.  Only a fragment's row goes from lane to
 // lane.  Positions of several tables, or of an offsets array that does not add up, take the general path below, where every lane
 // resolves its own position and finds out for every fragment whose row it is.
 // Bound: the gather of the rows and the stream of the output, which is written past the caches: nothing here reads it again, and the
@@ -870,13 +870,13 @@ struct SeqFragment<__half, 0> {
 template <typename WT, typename IT, int IO>
 __device__ __forceinline__ void lookup_seq_rows(
     const WT* __restrict__ weights, const IT* __restrict__ indices, const IT* __restrict__ offsets, const int32_t* __restrict__ D_off,
-    const int64_t* __restrict__ w_off, const int64_t* __restrict__ row_base, const int T, const int64_t p0, const int64_t nnz,
+    const int64_t* __restrict__ w_off, const int64_t* __restrict__ row_base, const int T, const int64_t p0, const int n,
     void* __restrict__ out, const int64_t out_elems, int32_t* err) {
     using F4 = SeqFragment<WT, IO>;
     constexpr uint32_t kF = F4::kElems;
     const int lane = lane_id();
     const int64_t p = p0 + lane;
-    const bool valid = p < nnz;
+    const bool valid = lane < n;
     // table of the position: the last t with offsets[t] <= p (empty tables are skipped by construction)
     int t = 0;
     {
@@ -952,12 +952,12 @@ __device__ __forceinline__ void lookup_seq_rows(
 template <typename WT, typename IT, int IO>
 __global__ __launch_bounds__(kFwdThreads, 8) void lookup_seq_kernel(
     const WT* __restrict__ weights, const IT* __restrict__ indices, const IT* __restrict__ offsets, const int32_t* __restrict__ D_off,
-    const int64_t* __restrict__ w_off, const int64_t* __restrict__ row_base, const int T, const int64_t nnz,
+    const int64_t* __restrict__ w_off, const int64_t* __restrict__ row_base, const int T, const int64_t nnz, const int each,
     void* __restrict__ out, const int64_t out_elems, int32_t* err) {
     const int lane = lane_id();
-    const int64_t p0 = ((int64_t)blockIdx.x * (kFwdThreads / kWave) + (threadIdx.x >> 6)) * kWave;
+    const int64_t p0 = ((int64_t)blockIdx.x * (kFwdThreads / kWave) + (threadIdx.x >> 6)) * each;
     if (p0 >= nnz) return;
-    const int n = (int)((nnz - p0) < (int64_t)kWave ? (nnz - p0) : (int64_t)kWave);
+    const int n = (int)((nnz - p0) < (int64_t)each ? (nnz - p0) : (int64_t)each);
     const int64_t my_id = (int64_t)indices[p0 + (lane < n ? lane : n - 1)];
     // the first table that ends behind p0, all that is needed of it, and the elements of the blocks before its own; 64 tables a round
     int t = -1, D = 0;
@@ -982,7 +982,7 @@ __global__ __launch_bounds__(kFwdThreads, 8) void lookup_seq_kernel(
     }
     const int64_t dst = wave_sum_i64(part) + (p0 - start) * D;
     if (t < 0 || start < 0 || start > p0 || end < p0 + n || dst < 0 || dst + (int64_t)n * D > out_elems) {
-        lookup_seq_rows<WT, IT, IO>(weights, indices, offsets, D_off, w_off, row_base, T, p0, nnz, out, out_elems, err);
+        lookup_seq_rows<WT, IT, IO>(weights, indices, offsets, D_off, w_off, row_base, T, p0, n, out, out_elems, err);
         return;
     }
     const WT* const table = weights + w0;
@@ -1010,13 +1010,31 @@ __global__ __launch_bounds__(kFwdThreads, 8) void lookup_seq_kernel(
     }
 }
 
+// Positions per wavefront, at most 64 and in whole powers of two.  64 rows of 1024 columns are 64 steps of loads one behind the other:
+// a small batch waits for that chain, and in a large one the wavefronts write 128 to 256 KB apart, which meets the same channels.  So a
+// wavefront gets about 1024 fragments (by the mean width of the tables, as the host does not know where the positions lie), at least
+// 16 positions, for it looks its table up once; and where that leaves fewer than 2048 wavefronts, down to a step's 256 fragments.
+// A search per lane and 64 positions / this with 64 / 32 / 16 / 8, us, tables of 100 k rows, Zipf 1.2 (the last: of 9 to 84 rows):
+//   8 x 1000 of 64, 256, 1024 fp32 columns into bfloat16   11.1 35.5 137 / 9.7 27.6 99.7 / 9.3 15.7 52.6 / 9.3 9.9 28.8 / 9.1 8.7 15.9
+//   8 x 10000, 1024 columns, and a reader of the output    278 / 199 / 155 / 131 / 129; 256 binary16 columns into fp32 51 / 52 / 49 / 45 / 44
+//   8 x 100000 of 16, 64, 256 fp32 columns                 16.7 52 272 / 11.8 40 180 / 12.8 39 148 / 19.4 38 147 / 35 43 142
+//   5 x 430000 of 16 and 1024 columns into bfloat16        727 / 566 / 524 / 483 / 557
+static int seq_positions(const tbe_handle* h, const int64_t nnz, const int out_io) {
+    const int elems = h->dtype == TBE_F32 || out_io == 0 ? 4 : 8;   // of a fragment
+    const int64_t row = h->sumD / ((int64_t)h->T * elems) > 0 ? h->sumD / ((int64_t)h->T * elems) : 1;
+    int each = kWave;
+    while (each > 16 && each * row > 1024 && nnz < (int64_t)1 << 30) each /= 2;   // (a grid has fewer than 2^32 lanes)
+    while (each > 4 && each * row > kSeqInFlight * kWave && nnz < (int64_t)each * 2048) each /= 2;
+    return each;
+}
+
 template <typename WT, typename IT>
-static void launch_lookup_seq_as(const tbe_handle* h, const dim3 grid, const void* tables, const void* indices, const void* offsets,
+static void launch_lookup_seq_as(const tbe_handle* h, const dim3 grid, const int each, const void* tables, const void* indices, const void* offsets,
                                  int64_t nnz, void* out, int out_io, int64_t out_elems, hipStream_t s) {
     auto go = [&](auto io) {
         lookup_seq_kernel<WT, IT, decltype(io)::value><<<grid, kFwdThreads, 0, s>>>(
             static_cast<const WT*>(tables), static_cast<const IT*>(indices), static_cast<const IT*>(offsets), h->d_D_off, h->d_w_off,
-            h->d_row_base, h->T, nnz, out, out_elems, h->d_err);
+            h->d_row_base, h->T, nnz, each, out, out_elems, h->d_err);
     };
     if (out_io == 0) go(std::integral_constant<int, 0>{});
     else if (out_io == 1) go(std::integral_constant<int, 1>{});
@@ -1026,15 +1044,16 @@ static void launch_lookup_seq_as(const tbe_handle* h, const dim3 grid, const voi
 hipError_t launch_lookup_seq(const tbe_handle* h, const void* tables, const void* indices, const void* offsets,
                              int idx32, int64_t nnz, void* out, int out_io, int64_t out_elems, hipStream_t s) {
     if (nnz == 0) return hipSuccess;
-    const int64_t per_block = (int64_t)(kFwdThreads / kWave) * kWave;
+    const int each = seq_positions(h, nnz, out_io);
+    const int64_t per_block = (int64_t)(kFwdThreads / kWave) * each;
     const dim3 grid((unsigned)((nnz + per_block - 1) / per_block));
     LaunchTimer tm(h, s, "lookup_seq");
     if (h->dtype == TBE_F32) {
-        if (idx32) launch_lookup_seq_as<float, int32_t>(h, grid, tables, indices, offsets, nnz, out, out_io, out_elems, s);
-        else launch_lookup_seq_as<float, int64_t>(h, grid, tables, indices, offsets, nnz, out, out_io, out_elems, s);
+        if (idx32) launch_lookup_seq_as<float, int32_t>(h, grid, each, tables, indices, offsets, nnz, out, out_io, out_elems, s);
+        else launch_lookup_seq_as<float, int64_t>(h, grid, each, tables, indices, offsets, nnz, out, out_io, out_elems, s);
     } else {
-        if (idx32) launch_lookup_seq_as<__half, int32_t>(h, grid, tables, indices, offsets, nnz, out, out_io, out_elems, s);
-        else launch_lookup_seq_as<__half, int64_t>(h, grid, tables, indices, offsets, nnz, out, out_io, out_elems, s);
+        if (idx32) launch_lookup_seq_as<__half, int32_t>(h, grid, each, tables, indices, offsets, nnz, out, out_io, out_elems, s);
+        else launch_lookup_seq_as<__half, int64_t>(h, grid, each, tables, indices, offsets, nnz, out, out_io, out_elems, s);
     }
     tm.done();
     return hipGetLastError();
