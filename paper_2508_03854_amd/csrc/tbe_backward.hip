@@ -742,6 +742,25 @@ SegArgs seg_args(const tbe_handle* h, const Workspace& w, char* ws, const void* 
     return a;
 }
 
+// Whether the rows that are streamed gain by it, in all, as far as the host can know which those are.  Rows that fill whole 64-byte
+// pieces do, and those so wide that the first and the last piece count little.  Of other rows neighbours share pieces, and past the caches
+// a part of a piece is a read and a write of its own: that costs a row about as much as 256 bytes of the others gain.  8 tables, 564 MB
+// of rows in use with one or two lookups each, update alone, cached / streamed, us: fp32 of 8, 12, 16, 20, 24, 32, 36, 40 columns 1175 984
+// 636 732 628 385 569 515 / 1422 1172 594 853 711 349 629 529; of 48, 52, 84, 92, 100, 104, 116, 132 436 488 441 415 383 396 396 489 / 399
+// 507 449 421 394 377 380 474; binary16 of 16, 24, 32, 40, 56, 120, 136, 200 1027 990 669 888 678 588 895 661 / 1229 1149 653 918 759 594
+// 890 648.  Asked for every table in the kernel itself, it cost the loop the scalar registers that it spills: 886 -> 991 at the 40.
+static bool rows_gain_by_streams(const tbe_handle* h, const int64_t n) {
+    const int64_t size = h->dtype == TBE_F32 ? 4 : 2, each = n / h->T + 1;
+    int64_t gain = 0;
+    for (int t = 0; t < h->T; ++t) {
+        if (h->D[t] > 256) continue;   // (never streamed)
+        const int64_t bytes = h->D[t] * size;
+        const bool good = ((h->w_off[t] * size | bytes) & 63) == 0 || bytes > 400 || h->D[t] > 128;
+        gain += (h->rows[t] < each ? h->rows[t] : each) * (good ? bytes : -256);
+    }
+    return gain > 0;
+}
+
 hipError_t launch_segment_update(const tbe_handle* h, const Workspace& w, char* ws, const void* grad_out, int grad_io,
                                  const void* offsets, int idx32, int32_t B, tbe_pooling pooling, float lr, float eps, float c,
                                  void* tables, float* state, int seq, hipStream_t s) {
@@ -754,6 +773,7 @@ hipError_t launch_segment_update(const tbe_handle* h, const Workspace& w, char* 
     a.state = state;
     const uint64_t grad_bytes = (uint64_t)B * (uint64_t)h->sumD * (grad_io == 0 ? 4u : 2u);   // (of sequences next to nothing: they are read once)
     a.stream_from = grad_bytes < kInfinityCacheBytes ? kInfinityCacheBytes - grad_bytes : 0u;
+    if ((uint64_t)(w.n < h->total_rows ? w.n : h->total_rows) * a.row_bytes > a.stream_from && !rows_gain_by_streams(h, w.n)) a.stream_from = UINT64_MAX;
     a.long_spans = long_spans(h, B, seq, grad_io == 0 ? 4u : 2u);
     const bool mean = pooling == TBE_MEAN;
     if (a.dense_n) {
