@@ -20,10 +20,12 @@ def test_mean_of_every_size(M, count, dtype):
     dt = torch.float32 if dtype == "f32" else torch.float16
     g = torch.Generator(device="cuda").manual_seed(M + count)
     reps = [torch.empty(count + 16, dtype=dt, device="cuda").uniform_(-1, 1, generator=g) for _ in range(M)]
-    want = reps[0].float()
+    want = reps[0].float().clone()            # (of fp32 replicas .float() is the replica itself)
     for r in reps[1:]:
         want += r.float()
-    want /= M
+    # the correctly rounded quotient (53 bits are more than twice 24 and two); in fp32 the library multiplies by a rounded 1 / M
+    for part in want.split(1 << 24):
+        part.copy_((part.double() / M).float())
     tails = [r[count:].clone() for r in reps]
     tbe = TBE([16], [8], dtype)
     tbe.replica_mean([r[:count] for r in reps])
