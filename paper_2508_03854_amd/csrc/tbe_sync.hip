@@ -35,8 +35,13 @@ __device__ __forceinline__ uint4 pack(const float (&x)[8]) {   // binary16, to n
 // the Infinity Cache holds (LARGE) read past them too, two pieces in flight; smaller ones find part of themselves there, and have the
 // workgroups to fill the chip at once instead.  Plain accesses / LARGE / the other, us: 4 x 60 M fp32 (960 MB) 378 / 354 / 379; 8 x
 // 10 M fp32 (320 MB) 105 / 113 / 94; 2 x 40 M fp32 (320) 109 / 111 / 105; 4 x 20 M binary16 (160) 48 / 55 / 46.
+// Many replicas that all fit the Infinity Cache are written to it (STREAM off), where they are next read; of a few replicas it makes no
+// difference.  The mean, and with a reader of all replicas behind it, us, STREAM off / on: 5 x 8 M fp32 (160 MB) 48 100 / 48 101; 6 x
+// 4.2 M (100) 31 67 / 31 71; 8 x 4 M (128) 38 85 / 40 91; 8 x 6.2 M (200) 59 125 / 62 136; 8 x 10.6 M (340) 123 241 / 101 226; 16 x 4.2 M
+// (270) 87 197 / 97 207; 16 x 6.2 M (400) 177 323 / 146 294; 12 x 10.4 M binary16 (250) 74 175 / 82 177; 7 x 11.2 M (157) 48 107 / 49 111.
 constexpr size_t kLargeReplicas = (size_t)512 << 20;   // bytes of all of them
-template <typename WT, bool LARGE>
+static bool stream_means(const int M, const size_t bytes) { return M <= 5 || bytes > (size_t)(M > 8 ? 288 : 256) << 20; }
+template <typename WT, bool LARGE, bool STREAM>
 __global__ __launch_bounds__(256) void replica_mean_kernel(const ReplicaPtrs r, const int M, const size_t nvec,
                                                            const size_t count) {
     constexpr int V = RowIO<WT>::kVec;
@@ -77,7 +82,11 @@ __global__ __launch_bounds__(256) void replica_mean_kernel(const ReplicaPtrs r, 
         for (int m = 0; m < M; ++m)
 #pragma unroll
             for (int u = 0; u < U; ++u)
-                if (i0 + u * blockDim.x < nvec) nt_store16(static_cast<WT*>(r.p[m]) + (i0 + u * blockDim.x) * V, mean[u]);
+                if (i0 + u * blockDim.x < nvec) {
+                    WT* const dst = static_cast<WT*>(r.p[m]) + (i0 + u * blockDim.x) * V;
+                    if (STREAM) nt_store16(dst, mean[u]);
+                    else *reinterpret_cast<uint4*>(dst) = mean[u];
+                }
     }
     // the last count % V elements, one thread each
     const size_t tail0 = nvec * V;
@@ -92,12 +101,14 @@ __global__ __launch_bounds__(256) void replica_mean_kernel(const ReplicaPtrs r, 
 
 template <typename WT>
 static void launch_mean(const ReplicaPtrs& r, int M, size_t count, hipStream_t s) {
-    const size_t nvec = count / RowIO<WT>::kVec;
-    if ((size_t)M * count * sizeof(WT) > kLargeReplicas) {
-        replica_mean_kernel<WT, true><<<256 * 8, 256, 0, s>>>(r, M, nvec, count);
+    const size_t nvec = count / RowIO<WT>::kVec, bytes = (size_t)M * count * sizeof(WT);
+    if (bytes > kLargeReplicas) {
+        replica_mean_kernel<WT, true, true><<<256 * 8, 256, 0, s>>>(r, M, nvec, count);
     } else {
         const size_t need = nvec / 256 + 1;   // (at least one workgroup, for the last few elements)
-        replica_mean_kernel<WT, false><<<(unsigned)(need < 16384 ? need : 16384), 256, 0, s>>>(r, M, nvec, count);
+        const unsigned grid = (unsigned)(need < 16384 ? need : 16384);
+        if (stream_means(M, bytes)) replica_mean_kernel<WT, false, true><<<grid, 256, 0, s>>>(r, M, nvec, count);
+        else replica_mean_kernel<WT, false, false><<<grid, 256, 0, s>>>(r, M, nvec, count);
     }
 }
 

@@ -32,3 +32,13 @@ def test_mean_of_every_size(M, count, dtype):
     for r, tail in zip(reps, tails):
         assert torch.equal(r[:count], want[:count].to(dt)) and torch.equal(r[count:], tail)
     tbe.close()
+
+
+@pytest.mark.parametrize("M,count,dtype", [
+    (6, 1, "f32"), (6, 5, "f16"), (7, 1023, "f16"), (6, 1024 * 256 + 3, "f32"),
+    (6, (1 << 26) // 6, "f32"), (6, (1 << 26) // 6 + 1, "f32"),               # 256 MB together, and just above
+    (8, (1 << 24) + 9, "f16"), (9, (288 << 18) // 9, "f32"), (9, (288 << 18) // 9 + 2, "f32"), (16, (288 << 19) // 16 + 8, "f16"),
+])
+def test_mean_of_many_replicas(M, count, dtype):
+    """More replicas than are always written past the caches, on either side of the sizes up to which they are not."""
+    test_mean_of_every_size(M, count, dtype)
