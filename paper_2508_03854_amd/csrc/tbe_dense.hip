@@ -237,7 +237,7 @@ __device__ __forceinline__ void dense_run(const SegArgs& a, const uint32_t cb, c
                 // ---- stream the block's gradient rows, 16 bags per step; a wavefront takes every splits-th step
                 const int steps = (int)((nb + 15u) >> 4);
                 const char* const gblk = gtab + (int64_t)b0 * pitch;
-                // (a bag behind the batch's end has zero counts: any finite gradient row will do, the block's last)
+                // (a bag behind the batch's end has zero counts: the block's last will do, and where that is not finite the sums are redone)
                 auto load_step = [&](raw_t (&x)[8], const int j) {
                     if (nb == (uint32_t)kDenseBags) {
                         const char* const row0 = gblk + (int64_t)(j * 16) * pitch;
