@@ -27,27 +27,11 @@ static size_t hist_cap(int64_t N, int nseg) {
     const size_t few = std::min((size_t)512 << 10, (size_t)4096 * ((size_t)N / 1024 + (size_t)nseg + 2));   // 2048 bins, tiles of 1024
     return c > few ? c : few;
 }
-SortShape sort_shape(const tbe_handle* h, int64_t N) {
+// ... by passes over digits
+static SortShape pass_shape(const tbe_handle* h, int64_t N) {
     SortShape sh;
     sh.nseg = h->segmented ? h->T : 1;
-    // One launch where keys are local to their segment and reading a segment once per range of it costs less than two launches a
-    // pass.  That grows with the longest segment, of which the host knows only that all of them together are N: hence the bound on N for
-    // the batch that is one table's after all, and on the average, beyond which most batches have such a table.  Prepare calls with nearly
-    // all ids in one of 26 tables, passes / one launch, us: 48000 ids 36 to 65 / 24 to 61, 65536 ids of 100000 rows 39 to 74 / 28 to 76,
-    // and of tables of at most 2000 rows, which take one pass of wide digits, 30 to 44 / 33 to 52, where spread over the tables 23 to 28 /
-    // 17 to 22.  Very many tables have a workgroup of 1024 threads each for a few ids: 1000 tables x 10 and x 60 ids 48 -> 50 and 51 ->
-    // 60, 300 x 1 35 -> 24.
-    sh.small = (h->segmented || h->T == 1) && sh.nseg <= kSmallTables && (N <= kSmallMax || (N <= kSmallMaxMany && N <= kSmallSegment * sh.nseg));
-    if (sh.small) {
-        sh.passes = 1;
-        sh.bits = h->sort_bits;
-        sh.bins = 0;
-        sh.hist_bytes = 0;
-        sh.self_scan = true;
-        sh.chunk = sh.tile = kSmallChunk;
-        sh.max_chunks = (int)((N + kSmallChunk - 1) / kSmallChunk) + sh.nseg;
-        return sh;
-    }
+    sh.small = false;
     sh.self_scan = N <= kSelfScanMax;
     const int64_t few = kSelfScanChunks * sh.nseg;   // chunks in all
     if (sh.self_scan && N <= 32 * 4096 && N <= few * 1024) sh.tile = 1024;
@@ -66,6 +50,33 @@ SortShape sort_shape(const tbe_handle* h, int64_t N) {
         sh.bins = sh.bits <= 8 ? 256 : (sh.bits <= 10 ? 1024 : 2048);
         sh.hist_bytes = (size_t)(sh.self_scan ? 2 : 4) * (size_t)sh.bins * (size_t)(sh.max_chunks + 1);
         if (sh.hist_bytes <= hist_cap(N, sh.nseg)) break;
+    }
+    return sh;
+}
+SortShape sort_shape(const tbe_handle* h, int64_t N) {
+    SortShape sh = pass_shape(h, N);
+    // One launch where keys are local to their segment and reading a segment once per range of it costs less than two launches a
+    // pass.  That grows with the longest segment, of which the host knows only that all of them together are N: hence the bound on N for
+    // the batch that is one table's after all, and on the average, beyond which most batches have such a table.  Prepare calls with nearly
+    // all ids in one of 26 tables, passes / one launch, us: 48000 ids 36 to 65 / 24 to 61, 65536 ids of 100000 rows 39 to 74 / 28 to 76,
+    // and of tables of at most 2000 rows, which take one pass of wide digits, 30 to 44 / 33 to 52, where spread over the tables 23 to 28 /
+    // 17 to 22.
+    // A compute unit has room for one of its workgroups, and a round of 256 of them costs about as much as a pass.  A round more than
+    // passes is slower, whatever the ids: 236 tables x 161 ids of 60 / 1000 / 100000 rows (1 / 2 / 3 passes, two rounds) 22 30 38 / 24 25
+    // 26, 500 tables x 15 (three rounds) 22 30 38 / 32 33 34, 300 tables x 7 (two) 20 28 36 / 23 23 25, 150 x 400 (two) of 60, 3000 rows 25
+    // 33 / 27 28.  As many rounds as passes, but more than one, lose more with long segments than they gain without: three quarters of
+    // 38000 and of 60000 ids in one of 250 tables 32 39 47, 36 44 52 / 44 42 45, 54 53 58, of 13000 28 35 43 / 30 30 31.
+    const int64_t ranges = (N + kSmallChunk - 1) / kSmallChunk + sh.nseg, rounds = (ranges + 255) / 256;
+    if ((h->segmented || h->T == 1) && sh.nseg <= kSmallTables && rounds <= (rounds > 1 && N > 2 * kSmallMax ? sh.passes - 1 : sh.passes) &&
+        (N <= kSmallMax || (N <= kSmallMaxMany && N <= kSmallSegment * sh.nseg))) {
+        sh.small = true;
+        sh.passes = 1;
+        sh.bits = h->sort_bits;
+        sh.bins = 0;
+        sh.hist_bytes = 0;
+        sh.self_scan = true;
+        sh.chunk = sh.tile = kSmallChunk;
+        sh.max_chunks = (int)ranges;
     }
     return sh;
 }
