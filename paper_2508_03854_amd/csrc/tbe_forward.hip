@@ -699,10 +699,19 @@ static void launch_forward_nc(const tbe_handle* h, int first, int n, const void*
                                                                       list, n, B, nnz, h->sumD, out, out_io, h->d_err);
 }
 
-// Workgroups from which a launch of lane groups hands bags out by length: as many as the chip holds at a time.  Smaller ones gain nothing
+// A launch of lane groups hands bags out by length if it has as many workgroups as the chip holds at a time - smaller ones gain nothing
 // by it that can be told from the noise: 8 tables x 4096 bags, 1 + Poisson(10) ids, 8 fp32 columns 13.9 / 14.0 us, 64 binary16 14.1 / 13.6,
-// 64 fp32 14.5 / 14.2; Poisson(3) 13.9 / 13.9, 13.4 / 13.5, 13.6 / 13.6.
+// 64 fp32 14.5 / 14.2 - and if the bags are long enough on average for what they then save each other.  The order is a chain of a few
+// hundred cycles for every wavefront, and two bags beside each other have less to save than sixteen: hence the square of the lanes per
+// row.  64 tables x 16384 bags, for 32 lanes 26 x 4096, of 100 rows, fp32, Poisson(3), (8), (25), lognormal of mean 1.3, 3, 7, 20, not / by
+// length: 4 lanes 48 67 140, 50 78 117 232 / 45 62 127, 51 66 97 197; 8 lanes 67 90 177, 68 95 143 293 / 70 87 162, 73 92 128 259; 16 lanes
+// (26 x 4096) 18.8 23.1 40.5, 22.0 27.2 38.8 72 / 20.4 23.6 39.4, 23.4 28.5 38.3 68; 32 lanes 30.5 37.2 60.6, 30.7 49.7 58.0 102 / 32.7 38.3
+// 59.8, 32.3 52.0 59.0 99.  Of 100000 rows, which are fetched from further away, 8 lanes 106 189 497, 87 141 227 487 / 100 184 514, 85 124 209
+// 470, 16 and 32 lanes 0 to 4 % slower below a mean of 7, then the same.
 constexpr int64_t kByLengthWorkgroups = 2048;
+static bool by_length(const int64_t workgroups, const int64_t lookups, const int64_t bags, const int lpr) {
+    return workgroups >= kByLengthWorkgroups && lookups >= bags * (lpr * lpr) / 32;   // (of the whole batch: the host does not know whose they are)
+}
 // Do the lane groups of class c write their parts of the output past the caches, which are then left to the rows?  Not where that leaves
 // parts of 64-byte pieces to other workgroups, which are then fetched and written again: 26 tables x 32768 bags of one id, us, plain / past
 // the caches: 12 fp32 columns 33.5 / 51, 28 55 / 83, 4 and 8 columns into bfloat16 34 / 36; but 16 columns, 64 bytes, 33.5 / 33, of 5 and 10
@@ -758,7 +767,7 @@ static void launch_forward_groups(const tbe_handle* h, const void* tables, const
             if (stream) launch(mean_c, by_length_c, std::true_type{});
             else launch(mean_c, by_length_c, std::false_type{});
         };
-        if (groups >= kByLengthWorkgroups) {
+        if (by_length(groups, nnz, (int64_t)h->T * B, 1 << lpr_log2)) {
             grid = dim3((unsigned)groups);
             if (mean) go(std::true_type{}, std::true_type{});
             else go(std::false_type{}, std::true_type{});

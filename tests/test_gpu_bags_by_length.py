@@ -68,3 +68,28 @@ def test_bags_of_one_length(D, dtype, length, odd):
     counts.index_add_(0, torch.repeat_interleave(torch.arange(B, device=dev), lens) * R + idx, torch.ones(idx.numel(), device=dev))
     assert torch.equal(out, counts.view(B, R) @ w.view(R, D).float())
     tbe.close()
+
+
+@pytest.mark.parametrize("D,dtype,mean", [(16, "f32", 0.5), (32, "f32", 2), (64, "f16", 2), (64, "f32", 8), (128, "f16", 8), (128, "f32", 32), (256, "f16", 32)])
+@pytest.mark.parametrize("fewer", [0, 1])
+def test_bags_long_enough_on_average(D, dtype, mean, fewer):
+    """Bags of very different lengths, with as many lookups as have them handed out by length, and one fewer."""
+    if not torch.cuda.is_available():
+        pytest.skip("no GPU")
+    from paper_2508_03854_amd import TBE
+    R, B, dev = 50, 32_768 if D > 32 else 132_000, "cuda"
+    tbe = TBE([R], [D], dtype)
+    tbe.set_tunable("hot_rows_min_workgroups", -1)
+    g = torch.Generator(device=dev).manual_seed(D)
+    w = torch.randint(-2, 3, (R * D,), generator=g, device=dev).to(tbe.torch_dtype)   # exact sums in any order
+    n = int(B * mean) - fewer
+    lens = torch.bincount((torch.rand(n, generator=g, device=dev) ** 1.5 * B).long().clamp_(max=B - 1), minlength=B)
+    lens = lens[torch.randperm(B, generator=g, device=dev)]
+    off = torch.zeros(B + 1, dtype=torch.int64, device=dev)
+    torch.cumsum(lens, 0, out=off[1:])
+    idx = torch.randint(0, R, (n,), generator=g, device=dev)
+    out = tbe.forward(w, idx, off, B, "sum", out=torch.full((B, D), 7.0, device=dev))
+    counts = torch.zeros(B * R, device=dev)
+    counts.index_add_(0, torch.repeat_interleave(torch.arange(B, device=dev), lens) * R + idx, torch.ones(n, device=dev))
+    assert torch.equal(out, counts.view(B, R) @ w.view(R, D).float())
+    tbe.close()
