@@ -192,7 +192,8 @@ __global__ __launch_bounds__(kRsThreads) void radix_hist_kernel(const SortArgs a
 
 // Large batches: every chunk's count of a digit becomes the sum of those of all chunks before it, chunk nchunks gets the sum of all; a
 // chunk's place within its segment is the difference to the segment's first.  A workgroup takes kScanDigits digits of all chunks, a
-// thread one of them in a run of consecutive chunks, held in registers.
+// thread one of them in a run of consecutive chunks, held in registers (up to 66 of 128: four others are spilled, 20 bytes a lane, at
+// every size, for all sizes share the kernel).
 // Bound: latency.  All histograms, scans and scatters of a step with a row of all chunks per digit (256 scattered words for every
 // chunk's workgroups) / a row of all digits per chunk (every scan workgroup reads all of it) / this, us: 32 tables,
 // 26 M lookups 124 + 58 + 301 / 98 + 98 + 287 / 101 + 54 + 289; 16 tables, 5.5 M 45 + 24 + 92 / 39 + 28 + 89 / 39 + 19 + 89; 64 tables, 65 M
