@@ -23,3 +23,27 @@ def test_rows_on_both_sides_of_a_long_one(T, D, each):
         ids.append(torch.cat([fixed, more])[torch.randperm(each, generator=g, device=dev)])
         lens.append(torch.bincount(torch.randint(0, 64, (each,), generator=g, device=dev), minlength=64))
     check(T, 4000, D, 64, torch.cat(lens), torch.cat(ids), seed=each)
+
+
+@pytest.mark.parametrize("D,N,spans", [
+    (260, 12288, [[1023, 1024, 1025, 1026], [2048, 2000], [4090]]),            # 64 parts of 16 lookups, and of 64
+    (1024, 12288, [[4096], [4000, 65], [17, 33, 65, 1100]]),
+    (132, 24576, [[2047, 2048, 2049], [4095, 4033], [8000]]),                  # of 32 lookups
+    (256, 8192, [[4096, 4000]]),
+    (132, 65536, [[60000], [2100], []] + [[]] * 6),
+])
+def test_rows_of_many_fine_parts(D, N, spans):
+    """Rows that have as many fine parts as a row may have, one more, and so many that coarse ones are more."""
+    dev, T = "cuda", len(spans)
+    g = torch.Generator(device=dev).manual_seed(N + D)
+    ids, lens = [], []
+    left = N - sum(map(sum, spans))
+    for t in range(T):
+        fixed = [torch.full((s,), 7 * i + t, device=dev) for i, s in enumerate(spans[t])]
+        more = min(left, N // T // 3 + 5) if t < T - 1 else left
+        left -= more
+        all_ids = torch.cat(fixed + [torch.randint(200, 4000, (more,), generator=g, device=dev)])
+        n = all_ids.numel()
+        ids.append(all_ids[torch.randperm(n, generator=g, device=dev)])
+        lens.append(torch.bincount(torch.randint(0, 64, (n,), generator=g, device=dev), minlength=64))
+    check(T, 4000, D, 64, torch.cat(lens), torch.cat(ids), seed=N)
